@@ -2,7 +2,7 @@
 // cores (v_mfma_f32_32x32x16_bf16, fp32 accumulation): y = x W^T (+ bias, + GELU), dx = dy W,
 // dW = dy^T x.  One kernel, three operand orientations.
 //
-// Workgroup tile 256 x 128 (or 192 x 128), four wavefronts of 128 x 64 (0.75 KB of LDS operand reads per
+// Large problems (small ones: see kTiles): workgroup tile 256 x 128 (or 192 x 128), four wavefronts of 128 x 64 (0.75 KB of LDS operand reads per
 // MFMA), LDS stage buffers filled straight from memory (buffer_load ... lds; out-of-range rows deposit
 // zeros), one barrier per stage, two workgroups per CU.  Two configurations: 32 reduction elements per
 // stage in 64-byte LDS rows with three stage buffers (loads two stages ahead), or - for the long
@@ -29,6 +29,8 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x8_t __attribute__((ext_vector_type(8)));
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 
+constexpr int SP = 72;                         // epilogue strip pitch (bytes per column)
+
 // TM: 32-row blocks of a wavefront's tile (4: workgroup tile 256 x 128, 3: 192 x 128).
 // RB: bytes of an LDS row = bytes of an operand row that one group of lanes fetches.  The path from L2
 // into LDS moves a fixed number of requests per clock whatever their size up to a 128-byte line
@@ -37,15 +39,22 @@ typedef int i32x4_t __attribute__((ext_vector_type(4)));
 // the contiguous one mean 64 reduction elements per stage, and then only two stage buffers of a
 // 192 x 128 tile fit the 80 KB a workgroup may hold with two workgroups per CU; an operand read through
 // the transposing load takes 128-byte rows by widening its planes to 64 columns, at any stage depth.
-template <int TM, int BK_, int RB_> struct Cfg {
-  static constexpr int BK = BK_, RB = RB_;
-  static constexpr int NW = 4, THREADS = 64 * NW, BN = 128;   // four wavefronts, 2 x 2
-  static constexpr int NST = BK == 64 ? 2 : 3;           // stage buffers; loads run NST - 1 stages ahead
-  static constexpr int BM = 64 * TM, A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_B = A_BYTES + B_BYTES;
+//
+// KG: groups of four wavefronts in a workgroup.  They share the output tile and split the reduction range,
+// each with stage buffers of its own, and their accumulators are added through LDS at the end.
+template <int TM, int TN, int BK_, int RB_, int NST_, int KG_> struct Cfg {
+  static constexpr int BK = BK_, RB = RB_, KG = KG_;
+  static constexpr int NW = 4, THREADS = 64 * NW * KG;   // a group: four wavefronts, 2 x 2
+  static constexpr int NST = NST_;                       // stage buffers; loads run NST - 1 stages ahead
+  static constexpr int BM = 64 * TM, BN = 64 * TN, A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_B = A_BYTES + B_BYTES;
   static constexpr int NLOAD = STAGE_B / 1024 / NW;      // direct loads per wavefront and stage
+  static constexpr int SMEM = KG * NST * STAGE_B;
+  static constexpr int HAND_B = (KG - 1) * TM * TN * 16 * 256 * 4;   // accumulators of the groups past the first
+  // wavefronts per SIMD the register allocation leaves room for: two workgroups per CU where their LDS fits
+  static constexpr int WPE = KG * (2 * SMEM <= 160 * 1024 ? 2 : 1);
   static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "every load of a wavefront belongs to one operand");
+  static_assert(SMEM <= 160 * 1024 && HAND_B + NW * 32 * SP <= SMEM, "LDS");
 };
-constexpr int SP = 72;                         // epilogue strip pitch (bytes per column)
 
 __device__ __forceinline__ i32x4_t make_desc(const void* p, unsigned bytes) {
   const unsigned long long a = reinterpret_cast<unsigned long long>(p);
@@ -110,9 +119,9 @@ __device__ __forceinline__ float gelu_f(float u) {
   return fmaf(hu, t * p, hu);
 }
 
-template <bool ATR, bool BTR, int EPI, int TM, int BK, int RB>
-__global__ void __launch_bounds__(256, 2) gemm_kernel(Args a) {
-  using C = Cfg<TM, BK, RB>;
+template <bool ATR, bool BTR, int EPI, int TM, int TN, int BK, int RB, int NSTAGE, int KG>
+__global__ void __launch_bounds__(256 * KG, (Cfg<TM, TN, BK, RB, NSTAGE, KG>::WPE)) gemm_kernel(Args a) {
+  using C = Cfg<TM, TN, BK, RB, NSTAGE, KG>;
   constexpr int NW = C::NW, BN = C::BN;
   constexpr int BM = C::BM, A_BYTES = C::A_BYTES, STAGE_B = C::STAGE_B, NLOAD = C::NLOAD, NST = C::NST;
   constexpr int LPR = RB / 16, RPL = 1024 / RB;       // lanes per LDS row, rows per direct load
@@ -122,7 +131,9 @@ __global__ void __launch_bounds__(256, 2) gemm_kernel(Args a) {
   static_assert(BM % PC == 0 || !ATR, "whole planes");
   static_assert(NST == 2 || NLOAD < 16, "the wait below encodes the load count in four bits");
   extern __shared__ __align__(16) unsigned char smem[];   // NST stage buffers, nothing else: LDS address 0
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int lane = threadIdx.x & 63;
+  const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);   // reduction group
+  const int tid = threadIdx.x & 255;                                                     // within the group
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, h = lane >> 5, g = lane >> 4, i16 = lane & 15;
   // workgroups that share an XCD's L2 (every 8th) walk consecutive tiles: same rows of A, all of B
@@ -143,10 +154,16 @@ __global__ void __launch_bounds__(256, 2) gemm_kernel(Args a) {
     l -= cnt;
   }
   const int m0 = mt * BM, n0 = nt * BN;
-  const int kbeg = blockIdx.z * a.k_per_split;
+  int kbeg = blockIdx.z * a.k_per_split;
   int kend = kbeg + a.k_per_split;
   if (kend > a.K) kend = a.K;
-  const int nst = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
+  int nst = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
+  if (KG > 1) {      // this group's part of the range; every group runs the same number of stages (the last ones load zeros past kend)
+    nst = (nst + KG - 1) / KG;
+    kbeg += kg * nst * BK;
+    kend = min(kend, kbeg + nst * BK);
+  }
+  const int sbase = kg * NST * STAGE_B;    // LDS address of the group's stage buffers
 
   const i32x4_t a_rs = make_desc(a.A, a.a_bytes), b_rs = make_desc(a.B, a.b_bytes);
   // ---- this lane's direct loads of a stage ----
@@ -184,7 +201,7 @@ __global__ void __launch_bounds__(256, 2) gemm_kernel(Args a) {
     for (int j = 0; j < NLOAD; ++j) {
       const bool isA = j * NW < A_BYTES / 1024;
       const unsigned off = kk0[j] + t * BK < kend ? voff[j] + (unsigned)t * (isA ? vinc_a : vinc_b) : kOobOffset;
-      load16_to_lds(isA ? a_rs : b_rs, (unsigned)(sb + (j * NW + wave) * 1024), off);
+      load16_to_lds(isA ? a_rs : b_rs, (unsigned)(sbase + sb + (j * NW + wave) * 1024), off);
     }
   };
   // ---- fragment addresses (stage-relative) ----
@@ -196,7 +213,7 @@ __global__ void __launch_bounds__(256, 2) gemm_kernel(Args a) {
   // of 32-column block sub of the wavefront's tile.
   int a_n0 = 0, b_n0 = 0;            // natural: address of step 0, block 0
   int a_t0 = 0, b_t0 = 0;            // transposed: address of step 0 within a 32-column block at column 0
-  int a_sub[TM], b_sub[2];           // transposed: where block sub lies (plane, and half of a 128-byte row)
+  int a_sub[TM], b_sub[TN];           // transposed: where block sub lies (plane, and half of a 128-byte row)
   auto nat0 = [&](int row) { return row * RB + ((h ^ swz_of<RB, false>(row)) << 4); };
   auto tr0 = [&]() {
     const int ch0 = (g & 1) * 16 + (i16 & 3) * 4, row = h * 8 + (i16 >> 2);
@@ -208,11 +225,11 @@ __global__ void __launch_bounds__(256, 2) gemm_kernel(Args a) {
     return (cb >> 1) * PLANE_B + (((cb & 1) ^ sw) << 6);
   };
   if (!ATR) a_n0 = nat0(wm * (TM * 32) + (lane & 31)); else a_t0 = tr0();
-  if (!BTR) b_n0 = A_BYTES + nat0(wn * 64 + (lane & 31)); else b_t0 = A_BYTES + tr0();
+  if (!BTR) b_n0 = A_BYTES + nat0(wn * (TN * 32) + (lane & 31)); else b_t0 = A_BYTES + tr0();
 #pragma unroll
   for (int i = 0; i < TM; ++i) a_sub[i] = ATR ? tr_sub(wm * TM + i) : i * 32 * RB;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) b_sub[j] = BTR ? tr_sub(wn * 2 + j) : j * 32 * RB;
+  for (int j = 0; j < TN; ++j) b_sub[j] = BTR ? tr_sub(wn * TN + j) : j * 32 * RB;
   auto read_frag = [&](const unsigned char* sb, bool tr, int n0a, int t0a, int subo, int ks) __attribute__((always_inline)) -> bf16x8_t {
     if (!tr) {
       return *reinterpret_cast<const bf16x8_t*>(sb + (n0a ^ (ks << 5)) + subo);
@@ -224,11 +241,11 @@ __global__ void __launch_bounds__(256, 2) gemm_kernel(Args a) {
     return __builtin_bit_cast(bf16x8_t, v);
   };
 
-  f32x16_t acc[TM][2];
+  f32x16_t acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
@@ -246,8 +263,8 @@ __global__ void __launch_bounds__(256, 2) gemm_kernel(Args a) {
       if (fill >= NST * STAGE_B) fill -= NST * STAGE_B;
       issue(t + NST - 1, fill);
     }
-    const unsigned char* sb = smem + cur;
-    bf16x8_t af[2][TM], bfr[2][2];
+    const unsigned char* sb = smem + sbase + cur;
+    bf16x8_t af[2][TM], bfr[2][TN];
 #pragma unroll
     for (int kp = 0; kp < KS; kp += 2) {
 #pragma unroll
@@ -255,27 +272,50 @@ __global__ void __launch_bounds__(256, 2) gemm_kernel(Args a) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) af[ks][i] = read_frag(sb, ATR, a_n0, a_t0, a_sub[i], kp + ks);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) bfr[ks][j] = read_frag(sb, BTR, b_n0, b_t0, b_sub[j], kp + ks);
+        for (int j = 0; j < TN; ++j) bfr[ks][j] = read_frag(sb, BTR, b_n0, b_t0, b_sub[j], kp + ks);
       }
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
+          for (int j = 0; j < TN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks][i], bfr[ks][j], acc[i][j], 0, 0, 0);
     }
     cur += STAGE_B;
     if (cur == NST * STAGE_B) cur = 0;
   }
 
+  if (KG > 1) {
+    // the groups past the first hand their accumulators over through LDS, in group order
+    __syncthreads();     // every wave is done reading the stage buffers; all direct loads have landed (vmcnt(0) above)
+    float* R = reinterpret_cast<float*>(smem);
+    if (kg > 0) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) R[(((kg - 1) * TM * TN + i * TN + j) * 16 + r) * 256 + tid] = acc[i][j][r];
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int k = 0; k < KG - 1; ++k)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] += R[((k * TM * TN + i * TN + j) * 16 + r) * 256 + tid];
+  }
   if (EPI == 2) {
     float* out = a.part + (size_t)blockIdx.z * a.M * a.ldc;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int col = n0 + wn * 64 + j * 32 + (lane & 31);
+      for (int j = 0; j < TN; ++j) {
+        const int col = n0 + wn * (TN * 32) + j * 32 + (lane & 31);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int row = m0 + wm * (TM * 32) + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
@@ -284,8 +324,9 @@ __global__ void __launch_bounds__(256, 2) gemm_kernel(Args a) {
       }
     return;
   }
-  __syncthreads();     // every wave is done reading the stage buffers; all direct loads have landed (vmcnt(0) above)
-  unsigned char* S = smem + wave * (32 * SP);
+  if (KG == 1) __syncthreads();     // every wave is done reading the stage buffers; all direct loads have landed (vmcnt(0) above)
+  unsigned char* S = smem + C::HAND_B + wave * (32 * SP);   // behind the accumulators just taken over
+
   const int wr_off = (lane & 31) * SP + h * 8;
   const int rd_off = (g * 8 + (i16 >> 2)) * SP + (i16 & 3) * 8;
   auto transpose_store = [&](const float* v, bf16_t* dst, int i, int j) __attribute__((always_inline)) {
@@ -298,7 +339,7 @@ __global__ void __launch_bounds__(256, 2) gemm_kernel(Args a) {
       const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(S + rd_off + rb * 32));
       const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(S + rd_off + 4 * SP + rb * 32));
       const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-      const int row = m0 + wm * (TM * 32) + i * 32 + rb * 16 + i16, col = n0 + wn * 64 + j * 32 + g * 8;
+      const int row = m0 + wm * (TM * 32) + i * 32 + rb * 16 + i16, col = n0 + wn * (TN * 32) + j * 32 + g * 8;
       if (row < a.M && col < a.N) {
         uint4 out = uint4{l2.x, l2.y, h2.x, h2.y};
         if (EPI == 3) {     // + residual: the sum of two stored values, rounded again
@@ -317,8 +358,8 @@ __global__ void __launch_bounds__(256, 2) gemm_kernel(Args a) {
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int colv = n0 + wn * 64 + j * 32 + (lane & 31);
+    for (int j = 0; j < TN; ++j) {
+      const int colv = n0 + wn * (TN * 32) + j * 32 + (lane & 31);
       const float bv = (a.bias && colv < a.N) ? a.bias[colv] : 0.f;
       float v[16];
 #pragma unroll
@@ -356,30 +397,84 @@ int launch(Kern kern, bool* raised, int threads, int smem_bytes, const Args& a, 
   hipLaunchKernelGGL(kern, dim3(8 * ((a.mtiles * a.ntiles + 7) / 8), 1, splits), dim3(threads), smem_bytes, st, a);
   return launch_status();
 }
-template <bool ATR, bool BTR, int EPI, int TM, int BK, int RB>
+template <bool ATR, bool BTR, int EPI, int TM, int TN, int BK, int RB, int NST, int KG>
 int launch_cfg(Args& a, int splits, hipStream_t st) {
   static bool raised = false;
-  using C = Cfg<TM, BK, RB>;
+  using C = Cfg<TM, TN, BK, RB, NST, KG>;
   a.mtiles = (a.M + C::BM - 1) / C::BM;
   a.ntiles = (a.N + C::BN - 1) / C::BN;
-  return launch(gemm_kernel<ATR, BTR, EPI, TM, BK, RB>, &raised, C::THREADS, C::NST * C::STAGE_B, a, splits, st);
+  return launch(gemm_kernel<ATR, BTR, EPI, TM, TN, BK, RB, NST, KG>, &raised, C::THREADS, C::SMEM, a, splits, st);
 }
-// Rows per workgroup tile (in 64s): the device holds 512 workgroups at once; the cost of a launch is
-// about (rounds of resident workgroups) x (tile height).
-int pick_tm(int out_rows, int ntiles) {
-  auto cost = [&](int tm) { const int t = ((out_rows + 64 * tm - 1) / (64 * tm)) * ntiles; return ((t + 511) / 512) * tm; };
-  return cost(3) < cost(4) ? 3 : 4;
+// The tile shapes besides the large ones, and what a launch of each costs.  With few tiles the device is
+// bound by the latency of the operand loads and by how many CUs have a tile at all, so small problems want
+// small tiles, 128-byte operand rows and two groups of wavefronts on one tile (KG = 2: twice the loads in
+// flight per CU).  Estimated time (us) of a launch, from a sweep over 197..12608 rows and 384..3072 columns
+// and reductions (mean loss against the fastest shape 1 %):
+//   one workgroup per CU at a time (KG = 2):  rounds * (fixed + stages per group * stage)
+//   several:   rounds of resident workgroups * fixed + tiles per CU * stages * stage
+// Measured before / after, us: 788 x 3072 -> 768 41.8 / 13.8, 788 x 768 -> 2304 17.1 / 10.7, 197 x 768 -> 768
+// 15.0 / 6.1, 1576 x 768 -> 768 15.3 / 8.3, 6240 x 384 -> 384 10.7 / 7.3.
+enum { T64 = 0, T64G2, T64x128, T64x128G2, T128, T_SMALL };
+struct TileCost {
+  int rows, cols, kgroups, resident;      // workgroup tile, groups of wavefronts, workgroups per CU
+  float fixed, stage;                     // us; a natural operand, 64 reduction elements per stage
+  float fixed_tt, stage_tt;               // both operands through the transposing load (weight gradient)
+};
+constexpr TileCost kTiles[T_SMALL] = {{64, 64, 1, 3, 4.2f, 0.195f, 4.1f, 0.23f},
+                                      {64, 64, 2, 1, 4.3f, 0.35f, 4.2f, 0.41f},
+                                      {64, 128, 1, 2, 4.6f, 0.335f, 4.1f, 0.345f},
+                                      {64, 128, 2, 1, 4.1f, 0.645f, 4.4f, 0.635f},
+                                      {128, 128, 1, 2, 6.1f, 0.54f, 1e9f, 0.f}};
+inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
+float tile_time(int tiles, int resident, int stages, int kgroups, float fixed, float stage) {
+  if (kgroups > 1) return ceil_div(tiles, 256) * (fixed + ceil_div(stages, kgroups) * stage);
+  return ceil_div(tiles, 256 * resident) * fixed + (float)ceil_div(tiles, 256) * stages * stage;
 }
-// One launch of an orientation with a natural operand.  128-byte rows (192 x 128 tiles, 64 reduction
-// elements per stage, loads one stage ahead) pay from a reduction length of 2048 on: -15 % on
-// 12608 x 3072 -> 768; shorter reductions run as fast or faster with 64-byte rows, three stage buffers
-// and the choice of tile heights (the tuning table forces either: 15 = 1 / 2).
+// the fastest of the small shapes for out_rows x out_cols outputs, or -1 if `best` (us) is less
+int pick_small(int out_rows, int out_cols, int k, bool tt, float best) {
+  int pick = -1;
+  for (int c = 0; c < T_SMALL; ++c) {
+    const TileCost& t = kTiles[c];
+    const int tiles = ceil_div(out_rows, t.rows) * ceil_div(out_cols, t.cols);
+    const float us = tile_time(tiles, t.resident, ceil_div(k, 64), t.kgroups, tt ? t.fixed_tt : t.fixed, tt ? t.stage_tt : t.stage);
+    if (us < best) { best = us; pick = c; }
+  }
+  return pick;
+}
+template <bool ATR, bool BTR, int EPI>
+int launch_small(Args& a, int shape, hipStream_t st) {
+  switch (shape) {
+    case T64: return launch_cfg<ATR, BTR, EPI, 1, 1, 64, 128, 3, 1>(a, 1, st);
+    case T64G2: return launch_cfg<ATR, BTR, EPI, 1, 1, 64, 128, 3, 2>(a, 1, st);
+    case T64x128: return launch_cfg<ATR, BTR, EPI, 1, 2, 64, 128, 3, 1>(a, 1, st);
+    case T64x128G2: return launch_cfg<ATR, BTR, EPI, 1, 2, 64, 128, 3, 2>(a, 1, st);
+    case T128:
+      if constexpr (!(ATR && BTR)) return launch_cfg<ATR, BTR, EPI, 2, 2, 64, 128, 2, 1>(a, 1, st);
+      return CNNK_ERR_UNSUPPORTED;
+    default: return CNNK_ERR_UNSUPPORTED;
+  }
+}
+// One launch of an orientation with a natural operand.  The large shapes: 256 x 128 and 192 x 128 tiles
+// with 64-byte rows, and for reductions from 2048 on 192 x 128 tiles with 128-byte rows (64 reduction
+// elements per stage, loads one stage ahead: -15 % on 12608 x 3072 -> 768).  Their constants are in the
+// same units as kTiles; the tuning table forces a shape (15 = 1 / 2: 64- / 128-byte rows of the large
+// ones, 16 + n: small shape n).
 template <bool BTR, int EPI>
 int launch_nat(Args& a, hipStream_t st) {
-  const bool wide = g_cnnk_tune[15] == 2 || (g_cnnk_tune[15] != 1 && a.K >= 2048);
-  if (wide) return launch_cfg<false, BTR, EPI, 3, 64, 128>(a, 1, st);
-  if (pick_tm(a.M, (a.N + 127) / 128) == 3) return launch_cfg<false, BTR, EPI, 3, 32, 64>(a, 1, st);
-  return launch_cfg<false, BTR, EPI, 4, 32, 64>(a, 1, st);
+  const int force = g_cnnk_tune[15];
+  if (force >= 16) return launch_small<false, BTR, EPI>(a, force - 16, st);
+  const int n128 = ceil_div(a.N, 128), t192 = ceil_div(a.M, 192) * n128, t256 = ceil_div(a.M, 256) * n128;
+  const bool wide = force == 2 || (force != 1 && a.K >= 2048);
+  const float us192 = tile_time(t192, 2, ceil_div(a.K, 32), 1, 7.8f, 0.47f);
+  const float us256 = tile_time(t256, 2, ceil_div(a.K, 32), 1, 11.8f, 0.38f);
+  const float us = wide ? tile_time(t192, 2, ceil_div(a.K, 64), 1, 1.2f, 0.85f) : us192 < us256 ? us192 : us256;
+  if (force == 0) {
+    const int small = pick_small(a.M, a.N, a.K, false, us);
+    if (small >= 0) return launch_small<false, BTR, EPI>(a, small, st);
+  }
+  if (wide) return launch_cfg<false, BTR, EPI, 3, 2, 64, 128, 2, 1>(a, 1, st);
+  if (us192 < us256) return launch_cfg<false, BTR, EPI, 3, 2, 32, 64, 3, 1>(a, 1, st);
+  return launch_cfg<false, BTR, EPI, 4, 2, 32, 64, 3, 1>(a, 1, st);
 }
 
 bool fits32(long long rows, long long cols) { return rows * cols * 2 < 2147483647LL; }
@@ -430,8 +525,19 @@ int gemm_bf16_wgrad(long long rows, int K, int N, const bf16_t* x, const bf16_t*
   a.k_per_split = stages * 32;
   a.part = splits > 1 ? (float*)ws : dw;
   a.a_bytes = (unsigned)(rows * N * 2); a.b_bytes = (unsigned)(rows * K * 2);
+  const int force = g_cnnk_tune[15];
+  if (force == 0 || force >= 16) {
+    // the split launch and its sum, in the units of kTiles
+    const float us = 12.f + 0.6f * stages + 0.2f * splits;
+    const int small = force >= 16 ? force - 16 : pick_small(N, K, (int)rows, true, us);
+    if (small >= 0 && small != T128) {
+      a.part = dw;
+      a.k_per_split = (int)rows;
+      return launch_small<true, true, 2>(a, small, st);
+    }
+  }
   // 64-column planes (128-byte rows) measured 5-10 % slower here than 32-column ones; kept selectable
-  const int rc = g_cnnk_tune[15] == 2 ? launch_cfg<true, true, 2, 4, 32, 128>(a, splits, st) : launch_cfg<true, true, 2, 4, 32, 64>(a, splits, st);
+  const int rc = force == 2 ? launch_cfg<true, true, 2, 4, 2, 32, 128, 3, 1>(a, splits, st) : launch_cfg<true, true, 2, 4, 2, 32, 64, 3, 1>(a, splits, st);
   if (rc != CNNK_OK || splits == 1) return rc;
   const size_t n = (size_t)N * K;
   size_t blocks = (n / 4 + 255) / 256;

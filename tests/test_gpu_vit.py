@@ -137,6 +137,20 @@ def test_linear_layers(K, rows, Kd, N, dtype):
         cnnk.cnnk_tune(15, 0)
 
 
+# The tile shapes for small problems (64 x 64, 64 x 128 and 128 x 128 tiles, one or two groups of wavefronts
+# that split the reduction), each forced: single ragged tiles, a reduction shorter than one stage, stage
+# counts that the groups share unevenly (1, 3, 13 stages), and several tiles in both directions.
+@pytest.mark.parametrize("shape", range(5))
+@pytest.mark.parametrize("rows,Kd,N", [(1, 8, 8), (65, 72, 136), (130, 192, 64), (197, 776, 264), (788, 384, 1152)])
+def test_linear_small_tiles(K, rows, Kd, N, shape):
+    from paper_2503_23186_amd import cnnk
+    cnnk.cnnk_tune(15, 16 + shape)
+    try:
+        _linear_case(K, rows, Kd, N, "bf16")
+    finally:
+        cnnk.cnnk_tune(15, 0)
+
+
 def _linear_case(K, rows, Kd, N, dtype):
     rng = np.random.default_rng(rows + Kd + N)
     x = rep(rng.standard_normal((rows, Kd)), dtype)
