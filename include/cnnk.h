@@ -259,8 +259,9 @@ typedef struct cnnk_buffers {
    *    stream reaches the first other reader of the same input.
    * The step forks with ev_fork (recorded on `stream`, waited for on aux_stream) and joins with
    * ev_join (the other way round), the last time in front of the update of the remaining
-   * parameters.  aux_stream must not carry other work during the call and must have the default
-   * priority; both events are hipEvent_t handles created by the caller (timing may be disabled).
+   * parameters.  aux_stream must have the default priority; several steps may share one (what they
+   * put there then runs in the order of the calls).  Both events are hipEvent_t handles created by
+   * the caller for this buffer set alone (timing and the system-scope fence may be disabled).
    * With an aux stream the workspace must be twice cnnk_train_step_workspace_bytes.  Results are
    * bit-reproducible for a given mode; between the modes they differ by fp32 rounding (the forked
    * weight gradients split their reduction over fewer workgroups). */

@@ -418,11 +418,12 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
           return CNNK_ERR_HIP;
         rc = dgrad();
         if (rc != CNNK_OK) return rc;
-        // The update of this layer's weights follows its weight gradient on the second stream, once
-        // the data gradient (the last reader of the weights in this step) is done: the event is
-        // re-recorded behind it, and the split-K reduction of the weight gradient waits for it and
-        // applies the update in the same launch (a separate launch where nothing is reduced).
-        const bool after_dgrad = l.in0 != 0;
+        // The update of this layer's weights follows its weight gradient on the second stream, in the
+        // split-K reduction's launch (a separate launch where nothing is reduced).  A data gradient that
+        // reads the weights themselves must be done by then: the event is re-recorded behind it and the
+        // update waits for it.  The matrix-core kernels read the transposed copies made before the backward
+        // pass, so nothing waits for them.
+        const bool after_dgrad = l.in0 != 0 && w.wt_off[i] == (size_t)-1;
         if (after_dgrad && hipEventRecord((hipEvent_t)B->ev_fork, (hipStream_t)stream) != hipSuccess)
           return CNNK_ERR_HIP;
         SgdFuse fuse{B->param[l.p0], B->mom[l.p0], (bf16 && B->param_lp) ? B->param_lp[l.p0] : nullptr,

@@ -125,10 +125,10 @@ class StepRunner:
         b.events = None
         b.n_events = 0
         # second stream (default priority) + two events for the weight gradients
-        self.aux_stream = torch.cuda.Stream(device=self.dev) if two_streams else None
+        self.aux_stream = cnnk.aux_stream(self.dev) if two_streams else None
         b.aux_stream = self.aux_stream.cuda_stream if two_streams else None
-        b.ev_fork = cnnk.hip_event_create() if two_streams else None
-        b.ev_join = cnnk.hip_event_create() if two_streams else None
+        b.ev_fork = cnnk.hip_order_event_create() if two_streams else None
+        b.ev_join = cnnk.hip_order_event_create() if two_streams else None
         self.buffers = b
         self._events = None
 

@@ -228,7 +228,7 @@ class VitRunner:
             raise ValueError("unsupported ViT configuration")
         self.arena = torch.zeros(self.arena_bytes, dtype=torch.uint8, device=self.dev)
         self.ws = torch.zeros(max(self.ws_bytes, 256) * (2 if two_streams else 1), dtype=torch.uint8, device=self.dev)
-        self.aux_stream = torch.cuda.Stream(device=self.dev) if two_streams else None
+        self.aux_stream = cnnk.aux_stream(self.dev) if two_streams else None
         n = len(table)
         arr = lambda ts: (C.c_void_p * n)(*[None if t is None else t.data_ptr() for t in ts])
         self._keep = [arr(self.param), arr(self.param_lp), arr(self.grad), arr(self.mom)]
@@ -238,8 +238,8 @@ class VitRunner:
                                   None if self.probs is None else self.probs.data_ptr(), self.arena.data_ptr(),
                                   self.arena_bytes, self.ws.data_ptr(), self.ws.numel(), None, 0,
                                   self.aux_stream.cuda_stream if two_streams else None,
-                                  cnnk.hip_event_create() if two_streams else None,
-                                  cnnk.hip_event_create() if two_streams else None)
+                                  cnnk.hip_order_event_create() if two_streams else None,
+                                  cnnk.hip_order_event_create() if two_streams else None)
         self.n_calls = cnnk_vit_step_calls(self.desc)
         self.call_names = [cnnk_vit_step_call_name(self.desc, i) for i in range(self.n_calls)]
         self._events = None
