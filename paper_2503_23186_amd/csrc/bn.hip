@@ -20,6 +20,9 @@ inline int reduce_blocks(size_t m, int C) {
   const int rows = kT / (C / 8);
   // at least 8 rows per thread (ResNet-18 b256 step: 2.215 ms with 4, 2.195 with 8, 2.27 with 16)
   size_t nb = (m + (size_t)rows * 8 - 1) / ((size_t)rows * 8);
+  // a tensor that leaves CUs idle that way: one round of four rows per thread (the launch is then a
+  // chain of memory latencies, and a shorter one)
+  if (nb < 256) nb = (m + (size_t)rows * 4 - 1) / ((size_t)rows * 4);
   if (nb > kMaxBlocks) nb = kMaxBlocks;
   // every workgroup ends with 2*C scattered 4-byte writes of its partial sums: with many channels
   // fewer, longer-lived workgroups are cheaper (C = 1024: 256 instead of 2048; ResNet-50
@@ -539,10 +542,11 @@ __global__ void __launch_bounds__(kT) bwd_apply_kernel(const T* __restrict__ dy,
   });
 }
 
-// Grid of the element-wise kernels: every thread gets about eight rows, capped.
+// Grid of the element-wise kernels: every thread gets about eight rows (four where eight leave CUs idle), capped.
 inline unsigned row_blocks(size_t m, int C) {
   const int rows = kT / (C / 8);
   size_t b = (m + (size_t)rows * 8 - 1) / ((size_t)rows * 8);
+  if (b < 256) b = (m + (size_t)rows * 4 - 1) / ((size_t)rows * 4);
   if (b > 4096) b = 4096;
   return (unsigned)(b < 1 ? 1 : b);
 }

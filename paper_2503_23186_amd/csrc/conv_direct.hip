@@ -77,21 +77,36 @@ __global__ void __launch_bounds__(256) direct_wgrad_kernel(ConvGeom g, const T* 
   int t = i / g.Cin;
   const int s = t % g.S; t /= g.S;
   const int r = t % g.R;
-  const int k = t / g.R;
+  const int kk = t / g.R;
   const long M = (long)g.N * g.Ho * g.Wo;
   const long m0 = (long)blockIdx.y * chunk;
   const long m1 = (m0 + chunk < M) ? m0 + chunk : M;
+  // Eight positions per round, all loads issued before the first product (one position at a time is a
+  // chain of memory latencies behind 64-bit divisions: 29 us for a 3->16 gradient of 8192 positions,
+  // 9 us so); a position outside the image or the range reads element 0 and multiplies zero.  The
+  // position's coordinates advance by one, as the positions do.
+  int wo, ho, n;
+  {
+    wo = (int)(m0 % g.Wo);
+    const long q = m0 / g.Wo;
+    ho = (int)(q % g.Ho);
+    n = (int)(q / g.Ho);
+  }
   float acc = 0.f;
-  for (long m = m0; m < m1; ++m) {
-    const int wo = (int)(m % g.Wo);
-    const long q = m / g.Wo;
-    const int ho = (int)(q % g.Ho);
-    const int n = (int)(q / g.Ho);
-    const int hi = ho * g.stride + r - g.pad;
-    const int wi = wo * g.stride + s - g.pad;
-    if (hi < 0 || hi >= g.H || wi < 0 || wi >= g.W) continue;
-    acc = fmaf(Elem<T>::ld(dy + (size_t)m * g.Cout + k),
-               Elem<T>::ld(x + (((size_t)n * g.H + hi) * g.W + wi) * g.Cin + c), acc);
+  for (long m = m0; m < m1; m += 8) {
+    float dv[8], xv[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int hi = ho * g.stride + r - g.pad, wi = wo * g.stride + s - g.pad;
+      const bool ok = m + k < m1 && hi >= 0 && hi < g.H && wi >= 0 && wi < g.W;
+      const float d = Elem<T>::ld(dy + (ok ? (size_t)(m + k) * g.Cout + kk : (size_t)0));
+      xv[k] = Elem<T>::ld(x + (ok ? (((size_t)n * g.H + hi) * g.W + wi) * g.Cin + c : (size_t)0));
+      dv[k] = d;
+      if (!ok) { dv[k] = 0.f; xv[k] = 0.f; }
+      if (++wo == g.Wo) { wo = 0; if (++ho == g.Ho) { ho = 0; ++n; } }
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc = fmaf(dv[k], xv[k], acc);
   }
   part[(size_t)blockIdx.y * nw + i] = acc;
 }

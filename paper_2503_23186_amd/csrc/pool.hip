@@ -80,39 +80,47 @@ __global__ void __launch_bounds__(kT) maxpool_bwd_kernel(const T* __restrict__ d
   }
 }
 
+// Global average pool.  One workgroup per image and group of L channel octets: L threads side by side read
+// a position's channels, 256 / L positions at a time, and the per-thread sums (four loads in flight) are
+// combined through LDS in position order.  Bound by the latency of a thread's chain of loads: with a
+// thread per octet that walks all positions, 8 images of 16 channels at 32 x 32 took 73 us on 16 threads;
+// here 4.6 us.
 template <typename T>
-__global__ void __launch_bounds__(kT) gap_fwd_kernel(const T* __restrict__ x, T* __restrict__ y, int N, int HW,
-                                                     int C) {
-  const int C8 = C / 8;
-  const size_t total = (size_t)N * C8;
-  const size_t i = (size_t)blockIdx.x * kT + threadIdx.x;
-  if (i >= total) return;
-  const int c8 = (int)(i % C8);
-  const size_t n = i / C8;
+__global__ void __launch_bounds__(kT) gap_fwd_kernel(const T* __restrict__ x, T* __restrict__ y, int HW, int C, int L) {
+  __shared__ float red[kT * 8];
+  const int o = threadIdx.x % L, p0 = threadIdx.x / L, P = kT / L;
+  const int c8 = blockIdx.y * L + o;
+  const size_t n = blockIdx.x;
   float acc[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-  // eight positions' loads in flight at a time; the additions keep the order p = 0, 1, 2, ...
-  int p = 0;
-  for (; p + 8 <= HW; p += 8) {
-    float v[8][8];
+  if (c8 * 8 < C) {
+    const T* base = x + n * HW * C + c8 * 8;
+    for (int p = p0; p < HW; p += 4 * P) {
+      float v[4][8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) load8(x + (n * HW + p + k) * C + c8 * 8, v[k]);
+      for (int k = 0; k < 4; ++k) load8(base + (size_t)(p + k * P < HW ? p + k * P : p) * C, v[k]);
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
+      for (int k = 0; k < 4; ++k)
+        if (p + k * P < HW)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] += v[k][e];
+          for (int e = 0; e < 8; ++e) acc[e] += v[k][e];
+    }
   }
-  for (; p < HW; ++p) {
-    float v[8];
-    load8(x + (n * HW + p) * C + c8 * 8, v);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += v[e];
+  for (int e = 0; e < 8; ++e) red[e * kT + threadIdx.x] = acc[e];   // [e][position slot][octet]
+  for (int s = P / 2; s > 0; s >>= 1) {
+    __syncthreads();
+    if (p0 < s)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) red[e * kT + threadIdx.x] += red[e * kT + threadIdx.x + s * L];
   }
-  const float inv = 1.f / (float)HW;
+  if (p0 == 0 && c8 * 8 < C) {
+    const float inv = 1.f / (float)HW;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] *= inv;
-  store8(y + i * 8, acc);
+    for (int e = 0; e < 8; ++e) acc[e] = red[e * kT + o] * inv;
+    store8(y + n * C + c8 * 8, acc);
+  }
 }
 
 template <typename T>
@@ -186,12 +194,16 @@ extern "C" int cnnk_pool_fwd(const cnnk_pool_desc* d, const void* x, void* y, un
     else
       maxpool_fwd_kernel<float><<<ew_blocks(total), kT, 0, st>>>((const float*)x, (float*)y, argmax, d->N, d->H, d->W, d->C);
   } else {
-    const size_t total = (size_t)d->N * (d->C / 8);
-    const unsigned nb = (unsigned)((total + kT - 1) / kT);
+    // octets per workgroup: a power of two, enough of them for 64-byte reads, and no more threads across
+    // the positions than there are positions
+    const int HW = d->H * d->W;
+    int L = 4;
+    while (L < 32 && L * 8 < d->C && (L * HW < kT || d->N * ((d->C / 8 + L - 1) / L) > 1024)) L *= 2;
+    const dim3 grid((unsigned)d->N, (unsigned)((d->C / 8 + L - 1) / L));
     if (d->dtype == CNNK_BF16)
-      gap_fwd_kernel<bf16_t><<<nb, kT, 0, st>>>((const bf16_t*)x, (bf16_t*)y, d->N, d->H * d->W, d->C);
+      gap_fwd_kernel<bf16_t><<<grid, kT, 0, st>>>((const bf16_t*)x, (bf16_t*)y, HW, d->C, L);
     else
-      gap_fwd_kernel<float><<<nb, kT, 0, st>>>((const float*)x, (float*)y, d->N, d->H * d->W, d->C);
+      gap_fwd_kernel<float><<<grid, kT, 0, st>>>((const float*)x, (float*)y, HW, d->C, L);
   }
   return launch_status();
 }

@@ -12,6 +12,10 @@ namespace {
 // grid budget (in compute units) of a weight gradient that runs beside the backward pass: measured
 // optimum on ResNet-18 b256 (96..128 are within 1 %, 64 and 192 are 3 % slower)
 constexpr int kAuxWgradCus = 112;
+// Flops of the convolutions of a step from which its second stream is used.  Below, the step is a chain of
+// launches of a few us and the events between the streams cost more than the overlap gives (tiny CNN of
+// 21 MFLOP: 184 us with, 160 us without; VGG-style network at batch 16, 7 GFLOP: even).
+constexpr double kAuxMinFlops = 2e9;
 constexpr int kStatSlots = 4;   // convolutions whose per-channel sums may be pending at once
 constexpr size_t kStatBytes = kStatSlots * 2 * 2048 * sizeof(float);
 
@@ -23,6 +27,7 @@ struct Walk {
   std::vector<size_t> wt_off;        // per layer: offset into that region, or (size_t)-1
   int x8_layer = -1;                 // first-layer convolution with fewer than 8 input channels, if any:
   size_t x8_off = 0;                 // its 8-channel copy of the network input lives in the same region
+  double flops = 0;                  // of the convolutions, forward and backward
   int dtype = -1;
 };
 
@@ -71,6 +76,7 @@ int walk_layers(const cnnk_layer* L, int n, int n_slots, int n_params, Walk* w) 
              set_elems(w->slot_elems, l.in0, (size_t)d.N * d.H * d.W * d.Cin) &&
              set_elems(w->slot_elems, l.out, (size_t)d.N * Ho * Wo * d.Cout) &&
              set_elems(w->param_elems, l.p0, (size_t)d.Cout * d.R * d.S * d.Cin);
+        w->flops += 2.0 * d.N * Ho * Wo * d.Cout * d.R * d.S * d.Cin * (l.in0 == 0 ? 2 : 3);
         for (int p = 0; p < 3; ++p) w->ws = max_sz(w->ws, cnnk_conv2d_workspace_bytes(&d, p));
         if (dgrad_pretransposed(l)) {
           w->wt_off[i] = w->wt_bytes;
@@ -213,7 +219,7 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
   hipStream_t aux = nullptr;
   if (B->aux_stream && B->ev_fork && B->ev_join && !timing) {
     if (B->ws_bytes < 2 * ws_one) return CNNK_ERR_WORKSPACE;
-    aux = (hipStream_t)B->aux_stream;
+    if (w.flops >= kAuxMinFlops) aux = (hipStream_t)B->aux_stream;
   }
   void* const aux_ws = static_cast<char*>(B->ws) + ws_one;
   const size_t aux_wsb = aux ? B->ws_bytes - ws_one : 0;

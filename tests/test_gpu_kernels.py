@@ -430,3 +430,19 @@ def test_sgd_unaligned_tensors(K):
     torch.cuda.synchronize()
     assert max_rel_err(host(gw[1:]), w_ref) <= 1e-6 and max_rel_err(host(gv[1:]), v_ref) <= 1e-6
     assert host(gw[:1])[0] == w[0] and host(gv[:1])[0] == v[0]
+
+
+# one position, fewer positions than threads, many; one octet, a ragged last group of octets, the most; and a
+# batch that widens the groups
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shape", [(3, 1, 1, 8), (2, 3, 5, 40), (2, 4, 4, 2048), (8, 32, 32, 16), (700, 2, 2, 72)])
+def test_global_average_pool(K, shape, dtype):
+    N, H, W, C = shape
+    x = rep(np.random.default_rng(H * W + C).standard_normal(shape), dtype)
+    d = K.pool_desc(N, H, W, C, K.BF16 if dtype == "bf16" else K.F32, K.POOL_GAP)
+    got = torch.zeros((N, 1, 1, C), dtype=dev(x, dtype).dtype, device="cuda:0")
+    K.cnnk_pool_fwd(d, dev(x, dtype), got, None)
+    torch.cuda.synchronize()
+    # bf16 storage: eight significant bits, so a rounding of 2^-8 of the largest element plus the fp32 sum's
+    # own error; fp32: 1024 additions in short chains
+    assert max_rel_err(host(got), ref.pool_fwd(x, "gap")[0]) <= (4e-3 if dtype == "bf16" else 1e-6)
