@@ -294,8 +294,9 @@ int cnnk_train_step(const cnnk_layer* layers, int n_layers, const cnnk_buffers* 
 /* Validation pass of Algorithm 1's epoch loop on one batch: the forward half of cnnk_train_step
  * over the same layer list in inference mode (every batch norm normalises with
  * buf->bn_running, which must be given), then loss, pred and, if n_correct is not NULL,
- * *n_correct += #{pred == label}.  Reads param / param_lp and bn_running; overwrites act[1..],
- * pool_idx, probs (if given) and the workspace; leaves parameters, gradients, momentum, saved and
+ * *n_correct += #{pred == label}.  Reads param / param_lp and bn_running; may overwrite act[1..]
+ * (the output of a convolution that only one batch norm or sum reads is not stored: that layer is part
+ * of the convolution's launch), pool_idx, probs (if given) and the workspace; leaves parameters, gradients, momentum, saved and
  * running statistics untouched.  Runs on `stream` alone (aux_stream and events are ignored); the
  * workspace of cnnk_train_step_workspace_bytes suffices. */
 int cnnk_eval_step(const cnnk_layer* layers, int n_layers, const cnnk_buffers* buf,

@@ -15,6 +15,50 @@ static inline ConvGeom make_geom(const cnnk_conv_desc* d) {
   return g;
 }
 
+// What a forward kernel does with its fp32 accumulators before it rounds and stores them, for the validation
+// pass: an inference-mode batch norm (gamma null: none), a residual added to the rounded value, a ReLU.
+// The convolution's own output is then never stored.
+struct ConvTail {
+  const float* gamma;
+  const float* beta;
+  const float* mean;
+  const float* var;
+  float eps;
+  const bf16_t* res;   // nullable: same shape as the output
+  int relu;
+};
+// y = act(sc * acc + bi) per channel, the coefficients of channel c
+__device__ __forceinline__ void tail_coef(const ConvTail& t, int c, bool ok, float* sc, float* bi) {
+  *sc = 1.f;
+  *bi = 0.f;
+  if (t.gamma && ok) {
+    *sc = t.gamma[c] * (1.f / sqrtf(t.var[c] + t.eps));
+    *bi = fmaf(-t.mean[c], *sc, t.beta[c]);
+  }
+}
+// one accumulator (16 pixels of one channel) through the batch norm and, unless a residual follows, the ReLU
+__device__ __forceinline__ f32x16_t tail_acc(f32x16_t v, float sc, float bi, bool relu) {
+  f32x16_t o;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const float t = fmaf(v[r], sc, bi);
+    o[r] = relu && !(t > 0.f) ? 0.f : t;
+  }
+  return o;
+}
+// residual and ReLU on eight stored channels
+__device__ __forceinline__ uint4 tail_residual(const ConvTail& t, uint4 v, uint4 res) {
+  float x[8], r[8];
+  unpack8(v, x);
+  unpack8(res, r);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    x[e] += r[e];
+    if (t.relu) x[e] = x[e] > 0.f ? x[e] : 0.f;
+  }
+  return uint4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
+}
+
 // direct kernels (any shape, both dtypes)
 size_t conv_direct_wgrad_ws(const ConvGeom& g);
 int conv_direct_fwd(const ConvGeom& g, int dtype, const void* x, const void* w, void* y, hipStream_t st);
@@ -28,7 +72,7 @@ int reduce_partials(const float* part, float* out, int n, int P, hipStream_t st)
 bool conv_mfma_supported(const ConvGeom& g, int pass);
 size_t conv_mfma_ws(const ConvGeom& g, int pass, bool want_stats);
 int conv_mfma_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y, float* ch_sum,
-                  float* ch_sumsq, void* ws, hipStream_t st);
+                  float* ch_sumsq, void* ws, hipStream_t st, const ConvTail* tail = nullptr);
 int conv_mfma_dgrad(const ConvGeom& g, const bf16_t* dy, const bf16_t* w, bf16_t* dx, int accumulate,
                     void* ws, hipStream_t st);
 int conv_mfma_wgrad(const ConvGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, void* ws,
@@ -55,7 +99,8 @@ int conv_mfma_dgrad_pt(const ConvGeom& g, const bf16_t* dy, const bf16_t* wt, bf
 // 3x3 stride-1 kernels with the input patch resident in LDS (forward, data gradient)
 bool conv_patch_supported(const ConvGeom& g, int pass);
 int conv_patch_stat_rows(const ConvGeom& g);
-int conv_patch_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y, float* stats, hipStream_t st);
+int conv_patch_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y, float* stats, hipStream_t st,
+                   const ConvTail* tail = nullptr);
 int conv_patch_dgrad(const ConvGeom& g, const bf16_t* dy, const bf16_t* wt, bf16_t* dx, int accumulate,
                      hipStream_t st);
 
@@ -71,7 +116,7 @@ int conv_wgrad_dma_launch(const ConvGeom& g, const bf16_t* x, const bf16_t* dy, 
 bool conv_pad_supported(const ConvGeom& g);
 size_t conv_pad_ws(const ConvGeom& g, int pass, bool want_stats);
 int conv_pad_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y, float* ch_sum, float* ch_sumsq,
-                 void* ws, hipStream_t st);
+                 void* ws, hipStream_t st, const ConvTail* tail = nullptr);
 int conv_pad_wgrad(const ConvGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, void* ws, hipStream_t st);
 // Hook 1 of 3 (see "Hooks between cnnk_train_step and the convolution entry points" below).
 // The forward and the weight-gradient call of such a layer both need the 8-channel copy of x.  When
@@ -90,7 +135,7 @@ extern thread_local X8Cache* t_cnnk_x8_cache;
 bool conv_first_supported(const ConvGeom& g);
 size_t conv_first_ws(const ConvGeom& g);
 int conv_first_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y, float* ch_sum, float* ch_sumsq,
-                   void* ws, hipStream_t st);
+                   void* ws, hipStream_t st, const ConvTail* tail = nullptr);
 bool conv_first_wgrad_supported(const ConvGeom& g);   // additionally W % 16 == 0
 size_t conv_first_wgrad_ws(const ConvGeom& g);
 int conv_first_wgrad(const ConvGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, void* ws, hipStream_t st);
@@ -133,6 +178,12 @@ extern int g_cnnk_tune[16];
 // of the backward pass: fewer, longer-lived workgroups leave the other stream room to run.
 // Workspace sizes are always computed for the whole device (the upper bound).
 extern thread_local int t_cnnk_wgrad_cus;
+
+// Forward convolution with a tail (no per-channel sums), for the shapes a matrix-core kernel takes
+// (conv_tail_supported); CNNK_ERR_UNSUPPORTED, and nothing launched, for the others.
+bool conv_tail_supported(const cnnk_conv_desc* d);
+int conv_fwd_tail(const cnnk_conv_desc* d, const void* x, const void* w, void* y, const ConvTail& tail, void* ws,
+                  size_t ws_bytes, hipStream_t st);
 
 // per-channel sum / sum of squares of a tensor with C channels (used when the conv kernel
 // itself does not produce them)

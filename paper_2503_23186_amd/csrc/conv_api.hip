@@ -78,6 +78,25 @@ extern "C" int cnnk_conv2d_fwd(const cnnk_conv_desc* d, const void* x, const voi
   return rc;
 }
 
+bool conv_tail_supported(const cnnk_conv_desc* d) {
+  const ConvGeom g = make_geom(d);
+  return g.Cout % 8 == 0 && (use_mfma(d, g, CNNK_PASS_FWD) || use_first(d, g) || use_pad(d, g, CNNK_PASS_FWD));
+}
+
+int conv_fwd_tail(const cnnk_conv_desc* d, const void* x, const void* w, void* y, const ConvTail& tail, void* ws,
+                  size_t ws_bytes, hipStream_t st) {
+  const ConvGeom g = make_geom(d);
+  if (use_mfma(d, g, CNNK_PASS_FWD))
+    return conv_mfma_fwd(g, (const bf16_t*)x, (const bf16_t*)w, (bf16_t*)y, nullptr, nullptr, ws, st, &tail);
+  if (use_first(d, g))
+    return conv_first_fwd(g, (const bf16_t*)x, (const bf16_t*)w, (bf16_t*)y, nullptr, nullptr, ws, st, &tail);
+  if (use_pad(d, g, CNNK_PASS_FWD)) {
+    if (!ws || ws_bytes < cnnk_conv2d_workspace_bytes(d, CNNK_PASS_FWD)) return CNNK_ERR_WORKSPACE;
+    return conv_pad_fwd(g, (const bf16_t*)x, (const bf16_t*)w, (bf16_t*)y, nullptr, nullptr, ws, st, &tail);
+  }
+  return CNNK_ERR_UNSUPPORTED;
+}
+
 extern "C" int cnnk_conv2d_dgrad(const cnnk_conv_desc* d, const void* dy, const void* w, void* dx, int accumulate,
                                  void* ws, size_t ws_bytes, void* stream) {
   int rc = cnnk_validate_conv(d);

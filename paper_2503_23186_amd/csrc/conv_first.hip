@@ -21,6 +21,7 @@ struct FirstArgs {
   float* stats;    // nullable: [2][Cout][nblocks] per-workgroup column sums and sums of squares
   int N, H, W, Cout, M, nblocks;
   FastDiv dW, dH;
+  ConvTail tail;   // TAIL kernels only
 };
 
 __device__ __forceinline__ bf16x8_t pack8(const bf16_t* v) {
@@ -30,7 +31,8 @@ __device__ __forceinline__ bf16x8_t pack8(const bf16_t* v) {
 }
 
 // TN: 32-column tiles of output channels (1: Cout <= 32, 2: Cout <= 64)
-template <int TN>
+// TAIL: the epilogue applies a ConvTail (validation pass)
+template <int TN, bool TAIL>
 __global__ void __launch_bounds__(kT) first_fwd_kernel(FirstArgs a) {
   constexpr int LDW = TN * 32 + 8;
   __shared__ __align__(16) bf16_t strips[kT / 64][8][LDW];
@@ -127,6 +129,17 @@ __global__ void __launch_bounds__(kT) first_fwd_kernel(FirstArgs a) {
     }
   }
 
+  if constexpr (TAIL) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      float sc, bi;
+      const int c = j * 32 + (lane & 31);
+      tail_coef(a.tail, c, c < a.Cout, &sc, &bi);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) acc[i][j] = tail_acc(acc[i][j], sc, bi, a.tail.relu && !a.tail.res);
+    }
+  }
+
   // wave-local epilogue: 8 rows x TN*32 columns at a time through the wave's LDS strip
   bf16_t* Cw = &strips[wave][0][0];
   constexpr int CH = TN * 4;   // 16-byte chunks per strip row
@@ -145,8 +158,11 @@ __global__ void __launch_bounds__(kT) first_fwd_kernel(FirstArgs a) {
       asm volatile("" ::: "memory");
       if (lrow < 8) {
         const int m = m0 + i * 32 + q * 8 + lrow, co = ch * 8;
-        if (m < a.M && co < a.Cout)
-          *reinterpret_cast<uint4*>(a.y + (size_t)m * a.Cout + co) = *reinterpret_cast<const uint4*>(Cw + lrow * LDW + ch * 8);
+        if (m < a.M && co < a.Cout) {
+          uint4 v = *reinterpret_cast<const uint4*>(Cw + lrow * LDW + ch * 8);
+          if (TAIL && a.tail.res) v = tail_residual(a.tail, v, *reinterpret_cast<const uint4*>(a.tail.res + (size_t)m * a.Cout + co));
+          *reinterpret_cast<uint4*>(a.y + (size_t)m * a.Cout + co) = v;
+        }
       }
       asm volatile("" ::: "memory");
     }
@@ -311,8 +327,9 @@ size_t conv_first_ws(const ConvGeom& g) {
 }
 
 int conv_first_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y, float* ch_sum, float* ch_sumsq,
-                   void* ws, hipStream_t st) {
+                   void* ws, hipStream_t st, const ConvTail* tail) {
   FirstArgs a{};
+  if (tail) a.tail = *tail;
   a.x = x; a.w = w; a.y = y;
   a.stats = ch_sum ? reinterpret_cast<float*>(ws) : nullptr;
   a.N = g.N; a.H = g.H; a.W = g.W; a.Cout = g.Cout;
@@ -320,8 +337,13 @@ int conv_first_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* 
   a.nblocks = conv_first_stat_rows(g);
   a.dW.init((unsigned)g.W);
   a.dH.init((unsigned)g.H);
-  if (g.Cout <= 32) first_fwd_kernel<1><<<a.nblocks, kT, 0, st>>>(a);
-  else first_fwd_kernel<2><<<a.nblocks, kT, 0, st>>>(a);
+  if (tail) {
+    if (g.Cout <= 32) first_fwd_kernel<1, true><<<a.nblocks, kT, 0, st>>>(a);
+    else first_fwd_kernel<2, true><<<a.nblocks, kT, 0, st>>>(a);
+    return launch_status();
+  }
+  if (g.Cout <= 32) first_fwd_kernel<1, false><<<a.nblocks, kT, 0, st>>>(a);
+  else first_fwd_kernel<2, false><<<a.nblocks, kT, 0, st>>>(a);
   if (launch_status() != CNNK_OK) return CNNK_ERR_HIP;
   if (!ch_sum) return CNNK_OK;
   return channel_sums_finalize(a.stats, a.nblocks, g.Cout, ch_sum, ch_sumsq, st);

@@ -96,7 +96,7 @@ size_t conv_pad_ws(const ConvGeom& g, int pass, bool want_stats) {
 }
 
 int conv_pad_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y, float* ch_sum, float* ch_sumsq,
-                 void* ws, hipStream_t st) {
+                 void* ws, hipStream_t st, const ConvTail* tail) {
   char* base = static_cast<char*>(ws);
   X8Cache* cache = t_cnnk_x8_cache;
   bf16_t* x8 = cache ? cache->buf : reinterpret_cast<bf16_t*>(base);
@@ -106,7 +106,7 @@ int conv_pad_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y,
   if (cache) cache->valid = true;
   pad_channels_kernel<<<pad_blocks(px + wr), 256, 0, st>>>(x, x8, px, w, w8, wr, g.Cin);
   if (launch_status() != CNNK_OK) return CNNK_ERR_HIP;
-  return conv_mfma_fwd(padded(g), x8, w8, y, ch_sum, ch_sumsq, rest, st);
+  return conv_mfma_fwd(padded(g), x8, w8, y, ch_sum, ch_sumsq, rest, st, tail);
 }
 
 int conv_pad_wgrad(const ConvGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, void* ws, hipStream_t st) {

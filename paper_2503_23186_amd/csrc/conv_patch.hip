@@ -33,6 +33,7 @@ struct PatchArgs {
   int perm;           // row permutation of the pixel tile, see tile_pixel()
   int toff_h[9], toff_w[9], widx[9];  // patch offset (0..2, 0..2) and weight tap of each step
   FastDiv dPW, dPH, dW, dTH, dH;      // divisors used to decode pixel indices
+  ConvTail tail;                      // TAIL kernels only
 };
 
 // LDS rows are dense 64-byte rows (32 channels) whose four 16-byte chunks are XOR-swizzled with
@@ -90,7 +91,9 @@ __device__ __forceinline__ int tile_pixel(int rho, int perm) {
 // The path from L2 into a CU moves a fixed number of requests per clock whatever their size up to a
 // 128-byte line, and a workgroup of these layers streams all 4.6 K reduction rows of its 64 filters
 // (590 KB with 512 channels): in 64-byte pieces that alone took longer than the MFMAs.
-template <int BM, int BN, int WM, int WN, int OCC, int PL, int KG>
+//
+// TAIL: the epilogue applies a ConvTail (validation pass) instead of writing statistics or accumulating.
+template <int BM, int BN, int WM, int WN, int OCC, int PL, int KG, bool TAIL>
 __global__ void __launch_bounds__(kThreads * KG, OCC) patch_kernel(PatchArgs a) {
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
   constexpr int B_IT = (BN + 63) / 64;  // 64 weight rows per pass (4 chunks of 8 channels per row)
@@ -315,7 +318,16 @@ __global__ void __launch_bounds__(kThreads * KG, OCC) patch_kernel(PatchArgs a) 
   // mtiles * WM rows in all, reduced by a finalising kernel), then eight passes of 8 rows x 64
   // columns through LDS so that every lane stores 16 contiguous bytes.
   auto epilogue = [&](int mtile, int par) __attribute__((always_inline)) {
-    if (a.stats) {
+    if (TAIL) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        float sc, bi;
+        const int col = nt * BN + wn * TN * 32 + j * 32 + (lane & 31);
+        tail_coef(a.tail, col, col < a.Cd, &sc, &bi);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[i][j] = tail_acc(acc[i][j], sc, bi, a.tail.relu && !a.tail.res);
+      }
+    } else if (a.stats) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         float s1 = 0.f, s2 = 0.f;
@@ -350,6 +362,18 @@ __global__ void __launch_bounds__(kThreads * KG, OCC) patch_kernel(PatchArgs a) 
     const int g4 = lane >> 4, i16 = lane & 15;
     const int wr_off = (lane & 31) * SP + (lane >> 5) * 8;
     const int rd_off = (g4 * 8 + (i16 >> 2)) * SP + (i16 & 3) * 8;
+    uint4 rv[TAIL ? TM * TN * 2 : 1];    // the residual's pieces of the whole tile, in flight together
+    if (TAIL && a.tail.res) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb) {
+            const int m = mbase + tile_pixel(wm * TM * 32 + i * 32 + rb * 16 + i16, a.perm), co = nt * BN + wn * TN * 32 + j * 32 + g4 * 8;
+            rv[(i * TN + j) * 2 + rb] = *reinterpret_cast<const uint4*>(a.tail.res + (m < M && co < a.Cd ? (size_t)m * a.Cd + co : (size_t)0));
+          }
+    }
     uint4 pend[2];
     int pend_i = 0, pend_j = 0;
     auto flush = [&](int i, int j) __attribute__((always_inline)) {
@@ -359,7 +383,9 @@ __global__ void __launch_bounds__(kThreads * KG, OCC) patch_kernel(PatchArgs a) 
         const int m = mbase + tile_pixel(row, a.perm), co = nt * BN + wn * TN * 32 + j * 32 + g4 * 8;
         if (m < M && co < a.Cd) {
           bf16_t* dp = a.dst + (size_t)m * a.Cd + co;
-          if (a.accumulate) {
+          if (TAIL) {
+            *reinterpret_cast<uint4*>(dp) = a.tail.res ? tail_residual(a.tail, pend[rb], rv[(i * TN + j) * 2 + rb]) : pend[rb];
+          } else if (a.accumulate) {
             float o[8], nw[8];
             load8(dp, o);
             unpack8(pend[rb], nw);
@@ -491,9 +517,9 @@ size_t patch_smem(int patch_px) {
   return (size_t)2 * (patch_px * 64 < 4 * 32 * 72 ? 4 * 32 * 72 : patch_px * 64) + (size_t)6 * BN * 64;
 }
 
-template <int BM, int BN, int WM, int WN, int OCC, int PL, int KG>
+template <int BM, int BN, int WM, int WN, int OCC, int PL, int KG, bool TAIL>
 int launch_patch_kg(PatchArgs& a, hipStream_t st) {
-  auto kern = patch_kernel<BM, BN, WM, WN, KG == 1 ? OCC : 1, PL, KG>;
+  auto kern = patch_kernel<BM, BN, WM, WN, KG == 1 ? OCC : 1, PL, KG, TAIL>;
   static bool attr_done = false;
   if (!attr_done) {
     const int most = KG * (int)patch_smem<BM, BN>(PL * kPxPerLoad) + 128;   // the largest patch the template takes
@@ -507,7 +533,7 @@ int launch_patch_kg(PatchArgs& a, hipStream_t st) {
   return launch_status();
 }
 
-template <int BM, int BN, int WM, int WN, int OCC, int PL>
+template <int BM, int BN, int WM, int WN, int OCC, int PL, bool TAIL>
 int launch_patch(PatchArgs& a, hipStream_t st) {
   const long M = (long)a.N * a.H * a.W;
   a.ntiles = (a.Cd + BN - 1) / BN;
@@ -522,7 +548,7 @@ int launch_patch(PatchArgs& a, hipStream_t st) {
   // (an even number of channel chunks, both groups' buffers within the CU's 160 KB)
   const bool split = a.tpb == 1 && (long)a.ntiles * a.mtiles < 512 && (a.Cs / CK) % 2 == 0 && g_cnnk_tune[13] >= 0 &&
                      2 * patch_smem<BM, BN>(a.TI * (a.TH + 2) * (a.W + 2)) + 128 <= 160 * 1024;
-  return split ? launch_patch_kg<BM, BN, WM, WN, OCC, PL, 2>(a, st) : launch_patch_kg<BM, BN, WM, WN, OCC, PL, 1>(a, st);
+  return split ? launch_patch_kg<BM, BN, WM, WN, OCC, PL, 2, TAIL>(a, st) : launch_patch_kg<BM, BN, WM, WN, OCC, PL, 1, TAIL>(a, st);
 }
 
 bool plan_patch(const ConvGeom& g, int Cs, int Cd, PatchPlan* p) {
@@ -553,17 +579,18 @@ bool plan_patch(const ConvGeom& g, int Cs, int Cd, PatchPlan* p) {
   return tile_geometry(g, p->bm, cand[best][2] * kPxPerLoad, &p->ti, &p->th);
 }
 
+template <bool TAIL>
 int run_patch(const ConvGeom& g, PatchArgs& a, const PatchPlan& p, hipStream_t st) {
   a.TI = p.ti; a.TH = p.th;
   a.perm = (a.W == 8 && a.TH == 8) ? 1 : (a.W == 4 && a.TH == 4 && a.TI % 4 == 0) ? 2 : 0;
   if (g_cnnk_tune[7] < 0) a.perm = 0;
   a.dPW.init(a.W + 2); a.dPH.init(a.TH + 2); a.dW.init(a.W); a.dTH.init(a.TH); a.dH.init(a.H);
-  if (p.bm == 256 && p.bn == 128) return launch_patch<256, 128, 2, 2, 2, 6>(a, st);
+  if (p.bm == 256 && p.bn == 128) return launch_patch<256, 128, 2, 2, 2, 6, TAIL>(a, st);
   if (p.bm == 256 && p.bn == 64)
-    return a.TI * (a.TH + 2) * (a.W + 2) <= 6 * kPxPerLoad ? launch_patch<256, 64, 4, 1, 2, 6>(a, st)
-                                                            : launch_patch<256, 64, 4, 1, 2, 7>(a, st);
-  if (p.bm == 128 && p.bn == 128) return launch_patch<128, 128, 2, 2, 2, 5>(a, st);
-  if (p.bm == 128 && p.bn == 64) return launch_patch<128, 64, 4, 1, 2, 5>(a, st);
+    return a.TI * (a.TH + 2) * (a.W + 2) <= 6 * kPxPerLoad ? launch_patch<256, 64, 4, 1, 2, 6, TAIL>(a, st)
+                                                            : launch_patch<256, 64, 4, 1, 2, 7, TAIL>(a, st);
+  if (p.bm == 128 && p.bn == 128) return launch_patch<128, 128, 2, 2, 2, 5, TAIL>(a, st);
+  if (p.bm == 128 && p.bn == 64) return launch_patch<128, 64, 4, 1, 2, 5, TAIL>(a, st);
   (void)g;
   return CNNK_ERR_UNSUPPORTED;
 }
@@ -585,7 +612,8 @@ int conv_patch_stat_rows(const ConvGeom& g) {
   return (int)(((long)g.N * g.H * g.W + p.bm - 1) / p.bm) * wm;
 }
 
-int conv_patch_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y, float* stats, hipStream_t st) {
+int conv_patch_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y, float* stats, hipStream_t st,
+                   const ConvTail* tail) {
   PatchPlan p;
   if (!plan_patch(g, g.Cin, g.Cout, &p)) return CNNK_ERR_UNSUPPORTED;
   PatchArgs a{};
@@ -595,7 +623,9 @@ int conv_patch_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* 
     for (int s = 0; s < 3; ++s) {
       a.toff_h[r * 3 + s] = r; a.toff_w[r * 3 + s] = s; a.widx[r * 3 + s] = r * 3 + s;
     }
-  return run_patch(g, a, p, st);
+  if (!tail) return run_patch<false>(g, a, p, st);
+  a.tail = *tail;
+  return run_patch<true>(g, a, p, st);
 }
 
 // wt: weights already transposed to [Cin][9][Cout]
@@ -611,5 +641,5 @@ int conv_patch_dgrad(const ConvGeom& g, const bf16_t* dy, const bf16_t* wt, bf16
     for (int s = 0; s < 3; ++s) {
       a.toff_h[r * 3 + s] = 2 - r; a.toff_w[r * 3 + s] = 2 - s; a.widx[r * 3 + s] = r * 3 + s;
     }
-  return run_patch(g, a, p, st);
+  return run_patch<false>(g, a, p, st);
 }

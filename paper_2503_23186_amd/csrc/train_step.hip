@@ -548,8 +548,52 @@ extern "C" int cnnk_eval_step(const cnnk_layer* L, int n, const cnnk_buffers* B,
   }
   void* ws = static_cast<char*>(B->ws) + kStatBytes + w.wt_bytes;
   const size_t wsb = B->ws_bytes - kStatBytes - w.wt_bytes;
+  // A convolution whose output goes into nothing but one batch norm (or one sum) is run when the walk
+  // reaches that layer, which then is the tail of the convolution's own launch: the pass over the
+  // convolution's output is saved (ResNet-50 at batch 200: 0.7 of 2.2 ms).  Only where every tensor has one
+  // writer, so that the convolution's input is what it was.
+  std::vector<int> tail_of(n, -1);    // tail_of[j] = i: layer j runs as the tail of convolution i
+  std::vector<char> deferred(n, 0);
+  if (bf16) {
+    std::vector<int> readers(w.slot_elems.size(), 0), writers(w.slot_elems.size(), 0), conv_of(w.slot_elems.size(), -1);
+    for (int i = 0; i < n; ++i) {
+      const cnnk_layer& l = L[i];
+      ++readers[l.in0];
+      if ((l.op == CNNK_OP_BN || l.op == CNNK_OP_ADD) && l.in1 >= 0) ++readers[l.in1];
+      if (l.op != CNNK_OP_FC_LOSS) ++writers[l.out];
+      if (l.op == CNNK_OP_CONV) conv_of[l.out] = i;
+    }
+    bool single = writers[0] == 0;
+    for (size_t s = 0; s < writers.size(); ++s) single = single && writers[s] <= 1;
+    auto alone = [&](int slot) { return slot >= 0 && conv_of[slot] >= 0 && readers[slot] == 1 ? conv_of[slot] : -1; };
+    for (int j = 0; j < n && single; ++j) {
+      const cnnk_layer& l = L[j];
+      int i = -1;
+      if (l.op == CNNK_OP_BN) i = alone(l.in0);
+      if (l.op == CNNK_OP_ADD && l.in0 != l.in1) i = alone(l.in0) >= 0 ? alone(l.in0) : alone(l.in1);
+      if (i < 0 || i > j || !conv_tail_supported(&L[i].d.conv)) continue;
+      if (l.op == CNNK_OP_BN && l.d.bn.C != L[i].d.conv.Cout) continue;
+      tail_of[j] = i;
+      deferred[i] = 1;
+    }
+  }
   for (int i = 0; i < n && rc == CNNK_OK; ++i) {
     const cnnk_layer& l = L[i];
+    if (deferred[i]) continue;
+    if (tail_of[i] >= 0) {
+      const cnnk_layer& c = L[tail_of[i]];
+      ConvTail t{};
+      if (l.op == CNNK_OP_BN) {
+        t.gamma = B->param[l.p0]; t.beta = B->param[l.p1];
+        t.mean = B->bn_running[i]; t.var = B->bn_running[i] + l.d.bn.C;
+        t.eps = l.d.bn.eps; t.relu = l.d.bn.relu;
+        t.res = l.in1 >= 0 ? static_cast<const bf16_t*>(B->act[l.in1]) : nullptr;
+      } else {
+        t.res = static_cast<const bf16_t*>(B->act[l.in0 == c.out ? l.in1 : l.in0]);
+      }
+      rc = conv_fwd_tail(&c.d.conv, B->act[c.in0], B->param_lp[c.p0], B->act[l.out], t, ws, wsb, (hipStream_t)stream);
+      continue;
+    }
     switch (l.op) {
       case CNNK_OP_CONV: {
         const void* wt = bf16 ? B->param_lp[l.p0] : (const void*)B->param[l.p0];

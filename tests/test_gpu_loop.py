@@ -350,3 +350,43 @@ def test_strategy_selection_from_a_measured_profile():
         want_t, want_a = asa_ref.solve_brute_force(as_dicts, 4, 2, bw, 5e-6, caps)
         assert want_a is not None and plan.time == pytest.approx(want_t, rel=1e-12)
         assert asa_ref.feasible(as_dicts, plan.assignment, 4, 2, caps)
+
+
+# A convolution that runs with its batch norm (and residual, and ReLU) as the tail of its launch: the patch
+# kernels (3x3 stride 1; a ragged channel tile, an even number of chunks split over wave groups), the gathered
+# kernel (1x1, strided, ragged rows), with and without a residual.  Each tail is checked on the tensor that the
+# launch before it left on the device.
+@pytest.mark.parametrize("k,stride,c0,c1,size,batch", [(3, 1, 32, 72, 16, 2), (3, 1, 64, 64, 8, 9), (3, 1, 128, 64, 4, 3), (1, 1, 64, 256, 7, 3),
+                                                       (1, 1, 24, 40, 5, 1), (3, 2, 32, 64, 9, 2), (1, 2, 64, 136, 8, 5)])
+def test_convolution_tail_of_the_validation_pass(k, stride, c0, c1, size, batch):
+    from paper_2503_23186_amd import StepRunner
+    net = WL.Net("tail", batch, "bf16")
+    a = net.bn(net.conv(net.slot(batch, size, size, 3), c0, 3, 1))
+    r = net.bn(net.conv(a, c1, 1, stride), relu=False)
+    y0 = net.bn(net.conv(a, c1, k, stride))
+    y1 = net.bn(net.conv(a, c1, k, stride), relu=True, res=r)
+    t = net.add(net.conv(y1, c1, 1, 1), y0)
+    net.fc_loss(net.pool(t, "gap"))
+    inp = WL.make_inputs(net, 7, perturb_bn=True)
+    running = perturbed_running(net, 9)
+    run = StepRunner(net.layers, net.slots, [p["shape"] for p in net.params], net.dtype)
+    run.load(inp["x"], inp["labels"], inp["params"], inp["mom"])
+    for i, (rm, rv) in running.items():
+        run.bn_running[i].copy_(torch.from_numpy(np.stack([rm, rv]).astype(np.float32)))
+    cnnk().cnnk_eval_step(run.c_layers, len(net.layers), run.buffers, run.labels, run.loss, run.pred, None,
+                          torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    convs = {L["y"]: L for L in net.layers if L["op"] == "conv"}
+    for i, L in enumerate(net.layers):
+        if L["op"] == "bn":
+            cv = convs[L["x"]]
+            z = ops.conv2d_fwd(host(run.act[cv["x"]]), inp["params"][cv["w"]], cv["stride"], cv["pad"])
+            res = host(run.act[L["res"]]) if L["res"] >= 0 else None
+            want = ops.bn_relu_infer(z, inp["params"][L["gamma"]], inp["params"][L["beta"]], *running[i], relu=bool(L["relu"]), residual=res)
+        elif L["op"] == "add":
+            cv = convs[L["a"]]
+            want = ops.conv2d_fwd(host(run.act[cv["x"]]), inp["params"][cv["w"]], cv["stride"], cv["pad"]) + host(run.act[L["b"]])
+        else:
+            continue
+        # one bf16 rounding (2^-8 of the largest element), and a second one where a residual is added
+        assert max_rel_err(host(run.act[L["y"]]), want) <= (8e-3 if L["op"] == "add" or L["res"] >= 0 else 4e-3), (i, L)
