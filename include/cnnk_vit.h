@@ -117,7 +117,10 @@ int cnnk_vit_embed_bwd(const cnnk_embed_desc* d, const void* dtok, void* dz, flo
  * pass reaches them, so the step forks each onto aux_stream and joins before the update; beside the
  * main stream they fill the compute units that its launches leave idle.  ws must then hold twice
  * cnnk_vit_workspace_bytes (the forked calls use the upper half).  Ignored while `events` is set (a
- * call's time is then its own).  Results are bit-identical with and without it. */
+ * call's time is then its own).  Results are bit-identical with and without it.
+ * bf16 steps without `events` make the weight gradients, bias gradients, layer norms' final sums and
+ * updates of several blocks in shared launches and take GELU's gradient inside fc2's data gradient;
+ * with `events` the calls are made one by one.  The two agree to the rounding of the sums. */
 typedef struct { int B, image, patch, dim, heads, layers, mlp, classes; int dtype; float ln_eps; } cnnk_vit_desc;
 typedef struct cnnk_vit_buffers {
   int n_params;

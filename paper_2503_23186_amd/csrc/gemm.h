@@ -11,6 +11,23 @@ int gemm_bf16_fwd(long long rows, int K, int N, const bf16_t* x, const bf16_t* w
                   bf16_t* u, bf16_t* y, hipStream_t st);
 // dx = dy w
 int gemm_bf16_dgrad(long long rows, int K, int N, const bf16_t* dy, const bf16_t* w, bf16_t* dx, hipStream_t st);
+// dg = dy w, du = dg (as stored) * gelu'(u): the data gradient through the layer and the activation before it
+int gemm_bf16_dgrad_gelu(long long rows, int K, int N, const bf16_t* dy, const bf16_t* w, const bf16_t* u, bf16_t* dg, bf16_t* du,
+                         hipStream_t st);
 // dw = dy^T x (fp32); ws: gemm_bf16_wgrad_ws bytes of partial sums
 size_t gemm_bf16_wgrad_ws(long long rows, int K, int N);
 int gemm_bf16_wgrad(long long rows, int K, int N, const bf16_t* x, const bf16_t* dy, float* dw, void* ws, hipStream_t st);
+// The same for up to gemm_bf16_wgrad_group_max() layers in one launch, each with (db not null) the column sums of
+// its dy.  K and N multiples of 8, 16-byte aligned pointers, every matrix below 2 GiB.
+struct GemmWgrad {
+  const bf16_t* dy;    // [rows][N]
+  const bf16_t* x;     // [rows][K]
+  float* dw;           // [N][K]
+  float* db;           // [N], nullable
+  long long rows;
+  int K, N;
+};
+int gemm_bf16_wgrad_group_max();
+int gemm_bf16_wgrad_tiles(int K, int N);      // workgroups of a large group that one layer stands for
+size_t gemm_bf16_wgrad_group_ws(const GemmWgrad* p, int n);      // reads rows, K, N only
+int gemm_bf16_wgrad_group(const GemmWgrad* p, int n, void* ws, hipStream_t st);

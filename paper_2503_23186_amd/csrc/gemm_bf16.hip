@@ -86,15 +86,17 @@ struct Args {
   const bf16_t* A;
   const bf16_t* B;
   bf16_t* C;          // bf16 output [M][N] (EPI 0, 1)
-  bf16_t* C2;         // EPI 1: gelu(C)
-  float* part;        // EPI 2: fp32 partials [splits][M][N]
+  bf16_t* C2;         // EPI 1: gelu(C); EPI 4: C * gelu'(res)
+  float* part;        // EPI 2: fp32 output, or partials zstride elements apart
+  float* rsum;        // EPI 2, nullable: [M] sums of A over the reduction (likewise zstride apart)
+  size_t zstride;
   const float* bias;  // [N] or null
-  const bf16_t* res;  // EPI 3: [M][N] added to the rounded output (a residual connection)
+  const bf16_t* res;  // EPI 3: [M][N] added to the rounded output (a residual connection); EPI 4: gelu's argument
   int M, N, K;        // output rows, output columns, reduction length
   int lda, ldb, ldc;
   int k_per_split;    // reduction elements per blockIdx.z (a multiple of BK)
   int mtiles, ntiles;
-  unsigned a_bytes, b_bytes;
+  unsigned a_bytes, b_bytes, c_bytes;
 };
 
 // gelu(u) = u/2 (1 + erf(u / sqrt 2)) with erf(t) = t P(t^2) on |t| <= 3, P of degree 8 fitted to erf(t) / t
@@ -119,8 +121,30 @@ __device__ __forceinline__ float gelu_f(float u) {
   return fmaf(hu, t * p, hu);
 }
 
+// gelu'(u) = Phi(u) + u phi(u).  erfc(|u| / sqrt 2) by Abramowitz and Stegun 7.1.26 (absolute error 1.5e-7),
+// whose exponential is phi's.
+__device__ __forceinline__ float gelu_grad_f(float u) {
+  const float e = __expf(-0.5f * u * u);
+  const float t = __builtin_amdgcn_rcpf(fmaf(fabsf(u), 0.3275911f * 0.70710678f, 1.0f));
+  float p = 1.061405429f;
+  p = fmaf(p, t, -1.453152027f);
+  p = fmaf(p, t, 1.421413741f);
+  p = fmaf(p, t, -0.284496736f);
+  p = fmaf(p, t, 0.254829592f);
+  const float q = 0.5f * p * t * e;                 // Phi(-|u|)
+  return fmaf(u * 0.39894228040143268f, e, u < 0.f ? q : 1.0f - q);
+}
+
+// sum of the eight bf16 elements of an operand fragment
+__device__ __forceinline__ float sum8(bf16x8_t f) {
+  float v[8];
+  unpack8(__builtin_bit_cast(uint4, f), v);
+  return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+}
+
+// One workgroup's tile (mt, nt) over the reduction range of split z.
 template <bool ATR, bool BTR, int EPI, int TM, int TN, int BK, int RB, int NSTAGE, int KG>
-__global__ void __launch_bounds__(256 * KG, (Cfg<TM, TN, BK, RB, NSTAGE, KG>::WPE)) gemm_kernel(Args a) {
+__device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) {
   using C = Cfg<TM, TN, BK, RB, NSTAGE, KG>;
   constexpr int NW = C::NW, BN = C::BN;
   constexpr int BM = C::BM, A_BYTES = C::A_BYTES, STAGE_B = C::STAGE_B, NLOAD = C::NLOAD, NST = C::NST;
@@ -136,25 +160,8 @@ __global__ void __launch_bounds__(256 * KG, (Cfg<TM, TN, BK, RB, NSTAGE, KG>::WP
   const int tid = threadIdx.x & 255;                                                     // within the group
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, h = lane >> 5, g = lane >> 4, i16 = lane & 15;
-  // workgroups that share an XCD's L2 (every 8th) walk consecutive tiles: same rows of A, all of B
-  // (the grid is 8 * ceil(tiles / 8) workgroups; the few past the end leave at once).  An XCD owns a
-  // contiguous range of the row-major tile list, i.e. a band of tile rows, and walks it column by
-  // column: the workgroups in flight on it then share the band's rows of A, which stay in its L2,
-  // while B streams through once per XCD.
-  const int ntot = a.mtiles * a.ntiles, chunk = (ntot + 7) >> 3;
-  const int c0 = (blockIdx.x & 7) * chunk, c1 = min(c0 + chunk, ntot);
-  int l = blockIdx.x >> 3;
-  if (c0 + l >= c1) return;
-  const int r0 = c0 / a.ntiles, s0 = c0 - r0 * a.ntiles, r1 = (c1 - 1) / a.ntiles, e1 = (c1 - 1) - r1 * a.ntiles + 1;
-  int mt = r0, nt = 0;
-  for (; nt < a.ntiles; ++nt) {
-    const int first = nt >= s0 ? 1 : 0;                 // the band's first row has this column
-    const int cnt = r0 == r1 ? ((nt >= s0 && nt < e1) ? 1 : 0) : (r1 - r0 - 1) + first + (nt < e1 ? 1 : 0);
-    if (l < cnt) { mt = r0 + l + (1 - first); break; }
-    l -= cnt;
-  }
   const int m0 = mt * BM, n0 = nt * BN;
-  int kbeg = blockIdx.z * a.k_per_split;
+  int kbeg = z * a.k_per_split;
   int kend = kbeg + a.k_per_split;
   if (kend > a.K) kend = a.K;
   int nst = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
@@ -249,6 +256,13 @@ __global__ void __launch_bounds__(256 * KG, (Cfg<TM, TN, BK, RB, NSTAGE, KG>::WP
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
+  // sums of A over the reduction (a bias gradient), by the wavefronts that hold the first column of tiles:
+  // the operand is in their registers, and the vector ALU has room beside the MFMAs
+  const bool row_sums = EPI == 2 && KG == 1 && a.rsum != nullptr && nt == 0 && wn == 0;
+  float rs[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) rs[i] = 0.f;
+
 #pragma unroll
   for (int d = 0; d < NST - 1; ++d)
     if (d < nst) issue(d, d * STAGE_B);
@@ -281,6 +295,12 @@ __global__ void __launch_bounds__(256 * KG, (Cfg<TM, TN, BK, RB, NSTAGE, KG>::WP
 #pragma unroll
           for (int j = 0; j < TN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks][i], bfr[ks][j], acc[i][j], 0, 0, 0);
+      if (row_sums) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int i = 0; i < TM; ++i) rs[i] += sum8(af[ks][i]);
+      }
     }
     cur += STAGE_B;
     if (cur == NST * STAGE_B) cur = 0;
@@ -310,7 +330,15 @@ __global__ void __launch_bounds__(256 * KG, (Cfg<TM, TN, BK, RB, NSTAGE, KG>::WP
           for (int r = 0; r < 16; ++r) acc[i][j][r] += R[((k * TM * TN + i * TN + j) * 16 + r) * 256 + tid];
   }
   if (EPI == 2) {
-    float* out = a.part + (size_t)blockIdx.z * a.M * a.ldc;
+    float* out = a.part + (size_t)z * a.zstride;
+    if (row_sums) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const float t = rs[i] + __shfl_xor(rs[i], 32, 64);     // the two halves of every reduction step
+        const int row = m0 + wm * (TM * 32) + i * 32 + lane;
+        if (lane < 32 && row < a.M) a.rsum[(size_t)z * a.zstride + row] = t;
+      }
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -329,7 +357,20 @@ __global__ void __launch_bounds__(256 * KG, (Cfg<TM, TN, BK, RB, NSTAGE, KG>::WP
 
   const int wr_off = (lane & 31) * SP + h * 8;
   const int rd_off = (g * 8 + (i16 >> 2)) * SP + (i16 & 3) * 8;
-  auto transpose_store = [&](const float* v, bf16_t* dst, int i, int j) __attribute__((always_inline)) {
+  // Loads and stores of the epilogue are buffer operations: a position outside the output reads zeros and
+  // stores nothing, without a branch, so the number in flight is known and a wait is for what it needs.
+  const __amdgpu_buffer_rsrc_t c_rs = make_rsrc(a.C, a.c_bytes);
+  const __amdgpu_buffer_rsrc_t c2_rs = EPI == 1 || EPI == 4 ? make_rsrc(a.C2, a.c_bytes) : c_rs;
+  const __amdgpu_buffer_rsrc_t r_rs = EPI == 3 || EPI == 4 ? make_rsrc(a.res, a.c_bytes) : c_rs;
+  auto place = [&](int i, int j, int rb) __attribute__((always_inline)) -> unsigned {
+    const int row = m0 + wm * (TM * 32) + i * 32 + rb * 16 + i16, col = n0 + wn * (TN * 32) + j * 32 + g * 8;
+    return row < a.M && col < a.N ? (unsigned)(row * a.ldc + col) * 2u : kOobOffset;
+  };
+  auto store16 = [&](__amdgpu_buffer_rsrc_t rs_, uint4 v, unsigned off) __attribute__((always_inline)) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4_t, v), rs_, (int)off, 0, 0);
+  };
+  // 32 x 32 values through the wave's strip: lane (g, i16) gets the eight columns g * 8 .. of rows i16 and 16 + i16
+  auto transpose = [&](const float* v, uint4* out) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       *reinterpret_cast<uint2*>(S + wr_off + q * 16) = make_uint2(pack_bf16x2(v[q * 4], v[q * 4 + 1]), pack_bf16x2(v[q * 4 + 2], v[q * 4 + 3]));
@@ -339,24 +380,22 @@ __global__ void __launch_bounds__(256 * KG, (Cfg<TM, TN, BK, RB, NSTAGE, KG>::WP
       const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(S + rd_off + rb * 32));
       const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(S + rd_off + 4 * SP + rb * 32));
       const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-      const int row = m0 + wm * (TM * 32) + i * 32 + rb * 16 + i16, col = n0 + wn * (TN * 32) + j * 32 + g * 8;
-      if (row < a.M && col < a.N) {
-        uint4 out = uint4{l2.x, l2.y, h2.x, h2.y};
-        if (EPI == 3) {     // + residual: the sum of two stored values, rounded again
-          float x[8], r[8];
-          unpack8(out, x);
-          load8(a.res + (size_t)row * a.ldc + col, r);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) x[e] += r[e];
-          out = uint4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
-        }
-        *reinterpret_cast<uint4*>(dst + (size_t)row * a.ldc + col) = out;
-      }
+      out[rb] = uint4{l2.x, l2.y, h2.x, h2.y};
     }
     asm volatile("" ::: "memory");
   };
+  // the residual (or gelu's argument) of a 32-row block is fetched while the block before it is worked on
+  uint4 rv[2][TN][2];
+  auto fetch = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) rv[i & 1][j][rb] = buffer_load16(r_rs, place(i, j, rb), 0);
+  };
+  if (EPI == 3 || EPI == 4) fetch(0);
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    if ((EPI == 3 || EPI == 4) && i + 1 < TM) fetch(i + 1);
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int colv = n0 + wn * (TN * 32) + j * 32 + (lane & 31);
@@ -364,14 +403,120 @@ __global__ void __launch_bounds__(256 * KG, (Cfg<TM, TN, BK, RB, NSTAGE, KG>::WP
       float v[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) v[r] = acc[i][j][r] + bv;
-      transpose_store(v, a.C, i, j);
+      uint4 o[2];
+      transpose(v, o);
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        if (EPI == 3) {     // + residual: the sum of two stored values, rounded again
+          float x[8], r[8];
+          unpack8(o[rb], x);
+          unpack8(rv[i & 1][j][rb], r);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) x[e] += r[e];
+          o[rb] = uint4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
+        }
+        store16(c_rs, o[rb], place(i, j, rb));
+        if (EPI == 4) {     // the gradient of the activation's argument, from the gradient as stored
+          float x[8], r[8];
+          unpack8(o[rb], x);
+          unpack8(rv[i & 1][j][rb], r);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) x[e] *= gelu_grad_f(r[e]);
+          store16(c2_rs, uint4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])}, place(i, j, rb));
+        }
+      }
       if (EPI == 1) {
         // the activation of the value as stored
 #pragma unroll
         for (int r = 0; r < 16; ++r) v[r] = gelu_f(bf16_to_f32(f32_to_bf16_hw(v[r])));
-        transpose_store(v, a.C2, i, j);
+        transpose(v, o);
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) store16(c2_rs, o[rb], place(i, j, rb));
       }
     }
+  }
+}
+
+template <bool ATR, bool BTR, int EPI, int TM, int TN, int BK, int RB, int NSTAGE, int KG>
+__global__ void __launch_bounds__(256 * KG, (Cfg<TM, TN, BK, RB, NSTAGE, KG>::WPE)) gemm_kernel(Args a) {
+  // workgroups that share an XCD's L2 (every 8th) walk consecutive tiles: same rows of A, all of B
+  // (the grid is 8 * ceil(tiles / 8) workgroups; the few past the end leave at once).  An XCD owns a
+  // contiguous range of the row-major tile list, i.e. a band of tile rows, and walks it column by
+  // column: the workgroups in flight on it then share the band's rows of A, which stay in its L2,
+  // while B streams through once per XCD.
+  const int ntot = a.mtiles * a.ntiles, chunk = (ntot + 7) >> 3;
+  const int c0 = (blockIdx.x & 7) * chunk, c1 = min(c0 + chunk, ntot);
+  int l = blockIdx.x >> 3;
+  if (c0 + l >= c1) return;
+  const int r0 = c0 / a.ntiles, s0 = c0 - r0 * a.ntiles, r1 = (c1 - 1) / a.ntiles, e1 = (c1 - 1) - r1 * a.ntiles + 1;
+  int mt = r0, nt = 0;
+  for (; nt < a.ntiles; ++nt) {
+    const int first = nt >= s0 ? 1 : 0;                 // the band's first row has this column
+    const int cnt = r0 == r1 ? ((nt >= s0 && nt < e1) ? 1 : 0) : (r1 - r0 - 1) + first + (nt < e1 ? 1 : 0);
+    if (l < cnt) { mt = r0 + l + (1 - first); break; }
+    l -= cnt;
+  }
+  gemm_tile<ATR, BTR, EPI, TM, TN, BK, RB, NSTAGE, KG>(a, mt, nt, blockIdx.z);
+}
+
+// Several weight gradients in one launch.  Alone, one of ViT-B/16's has 18 to 72 tiles of 256 x 128 for 256
+// CUs and had to be split three to ten ways over its rows, each split a partial to write and to add up; the
+// tiles of two blocks together fill the device unsplit.
+constexpr int kGroupMax = 32;
+struct GroupProblem {
+  const bf16_t* dy;
+  const bf16_t* x;
+  float* dw;
+  float* db;
+  int rows, K, N, ntiles, tile0;
+};
+struct GroupArgs {
+  int count, tiles, splits;
+  GroupProblem p[kGroupMax];
+  float* part;                 // splits > 1: [splits][elements of all problems]
+  size_t zstride;              // elements of all problems
+  size_t off[kGroupMax];       // splits > 1: where problem i starts in a partial (dw, then db)
+};
+template <int TM, int TN, int BK, int RB, int NSTAGE>
+__global__ void __launch_bounds__(256, (Cfg<TM, TN, BK, RB, NSTAGE, 1>::WPE)) wgrad_group_kernel(GroupArgs ga) {
+  // an XCD (every 8th workgroup) owns a contiguous range of the tile list
+  const int chunk = (ga.tiles + 7) >> 3, l = blockIdx.x >> 3;
+  const int tile = (blockIdx.x & 7) * chunk + l;
+  if (l >= chunk || tile >= ga.tiles) return;
+  int i = 0;
+  while (i + 1 < ga.count && tile >= ga.p[i + 1].tile0) ++i;
+  const GroupProblem& p = ga.p[i];
+  Args a{};
+  a.A = p.dy; a.B = p.x;
+  a.M = p.N; a.N = p.K; a.K = p.rows; a.lda = p.N; a.ldb = p.K; a.ldc = p.K;
+  a.a_bytes = (unsigned)p.rows * (unsigned)p.N * 2u; a.b_bytes = (unsigned)p.rows * (unsigned)p.K * 2u;
+  const int stages = ((p.rows + BK - 1) / BK + ga.splits - 1) / ga.splits;
+  a.k_per_split = stages * BK;
+  if (ga.splits > 1) {
+    a.part = ga.part + ga.off[i];
+    a.rsum = p.db ? a.part + (size_t)p.N * p.K : nullptr;
+    a.zstride = ga.zstride;
+  } else {
+    a.part = p.dw;
+    a.rsum = p.db;
+  }
+  const int q = tile - p.tile0, mt = q / p.ntiles;
+  gemm_tile<true, true, 2, TM, TN, BK, RB, NSTAGE, 1>(a, mt, q - mt * p.ntiles, blockIdx.z);
+}
+// sums of the partials of a group, in split order
+__global__ void __launch_bounds__(256) sum_group_kernel(GroupArgs ga) {
+  for (size_t e = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; e < ga.zstride; e += (size_t)gridDim.x * 1024) {
+    float4 s = *reinterpret_cast<const float4*>(ga.part + e);
+    for (int z = 1; z < ga.splits; ++z) {
+      const float4 v = *reinterpret_cast<const float4*>(ga.part + (size_t)z * ga.zstride + e);
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+    int i = 0;
+    while (i + 1 < ga.count && e >= ga.off[i + 1]) ++i;
+    const size_t k = e - ga.off[i], nw = (size_t)ga.p[i].N * ga.p[i].K;      // both multiples of 8
+    if (k < nw) *reinterpret_cast<float4*>(ga.p[i].dw + k) = s;
+    else if (ga.p[i].db) *reinterpret_cast<float4*>(ga.p[i].db + (k - nw)) = s;
+  }
 }
 
 // out[i] = sum over splits (ascending) of part[z][i]; n a multiple of 4
@@ -496,7 +641,7 @@ int gemm_bf16_fwd(long long rows, int K, int N, const bf16_t* x, const bf16_t* w
   a.A = x; a.B = w; a.bias = bias; a.res = res;
   a.C = gelu ? u : y; a.C2 = gelu ? y : nullptr;
   a.M = (int)rows; a.N = N; a.K = K; a.lda = K; a.ldb = K; a.ldc = N; a.k_per_split = K;
-  a.a_bytes = (unsigned)(rows * K * 2); a.b_bytes = (unsigned)((long long)N * K * 2);
+  a.a_bytes = (unsigned)(rows * K * 2); a.b_bytes = (unsigned)((long long)N * K * 2); a.c_bytes = (unsigned)(rows * N * 2);
   if (res) return launch_nat<false, 3>(a, st);
   return gelu ? launch_nat<false, 1>(a, st) : launch_nat<false, 0>(a, st);
 }
@@ -505,8 +650,17 @@ int gemm_bf16_dgrad(long long rows, int K, int N, const bf16_t* dy, const bf16_t
   Args a{};
   a.A = dy; a.B = w; a.C = dx;
   a.M = (int)rows; a.N = K; a.K = N; a.lda = N; a.ldb = K; a.ldc = K; a.k_per_split = N;
-  a.a_bytes = (unsigned)(rows * N * 2); a.b_bytes = (unsigned)((long long)N * K * 2);
+  a.a_bytes = (unsigned)(rows * N * 2); a.b_bytes = (unsigned)((long long)N * K * 2); a.c_bytes = (unsigned)(rows * K * 2);
   return launch_nat<true, 0>(a, st);
+}
+
+int gemm_bf16_dgrad_gelu(long long rows, int K, int N, const bf16_t* dy, const bf16_t* w, const bf16_t* u, bf16_t* dg, bf16_t* du,
+                         hipStream_t st) {
+  Args a{};
+  a.A = dy; a.B = w; a.C = dg; a.C2 = du; a.res = u;
+  a.M = (int)rows; a.N = K; a.K = N; a.lda = N; a.ldb = K; a.ldc = K; a.k_per_split = N;
+  a.a_bytes = (unsigned)(rows * N * 2); a.b_bytes = (unsigned)((long long)N * K * 2); a.c_bytes = (unsigned)(rows * K * 2);
+  return launch_nat<true, 4>(a, st);
 }
 
 size_t gemm_bf16_wgrad_ws(long long rows, int K, int N) {
@@ -524,6 +678,7 @@ int gemm_bf16_wgrad(long long rows, int K, int N, const bf16_t* x, const bf16_t*
   const int stages = (((int)rows + 31) / 32 + splits - 1) / splits;
   a.k_per_split = stages * 32;
   a.part = splits > 1 ? (float*)ws : dw;
+  a.zstride = (size_t)N * K;
   a.a_bytes = (unsigned)(rows * N * 2); a.b_bytes = (unsigned)(rows * K * 2);
   const int force = g_cnnk_tune[15];
   if (force == 0 || force >= 16) {
@@ -543,5 +698,80 @@ int gemm_bf16_wgrad(long long rows, int K, int N, const bf16_t* x, const bf16_t*
   size_t blocks = (n / 4 + 255) / 256;
   if (blocks > 2048) blocks = 2048;
   sum_partials_kernel<<<(unsigned)blocks, 256, 0, st>>>((const float*)ws, splits, n, dw);
+  return launch_status();
+}
+
+// ---- groups of weight gradients --------------------------------------------------------------------------
+namespace {
+struct GroupPlan {
+  bool large;      // 256 x 128 tiles, else 64 x 128
+  int tiles, splits;
+};
+int group_tiles(const GemmWgrad* p, int n, int bm) {
+  int t = 0;
+  for (int i = 0; i < n; ++i) t += ceil_div(p[i].N, bm) * ceil_div(p[i].K, 128);
+  return t;
+}
+// 256 x 128 tiles where they give every CU one (unsplit), 64 x 128 tiles otherwise, the row range then split
+// until the device holds two workgroups per CU (but never below eight stages of 64 rows each).
+GroupPlan plan_group(const GemmWgrad* p, int n) {
+  GroupPlan g;
+  g.tiles = group_tiles(p, n, 256);
+  g.large = g.tiles >= 192;
+  g.splits = 1;
+  if (g.large) return g;
+  g.tiles = group_tiles(p, n, 64);
+  long long rows = p[0].rows;
+  for (int i = 1; i < n; ++i) rows = p[i].rows < rows ? p[i].rows : rows;
+  g.splits = 512 / g.tiles;
+  if (g.splits > (int)(rows / 512)) g.splits = (int)(rows / 512);
+  if (g.splits < 1) g.splits = 1;
+  return g;
+}
+size_t group_elems(const GemmWgrad* p, int n) {
+  size_t e = 0;
+  for (int i = 0; i < n; ++i) e += (size_t)p[i].N * p[i].K + p[i].N;
+  return e;
+}
+}  // namespace
+
+int gemm_bf16_wgrad_group_max() { return kGroupMax; }
+int gemm_bf16_wgrad_tiles(int K, int N) { return ceil_div(N, 256) * ceil_div(K, 128); }
+
+size_t gemm_bf16_wgrad_group_ws(const GemmWgrad* p, int n) {
+  const GroupPlan g = plan_group(p, n);
+  return g.splits > 1 ? (size_t)g.splits * group_elems(p, n) * sizeof(float) : 0;
+}
+
+int gemm_bf16_wgrad_group(const GemmWgrad* p, int n, void* ws, hipStream_t st) {
+  if (n < 1 || n > kGroupMax) return CNNK_ERR_SHAPE;
+  const GroupPlan g = plan_group(p, n);
+  GroupArgs a{};
+  a.count = n; a.splits = g.splits; a.part = (float*)ws; a.zstride = group_elems(p, n);
+  size_t off = 0;
+  for (int i = 0; i < n; ++i) {
+    const int nt = ceil_div(p[i].K, 128);
+    a.p[i] = GroupProblem{p[i].dy, p[i].x, p[i].dw, p[i].db, (int)p[i].rows, p[i].K, p[i].N, nt, a.tiles};
+    a.off[i] = off;
+    a.tiles += ceil_div(p[i].N, g.large ? 256 : 64) * nt;
+    off += (size_t)p[i].N * p[i].K + p[i].N;
+  }
+  const dim3 grid(8 * ((a.tiles + 7) / 8), 1, g.splits);
+  auto go = [&](auto kern, int smem, bool* raised) -> int {
+    if (!*raised) {
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess)
+        return CNNK_ERR_HIP;
+      *raised = true;
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, a);
+    return launch_status();
+  };
+  static bool raised_l = false, raised_s = false;
+  const int rc = g.large ? go(wgrad_group_kernel<4, 2, 32, 64, 3>, Cfg<4, 2, 32, 64, 3, 1>::SMEM, &raised_l)
+                         : go(wgrad_group_kernel<1, 2, 64, 128, 3>, Cfg<1, 2, 64, 128, 3, 1>::SMEM, &raised_s);
+  if (rc != CNNK_OK || g.splits == 1) return rc;
+  size_t blocks = (a.zstride / 4 + 255) / 256;
+  if (blocks > 2048) blocks = 2048;
+  sum_group_kernel<<<(unsigned)blocks, 256, 0, st>>>(a);
   return launch_status();
 }

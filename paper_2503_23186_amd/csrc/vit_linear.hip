@@ -3,6 +3,7 @@
 // the 1 x 1 convolution kernels followed by the bias / activation kernel.
 #include "common.h"
 #include "gemm.h"
+#include "vit.h"
 #include "../../include/cnnk_vit.h"
 
 extern int g_cnnk_tune[16];
@@ -23,6 +24,8 @@ cnnk_conv_desc as_conv(long long rows, int K, int N, int dtype) {
   return c;
 }
 }  // namespace
+
+bool linear_dense(long long rows, int K, int N, int dtype) { return check(rows, K, N, dtype) == CNNK_OK && fast(rows, K, N, dtype); }
 
 extern "C" size_t cnnk_linear_workspace_bytes(long long rows, int K, int N, int dtype) {
   if (check(rows, K, N, dtype) != CNNK_OK) return 0;

@@ -3,6 +3,7 @@
 // token assembly.  All are bound by memory traffic: 8- or 16-byte accesses, fp32 arithmetic,
 // reductions over rows as per-workgroup partial sums that a second launch adds in a fixed order.
 #include "common.h"
+#include "vit.h"
 #include "../../include/cnnk_vit.h"
 
 namespace {
@@ -199,6 +200,32 @@ __global__ void __launch_bounds__(kT) colsum_finalize_kernel(const float* __rest
   }
 }
 
+// The same for the partials of several layer norms, one per blockIdx.y.
+__global__ void __launch_bounds__(kT) ln_finalize_group_kernel(LnFinalizeTable t, int nb, int C) {
+  __shared__ float sm[4][64];
+  const int cl = threadIdx.x & 63, pl = threadIdx.x >> 6;
+  const int c = blockIdx.x * 64 + cl, n = 2 * C;
+  const float* __restrict__ part = t.part[blockIdx.y];
+  float s = 0.f;
+  if (c < n) {
+    int b = pl;
+    for (; b + 60 < nb; b += 64) {
+      float v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = part[(size_t)(b + 4 * k) * n + c];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) s += v[k];
+    }
+    for (; b < nb; b += 4) s += part[(size_t)b * n + c];
+  }
+  sm[pl][cl] = s;
+  __syncthreads();
+  if (pl == 0 && c < n) {
+    const float r = (sm[0][cl] + sm[1][cl]) + (sm[2][cl] + sm[3][cl]);
+    if (c < C) t.dgamma[blockIdx.y][c] = r; else t.dbeta[blockIdx.y][c - C] = r;
+  }
+}
+
 // ---- bias, GELU, residual ----------------------------------------------------------------------------
 __device__ __forceinline__ float gelu_f(float u) { return 0.5f * u * (1.0f + erff(u * 0.70710678118654752f)); }
 __device__ __forceinline__ float gelu_grad_f(float u) {
@@ -339,32 +366,51 @@ __global__ void __launch_bounds__(kT) embed_fwd_kernel(const T* __restrict__ z, 
 // (b ascending) of dtok[b][t].  One thread per octet of one image's token block.
 template <typename T>
 __global__ void __launch_bounds__(kT) embed_bwd_kernel(const T* __restrict__ dtok, T* __restrict__ dz,
-                                                       float* __restrict__ dpos, int B, int Tn, int D8) {
+                                                       float* __restrict__ dpos, float* __restrict__ dcls, int B, int Tn, int D8) {
   const size_t o = (size_t)blockIdx.x * kT + threadIdx.x;
   if (o >= (size_t)Tn * D8) return;
   const int t = (int)(o / (size_t)D8);
   float acc[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) acc[k] = 0.f;
-  for (int b = 0; b < B; ++b) {
-    float v[8];
-    load8(dtok + ((size_t)b * Tn * D8 + o) * 8, v);
+  // eight images' loads in flight at a time (one at a time, 96 images of 65 tokens took 35 us)
+  for (int b0 = 0; b0 < B; b0 += 8) {
+    float v[8][8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) acc[k] += v[k];
-    if (t > 0) store8(dz + ((size_t)b * (Tn - 1) * D8 + (o - (size_t)D8)) * 8, v);
+    for (int q = 0; q < 8; ++q) load8(dtok + ((size_t)min(b0 + q, B - 1) * Tn * D8 + o) * 8, v[q]);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (b0 + q >= B) break;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc[k] += v[q][k];
+      if (t > 0) store8(dz + ((size_t)(b0 + q) * (Tn - 1) * D8 + (o - (size_t)D8)) * 8, v[q]);
+    }
   }
   store8(dpos + o * 8, acc);
+  if (t == 0)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) dcls[o * 8 + k] = acc[k];
 }
 
-// dcls = dpos[0]; dbe[c] = sum over the patch positions t = 1.. (ascending) of dpos[t][c]
-__global__ void __launch_bounds__(kT) embed_bwd_finalize_kernel(const float* __restrict__ dpos, float* __restrict__ dbe,
-                                                                float* __restrict__ dcls, int Tn, int D) {
-  const int c = blockIdx.x * kT + threadIdx.x;
-  if (c >= D) return;
-  dcls[c] = dpos[c];
+// dbe[c] = sum over the patch positions t = 1.. of dpos[t][c]: 64 columns per workgroup, four threads per
+// column with sixteen loads in flight each (one thread's chain of 196 loads took 46 us), combined in order.
+__global__ void __launch_bounds__(kT) embed_bwd_finalize_kernel(const float* __restrict__ dpos, float* __restrict__ dbe, int Tn, int D) {
+  __shared__ float sm[4][64];
+  const int cl = threadIdx.x & 63, pl = threadIdx.x >> 6;
+  const int c = blockIdx.x * 64 + cl;
   float s = 0.f;
-  for (int t = 1; t < Tn; ++t) s += dpos[(size_t)t * D + c];
-  dbe[c] = s;
+  if (c < D) {
+    for (int t0 = 1 + pl; t0 < Tn; t0 += 64) {
+      float v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = t0 + 4 * k < Tn ? dpos[(size_t)(t0 + 4 * k) * D + c] : 0.f;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) s += v[k];
+    }
+  }
+  sm[pl][cl] = s;
+  __syncthreads();
+  if (pl == 0 && c < D) dbe[c] = (sm[0][cl] + sm[1][cl]) + (sm[2][cl] + sm[3][cl]);
 }
 
 __global__ void __launch_bounds__(kT) fill_zero_kernel(uint4* p, size_t n16) {
@@ -429,6 +475,21 @@ static void launch_ln_bwd(const cnnk_ln_desc* d, long long xs, int nb, const voi
     if (d->C <= 256) LN_BWD(1, 4); else if (d->C <= 1024) LN_BWD(4, 4); else LN_BWD(16, 4);
   }
 #undef LN_BWD
+}
+
+int ln_bwd_rows_partial(const cnnk_ln_desc* d, const void* dy, const void* x, const float* gamma, const float* stats,
+                        const void* dres, void* dx, float* part, hipStream_t st) {
+  const long long xs = d->x_stride ? d->x_stride : d->C;
+  const int nb = ln_bwd_blocks(d->rows);
+  if (d->dtype == CNNK_BF16) launch_ln_bwd<bf16_t>(d, xs, nb, dy, x, gamma, stats, dres, dx, part, st);
+  else launch_ln_bwd<float>(d, xs, nb, dy, x, gamma, stats, dres, dx, part, st);
+  return launch_status();
+}
+
+int ln_bwd_finalize_group(const cnnk_ln_desc* d, const LnFinalizeTable& t, hipStream_t st) {
+  if (t.count == 0) return CNNK_OK;
+  ln_finalize_group_kernel<<<dim3((2 * d->C + 63) / 64, t.count), kT, 0, st>>>(t, ln_bwd_blocks(d->rows), d->C);
+  return launch_status();
 }
 
 extern "C" int cnnk_layernorm_bwd(const cnnk_ln_desc* d, const void* dy, const void* x, const float* gamma,
@@ -560,21 +621,24 @@ extern "C" int cnnk_vit_embed_fwd(const cnnk_embed_desc* d, const void* z, const
   return launch_status();
 }
 
+int embed_bwd(const cnnk_embed_desc* d, const void* dtok, void* dz, float* dbe, float* dcls, float* dpos, hipStream_t st) {
+  const int Tn = (d->image / d->patch) * (d->image / d->patch) + 1;
+  const size_t octets = (size_t)Tn * d->dim / 8;
+  if (d->dtype == CNNK_BF16)
+    embed_bwd_kernel<bf16_t><<<(unsigned)((octets + kT - 1) / kT), kT, 0, st>>>((const bf16_t*)dtok, (bf16_t*)dz, dpos, dcls, d->B, Tn, d->dim / 8);
+  else
+    embed_bwd_kernel<float><<<(unsigned)((octets + kT - 1) / kT), kT, 0, st>>>((const float*)dtok, (float*)dz, dpos, dcls, d->B, Tn, d->dim / 8);
+  if (dbe) embed_bwd_finalize_kernel<<<(d->dim + 63) / 64, kT, 0, st>>>(dpos, dbe, Tn, d->dim);
+  return launch_status();
+}
+
 extern "C" int cnnk_vit_embed_bwd(const cnnk_embed_desc* d, const void* dtok, void* dz, float* dbe, float* dcls,
                                   float* dpos, void* stream) {
   const int rc = check_embed(d);
   if (rc != CNNK_OK) return rc;
   if (!dtok || !dz || !dbe || !dcls || !dpos) return CNNK_ERR_NULL;
   if (!aligned16(dtok) || !aligned16(dz) || !aligned16(dpos)) return CNNK_ERR_UNSUPPORTED;
-  const int Tn = (d->image / d->patch) * (d->image / d->patch) + 1;
-  const size_t octets = (size_t)Tn * d->dim / 8;
-  hipStream_t st = (hipStream_t)stream;
-  if (d->dtype == CNNK_BF16)
-    embed_bwd_kernel<bf16_t><<<(unsigned)((octets + kT - 1) / kT), kT, 0, st>>>((const bf16_t*)dtok, (bf16_t*)dz, dpos, d->B, Tn, d->dim / 8);
-  else
-    embed_bwd_kernel<float><<<(unsigned)((octets + kT - 1) / kT), kT, 0, st>>>((const float*)dtok, (float*)dz, dpos, d->B, Tn, d->dim / 8);
-  embed_bwd_finalize_kernel<<<(d->dim + kT - 1) / kT, kT, 0, st>>>(dpos, dbe, dcls, Tn, d->dim);
-  return launch_status();
+  return embed_bwd(d, dtok, dz, dbe, dcls, dpos, (hipStream_t)stream);
 }
 
 // used by the step: zero n bytes (n % 16 == 0, p 16-byte aligned) without a memset node

@@ -7,6 +7,8 @@
 #include <string.h>
 #include "common.h"
 #include "sgd.h"
+#include "gemm.h"
+#include "vit.h"
 #include "../../include/cnnk_vit.h"
 
 int cnnk_fill_zero(void* p, size_t bytes, hipStream_t st);   // vit_ops.hip
@@ -102,6 +104,33 @@ void layout(const Geo& g, Arena* a) {
 
 size_t max_sz(size_t a, size_t b) { return a > b ? a : b; }
 
+// Whether the backward pass runs with its weight gradients in groups: bf16, every product on the dense kernels.
+bool grouped(const Geo& g) {
+  const long long rows = (long long)g.rows;
+  return g.dtype == CNNK_BF16 && linear_dense(rows, g.d, 3 * g.d, g.dtype) && linear_dense(rows, g.d, g.d, g.dtype) &&
+         linear_dense(rows, g.d, g.m, g.dtype) && linear_dense(rows, g.m, g.d, g.dtype) && linear_dense((long long)g.B * g.n, g.K0, g.d, g.dtype);
+}
+// Blocks whose weight gradients share a launch: as many as give it about 400 workgroups (two for each of most
+// CUs; ViT-B/16: two blocks of 216), at most seven (28 products and the embedding's fit the table).
+int group_blocks(const Geo& g) {
+  const int t = gemm_bf16_wgrad_tiles(g.d, 3 * g.d) + gemm_bf16_wgrad_tiles(g.d, g.d) + gemm_bf16_wgrad_tiles(g.d, g.m) + gemm_bf16_wgrad_tiles(g.m, g.d);
+  int n = (400 + t - 1) / t;
+  if (n > 7) n = 7;
+  return n < 1 ? 1 : n;
+}
+// Shapes of the products of the group that ends with block l (the blocks l .. l + group_blocks - 1, or up to the
+// last one); block 0's group has the patch embedding as well.  Returns their number.
+int fill_group(const Geo& g, int l, GemmWgrad* p) {
+  int n = 0;
+  const int end = l + group_blocks(g) < g.L ? l + group_blocks(g) : g.L;
+  for (int k = l; k < end; ++k) {
+    const int kn[4][2] = {{g.m, g.d}, {g.d, g.m}, {g.d, g.d}, {g.d, 3 * g.d}};
+    for (int q = 0; q < 4; ++q) p[n++] = GemmWgrad{nullptr, nullptr, nullptr, nullptr, (long long)g.rows, kn[q][0], kn[q][1]};
+  }
+  if (l == 0) p[n++] = GemmWgrad{nullptr, nullptr, nullptr, nullptr, (long long)g.B * g.n, g.K0, g.d};
+  return n;
+}
+
 size_t workspace(const cnnk_vit_desc* v, const Geo& g) {
   size_t w = 0;
   const long long shapes[5][3] = {{(long long)g.B * g.n, g.K0, g.d}, {(long long)g.rows, g.d, 3 * g.d}, {(long long)g.rows, g.d, g.d},
@@ -113,6 +142,14 @@ size_t workspace(const cnnk_vit_desc* v, const Geo& g) {
   w = max_sz(w, cnnk_bias_act_workspace_bytes((long long)g.rows, g.m));
   cnnk_fc_desc fc = {g.B, g.d, g.classes, g.dtype};
   w = max_sz(w, cnnk_fc_workspace_bytes(&fc));
+  if (grouped(g)) {
+    for (int l = 0; l < g.L; l += group_blocks(g)) {
+      GemmWgrad p[32];
+      const int n = fill_group(g, l, p);
+      w = max_sz(w, gemm_bf16_wgrad_group_ws(p, n));
+    }
+    w = align_up(w, 256) + 2 * (size_t)g.L * align_up(cnnk_layernorm_workspace_bytes(&ln), 256);
+  }
   return align_up(w, 256);
 }
 
@@ -143,6 +180,112 @@ struct Walk {
     ++idx;
   }
 };
+
+size_t param_elems(const Geo& g, int k) {
+  const size_t d = (size_t)g.d, m = (size_t)g.m;
+  const size_t blk[B_COUNT] = {d, d, 3 * d * d, 3 * d, d * d, d, d, d, m * d, m, d * m, d};
+  const int p_tail = P_BLOCK0 + B_COUNT * g.L;
+  if (k == P_WE) return d * g.K0;
+  if (k == P_BE || k == P_CLS) return d;
+  if (k == P_POS) return (size_t)g.T * d;
+  if (k < p_tail) return blk[(k - P_BLOCK0) % B_COUNT];
+  if (k == p_tail || k == p_tail + 1) return d;
+  return k == p_tail + 2 ? (size_t)g.classes * d : (size_t)g.classes;
+}
+
+// SGD-momentum of parameters [k0, k1)
+int update_params(const Geo& g, const cnnk_vit_buffers* buf, int k0, int k1, float lr, float mu, float wd, hipStream_t st) {
+  SgdTable t;
+  t.count = 0;
+  int rc = CNNK_OK;
+  for (int k = k0; k < k1 && rc == CNNK_OK; ++k) {
+    const int i = t.count++;
+    t.w[i] = (float*)buf->param[k]; t.v[i] = (float*)buf->mom[k]; t.g[i] = (const float*)buf->grad[k];
+    t.wlp[i] = g.dtype == CNNK_BF16 ? buf->param_lp[k] : nullptr; t.n[i] = param_elems(g, k);
+    if (t.count == kSgdMaxTensors || k == k1 - 1) { rc = sgd_multi(t, lr, mu, wd, st); t.count = 0; }
+  }
+  return rc;
+}
+
+// The backward pass and the update with the products that only the update waits for in groups: the data-gradient
+// chain runs on `st`; the weight gradients of group_blocks(g) transformer blocks, with the bias gradients (column
+// sums of an operand that those products load anyway), the final sums of the blocks' layer norms and the update of
+// the blocks' parameters follow as three launches, on the second stream if there is one.  GELU's gradient is taken
+// in the epilogue of fc2's data gradient.  Per block 7 launches and half an event pair instead of 24 and 7: at batch
+// 8 the step was bound by enqueueing them, and at batch 64 split products for a fraction of the device each took 270
+// us a block where the grouped ones take 200.
+int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffers* buf, const Arena& A, float lr, float mu, float wd,
+                     bool two, hipStream_t st) {
+  const int d = g.d, m = g.m, T = g.T, G = group_blocks(g), p_tail = P_BLOCK0 + B_COUNT * g.L;
+  const long long rows = (long long)g.rows, prow = (long long)g.B * g.n;
+  const cnnk_ln_desc ln = {(int)g.rows, d, g.dtype, v->ln_eps, 0};
+  const cnnk_ln_desc ln_cls = {g.B, d, g.dtype, v->ln_eps, (long long)T * d};
+  const cnnk_attn_desc ad = {g.B, T, v->heads, d / v->heads, g.dtype};
+  const cnnk_embed_desc ed = {g.B, v->image, v->patch, d, g.dtype};
+  const size_t ln_bytes = align_up(cnnk_layernorm_workspace_bytes(&ln), 256), whole = workspace(v, g);
+  char* const base = (char*)buf->arena;
+  auto at = [&](int id, int l) -> bf16_t* { return (bf16_t*)(base + A.off[id] + A.size[id] * (size_t)(per_layer(id) ? l : 0)); };
+  auto P = [&](int k) { return (float*)buf->param[k]; };
+  auto Wm = [&](int k) { return (const bf16_t*)buf->param_lp[k]; };
+  auto Gr = [&](int k) { return (float*)buf->grad[k]; };
+  // the workspace: what a call needs, then the layer norms' partial sums (they live until their group's final sums)
+  char* const ws = (char*)buf->ws;
+  const size_t wsb = whole - 2 * (size_t)g.L * ln_bytes;
+  char* const ln_parts = ws + wsb;
+  const hipStream_t side = two ? (hipStream_t)buf->aux_stream : st;
+  void* const side_ws = two ? ws + buf->ws_bytes / 2 / 256 * 256 : ws;
+  int rc = cnnk_fill_zero(at(CNNK_VIT_DXOUT, g.L - 1), A.size[CNNK_VIT_DXOUT], st);
+  if (rc == CNNK_OK)
+    rc = cnnk_layernorm_bwd(&ln_cls, at(CNNK_VIT_DF, 0), at(CNNK_VIT_XOUT, g.L - 1), P(p_tail), (const float*)at(X_STATSF, 0), nullptr,
+                            at(CNNK_VIT_DXOUT, g.L - 1), Gr(p_tail), Gr(p_tail + 1), ws, wsb, st);
+  GemmWgrad pend[32];
+  LnFinalizeTable sums;
+  int np = 0;
+  sums.count = 0;
+  auto defer = [&](const bf16_t* dy, const bf16_t* x, int kw, int kb, long long r, int K, int N) {
+    pend[np++] = GemmWgrad{dy, x, Gr(kw), Gr(kb), r, K, N};
+  };
+  auto norm_bwd = [&](int slot, const bf16_t* dy, const bf16_t* x, int kg, const void* stats, const bf16_t* dres, bf16_t* dx) -> int {
+    float* part = (float*)(ln_parts + (size_t)slot * ln_bytes);
+    const int i = sums.count++;
+    sums.part[i] = part; sums.dgamma[i] = Gr(kg); sums.dbeta[i] = Gr(kg + 1);
+    return ln_bwd_rows_partial(&ln, dy, x, P(kg), (const float*)stats, dres, dx, part, st);
+  };
+  for (int l = g.L - 1; l >= 0 && rc == CNNK_OK; --l) {
+    const int p0 = P_BLOCK0 + B_COUNT * l;
+    const bf16_t* xin = l ? at(CNNK_VIT_XOUT, l - 1) : at(CNNK_VIT_TOK, 0);
+    bf16_t* dxin = l ? at(CNNK_VIT_DXOUT, l - 1) : at(CNNK_VIT_DTOK, 0);
+    const bf16_t *dxo = at(CNNK_VIT_DXOUT, l), *du = at(CNNK_VIT_DU, l), *dxm = at(CNNK_VIT_DXMID, l), *dqkv = at(CNNK_VIT_DQKV, l);
+    rc = gemm_bf16_dgrad_gelu(rows, m, d, dxo, Wm(p0 + B_W2), at(CNNK_VIT_U, l), at(CNNK_VIT_DG, l), at(CNNK_VIT_DU, l), st);
+    if (rc == CNNK_OK) rc = gemm_bf16_dgrad(rows, d, m, du, Wm(p0 + B_W1), at(CNNK_VIT_DH2, l), st);
+    if (rc == CNNK_OK) rc = norm_bwd(2 * l + 1, at(CNNK_VIT_DH2, l), at(CNNK_VIT_XMID, l), p0 + B_G2, at(X_STATS2, l), dxo, at(CNNK_VIT_DXMID, l));
+    if (rc == CNNK_OK) rc = gemm_bf16_dgrad(rows, d, d, dxm, Wm(p0 + B_WO), at(CNNK_VIT_DO, l), st);
+    if (rc == CNNK_OK) rc = cnnk_attention_bwd(&ad, at(CNNK_VIT_QKV, l), at(CNNK_VIT_O, l), at(CNNK_VIT_DO, l), (const float*)at(X_LSE, l), at(CNNK_VIT_DQKV, l), st);
+    if (rc == CNNK_OK) rc = gemm_bf16_dgrad(rows, d, 3 * d, dqkv, Wm(p0 + B_WQKV), at(CNNK_VIT_DH, l), st);
+    if (rc == CNNK_OK) rc = norm_bwd(2 * l, at(CNNK_VIT_DH, l), xin, p0 + B_G1, at(X_STATS1, l), dxm, dxin);
+    defer(dxo, at(CNNK_VIT_G, l), p0 + B_W2, p0 + B_C2, rows, m, d);
+    defer(du, at(CNNK_VIT_H2, l), p0 + B_W1, p0 + B_C1, rows, d, m);
+    defer(dxm, at(CNNK_VIT_O, l), p0 + B_WO, p0 + B_BO, rows, d, d);
+    defer(dqkv, at(CNNK_VIT_H, l), p0 + B_WQKV, p0 + B_BQKV, rows, d, 3 * d);
+    if (l == 0 && rc == CNNK_OK) {
+      rc = embed_bwd(&ed, at(CNNK_VIT_DTOK, 0), at(X_DZ0, 0), nullptr, Gr(P_CLS), Gr(P_POS), st);
+      defer(at(X_DZ0, 0), at(CNNK_VIT_PATCHES, 0), P_WE, P_BE, prow, g.K0, d);
+    }
+    if (l % G != 0 || rc != CNNK_OK) continue;
+    if (two && (hipEventRecord((hipEvent_t)buf->ev_fork, st) != hipSuccess || hipStreamWaitEvent(side, (hipEvent_t)buf->ev_fork, 0) != hipSuccess))
+      return CNNK_ERR_HIP;
+    rc = gemm_bf16_wgrad_group(pend, np, side_ws, side);
+    if (rc == CNNK_OK) rc = ln_bwd_finalize_group(&ln, sums, side);
+    const int last = l + G < g.L ? l + G : g.L;
+    if (rc == CNNK_OK) rc = update_params(g, buf, l ? p0 : 0, P_BLOCK0 + B_COUNT * last, lr, mu, wd, side);
+    np = 0;
+    sums.count = 0;
+  }
+  if (rc == CNNK_OK) rc = update_params(g, buf, p_tail, p_tail + 4, lr, mu, wd, st);
+  if (two && rc == CNNK_OK && (hipEventRecord((hipEvent_t)buf->ev_join, side) != hipSuccess || hipStreamWaitEvent(st, (hipEvent_t)buf->ev_join, 0) != hipSuccess))
+    rc = CNNK_ERR_HIP;
+  return rc;
+}
 
 int walk(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffers* buf, float lr, float mu, float wd, Walk& w,
          bool forward_only = false) {
@@ -217,6 +360,14 @@ int walk(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffers* buf, floa
                                 at(CNNK_VIT_DF, 0), Gr(p_tail + 2), Gr(p_tail + 3), ws, wsb, st);
   });
   // ---- backward ----
+  if (w.run && buf && !w.events && grouped(g)) {
+    bool ok = true;      // the grouped sums of split products store 16 bytes at a time
+    for (int k = 0; k < p_tail; ++k) ok = ok && (((size_t)buf->grad[k]) & 15) == 0;
+    if (ok) {
+      if (w.rc == CNNK_OK) w.rc = backward_grouped(v, g, buf, A, lr, mu, wd, two, w.st);
+      return w.rc;
+    }
+  }
   void* dxlast = at(CNNK_VIT_DXOUT, g.L - 1);
   w.call(-1, "head.zero", [&] { return cnnk_fill_zero(dxlast, A.size[CNNK_VIT_DXOUT], st); });
   w.call(-1, "head.ln.bwd", [&] {
@@ -260,27 +411,7 @@ int walk(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffers* buf, floa
       w.rc = CNNK_ERR_HIP;
   }
   w.call(-1, "update", [&] {
-    const int np = p_tail + 4;
-    const size_t sizes_blk[B_COUNT] = {(size_t)d, (size_t)d, (size_t)3 * d * d, (size_t)3 * d, (size_t)d * d, (size_t)d, (size_t)d, (size_t)d,
-                                       (size_t)m * d, (size_t)m, (size_t)d * m, (size_t)d};
-    SgdTable t;
-    t.count = 0;
-    int rc = CNNK_OK;
-    for (int k = 0; k < np && rc == CNNK_OK; ++k) {
-      size_t n;
-      if (k == P_WE) n = (size_t)d * g.K0;
-      else if (k == P_BE || k == P_CLS) n = (size_t)d;
-      else if (k == P_POS) n = (size_t)T * d;
-      else if (k < p_tail) n = sizes_blk[(k - P_BLOCK0) % B_COUNT];
-      else if (k == p_tail || k == p_tail + 1) n = (size_t)d;
-      else if (k == p_tail + 2) n = (size_t)g.classes * d;
-      else n = (size_t)g.classes;
-      const int i = t.count++;
-      t.w[i] = (float*)buf->param[k]; t.v[i] = (float*)buf->mom[k]; t.g[i] = (const float*)buf->grad[k];
-      t.wlp[i] = bf ? buf->param_lp[k] : nullptr; t.n[i] = n;
-      if (t.count == kSgdMaxTensors || k == np - 1) { rc = sgd_multi(t, lr, mu, wd, st); t.count = 0; }
-    }
-    return rc;
+    return update_params(g, buf, 0, p_tail + 4, lr, mu, wd, st);
   });
   return w.rc;
 }
