@@ -96,6 +96,13 @@ int conv_transpose_weights_multi(TransposeTable& t, hipStream_t st);
 int conv_mfma_dgrad_pt(const ConvGeom& g, const bf16_t* dy, const bf16_t* wt, bf16_t* dx, int accumulate,
                        hipStream_t st);
 
+// implicit GEMM with the operands loaded straight into LDS (conv_gemm.hip); the data gradient takes the weights as
+// they are.  stats: [2][Cout][conv_gemm_stat_rows].
+bool conv_gemm_supported(const ConvGeom& g, int pass);
+int conv_gemm_stat_rows(const ConvGeom& g);
+int conv_gemm_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y, float* stats, hipStream_t st, const ConvTail* tail);
+int conv_gemm_dgrad(const ConvGeom& g, const bf16_t* dy, const bf16_t* w, bf16_t* dx, int accumulate, hipStream_t st);
+
 // 3x3 stride-1 kernels with the input patch resident in LDS (forward, data gradient)
 bool conv_patch_supported(const ConvGeom& g, int pass);
 int conv_patch_stat_rows(const ConvGeom& g);
@@ -172,7 +179,8 @@ struct SgdFuse {
 };
 extern thread_local SgdFuse* t_cnnk_sgd_fuse;
 
-extern int g_cnnk_tune[16];
+constexpr int kTuneKeys = 24;
+extern int g_cnnk_tune[kTuneKeys];
 // Hook 3 of 3.  Compute units the weight-gradient kernels size their grids for (256 = the whole device).  The
 // training step lowers it for the weight gradients it runs on its second stream, beside the rest
 // of the backward pass: fewer, longer-lived workgroups leave the other stream room to run.

@@ -140,7 +140,7 @@ extern "C" const char* cnnk_status_string(int s) {
 }
 
 extern "C" int cnnk_tune(int key, int value) {
-  if (key < 0 || key >= 16) return CNNK_ERR_SHAPE;
+  if (key < 0 || key >= kTuneKeys) return CNNK_ERR_SHAPE;
   g_cnnk_tune[key] = value;
   return CNNK_OK;
 }

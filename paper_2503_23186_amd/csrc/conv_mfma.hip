@@ -14,7 +14,7 @@
 #include "common.h"
 #include "conv.h"
 
-int g_cnnk_tune[16] = {0};
+int g_cnnk_tune[kTuneKeys] = {0};
 thread_local int t_cnnk_wgrad_cus = 256;
 
 namespace {
@@ -705,6 +705,12 @@ size_t conv_mfma_ws(const ConvGeom& g, int pass, bool want_stats) {
 
 int conv_mfma_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y, float* ch_sum,
                   float* ch_sumsq, void* ws, hipStream_t st, const ConvTail* tail) {
+  if (conv_gemm_supported(g, CNNK_PASS_FWD)) {
+    float* stats = ch_sum ? reinterpret_cast<float*>(ws) : nullptr;
+    const int rc = conv_gemm_fwd(g, x, w, y, stats, st, tail);
+    if (rc != CNNK_OK || !ch_sum) return rc;
+    return channel_sums_finalize(stats, conv_gemm_stat_rows(g), g.Cout, ch_sum, ch_sumsq, st);
+  }
   if (conv_patch_supported(g, CNNK_PASS_FWD)) {
     float* stats = ch_sum ? reinterpret_cast<float*>(ws) : nullptr;
     int rc = conv_patch_fwd(g, x, w, y, stats, st, tail);
@@ -750,6 +756,7 @@ int conv_transpose_weights_multi(TransposeTable& t, hipStream_t st) {
 
 int conv_mfma_dgrad(const ConvGeom& g, const bf16_t* dy, const bf16_t* w, bf16_t* dx, int accumulate,
                     void* ws, hipStream_t st) {
+  if (conv_gemm_supported(g, CNNK_PASS_DGRAD)) return conv_gemm_dgrad(g, dy, w, dx, accumulate, st);
   const int T = g.R * g.S;
   bf16_t* wt = reinterpret_cast<bf16_t*>(ws);
   const int nw = g.Cout * T * g.Cin;

@@ -21,66 +21,13 @@
 // fp32 partials that a second kernel adds in a fixed order.
 #include "common.h"
 #include "gemm.h"
+#include "mfma_tile.h"
 
-extern int g_cnnk_tune[16];
+extern int g_cnnk_tune[];
 
 namespace {
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef short s16x8_t __attribute__((ext_vector_type(8)));
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
-
-constexpr int SP = 72;                         // epilogue strip pitch (bytes per column)
-
-// TM: 32-row blocks of a wavefront's tile (4: workgroup tile 256 x 128, 3: 192 x 128).
-// RB: bytes of an LDS row = bytes of an operand row that one group of lanes fetches.  The path from L2
-// into LDS moves a fixed number of requests per clock whatever their size up to a 128-byte line
-// (measured: 16 TB/s with 64-byte row segments, 32 TB/s with 128-byte ones), and with 64-byte rows that
-// path, not the matrix pipe, bounds the kernel.  128-byte rows of an operand whose reduction index is
-// the contiguous one mean 64 reduction elements per stage, and then only two stage buffers of a
-// 192 x 128 tile fit the 80 KB a workgroup may hold with two workgroups per CU; an operand read through
-// the transposing load takes 128-byte rows by widening its planes to 64 columns, at any stage depth.
-//
-// KG: groups of four wavefronts in a workgroup.  They share the output tile and split the reduction range,
-// each with stage buffers of its own, and their accumulators are added through LDS at the end.
-template <int TM, int TN, int BK_, int RB_, int NST_, int KG_> struct Cfg {
-  static constexpr int BK = BK_, RB = RB_, KG = KG_;
-  static constexpr int NW = 4, THREADS = 64 * NW * KG;   // a group: four wavefronts, 2 x 2
-  static constexpr int NST = NST_;                       // stage buffers; loads run NST - 1 stages ahead
-  static constexpr int BM = 64 * TM, BN = 64 * TN, A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_B = A_BYTES + B_BYTES;
-  static constexpr int NLOAD = STAGE_B / 1024 / NW;      // direct loads per wavefront and stage
-  static constexpr int SMEM = KG * NST * STAGE_B;
-  static constexpr int HAND_B = (KG - 1) * TM * TN * 16 * 256 * 4;   // accumulators of the groups past the first
-  // wavefronts per SIMD the register allocation leaves room for: two workgroups per CU where their LDS fits
-  static constexpr int WPE = KG * (2 * SMEM <= 160 * 1024 ? 2 : 1);
-  static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "every load of a wavefront belongs to one operand");
-  static_assert(SMEM <= 160 * 1024 && HAND_B + NW * 32 * SP <= SMEM, "LDS");
-};
-
-__device__ __forceinline__ i32x4_t make_desc(const void* p, unsigned bytes) {
-  const unsigned long long a = reinterpret_cast<unsigned long long>(p);
-  return i32x4_t{(int)(unsigned)a, (int)((unsigned)(a >> 32) & 0xffffu), (int)bytes, 0x00020000};
-}
-// lane i of the wavefront moves 16 bytes from byte offset voff of the buffer to LDS address
-// lds_addr + 16 i (zeros when voff is out of range).  Assembly, so that the compiler does not make
-// every later LDS read wait for all outstanding direct loads; the waits are explicit below.
-__device__ __forceinline__ void load16_to_lds(i32x4_t desc, unsigned lds_addr, unsigned voff) {
-  unsigned keep;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-               : "=&s"(keep)
-               : "s"(lds_addr), "v"(voff), "s"(desc)
-               : "memory");
-}
-// What the index of a 16-byte chunk is XORed with to give its position in the LDS row.  64-byte rows
-// read with 16-byte loads: row bits 2-3; read with the transposing load: nothing, four consecutive
-// rows are the 64 banks whatever the order inside a row.
-// 128-byte rows read with 16-byte loads (sixteen rows of one chunk per pass): with row bits 1-3, so that
-// the eight rows of either parity - a row's parity picks the half of the banks - sit on eight different
-// chunk positions.  128-byte rows read with the transposing load (four rows x 64 bytes per pass): the
-// two 64-byte halves swap on every second pair of rows, which puts the four rows on four bank quarters.
-template <int RB, bool TR> __device__ __forceinline__ int swz_of(int row) {
-  if (RB == 64) return TR ? 0 : (row >> 2) & 3;
-  return TR ? ((row >> 1) & 1) << 2 : (row >> 1) & 7;
-}
+template <bool ATR, bool BTR, int TM, int TN, int BK, int RB, int NST, int KG>
+using Cfg = Tile<ATR, BTR, TM, TN, 2, BK, RB, NST, KG>;
 
 struct Args {
   const bf16_t* A;
@@ -135,32 +82,54 @@ __device__ __forceinline__ float gelu_grad_f(float u) {
   return fmaf(u * 0.39894228040143268f, e, u < 0.f ? q : 1.0f - q);
 }
 
-// sum of the eight bf16 elements of an operand fragment
-__device__ __forceinline__ float sum8(bf16x8_t f) {
-  float v[8];
-  unpack8(__builtin_bit_cast(uint4, f), v);
-  return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-}
+// the operands of a dense product
+template <class C> struct DenseLoader {
+  i32x4_t a_rs, b_rs;
+  // byte offset of this lane's 16 bytes in stage 0, and their reduction index (the first element of a natural
+  // operand's, the row of a transposed one's); those of stage t are in range while kk0 + t * BK < kend
+  unsigned voff[C::NLOAD];
+  int kk0[C::NLOAD];
+  unsigned vinc_a, vinc_b;
+  int kend, t;
+  __device__ __forceinline__ void init(const Args& a, int m0, int n0, int kbeg, int kend_, int wave, int lane) {
+    a_rs = make_desc(a.A, a.a_bytes);
+    b_rs = make_desc(a.B, a.b_bytes);
+    kend = kend_;
+    vinc_a = C::ATR ? (unsigned)(C::BK * a.lda * 2) : C::BK * 2;
+    vinc_b = C::BTR ? (unsigned)(C::BK * a.ldb * 2) : C::BK * 2;
+#pragma unroll
+    for (int j = 0; j < C::NLOAD; ++j) {
+      const bool isA = j < C::NLOAD_A;
+      const int ld = isA ? a.lda : a.ldb, o0 = isA ? m0 : n0, olim = isA ? a.M : a.N;
+      const LoadSlot s = load_slot<C>(j, wave, lane);
+      if (!(isA ? C::ATR : C::BTR)) {
+        const int row = o0 + s.row;
+        kk0[j] = row < olim ? kbeg + 8 * s.chunk : (1 << 30);
+        voff[j] = (unsigned)((row * ld + kbeg + 8 * s.chunk) * 2);
+      } else {
+        const int col = o0 + s.plane * C::PC + 8 * s.chunk;
+        kk0[j] = col < olim ? kbeg + s.row : (1 << 30);
+        voff[j] = (unsigned)(((kbeg + s.row) * ld + col) * 2);
+      }
+    }
+  }
+  __device__ __forceinline__ void begin(int stage) { t = stage; }
+  __device__ __forceinline__ unsigned offset(int j) const {
+    return kk0[j] + t * C::BK < kend ? voff[j] + (unsigned)t * (j < C::NLOAD_A ? vinc_a : vinc_b) : kOobOffset;
+  }
+};
 
 // One workgroup's tile (mt, nt) over the reduction range of split z.
-template <bool ATR, bool BTR, int EPI, int TM, int TN, int BK, int RB, int NSTAGE, int KG>
+template <class C, int EPI>
 __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) {
-  using C = Cfg<TM, TN, BK, RB, NSTAGE, KG>;
-  constexpr int NW = C::NW, BN = C::BN;
-  constexpr int BM = C::BM, A_BYTES = C::A_BYTES, STAGE_B = C::STAGE_B, NLOAD = C::NLOAD, NST = C::NST;
-  constexpr int LPR = RB / 16, RPL = 1024 / RB;       // lanes per LDS row, rows per direct load
-  constexpr int PC = RB / 2, PLANE_B = BK * RB;       // a transposed operand: planes of BK reduction rows x PC columns
-  constexpr int KS = BK / 16;                         // MFMA reduction steps per stage
-  static_assert((ATR || BK * 2 == RB) && (BTR || BK * 2 == RB), "a natural operand's LDS row is its BK reduction elements");
-  static_assert(BM % PC == 0 || !ATR, "whole planes");
-  static_assert(NST == 2 || NLOAD < 16, "the wait below encodes the load count in four bits");
-  extern __shared__ __align__(16) unsigned char smem[];   // NST stage buffers, nothing else: LDS address 0
+  constexpr int TM = C::TM, TN = C::TN, BK = C::BK, KG = C::KG;
+  extern __shared__ __align__(16) unsigned char smem[];   // stage buffers, nothing else
   const int lane = threadIdx.x & 63;
   const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);   // reduction group
   const int tid = threadIdx.x & 255;                                                     // within the group
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1, h = lane >> 5, g = lane >> 4, i16 = lane & 15;
-  const int m0 = mt * BM, n0 = nt * BN;
+  const int wm = wave / C::WN, wn = wave % C::WN, h = lane >> 5, g = lane >> 4, i16 = lane & 15;
+  const int m0 = mt * C::BM, n0 = nt * C::BN;
   int kbeg = z * a.k_per_split;
   int kend = kbeg + a.k_per_split;
   if (kend > a.K) kend = a.K;
@@ -170,165 +139,17 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
     kbeg += kg * nst * BK;
     kend = min(kend, kbeg + nst * BK);
   }
-  const int sbase = kg * NST * STAGE_B;    // LDS address of the group's stage buffers
-
-  const i32x4_t a_rs = make_desc(a.A, a.a_bytes), b_rs = make_desc(a.B, a.b_bytes);
-  // ---- this lane's direct loads of a stage ----
-  // A load of the wavefront fills 1 KB of LDS: RPL rows of RB bytes, lane i the 16 bytes at 16 i, so
-  // the LPR lanes of a row ask for the (swizzled) chunks of one RB-byte segment of memory.
-  // kk0: reduction index of the lane's 16 bytes in stage 0 (its first element for a natural operand,
-  // its row for a transposed one); a load of stage t is in range while kk0 + t * BK < kend
-  unsigned voff[NLOAD];
-  int kk0[NLOAD];
-  const unsigned vinc_a = ATR ? (unsigned)(BK * a.lda * 2) : BK * 2, vinc_b = BTR ? (unsigned)(BK * a.ldb * 2) : BK * 2;
-#pragma unroll
-  for (int j = 0; j < NLOAD; ++j) {
-    const bool isA = j * NW < A_BYTES / 1024;           // blocks j * NW + wave: a compile-time property
-    const int qq = j * NW + wave - (isA ? 0 : A_BYTES / 1024);
-    const bool tr = isA ? ATR : BTR;
-    const int ld = isA ? a.lda : a.ldb;
-    const int o0 = isA ? m0 : n0, olim = isA ? a.M : a.N;
-    const int p = lane % LPR;
-    if (!tr) {
-      const int r = qq * RPL + lane / LPR;
-      const int c = p ^ swz_of<RB, false>(r);
-      const int row = o0 + r;
-      kk0[j] = row < olim ? kbeg + 8 * c : (1 << 30);
-      voff[j] = (unsigned)((row * ld + kbeg + 8 * c) * 2);
-    } else {
-      const int plane = qq / (BK / RPL), r = (qq % (BK / RPL)) * RPL + lane / LPR;
-      const int c = p ^ swz_of<RB, true>(r);
-      const int col = o0 + plane * PC + 8 * c;
-      kk0[j] = col < olim ? kbeg + r : (1 << 30);
-      voff[j] = (unsigned)(((kbeg + r) * ld + col) * 2);
-    }
-  }
-  auto issue = [&](int t, int sb) __attribute__((always_inline)) {
-#pragma unroll
-    for (int j = 0; j < NLOAD; ++j) {
-      const bool isA = j * NW < A_BYTES / 1024;
-      const unsigned off = kk0[j] + t * BK < kend ? voff[j] + (unsigned)t * (isA ? vinc_a : vinc_b) : kOobOffset;
-      load16_to_lds(isA ? a_rs : b_rs, (unsigned)(sbase + sb + (j * NW + wave) * 1024), off);
-    }
-  };
-  // ---- fragment addresses (stage-relative) ----
-  // natural: 16 bytes = reduction elements ks * 16 + h * 8 .. + 8 of row lane % 32 of a 32-row block;
-  // blocks lie 32 rows apart and the swizzle repeats every 16 rows.  The chunk index ks * 2 + h meets
-  // the swizzle in an XOR, so step ks is the address of step 0 XOR ks * 32 (128-byte rows) and the next
-  // row's 32 bytes on (64-byte rows).
-  // transposed: a pair of transposing reads, reduction rows ks * 16 + h * 8 + (lane % 16) / 4 and + 4,
-  // of 32-column block sub of the wavefront's tile.
-  int a_n0 = 0, b_n0 = 0;            // natural: address of step 0, block 0
-  int a_t0 = 0, b_t0 = 0;            // transposed: address of step 0 within a 32-column block at column 0
-  int a_sub[TM], b_sub[TN];           // transposed: where block sub lies (plane, and half of a 128-byte row)
-  auto nat0 = [&](int row) { return row * RB + ((h ^ swz_of<RB, false>(row)) << 4); };
-  auto tr0 = [&]() {
-    const int ch0 = (g & 1) * 16 + (i16 & 3) * 4, row = h * 8 + (i16 >> 2);
-    return row * RB + ((ch0 >> 3) << 4) + (ch0 & 7) * 2;        // 128-byte rows: which half of the row is in a_sub / b_sub
-  };
-  auto tr_sub = [&](int cb) {        // cb: 32-column block of the operand's tile
-    if (RB == 64) return cb * PLANE_B;
-    const int sw = swz_of<128, true>(i16 >> 2) >> 2;            // the same for every row this lane reads
-    return (cb >> 1) * PLANE_B + (((cb & 1) ^ sw) << 6);
-  };
-  if (!ATR) a_n0 = nat0(wm * (TM * 32) + (lane & 31)); else a_t0 = tr0();
-  if (!BTR) b_n0 = A_BYTES + nat0(wn * (TN * 32) + (lane & 31)); else b_t0 = A_BYTES + tr0();
-#pragma unroll
-  for (int i = 0; i < TM; ++i) a_sub[i] = ATR ? tr_sub(wm * TM + i) : i * 32 * RB;
-#pragma unroll
-  for (int j = 0; j < TN; ++j) b_sub[j] = BTR ? tr_sub(wn * TN + j) : j * 32 * RB;
-  auto read_frag = [&](const unsigned char* sb, bool tr, int n0a, int t0a, int subo, int ks) __attribute__((always_inline)) -> bf16x8_t {
-    if (!tr) {
-      return *reinterpret_cast<const bf16x8_t*>(sb + (n0a ^ (ks << 5)) + subo);
-    }
-    const unsigned char* q = sb + t0a + ks * 16 * RB + subo;
-    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)q);
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(q + 4 * RB));
-    const s16x8_t v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(bf16x8_t, v);
-  };
-
-  f32x16_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
+  DenseLoader<C> ld;
+  ld.init(a, m0, n0, kbeg, kend, wave, lane);
   // sums of A over the reduction (a bias gradient), by the wavefronts that hold the first column of tiles:
   // the operand is in their registers, and the vector ALU has room beside the MFMAs
-  const bool row_sums = EPI == 2 && KG == 1 && a.rsum != nullptr && nt == 0 && wn == 0;
+  constexpr bool ROWS = EPI == 2 && KG == 1;
+  const bool row_sums = ROWS && a.rsum != nullptr && nt == 0 && wn == 0;
+  f32x16_t acc[TM][TN];
   float rs[TM];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) rs[i] = 0.f;
-
-#pragma unroll
-  for (int d = 0; d < NST - 1; ++d)
-    if (d < nst) issue(d, d * STAGE_B);
-  int cur = 0;
-  for (int t = 0; t < nst; ++t) {
-    // this wave's loads of stage t have landed; those of the stages issued after it may stay in flight
-    if (NST == 3 && t + 1 < nst) __builtin_amdgcn_s_waitcnt(0x0f70 | NLOAD);
-    else __builtin_amdgcn_s_waitcnt(0x0f70);
-    __builtin_amdgcn_s_barrier();
-    if (t + NST - 1 < nst) {
-      int fill = cur + (NST - 1) * STAGE_B;
-      if (fill >= NST * STAGE_B) fill -= NST * STAGE_B;
-      issue(t + NST - 1, fill);
-    }
-    const unsigned char* sb = smem + sbase + cur;
-    bf16x8_t af[2][TM], bfr[2][TN];
-#pragma unroll
-    for (int kp = 0; kp < KS; kp += 2) {
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) af[ks][i] = read_frag(sb, ATR, a_n0, a_t0, a_sub[i], kp + ks);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) bfr[ks][j] = read_frag(sb, BTR, b_n0, b_t0, b_sub[j], kp + ks);
-      }
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks][i], bfr[ks][j], acc[i][j], 0, 0, 0);
-      if (row_sums) {
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-          for (int i = 0; i < TM; ++i) rs[i] += sum8(af[ks][i]);
-      }
-    }
-    cur += STAGE_B;
-    if (cur == NST * STAGE_B) cur = 0;
-  }
-
-  if (KG > 1) {
-    // the groups past the first hand their accumulators over through LDS, in group order
-    __syncthreads();     // every wave is done reading the stage buffers; all direct loads have landed (vmcnt(0) above)
-    float* R = reinterpret_cast<float*>(smem);
-    if (kg > 0) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) R[(((kg - 1) * TM * TN + i * TN + j) * 16 + r) * 256 + tid] = acc[i][j][r];
-    }
-    __syncthreads();
-    if (kg > 0) return;
-#pragma unroll
-    for (int k = 0; k < KG - 1; ++k)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] += R[((k * TM * TN + i * TN + j) * 16 + r) * 256 + tid];
-  }
+  tile_main_loop<C, ROWS>(ld, nst, kg, wave, lane, smem, acc, row_sums, rs);
+  if (EPI != 2 || KG > 1) tile_join_groups<C>(acc, kg, tid, smem);
+  if (kg > 0) return;
   if (EPI == 2) {
     float* out = a.part + (size_t)z * a.zstride;
     if (row_sums) {
@@ -352,11 +173,7 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
       }
     return;
   }
-  if (KG == 1) __syncthreads();     // every wave is done reading the stage buffers; all direct loads have landed (vmcnt(0) above)
   unsigned char* S = smem + C::HAND_B + wave * (32 * SP);   // behind the accumulators just taken over
-
-  const int wr_off = (lane & 31) * SP + h * 8;
-  const int rd_off = (g * 8 + (i16 >> 2)) * SP + (i16 & 3) * 8;
   // Loads and stores of the epilogue are buffer operations: a position outside the output reads zeros and
   // stores nothing, without a branch, so the number in flight is known and a wait is for what it needs.
   const __amdgpu_buffer_rsrc_t c_rs = make_rsrc(a.C, a.c_bytes);
@@ -365,24 +182,6 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
   auto place = [&](int i, int j, int rb) __attribute__((always_inline)) -> unsigned {
     const int row = m0 + wm * (TM * 32) + i * 32 + rb * 16 + i16, col = n0 + wn * (TN * 32) + j * 32 + g * 8;
     return row < a.M && col < a.N ? (unsigned)(row * a.ldc + col) * 2u : kOobOffset;
-  };
-  auto store16 = [&](__amdgpu_buffer_rsrc_t rs_, uint4 v, unsigned off) __attribute__((always_inline)) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4_t, v), rs_, (int)off, 0, 0);
-  };
-  // 32 x 32 values through the wave's strip: lane (g, i16) gets the eight columns g * 8 .. of rows i16 and 16 + i16
-  auto transpose = [&](const float* v, uint4* out) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      *reinterpret_cast<uint2*>(S + wr_off + q * 16) = make_uint2(pack_bf16x2(v[q * 4], v[q * 4 + 1]), pack_bf16x2(v[q * 4 + 2], v[q * 4 + 3]));
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-      const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(S + rd_off + rb * 32));
-      const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(S + rd_off + 4 * SP + rb * 32));
-      const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-      out[rb] = uint4{l2.x, l2.y, h2.x, h2.y};
-    }
-    asm volatile("" ::: "memory");
   };
   // the residual (or gelu's argument) of a 32-row block is fetched while the block before it is worked on
   uint4 rv[2][TN][2];
@@ -404,41 +203,34 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
 #pragma unroll
       for (int r = 0; r < 16; ++r) v[r] = acc[i][j][r] + bv;
       uint4 o[2];
-      transpose(v, o);
+      strip_transpose(S, lane, v, o);
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) {
-        if (EPI == 3) {     // + residual: the sum of two stored values, rounded again
-          float x[8], r[8];
-          unpack8(o[rb], x);
-          unpack8(rv[i & 1][j][rb], r);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) x[e] += r[e];
-          o[rb] = uint4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
-        }
-        store16(c_rs, o[rb], place(i, j, rb));
+        if (EPI == 3) o[rb] = add_bf16x8(o[rb], rv[i & 1][j][rb]);     // + residual: the sum of two stored values, rounded again
+        buffer_store16(c_rs, o[rb], place(i, j, rb));
         if (EPI == 4) {     // the gradient of the activation's argument, from the gradient as stored
           float x[8], r[8];
           unpack8(o[rb], x);
           unpack8(rv[i & 1][j][rb], r);
 #pragma unroll
           for (int e = 0; e < 8; ++e) x[e] *= gelu_grad_f(r[e]);
-          store16(c2_rs, uint4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])}, place(i, j, rb));
+          buffer_store16(c2_rs, uint4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])}, place(i, j, rb));
         }
       }
       if (EPI == 1) {
         // the activation of the value as stored
 #pragma unroll
         for (int r = 0; r < 16; ++r) v[r] = gelu_f(bf16_to_f32(f32_to_bf16_hw(v[r])));
-        transpose(v, o);
+        strip_transpose(S, lane, v, o);
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) store16(c2_rs, o[rb], place(i, j, rb));
+        for (int rb = 0; rb < 2; ++rb) buffer_store16(c2_rs, o[rb], place(i, j, rb));
       }
     }
   }
 }
 
 template <bool ATR, bool BTR, int EPI, int TM, int TN, int BK, int RB, int NSTAGE, int KG>
-__global__ void __launch_bounds__(256 * KG, (Cfg<TM, TN, BK, RB, NSTAGE, KG>::WPE)) gemm_kernel(Args a) {
+__global__ void __launch_bounds__(256 * KG, (Cfg<ATR, BTR, TM, TN, BK, RB, NSTAGE, KG>::WPE)) gemm_kernel(Args a) {
   // workgroups that share an XCD's L2 (every 8th) walk consecutive tiles: same rows of A, all of B
   // (the grid is 8 * ceil(tiles / 8) workgroups; the few past the end leave at once).  An XCD owns a
   // contiguous range of the row-major tile list, i.e. a band of tile rows, and walks it column by
@@ -456,7 +248,7 @@ __global__ void __launch_bounds__(256 * KG, (Cfg<TM, TN, BK, RB, NSTAGE, KG>::WP
     if (l < cnt) { mt = r0 + l + (1 - first); break; }
     l -= cnt;
   }
-  gemm_tile<ATR, BTR, EPI, TM, TN, BK, RB, NSTAGE, KG>(a, mt, nt, blockIdx.z);
+  gemm_tile<Cfg<ATR, BTR, TM, TN, BK, RB, NSTAGE, KG>, EPI>(a, mt, nt, blockIdx.z);
 }
 
 // Several weight gradients in one launch.  Alone, one of ViT-B/16's has 18 to 72 tiles of 256 x 128 for 256
@@ -478,7 +270,7 @@ struct GroupArgs {
   size_t off[kGroupMax];       // splits > 1: where problem i starts in a partial (dw, then db)
 };
 template <int TM, int TN, int BK, int RB, int NSTAGE>
-__global__ void __launch_bounds__(256, (Cfg<TM, TN, BK, RB, NSTAGE, 1>::WPE)) wgrad_group_kernel(GroupArgs ga) {
+__global__ void __launch_bounds__(256, (Cfg<true, true, TM, TN, BK, RB, NSTAGE, 1>::WPE)) wgrad_group_kernel(GroupArgs ga) {
   // an XCD (every 8th workgroup) owns a contiguous range of the tile list
   const int chunk = (ga.tiles + 7) >> 3, l = blockIdx.x >> 3;
   const int tile = (blockIdx.x & 7) * chunk + l;
@@ -501,7 +293,7 @@ __global__ void __launch_bounds__(256, (Cfg<TM, TN, BK, RB, NSTAGE, 1>::WPE)) wg
     a.rsum = p.db;
   }
   const int q = tile - p.tile0, mt = q / p.ntiles;
-  gemm_tile<true, true, 2, TM, TN, BK, RB, NSTAGE, 1>(a, mt, q - mt * p.ntiles, blockIdx.z);
+  gemm_tile<Cfg<true, true, TM, TN, BK, RB, NSTAGE, 1>, 2>(a, mt, q - mt * p.ntiles, blockIdx.z);
 }
 // sums of the partials of a group, in split order
 __global__ void __launch_bounds__(256) sum_group_kernel(GroupArgs ga) {
@@ -545,7 +337,7 @@ int launch(Kern kern, bool* raised, int threads, int smem_bytes, const Args& a, 
 template <bool ATR, bool BTR, int EPI, int TM, int TN, int BK, int RB, int NST, int KG>
 int launch_cfg(Args& a, int splits, hipStream_t st) {
   static bool raised = false;
-  using C = Cfg<TM, TN, BK, RB, NST, KG>;
+  using C = Cfg<ATR, BTR, TM, TN, BK, RB, NST, KG>;
   a.mtiles = (a.M + C::BM - 1) / C::BM;
   a.ntiles = (a.N + C::BN - 1) / C::BN;
   return launch(gemm_kernel<ATR, BTR, EPI, TM, TN, BK, RB, NST, KG>, &raised, C::THREADS, C::SMEM, a, splits, st);
@@ -767,8 +559,8 @@ int gemm_bf16_wgrad_group(const GemmWgrad* p, int n, void* ws, hipStream_t st) {
     return launch_status();
   };
   static bool raised_l = false, raised_s = false;
-  const int rc = g.large ? go(wgrad_group_kernel<4, 2, 32, 64, 3>, Cfg<4, 2, 32, 64, 3, 1>::SMEM, &raised_l)
-                         : go(wgrad_group_kernel<1, 2, 64, 128, 3>, Cfg<1, 2, 64, 128, 3, 1>::SMEM, &raised_s);
+  const int rc = g.large ? go(wgrad_group_kernel<4, 2, 32, 64, 3>, Cfg<true, true, 4, 2, 32, 64, 3, 1>::SMEM, &raised_l)
+                         : go(wgrad_group_kernel<1, 2, 64, 128, 3>, Cfg<true, true, 1, 2, 64, 128, 3, 1>::SMEM, &raised_s);
   if (rc != CNNK_OK || g.splits == 1) return rc;
   size_t blocks = (a.zstride / 4 + 255) / 256;
   if (blocks > 2048) blocks = 2048;

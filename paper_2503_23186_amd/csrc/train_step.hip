@@ -33,7 +33,8 @@ struct Walk {
 
 bool dgrad_pretransposed(const cnnk_layer& l) {
   if (l.op != CNNK_OP_CONV || l.in0 == 0 || l.d.conv.dtype != CNNK_BF16) return false;
-  return conv_mfma_supported(make_geom(&l.d.conv), CNNK_PASS_DGRAD);
+  const ConvGeom g = make_geom(&l.d.conv);
+  return conv_mfma_supported(g, CNNK_PASS_DGRAD) && !conv_gemm_supported(g, CNNK_PASS_DGRAD);   // the latter reads the weights as they are
 }
 
 bool set_elems(std::vector<size_t>& v, int id, size_t n) {

@@ -16,7 +16,7 @@ bool attn_mfma_supported(const cnnk_attn_desc* d);
 int attn_mfma_fwd(const cnnk_attn_desc* d, const void* qkv, void* o, float* lse, hipStream_t st);
 int attn_mfma_bwd(const cnnk_attn_desc* d, const void* qkv, const void* o, const void* d_o, const float* lse, void* dqkv,
                   hipStream_t st);
-extern int g_cnnk_tune[16];
+extern int g_cnnk_tune[];
 
 namespace {
 constexpr int kT = 256;

@@ -6,7 +6,7 @@
 #include "vit.h"
 #include "../../include/cnnk_vit.h"
 
-extern int g_cnnk_tune[16];
+extern int g_cnnk_tune[];
 
 namespace {
 int check(long long rows, int K, int N, int dtype) {

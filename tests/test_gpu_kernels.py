@@ -133,6 +133,25 @@ def test_conv_fwd_dgrad_wgrad(K, shape, dtype):
     assert max_rel_err(host(gdw), dw_ref) <= acc_tol
 
 
+# (N, H, W, Cin, Cout, R, stride): odd images (strided data gradients with parities of different sizes), channel tiles
+# that end inside a tile, 64 and 32 channels per stage in either direction, reductions shorter than the pipeline,
+# more stages than one group of an even split has, and one pixel
+DIRECT_LOAD_SHAPES = [(3, 9, 7, 64, 136, 3, 2), (2, 8, 8, 96, 160, 3, 2), (5, 7, 7, 128, 192, 1, 2), (1, 1, 1, 64, 32, 1, 1),
+                      (3, 10, 13, 32, 64, 1, 1), (2, 6, 9, 320, 64, 1, 1), (2, 5, 5, 64, 96, 3, 1), (7, 11, 5, 192, 320, 1, 1)]
+
+
+@pytest.mark.parametrize("tile", range(8))
+@pytest.mark.parametrize("shape", DIRECT_LOAD_SHAPES)
+def test_direct_load_kernels_every_tile(K, shape, tile):
+    """Forward (with channel sums) and data gradient through each tile shape of the kernels that load both operands
+    straight into LDS, within the bounds of the general test: one storage rounding of each output."""
+    K.cnnk_tune(16, tile + 1)
+    try:
+        test_conv_fwd_dgrad_wgrad(K, shape, "bf16")
+    finally:
+        K.cnnk_tune(16, 0)
+
+
 WG_SHAPES = [(4, 8, 8, 64, 128), (3, 16, 16, 64, 64), (2, 32, 32, 128, 64), (18, 4, 4, 64, 64), (5, 8, 8, 192, 64),
              (1, 32, 32, 64, 64)]
 
