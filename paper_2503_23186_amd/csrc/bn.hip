@@ -260,7 +260,8 @@ __device__ __forceinline__ void bn_scale_bias(float g, float b, float mu, float 
 
 template <typename T>
 __device__ __forceinline__ void bn_apply_rows(const T* __restrict__ x, const T* __restrict__ res, T* __restrict__ y,
-                                              size_t m, int C, int relu, const float* sc, const float* bi) {
+                                              size_t m, int C, int relu, const float* sc, const float* bi,
+                                              unsigned char* __restrict__ mask = nullptr) {
   const int lanes = C / 8, rows = kT / lanes;
   for_rows4<T>(m, C, lanes, rows, [&](size_t i0, size_t i1, size_t i2, size_t i3, auto NN) {
     constexpr int n = decltype(NN)::value;
@@ -286,6 +287,12 @@ __device__ __forceinline__ void bn_apply_rows(const T* __restrict__ x, const T* 
       if (relu) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[k][e] = v[k][e] > 0.f ? v[k][e] : 0.f;
+        if (mask) {
+          unsigned bits = 0;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) bits |= v[k][e] > 0.f ? 1u << e : 0u;
+          mask[idx[k] / 8] = (unsigned char)bits;
+        }
       }
       store8(y + idx[k], v[k]);
     }
@@ -300,7 +307,7 @@ __global__ void __launch_bounds__(kT) bn_apply_kernel(const T* __restrict__ x, c
                                                       const float* __restrict__ beta,
                                                       const float* __restrict__ mean,
                                                       const float* __restrict__ invstd, T* __restrict__ y,
-                                                      size_t m, int C, int relu) {
+                                                      size_t m, int C, int relu, unsigned char* __restrict__ mask) {
   const int o = threadIdx.x % (C / 8);
   float g[8], b[8], mu[8], is[8], sc[8], bi[8];
   load8(gamma + o * 8, g);
@@ -309,7 +316,7 @@ __global__ void __launch_bounds__(kT) bn_apply_kernel(const T* __restrict__ x, c
   load8(invstd + o * 8, is);
 #pragma unroll
   for (int e = 0; e < 8; ++e) bn_scale_bias(g[e], b[e], mu[e], is[e], &sc[e], &bi[e]);
-  bn_apply_rows<T>(x, res, y, m, C, relu, sc, bi);
+  bn_apply_rows<T>(x, res, y, m, C, relu, sc, bi, mask);
 }
 
 // Inference mode: the running statistics stand in for the batch's; nothing is reduced or updated.
@@ -345,7 +352,8 @@ __global__ void __launch_bounds__(kT) bn_apply_sums_kernel(const T* __restrict__
                                                            float* __restrict__ save_mean,
                                                            float* __restrict__ save_invstd,
                                                            float* __restrict__ rmean, float* __restrict__ rvar,
-                                                           T* __restrict__ y, size_t m, int C, int relu) {
+                                                           T* __restrict__ y, size_t m, int C, int relu,
+                                                           unsigned char* __restrict__ mask) {
   if (blockIdx.x == 0) {
     for (int c = threadIdx.x; c < C; c += kT) {
       const float mu = ch_sum[c] * inv_m;
@@ -371,20 +379,23 @@ __global__ void __launch_bounds__(kT) bn_apply_sums_kernel(const T* __restrict__
     const float is = rsqrtf(var + eps);
     bn_scale_bias(g[e], b[e], mu, is, &sc[e], &bi[e]);
   }
-  bn_apply_rows<T>(x, res, y, m, C, relu, sc, bi);
+  bn_apply_rows<T>(x, res, y, m, C, relu, sc, bi, mask);
 }
 
 // Partial sums of dz and dz*xhat.  MODE 0: no ReLU; 1: mask [y > 0]; 2: mask [x*sc + bi > 0]
-// recomputed with the forward's arithmetic (y is not read).  The element-wise kernel also knows
-// MODE 3: dz was written by this kernel into dres (the residual gradient is dz itself), read it there.
+// recomputed with the forward's arithmetic (y is not read); 4: `y` is the mask that the forward pass kept, one bit
+// per element.  The element-wise kernel also knows MODE 3: dz was written by this kernel into dres (the residual
+// gradient is dz itself), read it there.
 template <typename T, int MODE>
 __global__ void __launch_bounds__(kT) bwd_partial_kernel(const T* __restrict__ dy, const T* __restrict__ x,
-                                                         const T* __restrict__ y,
+                                                         const void* __restrict__ y_or_mask,
                                                          const float* __restrict__ gamma,
                                                          const float* __restrict__ beta,
                                                          const float* __restrict__ mean,
                                                          const float* __restrict__ invstd, size_t m, int C,
                                                          float* __restrict__ part, T* __restrict__ dz_out) {
+  const T* __restrict__ y = (const T*)y_or_mask;
+  const unsigned char* __restrict__ mask = (const unsigned char*)y_or_mask;
   const int lanes = C / 8, rows = kT / lanes;
   const int tid = threadIdx.x, o = tid % lanes, rl = tid / lanes;
   float acc[2][8];
@@ -407,12 +418,14 @@ __global__ void __launch_bounds__(kT) bwd_partial_kernel(const T* __restrict__ d
       constexpr int n = decltype(NN)::value;
       const size_t idx[4] = {i0, i1, i2, i3};
       float g[4][8], xv[4][8], yv[4][8];
+      unsigned mb[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k)
         if (k < n) {
           load8(dy + idx[k], g[k]);
           load8(x + idx[k], xv[k]);
           if (MODE == 1) load8(y + idx[k], yv[k]);
+          if (MODE == 4) mb[k] = mask[idx[k] / 8];
         }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -424,6 +437,10 @@ __global__ void __launch_bounds__(kT) bwd_partial_kernel(const T* __restrict__ d
         if (MODE == 2) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) g[k][e] = fmaf(xv[k][e], sc[e], bi[e]) > 0.f ? g[k][e] : 0.f;
+        }
+        if (MODE == 4) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) g[k][e] = (mb[k] >> e) & 1u ? g[k][e] : 0.f;
         }
         // the masked gradient is exact in the storage type (dy or 0): written here, it spares the
         // element-wise pass the reads of dy and y
@@ -463,7 +480,7 @@ __global__ void __launch_bounds__(kT) bwd_finalize_wide_kernel(const float* __re
 
 template <typename T, int MODE>
 __global__ void __launch_bounds__(kT) bwd_apply_kernel(const T* __restrict__ dy, const T* __restrict__ x,
-                                                       const T* __restrict__ y, const float* __restrict__ gamma,
+                                                       const void* __restrict__ y_or_mask, const float* __restrict__ gamma,
                                                        const float* __restrict__ beta,
                                                        const float* __restrict__ mean,
                                                        const float* __restrict__ invstd,
@@ -471,6 +488,8 @@ __global__ void __launch_bounds__(kT) bwd_apply_kernel(const T* __restrict__ dy,
                                                        const float* __restrict__ dbeta, T* __restrict__ dx,
                                                        T* __restrict__ dres, size_t m, int C, float inv_m,
                                                        int flags) {
+  const T* __restrict__ y = (const T*)y_or_mask;
+  const unsigned char* __restrict__ mask = (const unsigned char*)y_or_mask;
   const int lanes = C / 8, rows = kT / lanes;
   const int o = threadIdx.x % lanes;
   // dx = a * (dz - (dbeta + xhat * dgamma) / m), xhat = (x - mu) * is, a = gamma * is
@@ -499,12 +518,14 @@ __global__ void __launch_bounds__(kT) bwd_apply_kernel(const T* __restrict__ dy,
     constexpr int n = decltype(NN)::value;
     const size_t idx[4] = {i0, i1, i2, i3};
     float g[4][8], xv[4][8], yv[4][8];
+    unsigned mb[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       if (k < n) {
         load8((MODE == 3 ? dres : dy) + idx[k], g[k]);
         load8(x + idx[k], xv[k]);
         if (MODE == 1) load8(y + idx[k], yv[k]);
+        if (MODE == 4) mb[k] = mask[idx[k] / 8];
       }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -517,6 +538,10 @@ __global__ void __launch_bounds__(kT) bwd_apply_kernel(const T* __restrict__ dy,
       if (MODE == 2) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) g[k][e] = fmaf(xv[k][e], sc[e], bi[e]) > 0.f ? g[k][e] : 0.f;
+      }
+      if (MODE == 4) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) g[k][e] = (mb[k] >> e) & 1u ? g[k][e] : 0.f;
       }
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -590,10 +615,9 @@ extern "C" size_t cnnk_bn_workspace_bytes(const cnnk_bn_desc* d) {
   return align_up(channel_stats_ws((size_t)d->N * d->H * d->W, d->C), 256);
 }
 
-extern "C" int cnnk_bn_relu_fwd(const cnnk_bn_desc* d, const void* x, const void* residual, const float* gamma,
-                                const float* beta, void* y, float* save_mean, float* save_invstd,
-                                float* running_mean, float* running_var, const float* ch_sum,
-                                const float* ch_sumsq, void* ws, size_t ws_bytes, void* stream) {
+int bn_relu_fwd(const cnnk_bn_desc* d, const void* x, const void* residual, const float* gamma, const float* beta, void* y,
+                unsigned char* mask, float* save_mean, float* save_invstd, float* running_mean, float* running_var,
+                const float* ch_sum, const float* ch_sumsq, void* ws, size_t ws_bytes, void* stream) {
   int rc = validate_bn(d);
   if (rc != CNNK_OK) return rc;
   if (!x || !gamma || !beta || !y || !save_mean || !save_invstd) return CNNK_ERR_NULL;
@@ -625,22 +649,30 @@ extern "C" int cnnk_bn_relu_fwd(const cnnk_bn_desc* d, const void* x, const void
       bn_apply_sums_kernel<bf16_t><<<row_blocks(m, C), kT, 0, st>>>((const bf16_t*)x, (const bf16_t*)residual, gamma, beta,
                                                                  ch_sum, ch_sumsq, inv_m, unbias, d->eps, d->momentum,
                                                                  save_mean, save_invstd, running_mean, running_var,
-                                                                 (bf16_t*)y, m, C, d->relu);
+                                                                 (bf16_t*)y, m, C, d->relu, mask);
     else
       bn_apply_sums_kernel<float><<<row_blocks(m, C), kT, 0, st>>>((const float*)x, (const float*)residual, gamma, beta,
                                                                 ch_sum, ch_sumsq, inv_m, unbias, d->eps, d->momentum,
                                                                 save_mean, save_invstd, running_mean, running_var,
-                                                                (float*)y, m, C, d->relu);
+                                                                (float*)y, m, C, d->relu, mask);
     return launch_status();
   }
   if (launch_status() != CNNK_OK) return CNNK_ERR_HIP;
   if (d->dtype == CNNK_BF16)
     bn_apply_kernel<bf16_t><<<row_blocks(m, C), kT, 0, st>>>((const bf16_t*)x, (const bf16_t*)residual, gamma, beta,
-                                                          save_mean, save_invstd, (bf16_t*)y, m, C, d->relu);
+                                                          save_mean, save_invstd, (bf16_t*)y, m, C, d->relu, mask);
   else
     bn_apply_kernel<float><<<row_blocks(m, C), kT, 0, st>>>((const float*)x, (const float*)residual, gamma, beta,
-                                                         save_mean, save_invstd, (float*)y, m, C, d->relu);
+                                                         save_mean, save_invstd, (float*)y, m, C, d->relu, mask);
   return launch_status();
+}
+
+extern "C" int cnnk_bn_relu_fwd(const cnnk_bn_desc* d, const void* x, const void* residual, const float* gamma,
+                                const float* beta, void* y, float* save_mean, float* save_invstd,
+                                float* running_mean, float* running_var, const float* ch_sum,
+                                const float* ch_sumsq, void* ws, size_t ws_bytes, void* stream) {
+  return bn_relu_fwd(d, x, residual, gamma, beta, y, nullptr, save_mean, save_invstd, running_mean, running_var, ch_sum,
+                     ch_sumsq, ws, ws_bytes, stream);
 }
 
 extern "C" int cnnk_bn_relu_infer(const cnnk_bn_desc* d, const void* x, const void* residual, const float* gamma,
@@ -672,46 +704,55 @@ static int bn_bwd_launch(const cnnk_bn_desc* d, const void* dy, const void* x, c
   const int nb = reduce_blocks(m, C);
   const float inv_m = (float)(1.0 / (double)m);
   // a residual gradient that is written, not accumulated, is written by the first pass already
-  const bool dz_first = MODE == 1 && dresidual && !(flags & 2);
-  bwd_partial_kernel<T, MODE><<<nb, kT, 0, st>>>((const T*)dy, (const T*)x, (const T*)y, gamma, beta, save_mean,
+  const bool dz_first = (MODE == 1 || MODE == 4) && dresidual && !(flags & 2);
+  bwd_partial_kernel<T, MODE><<<nb, kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta, save_mean,
                                                  save_invstd, m, C, part, dz_first ? (T*)dresidual : nullptr);
   if (nb >= kWideFinalize) bwd_finalize_wide_kernel<<<C, kT, 0, st>>>(part, nb, C, dgamma, dbeta);
   else bwd_finalize_kernel<<<fin_blocks(C), kT, 0, st>>>(part, nb, C, dgamma, dbeta);
   if (dz_first)
-    bwd_apply_kernel<T, 3><<<row_blocks(m, C), kT, 0, st>>>((const T*)dy, (const T*)x, (const T*)y, gamma, beta,
+    bwd_apply_kernel<T, 3><<<row_blocks(m, C), kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta,
                                                             save_mean, save_invstd, dgamma, dbeta, (T*)dx,
                                                             (T*)dresidual, m, C, inv_m, flags);
   else
-    bwd_apply_kernel<T, MODE><<<row_blocks(m, C), kT, 0, st>>>((const T*)dy, (const T*)x, (const T*)y, gamma, beta,
+    bwd_apply_kernel<T, MODE><<<row_blocks(m, C), kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta,
                                                                save_mean, save_invstd, dgamma, dbeta, (T*)dx,
                                                                (T*)dresidual, m, C, inv_m, flags);
   return launch_status();
+}
+
+int bn_relu_bwd(const cnnk_bn_desc* d, const void* dy, const void* x, const void* y, const unsigned char* mask, const float* gamma,
+                const float* beta, const float* save_mean, const float* save_invstd, void* dx, void* dresidual, int flags,
+                float* dgamma, float* dbeta, void* ws, size_t ws_bytes, void* stream) {
+  int rc = validate_bn(d);
+  if (rc != CNNK_OK) return rc;
+  if (!dy || !x || !gamma || !save_mean || !save_invstd || !dx || !dgamma || !dbeta) return CNNK_ERR_NULL;
+  // ReLU mask: from y, or recomputed from x when y is withheld (no residual branch, beta given)
+  if (d->relu && !mask && !y && (!beta || dresidual)) return CNNK_ERR_NULL;
+  const int mode = !d->relu ? 0 : (mask ? 4 : y ? 1 : 2);
+  const size_t m = (size_t)d->N * d->H * d->W;
+  if (!ws || ws_bytes < channel_stats_ws(m, d->C)) return CNNK_ERR_WORKSPACE;
+  hipStream_t st = (hipStream_t)stream;
+  float* part = (float*)ws;
+#define CNNK_BN_BWD(T, MODE) \
+  return bn_bwd_launch<T, MODE>(d, dy, x, MODE == 4 ? (const void*)mask : y, gamma, beta, save_mean, save_invstd, dx, dresidual, flags, dgamma, \
+                                dbeta, part, st)
+  if (d->dtype == CNNK_BF16) {
+    if (mode == 0) CNNK_BN_BWD(bf16_t, 0);
+    if (mode == 1) CNNK_BN_BWD(bf16_t, 1);
+    if (mode == 4) CNNK_BN_BWD(bf16_t, 4);
+    CNNK_BN_BWD(bf16_t, 2);
+  }
+  if (mode == 0) CNNK_BN_BWD(float, 0);
+  if (mode == 1) CNNK_BN_BWD(float, 1);
+  if (mode == 4) CNNK_BN_BWD(float, 4);
+  CNNK_BN_BWD(float, 2);
+#undef CNNK_BN_BWD
 }
 
 extern "C" int cnnk_bn_relu_bwd(const cnnk_bn_desc* d, const void* dy, const void* x, const void* y,
                                 const float* gamma, const float* beta, const float* save_mean,
                                 const float* save_invstd, void* dx, void* dresidual, int flags, float* dgamma,
                                 float* dbeta, void* ws, size_t ws_bytes, void* stream) {
-  int rc = validate_bn(d);
-  if (rc != CNNK_OK) return rc;
-  if (!dy || !x || !gamma || !save_mean || !save_invstd || !dx || !dgamma || !dbeta) return CNNK_ERR_NULL;
-  // ReLU mask: from y, or recomputed from x when y is withheld (no residual branch, beta given)
-  if (d->relu && !y && (!beta || dresidual)) return CNNK_ERR_NULL;
-  const int mode = !d->relu ? 0 : (y ? 1 : 2);
-  const size_t m = (size_t)d->N * d->H * d->W;
-  if (!ws || ws_bytes < channel_stats_ws(m, d->C)) return CNNK_ERR_WORKSPACE;
-  hipStream_t st = (hipStream_t)stream;
-  float* part = (float*)ws;
-#define CNNK_BN_BWD(T, MODE) \
-  return bn_bwd_launch<T, MODE>(d, dy, x, y, gamma, beta, save_mean, save_invstd, dx, dresidual, flags, dgamma, \
-                                dbeta, part, st)
-  if (d->dtype == CNNK_BF16) {
-    if (mode == 0) CNNK_BN_BWD(bf16_t, 0);
-    if (mode == 1) CNNK_BN_BWD(bf16_t, 1);
-    CNNK_BN_BWD(bf16_t, 2);
-  }
-  if (mode == 0) CNNK_BN_BWD(float, 0);
-  if (mode == 1) CNNK_BN_BWD(float, 1);
-  CNNK_BN_BWD(float, 2);
-#undef CNNK_BN_BWD
+  return bn_relu_bwd(d, dy, x, y, nullptr, gamma, beta, save_mean, save_invstd, dx, dresidual, flags, dgamma, dbeta, ws,
+                     ws_bytes, stream);
 }

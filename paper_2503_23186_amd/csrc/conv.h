@@ -193,6 +193,15 @@ bool conv_tail_supported(const cnnk_conv_desc* d);
 int conv_fwd_tail(const cnnk_conv_desc* d, const void* x, const void* w, void* y, const ConvTail& tail, void* ws,
                   size_t ws_bytes, hipStream_t st);
 
+// cnnk_bn_relu_fwd / _bwd with the ReLU mask kept from one to the other: a bit per element (NHWC order, the lowest bit
+// of a byte first), m * C / 8 bytes.  Backward: with a mask, y is not read and may be null.
+int bn_relu_fwd(const cnnk_bn_desc* d, const void* x, const void* residual, const float* gamma, const float* beta, void* y,
+                unsigned char* mask, float* save_mean, float* save_invstd, float* running_mean, float* running_var,
+                const float* ch_sum, const float* ch_sumsq, void* ws, size_t ws_bytes, void* stream);
+int bn_relu_bwd(const cnnk_bn_desc* d, const void* dy, const void* x, const void* y, const unsigned char* mask, const float* gamma,
+                const float* beta, const float* save_mean, const float* save_invstd, void* dx, void* dresidual, int flags,
+                float* dgamma, float* dbeta, void* ws, size_t ws_bytes, void* stream);
+
 // per-channel sum / sum of squares of a tensor with C channels (used when the conv kernel
 // itself does not produce them)
 size_t channel_stats_ws(size_t m, int C);

@@ -265,3 +265,42 @@ def test_weight_transposes_on_either_stream_give_the_same_bits():
     a = _run_steps(net, inp, {}, two_streams=True, steps=3)
     b = _run_steps(net, inp, {12: -1}, two_streams=True, steps=3)
     _assert_same_bits(net, a, b)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("C,size,batch", [(8, 1, 1), (24, 5, 3), (64, 7, 9), (136, 4, 2), (1024, 3, 2), (2048, 2, 1)])
+def test_kept_relu_masks_give_the_gradients_that_y_gives(dtype, C, size, batch):
+    """A batch norm with a residual input keeps its ReLU mask in the step; the entry point, which takes the mask from
+    y, gives the same bits from the tensors that the step left: residual gradients written and accumulated."""
+    from paper_2503_23186_amd import StepRunner, cnnk
+    net = WL.Net("masks", batch, dtype)
+    a = net.bn(net.conv(net.slot(batch, size, size, 3), C, 3, 1))
+    r = net.bn(net.conv(a, C, 1, 1), relu=False)
+    t = net.bn(net.conv(a, C, 1, 1), relu=True, res=r)
+    for _ in range(2):
+        t = net.bn(net.conv(t, C, 1, 1), relu=True, res=a)
+    net.fc_loss(net.pool(t, "gap"))
+    inp = WL.make_inputs(net, 23, perturb_bn=True)
+    run = StepRunner(net.layers, net.slots, [p["shape"] for p in net.params], net.dtype)
+    run.load(inp["x"], inp["labels"], inp["params"], inp["mom"])
+    gains = [run.param[k].clone() for k in range(len(net.params))]
+    run.step(0.1, 0.9, 0.0)
+    checked = 0
+    for i, L in enumerate(net.layers):
+        if L["op"] != "bn" or L["res"] < 0:
+            continue
+        d = cnnk.bn_desc(batch, size, size, C, cnnk.BF16 if dtype == "bf16" else cnnk.F32, 1, 1e-5, 0.1)
+        dx, dres = torch.empty_like(run.dact[L["x"]]), torch.empty_like(run.dact[L["res"]])
+        dg, db = torch.empty(C, device="cuda:0"), torch.empty(C, device="cuda:0")
+        need = int(cnnk.cnnk_bn_workspace_bytes(d))
+        ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+        cnnk.cnnk_bn_relu_bwd(d, run.dact[L["y"]], run.act[L["x"]], run.act[L["y"]], gains[L["gamma"]], gains[L["beta"]],
+                              run.bn_save[i][0], run.bn_save[i][1], dx, dres, 0, dg, db, ws, need,
+                              torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(dx, run.dact[L["x"]]), (i, "dx")
+        assert torch.equal(dg, run.grad[L["gamma"]].view(-1)) and torch.equal(db, run.grad[L["beta"]].view(-1)), i
+        if L["res"] == r:
+            assert torch.equal(dres, run.dact[r])
+        checked += 1
+    assert checked == 3
