@@ -82,6 +82,10 @@ int conv_mfma_wgrad(const ConvGeom& g, const bf16_t* x, const bf16_t* dy, float*
 // in its own way.
 int conv_mfma_wgrad_partials(const ConvGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, void* ws,
                              const float** part, int* P, hipStream_t st);
+// what it runs for all shapes but those of conv_wgrad_patch (conv_wgrad_gemm.hip)
+size_t conv_wgrad_gemm_ws(const ConvGeom& g);
+int conv_wgrad_gemm(const ConvGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, void* ws, const float** part, int* P,
+                    hipStream_t st);
 
 // data gradient with weights already transposed to [Cin][R*S][Cout], and the batched transposition
 constexpr int kMaxTranspose = 32;

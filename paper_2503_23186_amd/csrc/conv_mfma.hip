@@ -7,9 +7,7 @@
 //    forward pass (source x, shifts r-pad / s-pad, source step = stride) and the data gradient
 //    (source dy, weights transposed to [Cin][tap][Cout], one launch class per output parity so
 //    that a strided layer only visits the taps that really contribute).
-//  * wgrad_kernel: weight gradient.  GEMM rows are output channels, columns are (tap, input
-//    channel), the reduction runs over output pixels, split across workgroups; both operands
-//    arrive channel-contiguous and are transposed in registers on their way into LDS.
+// The weight gradient's kernels are in conv_wgrad_gemm.hip and conv_wgrad_dma.hip.
 #include <type_traits>
 #include "common.h"
 #include "conv.h"
@@ -414,172 +412,6 @@ __global__ void __launch_bounds__(256) transpose_weights_multi_kernel(TransposeT
 }
 
 // ------------------------------------------------------------------------------------------
-struct WgradArgs {
-  const bf16_t* x;
-  const bf16_t* dy;
-  float* part;  // [splits][Cout][Q]
-  int N, H, W, Cin, Cout, R, S, stride, pad, Ho, Wo;
-  int M;      // N*Ho*Wo
-  int chunk;  // output positions per split (multiple of 64)
-  int Q;      // R*S*Cin
-  int qtiles;
-};
-
-__device__ __forceinline__ int swz(int row) { return (row & 7) ^ ((row >> 3) & 7); }
-
-template <int BMK, int BNQ, int WM, int WN>
-__global__ void __launch_bounds__(kThreads) wgrad_kernel(WgradArgs a) {
-  constexpr int BKP = 64;  // output positions per stage
-  constexpr int NA = (BMK / 8) * (BKP / 8), NB = (BNQ / 8) * (BKP / 8);
-  constexpr int TM = BMK / WM / 32, TN = BNQ / WN / 32;
-  static_assert(NA + NB <= kThreads && WM * WN == 4 && TM >= 1 && TN >= 1, "tile shape");
-  __shared__ __align__(16) bf16_t At[2][BMK * BKP];
-  __shared__ __align__(16) bf16_t Bt[2][BNQ * BKP];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave % WM, wn = wave / WM;
-  const int qt = blockIdx.x % a.qtiles, kt = blockIdx.x / a.qtiles;
-  const int m_begin = blockIdx.y * a.chunk;
-  const int m_end = min(m_begin + a.chunk, a.M);
-  const int nstage = (m_end - m_begin + BKP - 1) / BKP;
-
-  // role of this thread in the staging: one 8-position x 8-channel block of dy or of x
-  const bool isA = tid < NA, isB = !isA && tid < NA + NB;
-  int oct, po;  // channel octet, position octet inside the stage
-  if (isA) { oct = tid % (BMK / 8); po = tid / (BMK / 8); }
-  else { oct = (tid - NA) % (BNQ / 8); po = (tid - NA) / (BNQ / 8); }
-  int ch0 = 0, fr = 0, fs = 0;
-  bool chan_ok = false;
-  if (isA) {
-    ch0 = kt * BMK + oct * 8;
-    chan_ok = ch0 < a.Cout;
-  } else if (isB) {
-    const int q0 = qt * BNQ + oct * 8;
-    chan_ok = q0 < a.Q;
-    const int t = q0 / a.Cin;
-    ch0 = q0 % a.Cin;
-    fr = t / a.S;
-    fs = t % a.S;
-  }
-
-  f32x16_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // Every thread issues the same eight loads every stage; rows that do not exist (past the split's
-  // range, padding, a thread without a staging role) use the out-of-range buffer offset, which
-  // returns zeros without touching memory.  Straight-line loads let the compiler wait for exactly
-  // the loads it needs instead of draining the queue at every divergent join.
-  const __amdgpu_buffer_rsrc_t dy_rs = make_rsrc(a.dy, (unsigned)a.M * a.Cout * 2u);
-  const __amdgpu_buffer_rsrc_t x_rs = make_rsrc(a.x, (unsigned)a.N * a.H * a.W * a.Cin * 2u);
-  uint4 rg[8];
-  auto load_stage = [&](int s) __attribute__((always_inline)) {
-    const int m0 = m_begin + s * BKP + po * 8;
-    if (isA) {
-#pragma unroll
-      for (int p = 0; p < 8; ++p) {
-        const bool ok = chan_ok && m0 + p < m_end;
-        rg[p] = buffer_load16(dy_rs, ok ? (unsigned)((m0 + p) * a.Cout + ch0) * 2u : kOobOffset, 0);
-      }
-    } else {
-      int wo = m0 % a.Wo, q = m0 / a.Wo;
-      int ho = q % a.Ho, n = q / a.Ho;
-#pragma unroll
-      for (int p = 0; p < 8; ++p) {
-        const int hi = ho * a.stride + fr - a.pad, wi = wo * a.stride + fs - a.pad;
-        const bool ok = isB && chan_ok && m0 + p < m_end && (unsigned)hi < (unsigned)a.H && (unsigned)wi < (unsigned)a.W;
-        rg[p] = buffer_load16(x_rs, ok ? (unsigned)(((n * a.H + hi) * a.W + wi) * a.Cin + ch0) * 2u : kOobOffset, 0);
-        if (++wo == a.Wo) { wo = 0; if (++ho == a.Ho) { ho = 0; ++n; } }
-      }
-    }
-  };
-  auto store_stage = [&](int buf) __attribute__((always_inline)) {
-    if (!(isA || isB)) return;
-    bf16_t* T_ = isA ? At[buf] : Bt[buf];
-    const unsigned* rw = reinterpret_cast<const unsigned*>(rg);
-#pragma unroll
-    for (int c2 = 0; c2 < 4; ++c2) {
-      uint4 lo, hi;
-      unsigned* lw = reinterpret_cast<unsigned*>(&lo);
-      unsigned* hw = reinterpret_cast<unsigned*>(&hi);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const unsigned e = rw[(2 * j) * 4 + c2], o = rw[(2 * j + 1) * 4 + c2];
-        lw[j] = (e & 0xffffu) | (o << 16);
-        hw[j] = (e >> 16) | (o & 0xffff0000u);
-      }
-      const int rl = oct * 8 + 2 * c2, rh = rl + 1;
-      *reinterpret_cast<uint4*>(T_ + rl * BKP + ((po ^ swz(rl)) << 3)) = lo;
-      *reinterpret_cast<uint4*>(T_ + rh * BKP + ((po ^ swz(rh)) << 3)) = hi;
-    }
-  };
-  // One stage of MFMAs: the operands of 16-position slice kk+1 are read from LDS between the MFMAs
-  // of slice kk (two fragment sets, alternation pinned by the scheduling directives).
-  auto compute = [&](int cur) __attribute__((always_inline)) {
-    constexpr int KK = BKP / 16;
-    bf16x8_t af[2][TM], bfr[2][TN];
-    auto read_slice = [&](int kk, int set) {
-      const int chunk = kk * 2 + (lane >> 5);
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int row = wm * TM * 32 + i * 32 + (lane & 31);
-        af[set][i] = *reinterpret_cast<const bf16x8_t*>(At[cur] + row * BKP + ((chunk ^ swz(row)) << 3));
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int row = wn * TN * 32 + j * 32 + (lane & 31);
-        bfr[set][j] = *reinterpret_cast<const bf16x8_t*>(Bt[cur] + row * BKP + ((chunk ^ swz(row)) << 3));
-      }
-    };
-    read_slice(0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      if (kk + 1 < KK) read_slice(kk + 1, (kk + 1) & 1);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk & 1][i], bfr[kk & 1][j], acc[i][j], 0, 0, 0);
-      if (kk + 1 < KK) {
-#pragma unroll
-        for (int q = 0; q < TM * TN; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                    // one MFMA
-          if (q < TM + TN) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-
-  load_stage(0);
-  store_stage(0);
-  __syncthreads();
-  for (int s = 0; s < nstage; ++s) {
-    const int cur = s & 1;
-    load_stage(s + 1);        // past the last stage: zeros into the buffer nobody reads
-    compute(cur);
-    store_stage(cur ^ 1);
-    __syncthreads();
-  }
-
-  float* out = a.part + (size_t)blockIdx.y * a.Cout * a.Q;
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = kt * BMK + wm * TM * 32 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-        const int col = qt * BNQ + wn * TN * 32 + j * 32 + (lane & 31);
-        if (row < a.Cout && col < a.Q) out[(size_t)row * a.Q + col] = acc[i][j][r];
-      }
-}
-
 // ---------------------------------------------------------------------------- host side ----
 struct IgemmPlan {
   int bm, bn, bk;
@@ -659,22 +491,6 @@ int dispatch_igemm(const IgemmArgs& a, long maxM, const IgemmPlan& p, hipStream_
   return CNNK_ERR_UNSUPPORTED;
 }
 
-void wgrad_plan(const ConvGeom& g, int* bmk, int* chunk, int* splits, int cus = 256) {
-  const int Q = g.R * g.S * g.Cin;
-  const long M = (long)g.N * g.Ho * g.Wo;
-  *bmk = g.Cout > 64 ? 128 : 64;
-  const long tiles = (long)((g.Cout + *bmk - 1) / *bmk) * ((Q + 127) / 128);
-  const long target = g_cnnk_tune[3] > 0 ? g_cnnk_tune[3] : 3L * cus / (g.Cout <= 64 ? 1 : 2);   // 768 / 384 workgroups on the whole device
-  long want = (target + tiles - 1) / tiles;
-  const long maxs = (M + 255) / 256;
-  if (want > maxs) want = maxs;
-  if (want < 1) want = 1;
-  long ch = (M + want - 1) / want;
-  ch = (ch + 63) / 64 * 64;
-  *chunk = (int)ch;
-  *splits = (int)((M + ch - 1) / ch);
-}
-
 }  // namespace
 
 bool conv_mfma_supported(const ConvGeom& g, int pass) {
@@ -696,9 +512,7 @@ size_t conv_mfma_ws(const ConvGeom& g, int pass, bool want_stats) {
   if (pass == CNNK_PASS_DGRAD) return align_up((size_t)g.Cout * g.R * g.S * g.Cin * sizeof(bf16_t), 256);
   if (pass == CNNK_PASS_WGRAD) {
     if (conv_wgrad_patch_supported(g)) return conv_wgrad_patch_ws(g);
-    int bmk, chunk, splits;
-    wgrad_plan(g, &bmk, &chunk, &splits);
-    return splits > 1 ? (size_t)splits * g.Cout * g.R * g.S * g.Cin * sizeof(float) : 0;
+    return conv_wgrad_gemm_ws(g);
   }
   return 0;
 }
@@ -811,22 +625,7 @@ int conv_mfma_wgrad_partials(const ConvGeom& g, const bf16_t* x, const bf16_t* d
     *P = 1;
     return conv_wgrad_patch(g, x, dy, dw, ws, st);
   }
-  int bmk, chunk, splits;
-  wgrad_plan(g, &bmk, &chunk, &splits, t_cnnk_wgrad_cus);
-  WgradArgs a{};
-  a.x = x; a.dy = dy;
-  a.part = splits > 1 ? reinterpret_cast<float*>(ws) : dw;
-  a.N = g.N; a.H = g.H; a.W = g.W; a.Cin = g.Cin; a.Cout = g.Cout; a.R = g.R; a.S = g.S;
-  a.stride = g.stride; a.pad = g.pad; a.Ho = g.Ho; a.Wo = g.Wo;
-  a.M = g.N * g.Ho * g.Wo; a.chunk = chunk; a.Q = g.R * g.S * g.Cin;
-  a.qtiles = (a.Q + 127) / 128;
-  const int ktiles = (g.Cout + bmk - 1) / bmk;
-  dim3 grid(ktiles * a.qtiles, splits);
-  if (bmk == 128) hipLaunchKernelGGL((wgrad_kernel<128, 128, 2, 2>), grid, dim3(kThreads), 0, st, a);
-  else hipLaunchKernelGGL((wgrad_kernel<64, 128, 1, 4>), grid, dim3(kThreads), 0, st, a);
-  *part = a.part;
-  *P = splits;
-  return launch_status();
+  return conv_wgrad_gemm(g, x, dy, dw, ws, part, P, st);
 }
 
 int conv_mfma_wgrad(const ConvGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, void* ws,

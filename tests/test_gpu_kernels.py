@@ -176,6 +176,32 @@ def test_conv_wgrad_patch_kernel(K, shape, target):
         K.cnnk_tune(6, 0)
 
 
+# (N, H, W, Cin, Cout, R, stride): every tile of the kernel (64, 128, 256 output channels; 64, 128 columns), ended by the
+# tensor at 8 past or 8 short of it; columns of several taps in one 16-byte-piece row; fewer pixels than a stage
+WG_GEMM_SHAPES = [(1, 1, 1, 8, 8, 1, 1), (3, 5, 7, 64, 64, 1, 1), (2, 9, 9, 72, 56, 1, 1), (2, 8, 9, 56, 136, 1, 1), (5, 7, 5, 136, 120, 1, 1),
+                  (3, 11, 9, 64, 264, 1, 1), (2, 12, 11, 248, 256, 1, 1), (3, 9, 7, 24, 72, 1, 2), (2, 10, 10, 8, 264, 3, 2), (3, 7, 9, 24, 40, 3, 2),
+                  (2, 13, 8, 40, 200, 3, 2), (1, 64, 33, 64, 128, 1, 1)]
+
+
+@pytest.mark.parametrize("target", [1, 3, 40, 0])
+@pytest.mark.parametrize("shape", WG_GEMM_SHAPES)
+def test_conv_wgrad_gemm_kernel(K, shape, target):
+    """1x1 and strided weight gradients: one workgroup per output tile (plain stores), a few splits, more splits
+    than pixels allow, and the default; fp32 sums of at most 2112 products."""
+    N, H, W, Cin, Cout, R, st = shape
+    x, w, dy, pad = conv_inputs(shape, "bf16", 19)
+    d = K.conv_desc(N, H, W, Cin, Cout, R, R, st, pad, K.BF16)
+    K.cnnk_tune(3, target)
+    try:
+        gdw = torch.full(w.shape, 9.0, dtype=torch.float32, device="cuda:0")
+        ws, nb = ws_for(K.cnnk_conv2d_workspace_bytes(d, K.PASS_WGRAD))
+        K.cnnk_conv2d_wgrad(d, dev(x, "bf16"), dev(dy, "bf16"), gdw, ws, nb)
+        torch.cuda.synchronize()
+        assert max_rel_err(host(gdw), ref.conv2d_wgrad(x, dy, w.shape, st, pad)) <= 1e-4
+    finally:
+        K.cnnk_tune(3, 0)
+
+
 PATCH_TILES = [(256, 128), (256, 64), (128, 128), (128, 64)]
 PATCH_SHAPES = [(4, 8, 8, 64, 128), (2, 16, 16, 32, 64), (2, 32, 32, 32, 64), (18, 4, 4, 64, 136),
                 (5, 8, 8, 96, 72), (3, 16, 16, 64, 40), (1, 32, 32, 160, 32)]
