@@ -68,13 +68,14 @@ const char* cnnk_version(void);
  * permutation that keeps narrow images (W < 16) free of LDS bank conflicts; 8 = -1 keeps convolutions with
  * fewer than 8 input channels on the direct (plain-FMA) kernels; 11 = -1 keeps the first layer's forward
  * pass on the padded-input path; 9 = -1 makes cnnk_train_step hand y to
- * every batch-norm backward call (no mask recomputation); 12 = -1 keeps the weight transposes of
+ * every batch-norm backward call (masks neither recomputed nor kept); 12 = -1 keeps the weight transposes of
  * the data-gradient kernels on the main stream when cnnk_train_step has a second one; 14 = tiles that one workgroup of the
  * gathered implicit-GEMM kernels walks (0: as many as still fill every CU); 16 = n + 1 runs every bf16 convolution
  * of 32, 64, .. channels on tile shape n (0..7) of the kernels that load both operands straight into LDS (-1: none;
  * keys 0, 1, 2 and 14 keep layers off them, too); 13 = pixel tiles that one workgroup of
  * the 3x3 stride-1 LDS-patch kernels walks (0: as many as still leave two workgroups per CU; -1: one, and no
- * split of the reduction over two groups of wavefronts on grids of fewer than 512 workgroups).
+ * split of the reduction over two groups of wavefronts on grids of fewer than 512 workgroups); 17 = layers whose
+ * weight gradients cnnk_train_step forks onto its second stream together (1: one by one; at most 16).
  * Process-wide, not thread-safe. */
 int cnnk_tune(int key, int value);
 

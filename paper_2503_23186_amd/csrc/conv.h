@@ -173,6 +173,23 @@ int channel_sums_finalize(const float* part, int nb, int C, float* ch_sum, float
 // wait (nullable): an event the stream waits for between the weight-gradient kernel and the
 // reduction (the last reader of the old weights).  done is set when the fused launch was made;
 // callers fall back to a separate update otherwise (unsplit reductions, other reducers).
+// group (nullable): instead of being launched, the reduction and its update are appended to the group (while it has
+// room; done is set all the same), whose one launch the step makes later; the partial sums stay until then.
+constexpr int kReduceGroup = 16;
+struct ReduceItem {
+  const float* part;
+  float* out;
+  float* w;
+  float* v;
+  bf16_t* wlp;
+  int n, P, block0;
+};
+struct ReduceGroup {
+  int count;
+  float lr, mu, wd;
+  ReduceItem it[kReduceGroup];
+};
+int reduce_group(ReduceGroup& g, hipStream_t st);
 struct SgdFuse {
   float* w;
   float* v;
@@ -180,6 +197,7 @@ struct SgdFuse {
   float lr, mu, wd;
   hipEvent_t wait;
   bool done;
+  ReduceGroup* group;
 };
 extern thread_local SgdFuse* t_cnnk_sgd_fuse;
 

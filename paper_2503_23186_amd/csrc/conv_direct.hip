@@ -127,13 +127,14 @@ __device__ __forceinline__ float sgd_apply(float wi, float vi, float gi, const S
   return fmaf(-sg.lr, *vn, wi);
 }
 
+// workgroup `block` of the reduction of one tensor; mem: 256 float4 of LDS
 template <int GROUPS, bool SGD>
-__global__ void __launch_bounds__(256) reduce_partials_kernel(const float* __restrict__ part,
-                                                              float* __restrict__ out, int n, int P, SgdArgs sg) {
+__device__ __forceinline__ void reduce_block(const float* __restrict__ part, float* __restrict__ out, int n, int P,
+                                             const SgdArgs& sg, int block, float4* mem) {
   constexpr int COLS = 256 / GROUPS;
-  __shared__ float4 red[GROUPS][COLS];
+  float4(*red)[COLS] = reinterpret_cast<float4(*)[COLS]>(mem);
   const int col = threadIdx.x % COLS, grp = threadIdx.x / COLS;
-  const int i4 = blockIdx.x * COLS + col;   // float4 column
+  const int i4 = block * COLS + col;   // float4 column
   const int n4 = n >> 2;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   // weight and momentum of the fused update are fetched under the partial sums
@@ -186,7 +187,7 @@ __global__ void __launch_bounds__(256) reduce_partials_kernel(const float* __res
     }
   }
   // scalar tail (n not a multiple of 4)
-  if (blockIdx.x == 0 && threadIdx.x < (n & 3)) {
+  if (block == 0 && threadIdx.x < (n & 3)) {
     const int i = (n4 << 2) + threadIdx.x;
     float a = 0.f;
     for (int p = 0; p < P; ++p) a += part[(size_t)p * n + i];
@@ -199,6 +200,27 @@ __global__ void __launch_bounds__(256) reduce_partials_kernel(const float* __res
       if (sg.wlp) sg.wlp[i] = f32_to_bf16(wn);
     }
   }
+}
+
+template <int GROUPS, bool SGD>
+__global__ void __launch_bounds__(256) reduce_partials_kernel(const float* __restrict__ part,
+                                                              float* __restrict__ out, int n, int P, SgdArgs sg) {
+  __shared__ float4 mem[256];
+  reduce_block<GROUPS, SGD>(part, out, n, P, sg, blockIdx.x, mem);
+}
+
+// The reductions and updates of several tensors in one launch (each alone is 4 to 9 us, most of it the launch and
+// one chain of memory latencies).
+constexpr int kManyPartials = 32;      // from here on sixteen threads share a column, four below
+__global__ void __launch_bounds__(256) reduce_group_kernel(ReduceGroup g) {
+  __shared__ float4 mem[256];
+  int k = 0;
+  while (k + 1 < g.count && (int)blockIdx.x >= g.it[k + 1].block0) ++k;
+  const ReduceItem& t = g.it[k];
+  const SgdArgs sg{t.w, t.v, t.wlp, g.lr, g.mu, g.wd};
+  const int block = blockIdx.x - t.block0;
+  if (t.P >= kManyPartials) reduce_block<16, true>(t.part, t.out, t.n, t.P, sg, block, mem);
+  else reduce_block<4, true>(t.part, t.out, t.n, t.P, sg, block, mem);
 }
 
 void wgrad_split(const ConvGeom& g, int* chunk, int* P) {
@@ -261,19 +283,38 @@ int conv_direct_wgrad(const ConvGeom& g, int dtype, const void* x, const void* d
 
 thread_local SgdFuse* t_cnnk_sgd_fuse = nullptr;
 
+static unsigned reduce_blocks_for(int n, int P) { return (unsigned)(P >= kManyPartials ? (n / 4 + 15) / 16 + 1 : (n / 4 + 63) / 64 + 1); }
+
+int reduce_group(ReduceGroup& g, hipStream_t st) {
+  if (g.count == 0) return CNNK_OK;
+  int blocks = 0;
+  for (int k = 0; k < g.count; ++k) {
+    g.it[k].block0 = blocks;
+    blocks += (int)reduce_blocks_for(g.it[k].n, g.it[k].P);
+  }
+  reduce_group_kernel<<<blocks, 256, 0, st>>>(g);
+  g.count = 0;
+  return launch_status();
+}
+
 int reduce_partials(const float* part, float* out, int n, int P, hipStream_t st) {
-  const unsigned g16 = (unsigned)((n / 4 + 15) / 16 + 1), g4 = (unsigned)((n / 4 + 63) / 64 + 1);
+  const unsigned g16 = reduce_blocks_for(n, kManyPartials), g4 = reduce_blocks_for(n, 0);
   SgdFuse* f = t_cnnk_sgd_fuse;
   if (f && !f->done && ((((size_t)f->w | (size_t)f->v | (size_t)out) & 15) == 0) && (((size_t)f->wlp & 7) == 0)) {
+    if (f->group && f->group->count < kReduceGroup) {
+      f->group->it[f->group->count++] = ReduceItem{part, out, f->w, f->v, static_cast<bf16_t*>(f->wlp), n, P, 0};
+      f->done = true;
+      return CNNK_OK;
+    }
     if (f->wait && hipStreamWaitEvent(st, f->wait, 0) != hipSuccess) return CNNK_ERR_HIP;
     const SgdArgs sg{f->w, f->v, static_cast<bf16_t*>(f->wlp), f->lr, f->mu, f->wd};
-    if (P >= 32) reduce_partials_kernel<16, true><<<g16, 256, 0, st>>>(part, out, n, P, sg);
+    if (P >= kManyPartials) reduce_partials_kernel<16, true><<<g16, 256, 0, st>>>(part, out, n, P, sg);
     else reduce_partials_kernel<4, true><<<g4, 256, 0, st>>>(part, out, n, P, sg);
     f->done = true;
     return launch_status();
   }
   const SgdArgs none{nullptr, nullptr, nullptr, 0.f, 0.f, 0.f};
-  if (P >= 32) reduce_partials_kernel<16, false><<<g16, 256, 0, st>>>(part, out, n, P, none);
+  if (P >= kManyPartials) reduce_partials_kernel<16, false><<<g16, 256, 0, st>>>(part, out, n, P, none);
   else reduce_partials_kernel<4, false><<<g4, 256, 0, st>>>(part, out, n, P, none);
   return launch_status();
 }

@@ -32,6 +32,7 @@ struct Walk {
   std::vector<size_t> mask_off;      // per layer: offset of its ReLU mask, or (size_t)-1
   size_t mask_bytes = 0;             // ReLU masks (a bit per element) of the batch norms with a residual input
   double flops = 0;                  // of the convolutions, forward and backward
+  int convs = 0;
   int dtype = -1;
 };
 
@@ -48,6 +49,19 @@ bool set_elems(std::vector<size_t>& v, int id, size_t n) {
   if (id < 0 || id >= (int)v.size()) return false;
   if (v[id] == 0) { v[id] = n; return true; }
   return v[id] == n;
+}
+
+// Layers whose weight gradients share a fork of the second stream, and the launch of their reductions and updates.
+// Small steps are bound by enqueueing (ResNet-18 at batch 32: 1305 of 1334 us; a fork and its events cost as much as
+// several launches), so they take two at a time; large ones lose, because a weight gradient starts later and less of it
+// runs beside the data gradients.  us per step one by one / in pairs, by flops per convolution (forward and backward):
+// ResNet-50 b16 2.3 GF 3539 / 2623, ResNet-18 b32 5.3 GF 1212 / 1095, VGG-style b64 9.7 GF 415 / 403, ResNet-18 b64 10.7 GF
+// 1297 / 1219, b77 12.8 GF 1360 / 1363, VGG-style b128 19 GF 460 / 485, WRN-28-10 b64 72 GF 4119 / 4223.  Three to
+// sixteen at a time are slower than two everywhere but below 3 GF, where three and four are even.
+constexpr double kPairFlops = 11e9;
+int wgrad_group(const Walk& w) {
+  if (g_cnnk_tune[17] > 0) return g_cnnk_tune[17] < kReduceGroup ? g_cnnk_tune[17] : kReduceGroup;
+  return w.flops < kPairFlops * w.convs ? 2 : 1;
 }
 
 size_t max_sz(size_t a, size_t b) { return a > b ? a : b; }
@@ -85,6 +99,7 @@ int walk_layers(const cnnk_layer* L, int n, int n_slots, int n_params, Walk* w) 
              set_elems(w->slot_elems, l.in0, (size_t)d.N * d.H * d.W * d.Cin) &&
              set_elems(w->slot_elems, l.out, (size_t)d.N * Ho * Wo * d.Cout) &&
              set_elems(w->param_elems, l.p0, (size_t)d.Cout * d.R * d.S * d.Cin);
+        ++w->convs;
         w->flops += 2.0 * d.N * Ho * Wo * d.Cout * d.R * d.S * d.Cin * (l.in0 == 0 ? 2 : 3);
         for (int p = 0; p < 3; ++p) w->ws = max_sz(w->ws, cnnk_conv2d_workspace_bytes(&d, p));
         if (dgrad_pretransposed(l)) {
@@ -241,7 +256,7 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
   // read the whole output for it (a third of the first pass's reads: 45.5 -> 37.9 us per layer of ResNet-50 b256, where
   // these are the widest tensors, step 8.03 -> 7.98 ms; ResNet-18 b256 unchanged).
   unsigned char* const masks = reinterpret_cast<unsigned char*>(wt_region) + w.wt_bytes;
-  auto mask_of = [&](int i) { return w.mask_off[i] != (size_t)-1 ? masks + w.mask_off[i] : nullptr; };
+  auto mask_of = [&](int i) { return w.mask_off[i] != (size_t)-1 && g_cnnk_tune[9] >= 0 ? masks + w.mask_off[i] : nullptr; };
   void* ws = masks + w.mask_bytes;
   const size_t wsb = (aux ? ws_one : B->ws_bytes) - kStatBytes - w.wt_bytes - w.mask_bytes;
   GroupTimer timer(B, n, stream);
@@ -395,6 +410,57 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
   std::vector<char> written(w.slot_elems.size(), 0);
   std::vector<char> updated(w.param_elems.size(), 0);   // parameters already updated on the second stream
   written[L[n - 1].in0] = 1;
+  // Second stream, several layers at a time: one fork, their weight gradients, and one launch for all their
+  // reductions and updates.
+  const int group = aux && bf16 ? wgrad_group(w) : 1;
+  std::vector<int> pending;
+  auto flush = [&]() -> int {
+    if (pending.empty()) return CNNK_OK;
+    if (hipEventRecord((hipEvent_t)B->ev_fork, (hipStream_t)stream) != hipSuccess ||
+        hipStreamWaitEvent(aux, (hipEvent_t)B->ev_fork, 0) != hipSuccess)
+      return CNNK_ERR_HIP;
+    ReduceGroup rg;
+    rg.count = 0;
+    rg.lr = lr; rg.mu = momentum; rg.wd = weight_decay;
+    SgdTable rest;
+    rest.count = 0;
+    size_t used = 0;
+    int r = CNNK_OK;
+    for (int i : pending) {
+      const cnnk_layer& l = L[i];
+      // the partial sums of a layer stay until the group's launch: the next layer's follow them
+      if (used + cnnk_conv2d_workspace_bytes(&l.d.conv, CNNK_PASS_WGRAD) > aux_wsb) {
+        r = reduce_group(rg, aux);
+        if (r != CNNK_OK) return r;
+        used = 0;
+      }
+      void* const lp = B->param_lp ? B->param_lp[l.p0] : nullptr;
+      SgdFuse fuse{B->param[l.p0], B->mom[l.p0], lp, lr, momentum, weight_decay, nullptr, false, &rg};
+      X8Cache x8c{reinterpret_cast<bf16_t*>(wt_region + w.x8_off), x8_valid};
+      const int before = rg.count;
+      t_cnnk_sgd_fuse = &fuse;
+      t_cnnk_wgrad_cus = kAuxWgradCus;
+      if (i == w.x8_layer && x8_valid) t_cnnk_x8_cache = &x8c;
+      r = cnnk_conv2d_wgrad(&l.d.conv, B->act[l.in0], B->dact[l.out], B->grad[l.p0], static_cast<char*>(aux_ws) + used, aux_wsb - used, aux);
+      t_cnnk_x8_cache = nullptr;
+      t_cnnk_wgrad_cus = 256;
+      t_cnnk_sgd_fuse = nullptr;
+      if (r != CNNK_OK) return r;
+      if (rg.count > before) {
+        const ReduceItem& t = rg.it[before];
+        used = (size_t)(reinterpret_cast<const char*>(t.part + (size_t)t.n * t.P) - static_cast<const char*>(aux_ws));
+        used = (used + 255) / 256 * 256;
+      } else if (!fuse.done) {      // nothing to reduce
+        const int k = rest.count++;
+        rest.w[k] = B->param[l.p0]; rest.v[k] = B->mom[l.p0]; rest.g[k] = B->grad[l.p0];
+        rest.wlp[k] = lp; rest.n[k] = w.param_elems[l.p0];
+      }
+    }
+    pending.clear();
+    r = reduce_group(rg, aux);
+    if (r == CNNK_OK && rest.count) r = sgd_multi(rest, lr, momentum, weight_decay, aux);
+    return r;
+  };
   // Tried and dropped (ResNet-18 b256, same-box A/B): (1) the backward pass of a projection shortcut
   // on the second stream - queued behind the weight gradients there it made the main stream wait,
   // 2.45 vs 2.37 ms; (2) per-channel sums through exact 64-bit integer atomics (three fixed-point
@@ -436,6 +502,17 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
           if (rc == CNNK_OK) rc = dgrad();
           break;
         }
+        if (group > 1) {
+          rc = dgrad();
+          if (rc != CNNK_OK) return rc;
+          for (int k : pending)        // layers that share their weights are not updated in one launch
+            if (L[k].p0 == l.p0) { rc = flush(); break; }
+          if (rc != CNNK_OK) return rc;
+          pending.push_back(i);
+          updated[l.p0] = 1;
+          if ((int)pending.size() == group) rc = flush();
+          break;
+        }
         // dy and x are final here: fork the weight gradient onto the second stream
         if (hipEventRecord((hipEvent_t)B->ev_fork, (hipStream_t)stream) != hipSuccess ||
             hipStreamWaitEvent(aux, (hipEvent_t)B->ev_fork, 0) != hipSuccess)
@@ -451,7 +528,7 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
         if (after_dgrad && hipEventRecord((hipEvent_t)B->ev_fork, (hipStream_t)stream) != hipSuccess)
           return CNNK_ERR_HIP;
         SgdFuse fuse{B->param[l.p0], B->mom[l.p0], (bf16 && B->param_lp) ? B->param_lp[l.p0] : nullptr,
-                     lr, momentum, weight_decay, after_dgrad ? (hipEvent_t)B->ev_fork : nullptr, false};
+                     lr, momentum, weight_decay, after_dgrad ? (hipEvent_t)B->ev_fork : nullptr, false, nullptr};
         t_cnnk_sgd_fuse = &fuse;
         t_cnnk_wgrad_cus = kAuxWgradCus;
         X8Cache x8c{reinterpret_cast<bf16_t*>(wt_region + w.x8_off), x8_valid};
@@ -513,6 +590,8 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
     timer.end(g0 + 1);
     if (rc != CNNK_OK) return rc;
   }
+  rc = flush();
+  if (rc != CNNK_OK) return rc;
   // ---- parameter update -----------------------------------------------------------------------
   // With a second stream the parameters that are left (batch-norm and classifier parameters: their
   // gradients were computed on this stream) are updated first; the wait for the tail of the other

@@ -304,3 +304,27 @@ def test_kept_relu_masks_give_the_gradients_that_y_gives(dtype, C, size, batch):
             assert torch.equal(dres, run.dact[r])
         checked += 1
     assert checked == 3
+
+
+@pytest.mark.parametrize("group", [2, 5, 16])
+def test_grouped_weight_gradients_give_the_same_bits(group):
+    """Weight gradients forked onto the second stream one by one and several at a time, their reductions and updates
+    in one launch: the same kernels and orders of summation, so the same bits after two steps."""
+    from paper_2503_23186_amd import StepRunner, cnnk
+    net = WL.mini_resnet(batch=48, dtype="bf16", size=32, widths=(32, 72))
+    inp = WL.make_inputs(net, 29)
+    out = []
+    for g in (1, group):
+        cnnk.cnnk_tune(17, g)
+        try:
+            run = StepRunner(net.layers, net.slots, [p["shape"] for p in net.params], net.dtype)
+            run.load(inp["x"], inp["labels"], inp["params"], inp["mom"])
+            for _ in range(2):
+                run.step(0.1, 0.9, 1e-3)
+            torch.cuda.synchronize()
+        finally:
+            cnnk.cnnk_tune(17, 0)
+        out.append([t.clone() for t in run.param + run.mom + run.grad + [t for t in run.dact if t is not None]])
+    assert net.conv_flops()[1] > 2e9          # below, the step leaves its second stream unused
+    for k, (a, b) in enumerate(zip(*out)):
+        assert torch.equal(a, b), k
