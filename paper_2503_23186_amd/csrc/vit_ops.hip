@@ -75,9 +75,12 @@ __global__ void __launch_bounds__(kT) ln_fwd_kernel(const T* __restrict__ x, lon
 // A wavefront walks its rows RU at a time (1 as launched: two rows in flight cost the registers that
 // a second resident workgroup needs, 40 against 27 us at ViT-B/16's shape); per row two
 // wave reductions give the two projections that the normalisation removes; the lane keeps its
-// columns' contributions to dgamma / dbeta in registers over all its rows.  The four wavefronts of a
-// workgroup then add theirs in LDS one after the other (fixed order) and the workgroup writes one
-// partial row.  VW elements per access (8 where C allows), NV vectors of the row per lane.
+// columns' contributions to dgamma / dbeta in registers over all its rows.  Every wavefront leaves them in
+// LDS (16 bytes a lane: no bank conflicts; one wavefront after the other, each adding to the last one's in
+// 4-byte accesses 32 bytes apart, was a third of a small launch: 788 x 768 13.4 -> 8.3 us), and the
+// workgroup adds them in wavefront order and writes one partial row.  VW elements per access (8 where C allows;
+// 4 for 512 < C <= 768, where every lane then has three vectors instead of one and a half), NV vectors of the
+// row per lane.
 template <int VW, typename T> __device__ __forceinline__ void loadv(const T* p, float* f) {
   if (VW == 8) load8(p, f); else load4(p, f);
 }
@@ -89,7 +92,7 @@ template <typename T, int NV, int VW, int RU>
 __global__ void __launch_bounds__(kT) ln_bwd_kernel(const T* __restrict__ dy, const T* __restrict__ x, long long xs,
                                                     const float* __restrict__ g, const float* __restrict__ stats,
                                                     const T* dres, T* dx, float* __restrict__ part, int rows, int C) {
-  extern __shared__ float sm[];     // [2][C]
+  extern __shared__ __align__(16) float sm[];     // [wavefront][C]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float gg[NV][VW], ag[NV][VW], ab[NV][VW];
 #pragma unroll
@@ -153,23 +156,32 @@ __global__ void __launch_bounds__(kT) ln_bwd_kernel(const T* __restrict__ dy, co
       }
     }
   }
-  for (int w = 0; w < kT / 64; ++w) {
-    if (wave == w) {
+  // dgamma, then dbeta: every wavefront leaves its sums, then they are added in order
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int c = (i * 64 + lane) * VW;
-        if (c < C) {
+  for (int v = 0; v < 2; ++v) {
+    if (v) __syncthreads();
 #pragma unroll
-          for (int k = 0; k < VW; ++k) {
-            sm[c + k] = (w ? sm[c + k] : 0.f) + ag[i][k];
-            sm[C + c + k] = (w ? sm[C + c + k] : 0.f) + ab[i][k];
-          }
+    for (int i = 0; i < NV; ++i) {
+      const int c = (i * 64 + lane) * VW;
+      if (c < C) {
+#pragma unroll
+        for (int k = 0; k < VW; k += 4) {
+          const float* a = v ? &ab[i][k] : &ag[i][k];
+          *reinterpret_cast<float4*>(sm + wave * C + c + k) = make_float4(a[0], a[1], a[2], a[3]);
         }
       }
     }
     __syncthreads();
+    for (int c = threadIdx.x * 4; c < C; c += kT * 4) {
+      float4 t = *reinterpret_cast<const float4*>(sm + c);
+#pragma unroll
+      for (int w = 1; w < kT / 64; ++w) {
+        const float4 u = *reinterpret_cast<const float4*>(sm + w * C + c);
+        t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+      }
+      *reinterpret_cast<float4*>(part + (size_t)blockIdx.x * 2 * C + v * C + c) = t;
+    }
   }
-  for (int c = threadIdx.x; c < 2 * C; c += kT) part[(size_t)blockIdx.x * 2 * C + c] = sm[c];
 }
 
 // out[c] = sum_b part[b][c]; columns [0, n0) go to out0, the rest to out1.  A workgroup owns 64
@@ -422,7 +434,16 @@ inline unsigned grid_for(size_t work_items, unsigned cap = 8192) {
   return (unsigned)(b < 1 ? 1 : (b > cap ? cap : b));
 }
 inline int ln_nq(int C) { return C <= 256 ? 1 : C <= 1024 ? 4 : 16; }
-inline int ln_bwd_blocks(int rows) { int b = (rows + 7) / 8; return b < 1 ? 1 : (b > 768 ? 768 : b); }
+// Workgroups of the layer-norm backward pass: every wavefront gets the same number of rows, one up to 1600 rows (a
+// second one is another chain of latencies: 1576 x 768 12.6 us with two, 10.6 with one), at least two beyond (the
+// partial sums cost the final launch more than that saves: 3152 x 768 16.3 us with one, 12.5 with two), and no more
+// workgroups than are resident at once (12608 x 1024: 34.1 us with 20 workgroups more than that, 30.0 without).
+inline int ln_bwd_blocks(int rows, int C) {
+  const int most = 4 * (C <= 768 ? 1024 : C <= 1024 ? 768 : 512);
+  int per = (rows + most - 1) / most;
+  if (rows > 1600 && per < 2) per = 2;
+  return (rows + 4 * per - 1) / (4 * per);
+}
 inline bool aligned16(const void* p) { return (((size_t)p) & 15) == 0; }
 }  // namespace
 
@@ -461,16 +482,16 @@ extern "C" int cnnk_layernorm_fwd(const cnnk_ln_desc* d, const void* x, const fl
 
 extern "C" size_t cnnk_layernorm_workspace_bytes(const cnnk_ln_desc* d) {
   if (check_ln(d) != CNNK_OK) return 0;
-  return align_up((size_t)ln_bwd_blocks(d->rows) * 2 * d->C * sizeof(float), 256);
+  return align_up((size_t)ln_bwd_blocks(d->rows, d->C) * 2 * d->C * sizeof(float), 256);
 }
 
 template <typename T>
 static void launch_ln_bwd(const cnnk_ln_desc* d, long long xs, int nb, const void* dy, const void* x, const float* g,
                           const float* stats, const void* dres, void* dx, float* part, hipStream_t st) {
-  const size_t lds = (size_t)2 * d->C * sizeof(float);
+  const size_t lds = (size_t)(kT / 64) * d->C * sizeof(float);
 #define LN_BWD(NV, VW) ln_bwd_kernel<T, NV, VW, 1><<<nb, kT, lds, st>>>((const T*)dy, (const T*)x, xs, g, stats, (const T*)dres, (T*)dx, part, d->rows, d->C)
   if (d->C % 8 == 0 && xs % 8 == 0) {
-    if (d->C <= 512) LN_BWD(1, 8); else if (d->C <= 1024) LN_BWD(2, 8); else if (d->C <= 2048) LN_BWD(4, 8); else LN_BWD(8, 8);
+    if (d->C <= 512) LN_BWD(1, 8); else if (d->C <= 768) LN_BWD(3, 4); else if (d->C <= 1024) LN_BWD(2, 8); else if (d->C <= 2048) LN_BWD(4, 8); else LN_BWD(8, 8);
   } else {
     if (d->C <= 256) LN_BWD(1, 4); else if (d->C <= 1024) LN_BWD(4, 4); else LN_BWD(16, 4);
   }
@@ -480,7 +501,7 @@ static void launch_ln_bwd(const cnnk_ln_desc* d, long long xs, int nb, const voi
 int ln_bwd_rows_partial(const cnnk_ln_desc* d, const void* dy, const void* x, const float* gamma, const float* stats,
                         const void* dres, void* dx, float* part, hipStream_t st) {
   const long long xs = d->x_stride ? d->x_stride : d->C;
-  const int nb = ln_bwd_blocks(d->rows);
+  const int nb = ln_bwd_blocks(d->rows, d->C);
   if (d->dtype == CNNK_BF16) launch_ln_bwd<bf16_t>(d, xs, nb, dy, x, gamma, stats, dres, dx, part, st);
   else launch_ln_bwd<float>(d, xs, nb, dy, x, gamma, stats, dres, dx, part, st);
   return launch_status();
@@ -488,7 +509,7 @@ int ln_bwd_rows_partial(const cnnk_ln_desc* d, const void* dy, const void* x, co
 
 int ln_bwd_finalize_group(const cnnk_ln_desc* d, const LnFinalizeTable& t, hipStream_t st) {
   if (t.count == 0) return CNNK_OK;
-  ln_finalize_group_kernel<<<dim3((2 * d->C + 63) / 64, t.count), kT, 0, st>>>(t, ln_bwd_blocks(d->rows), d->C);
+  ln_finalize_group_kernel<<<dim3((2 * d->C + 63) / 64, t.count), kT, 0, st>>>(t, ln_bwd_blocks(d->rows, d->C), d->C);
   return launch_status();
 }
 
@@ -502,7 +523,7 @@ extern "C" int cnnk_layernorm_bwd(const cnnk_ln_desc* d, const void* dy, const v
   if (!aligned16(x) || !aligned16(dy) || !aligned16(dx) || !aligned16(gamma) || (dres && !aligned16(dres)) || !aligned16(ws))
     return CNNK_ERR_UNSUPPORTED;
   const long long xs = d->x_stride ? d->x_stride : d->C;
-  const int nb = ln_bwd_blocks(d->rows);
+  const int nb = ln_bwd_blocks(d->rows, d->C);
   hipStream_t st = (hipStream_t)stream;
   if (d->dtype == CNNK_BF16) launch_ln_bwd<bf16_t>(d, xs, nb, dy, x, gamma, stats, dres, dx, (float*)ws, st);
   else launch_ln_bwd<float>(d, xs, nb, dy, x, gamma, stats, dres, dx, (float*)ws, st);

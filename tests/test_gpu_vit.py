@@ -71,6 +71,15 @@ def test_layernorm(K, rows, C, stride, dtype):
         assert max_rel_err(host(gdg), dg) <= SUM_TOL[dtype] and max_rel_err(host(gdb), db) <= SUM_TOL[dtype]
 
 
+# rows on either side of each change in the number of rows of a wavefront, with the widths on either side of each
+# change of kernel and of resident workgroups
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,C", [(1600, 520), (1601, 768), (1602, 772), (4097, 64), (8193, 512), (3073, 1024), (6145, 776), (2049, 1032),
+                                    (3, 640), (5, 516)])
+def test_layernorm_row_splits(K, rows, C, dtype):
+    test_layernorm(K, rows, C, 0, dtype)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("rows,C", [(37, 32), (394, 3072), (100, 2304), (1000, 768), (3, 8), (129, 264)])
 def test_bias_activation_residual(K, rows, C, dtype):
