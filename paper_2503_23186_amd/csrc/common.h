@@ -4,6 +4,7 @@
 #include <stddef.h>
 #include <stdint.h>
 #include "../../include/cnnk.h"
+#include "fastdiv.h"
 
 typedef unsigned short bf16_t;  // raw bfloat16 bits
 
@@ -100,17 +101,6 @@ __device__ __forceinline__ float wave_max(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
 }
-
-// Division of small non-negative integers by a runtime constant without the ~30-instruction
-// hardware-less integer division: q = (x * magic) >> 32 with magic = floor(2^32 / d) + 1 is exact
-// whenever x * d < 2^32 (the excess x * (magic*d - 2^32) / (d * 2^32) stays below 1/d because
-// magic*d - 2^32 <= d).  Callers keep x * d far below that bound.
-struct FastDiv {
-  unsigned d, magic;
-  __host__ __device__ void init(unsigned dd) { d = dd; magic = dd > 1 ? (unsigned)(0x100000000ull / dd) + 1u : 0u; }
-  __device__ __forceinline__ int div(int x) const { return d > 1 ? (int)__umulhi((unsigned)x, magic) : x; }
-  __device__ __forceinline__ void divmod(int x, int* q, int* r) const { *q = div(x); *r = x - *q * (int)d; }
-};
 
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 static inline int conv_out(int H, int pad, int R, int stride) { return (H + 2 * pad - R) / stride + 1; }

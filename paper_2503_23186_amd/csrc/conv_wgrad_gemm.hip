@@ -73,9 +73,7 @@ template <class C, bool LIN> struct WgLoader {
     if (LIN) return p < m_end ? (unsigned)(p * a->Cin) * 2u + bcol[j] : kOobOffset;
     int q, wo, n, ho;
     a->dW.divmod(p < m_end ? p : 0, &q, &wo);
-    if (wo < 0) { wo += a->Wo; --q; }            // the quotient is one too large for some p >= 2^32 / Wo
     a->dH.divmod(q, &n, &ho);
-    if (ho < 0) { ho += a->Ho; --n; }
     const int hi = ho * a->stride + dr[j], wi = wo * a->stride + dc[j];
     const bool ok = p < m_end && (unsigned)hi < (unsigned)a->H && (unsigned)wi < (unsigned)a->W;
     return ok ? (unsigned)(((n * a->H + hi) * a->W + wi) * a->Cin) * 2u + bcol[j] : kOobOffset;

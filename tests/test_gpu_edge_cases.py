@@ -219,3 +219,46 @@ def test_relu_exactly_at_zero(K, with_res, dtype):
     # what a non-strict mask would have produced is far outside the tolerance (the test can fail)
     dz_wrong = dy * (y_in >= 0)
     assert abs(dz_wrong.reshape(-1, C).sum(0) - db_ref).max() > 0.2 * abs(db_ref).max()
+
+
+# more pixels times image width than 2^32: a 1x1 and a strided layer on the kernels with both operands loaded into LDS
+# (and the gathered kernel in the first one's data gradient), the patch kernels, the first layer's
+@pytest.mark.parametrize("N,size,Cin,Cout,R,stride", [(5, 1024, 96, 32, 1, 1), (5, 2048, 32, 32, 3, 2), (5, 1024, 32, 32, 3, 1),
+                                                      (5, 1024, 3, 32, 3, 1), (5, 1024, 64, 32, 1, 1)])
+def test_pixel_indices_of_large_images(K, N, size, Cin, Cout, R, stride):
+    """Outputs at row ends of the later images (and everywhere else) against fp32 products of shifted views."""
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(7)
+    pad, Ho = R // 2, (size + 2 * (R // 2) - R) // stride + 1
+    bf = dict(device="cuda:0", dtype=torch.bfloat16)
+    assert N * Ho * Ho * Ho > 2 ** 32
+    x = torch.randn((N, size, size, Cin), generator=g, **bf)
+    w = torch.randn((Cout, R, R, Cin), generator=g, **bf) * (Cin * R * R) ** -0.5
+    dy = torch.randn((N, Ho, Ho, Cout), generator=g, **bf)
+    d = K.conv_desc(N, size, size, Cin, Cout, R, R, stride, pad, K.BF16)
+    ws, nb = ws_for(max(K.cnnk_conv2d_workspace_bytes(d, p) for p in range(3)))
+    y, dx = torch.zeros_like(dy), torch.zeros_like(x)
+    dw = torch.zeros((Cout, R, R, Cin), device="cuda:0")
+    K.cnnk_conv2d_fwd(d, x, w, y, None, None, ws, nb)
+    if Cin > 8:
+        K.cnnk_conv2d_dgrad(d, dy, w, dx, 0, ws, nb)
+    K.cnnk_conv2d_wgrad(d, x, dy, dw, ws, nb)
+    torch.cuda.synchronize()
+    wf, dw_ref = w.float(), torch.zeros_like(dw)
+    for n in range(N):
+        xp = torch.nn.functional.pad(x[n].float(), (0, 0, pad, pad, pad, pad))
+        y_ref, dx_ref = torch.zeros((Ho, Ho, Cout), device="cuda:0"), torch.zeros_like(xp)
+        for r in range(R):
+            for s in range(R):
+                view = (slice(r, r + (Ho - 1) * stride + 1, stride), slice(s, s + (Ho - 1) * stride + 1, stride))
+                y_ref += xp[view] @ wf[:, r, s].T
+                dx_ref[view] += dy[n].float() @ wf[:, r, s]
+                dw_ref[:, r, s] += dy[n].float().reshape(-1, Cout).T @ xp[view].reshape(-1, Cin)
+        # one bf16 rounding of the result (2^-9) and fp32 sums of at most 864 terms
+        for name, got, want in (("y", y[n], y_ref), ("dx", dx[n], dx_ref[pad:pad + size, pad:pad + size])):
+            if name == "dx" and Cin <= 8:
+                continue
+            err = (got.float() - want).abs()
+            assert bool((err <= 2 ** -8 * want.abs() + 1e-4).all()), (name, n, err.max().item())
+    # sums of 5 M products of unit variance in two orders: 1e-6 of the terms' 2-norm is seen between such orders
+    assert ((dw - dw_ref).norm() / dw_ref.norm()).item() < 1e-4
