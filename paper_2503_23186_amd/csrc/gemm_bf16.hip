@@ -20,6 +20,7 @@
 // an output is rounded once.  The weight gradient splits the row range over blockIdx.z and writes
 // fp32 partials that a second kernel adds in a fixed order.
 #include "common.h"
+#include "gelu.h"
 #include "gemm.h"
 #include "mfma_tile.h"
 
@@ -45,42 +46,6 @@ struct Args {
   int mtiles, ntiles;
   unsigned a_bytes, b_bytes, c_bytes;
 };
-
-// gelu(u) = u/2 (1 + erf(u / sqrt 2)) with erf(t) = t P(t^2) on |t| <= 3, P of degree 8 fitted to erf(t) / t
-// (least squares on Chebyshev nodes, weighted so that the absolute error of erf is what is minimised;
-// evaluated in fp32: 2.1e-5), and t clamped to that range beyond it (1 - erf(3) = 2.2e-5).  Fourteen
-// full-rate instructions and no reciprocal or exponential: the epilogue runs on the vector ALU with
-// nothing to overlap it, and the ~25 instructions per element of an erfc-based form were a tenth of the
-// launch.  Absolute error of gelu below 4.4e-5 for every u, a hundredth of what the bf16 store rounds off.
-__device__ __forceinline__ float gelu_f(float u) {
-  const float t = fminf(fmaxf(u * 0.70710678118654752f, -3.0f), 3.0f);
-  const float s = t * t;
-  float p = 3.912539981e-08f;
-  p = fmaf(p, s, -1.883036475e-06f);
-  p = fmaf(p, s, 4.008835822e-05f);
-  p = fmaf(p, s, -5.029218737e-04f);
-  p = fmaf(p, s, 4.196857568e-03f);
-  p = fmaf(p, s, -2.499890141e-02f);
-  p = fmaf(p, s, 1.109308004e-01f);
-  p = fmaf(p, s, -3.752196431e-01f);
-  p = fmaf(p, s, 1.128250599e+00f);
-  const float hu = 0.5f * u;
-  return fmaf(hu, t * p, hu);
-}
-
-// gelu'(u) = Phi(u) + u phi(u).  erfc(|u| / sqrt 2) by Abramowitz and Stegun 7.1.26 (absolute error 1.5e-7),
-// whose exponential is phi's.
-__device__ __forceinline__ float gelu_grad_f(float u) {
-  const float e = __expf(-0.5f * u * u);
-  const float t = __builtin_amdgcn_rcpf(fmaf(fabsf(u), 0.3275911f * 0.70710678f, 1.0f));
-  float p = 1.061405429f;
-  p = fmaf(p, t, -1.453152027f);
-  p = fmaf(p, t, 1.421413741f);
-  p = fmaf(p, t, -0.284496736f);
-  p = fmaf(p, t, 0.254829592f);
-  const float q = 0.5f * p * t * e;                 // Phi(-|u|)
-  return fmaf(u * 0.39894228040143268f, e, u < 0.f ? q : 1.0f - q);
-}
 
 // the operands of a dense product
 template <class C> struct DenseLoader {

@@ -532,6 +532,6 @@ def test_grouped_backward_matches_call_by_call(batch, image, patch, dim, layers,
     for name in got[0]:
         for a, b in zip(got[0][name], got[1][name]):
             a, b = a.double(), b.double()
-            # the two differ in the order of fp32 sums and in gelu's derivative (1.5e-7): where that moves a stored
+            # the two differ in the order of fp32 sums and in gelu's derivative (1e-7 each): where that moves a stored
             # bf16 gradient by a unit (2^-8), the layers below see an error of that size in few elements
             assert (a - b).norm() <= 1e-2 * b.norm() + 1e-12, (name, ((a - b).norm() / b.norm()).item())
