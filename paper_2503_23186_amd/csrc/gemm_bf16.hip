@@ -35,7 +35,7 @@ struct Args {
   const bf16_t* B;
   bf16_t* C;          // bf16 output [M][N] (EPI 0, 1)
   bf16_t* C2;         // EPI 1: gelu(C); EPI 4: C * gelu'(res)
-  float* part;        // EPI 2: fp32 output, or partials zstride elements apart
+  float* part;        // EPI 2: fp32 output, or partials zstride elements apart; EPI 4: [WM * mtiles][N] column sums of C2 before it is rounded
   float* rsum;        // EPI 2, nullable: [M] sums of A over the reduction (likewise zstride apart)
   size_t zstride;
   const float* bias;  // [N] or null
@@ -157,6 +157,13 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
       for (int rb = 0; rb < 2; ++rb) rv[i & 1][j][rb] = buffer_load16(r_rs, place(i, j, rb), 0);
   };
   if (EPI == 3 || EPI == 4) fetch(0);
+  float cs[TN][8];      // EPI 4: this lane's rows' share of the column sums
+  if (EPI == 4) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) cs[j][e] = 0.f;
+  }
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     if ((EPI == 3 || EPI == 4) && i + 1 < TM) fetch(i + 1);
@@ -178,7 +185,10 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
           unpack8(o[rb], x);
           unpack8(rv[i & 1][j][rb], r);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) x[e] *= gelu_grad_f(r[e]);
+          for (int e = 0; e < 8; ++e) {
+            x[e] *= gelu_grad_f(r[e]);
+            cs[j][e] += x[e];            // a row past the end adds zero
+          }
           buffer_store16(c2_rs, uint4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])}, place(i, j, rb));
         }
       }
@@ -189,6 +199,23 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
         strip_transpose(S, lane, v, o);
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) buffer_store16(c2_rs, o[rb], place(i, j, rb));
+      }
+    }
+  }
+  if (EPI == 4) {
+    // the bias gradient of the layer below sums the products before they are rounded: one partial row per row of
+    // wavefronts, its sixteen lanes of a column added first
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) cs[j][e] += __shfl_xor(cs[j][e], o, 64);
+      const int col = n0 + wn * (TN * 32) + j * 32 + g * 8;
+      if (i16 == 0 && col < a.N) {
+        float* q = a.part + (size_t)(mt * C::WM + wm) * a.N + col;
+        *reinterpret_cast<float4*>(q) = make_float4(cs[j][0], cs[j][1], cs[j][2], cs[j][3]);
+        *reinterpret_cast<float4*>(q + 4) = make_float4(cs[j][4], cs[j][5], cs[j][6], cs[j][7]);
       }
     }
   }
@@ -356,27 +383,35 @@ int launch_small(Args& a, int shape, hipStream_t st) {
     default: return CNNK_ERR_UNSUPPORTED;
   }
 }
-// One launch of an orientation with a natural operand.  The large shapes: 256 x 128 and 192 x 128 tiles
-// with 64-byte rows, and for reductions from 2048 on 192 x 128 tiles with 128-byte rows (64 reduction
+// The shape of a launch of an orientation with a natural operand: one of kTiles or a large one, 256 x 128 and
+// 192 x 128 tiles with 64-byte rows, and for reductions from 2048 on 192 x 128 tiles with 128-byte rows (64 reduction
 // elements per stage, loads one stage ahead: -15 % on 12608 x 3072 -> 768).  Their constants are in the
 // same units as kTiles; the tuning table forces a shape (15 = 1 / 2: 64- / 128-byte rows of the large
-// ones, 16 + n: small shape n).
+// ones, 16 + n: small shape n; -1: no such shape).
+enum { L256 = T_SMALL, L192, L192_WIDE };
+int nat_shape(int M, int N, int K) {
+  const int force = g_cnnk_tune[15];
+  if (force >= 16) return force - 16 < T_SMALL ? force - 16 : -1;
+  const int n128 = ceil_div(N, 128), t192 = ceil_div(M, 192) * n128, t256 = ceil_div(M, 256) * n128;
+  const bool wide = force == 2 || (force != 1 && K >= 2048);
+  const float us192 = tile_time(t192, 2, ceil_div(K, 32), 1, 7.8f, 0.47f);
+  const float us256 = tile_time(t256, 2, ceil_div(K, 32), 1, 11.8f, 0.38f);
+  const float us = wide ? tile_time(t192, 2, ceil_div(K, 64), 1, 1.2f, 0.85f) : us192 < us256 ? us192 : us256;
+  if (force == 0) {
+    const int small = pick_small(M, N, K, false, us);
+    if (small >= 0) return small;
+  }
+  return wide ? L192_WIDE : us192 < us256 ? L192 : L256;
+}
 template <bool BTR, int EPI>
 int launch_nat(Args& a, hipStream_t st) {
-  const int force = g_cnnk_tune[15];
-  if (force >= 16) return launch_small<false, BTR, EPI>(a, force - 16, st);
-  const int n128 = ceil_div(a.N, 128), t192 = ceil_div(a.M, 192) * n128, t256 = ceil_div(a.M, 256) * n128;
-  const bool wide = force == 2 || (force != 1 && a.K >= 2048);
-  const float us192 = tile_time(t192, 2, ceil_div(a.K, 32), 1, 7.8f, 0.47f);
-  const float us256 = tile_time(t256, 2, ceil_div(a.K, 32), 1, 11.8f, 0.38f);
-  const float us = wide ? tile_time(t192, 2, ceil_div(a.K, 64), 1, 1.2f, 0.85f) : us192 < us256 ? us192 : us256;
-  if (force == 0) {
-    const int small = pick_small(a.M, a.N, a.K, false, us);
-    if (small >= 0) return launch_small<false, BTR, EPI>(a, small, st);
+  const int shape = nat_shape(a.M, a.N, a.K);
+  switch (shape) {
+    case L192_WIDE: return launch_cfg<false, BTR, EPI, 3, 2, 64, 128, 2, 1>(a, 1, st);
+    case L192: return launch_cfg<false, BTR, EPI, 3, 2, 32, 64, 3, 1>(a, 1, st);
+    case L256: return launch_cfg<false, BTR, EPI, 4, 2, 32, 64, 3, 1>(a, 1, st);
+    default: return launch_small<false, BTR, EPI>(a, shape, st);
   }
-  if (wide) return launch_cfg<false, BTR, EPI, 3, 2, 64, 128, 2, 1>(a, 1, st);
-  if (us192 < us256) return launch_cfg<false, BTR, EPI, 3, 2, 32, 64, 3, 1>(a, 1, st);
-  return launch_cfg<false, BTR, EPI, 4, 2, 32, 64, 3, 1>(a, 1, st);
 }
 
 bool fits32(long long rows, long long cols) { return rows * cols * 2 < 2147483647LL; }
@@ -411,10 +446,16 @@ int gemm_bf16_dgrad(long long rows, int K, int N, const bf16_t* dy, const bf16_t
   return launch_nat<true, 0>(a, st);
 }
 
+int gemm_bf16_dgrad_gelu_parts(long long rows, int K, int N) {
+  const int shape = nat_shape((int)rows, K, N);
+  const int bm = shape < 0 ? 64 : shape < T_SMALL ? kTiles[shape].rows : shape == L256 ? 256 : 192;
+  return 2 * ceil_div((int)rows, bm);
+}
+
 int gemm_bf16_dgrad_gelu(long long rows, int K, int N, const bf16_t* dy, const bf16_t* w, const bf16_t* u, bf16_t* dg, bf16_t* du,
-                         hipStream_t st) {
+                         float* sums, hipStream_t st) {
   Args a{};
-  a.A = dy; a.B = w; a.C = dg; a.C2 = du; a.res = u;
+  a.A = dy; a.B = w; a.C = dg; a.C2 = du; a.res = u; a.part = sums;
   a.M = (int)rows; a.N = K; a.K = N; a.lda = N; a.ldb = K; a.ldc = K; a.k_per_split = N;
   a.a_bytes = (unsigned)(rows * N * 2); a.b_bytes = (unsigned)((long long)N * K * 2); a.c_bytes = (unsigned)(rows * K * 2);
   return launch_nat<true, 4>(a, st);

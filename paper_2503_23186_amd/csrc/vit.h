@@ -10,15 +10,18 @@ bool linear_dense(long long rows, int K, int N, int dtype);
 // (cnnk_layernorm_workspace_bytes).  Arguments as checked by cnnk_layernorm_bwd.
 int ln_bwd_rows_partial(const cnnk_ln_desc* d, const void* dy, const void* x, const float* gamma, const float* stats,
                         const void* dres, void* dx, float* part, hipStream_t st);
-// the final sums of several layer norms of one descriptor in one launch
-constexpr int kLnGroupMax = 64;
-struct LnFinalizeTable {
+int ln_bwd_parts(const cnnk_ln_desc* d);       // rows of those partial sums
+
+// The final sums of several tables of partial column sums [parts][2 * C] in one launch: out0 gets the first C columns,
+// out1 the others.
+constexpr int kColumnSumsMax = 64;
+struct ColumnSums {
   int count;
-  const float* part[kLnGroupMax];
-  float* dgamma[kLnGroupMax];
-  float* dbeta[kLnGroupMax];
+  const float* part[kColumnSumsMax];
+  float* out0[kColumnSumsMax];
+  float* out1[kColumnSumsMax];
 };
-int ln_bwd_finalize_group(const cnnk_ln_desc* d, const LnFinalizeTable& t, hipStream_t st);
+int column_sums_group(const ColumnSums& t, int parts, int C, hipStream_t st);
 
 // cnnk_vit_embed_bwd on checked arguments; dbe null: the caller gets it elsewhere
 int embed_bwd(const cnnk_embed_desc* d, const void* dtok, void* dz, float* dbe, float* dcls, float* dpos, hipStream_t st);

@@ -212,8 +212,8 @@ __global__ void __launch_bounds__(kT) colsum_finalize_kernel(const float* __rest
   }
 }
 
-// The same for the partials of several layer norms, one per blockIdx.y.
-__global__ void __launch_bounds__(kT) ln_finalize_group_kernel(LnFinalizeTable t, int nb, int C) {
+// The same for several tables of partials, one per blockIdx.y.
+__global__ void __launch_bounds__(kT) column_sums_group_kernel(ColumnSums t, int nb, int C) {
   __shared__ float sm[4][64];
   const int cl = threadIdx.x & 63, pl = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + cl, n = 2 * C;
@@ -234,7 +234,7 @@ __global__ void __launch_bounds__(kT) ln_finalize_group_kernel(LnFinalizeTable t
   __syncthreads();
   if (pl == 0 && c < n) {
     const float r = (sm[0][cl] + sm[1][cl]) + (sm[2][cl] + sm[3][cl]);
-    if (c < C) t.dgamma[blockIdx.y][c] = r; else t.dbeta[blockIdx.y][c - C] = r;
+    if (c < C) t.out0[blockIdx.y][c] = r; else t.out1[blockIdx.y][c - C] = r;
   }
 }
 
@@ -507,9 +507,11 @@ int ln_bwd_rows_partial(const cnnk_ln_desc* d, const void* dy, const void* x, co
   return launch_status();
 }
 
-int ln_bwd_finalize_group(const cnnk_ln_desc* d, const LnFinalizeTable& t, hipStream_t st) {
+int ln_bwd_parts(const cnnk_ln_desc* d) { return ln_bwd_blocks(d->rows, d->C); }
+
+int column_sums_group(const ColumnSums& t, int parts, int C, hipStream_t st) {
   if (t.count == 0) return CNNK_OK;
-  ln_finalize_group_kernel<<<dim3((2 * d->C + 63) / 64, t.count), kT, 0, st>>>(t, ln_bwd_blocks(d->rows, d->C), d->C);
+  column_sums_group_kernel<<<dim3((2 * C + 63) / 64, t.count), kT, 0, st>>>(t, parts, C);
   return launch_status();
 }
 

@@ -131,6 +131,9 @@ int fill_group(const Geo& g, int l, GemmWgrad* p) {
   return n;
 }
 
+// partial sums of fc1's bias gradient, of one block
+size_t gelu_sums_bytes(const Geo& g) { return align_up(2 * ((g.rows + 63) / 64) * g.m * sizeof(float), 256); }
+
 size_t workspace(const cnnk_vit_desc* v, const Geo& g) {
   size_t w = 0;
   const long long shapes[5][3] = {{(long long)g.B * g.n, g.K0, g.d}, {(long long)g.rows, g.d, 3 * g.d}, {(long long)g.rows, g.d, g.d},
@@ -148,7 +151,7 @@ size_t workspace(const cnnk_vit_desc* v, const Geo& g) {
       const int n = fill_group(g, l, p);
       w = max_sz(w, gemm_bf16_wgrad_group_ws(p, n));
     }
-    w = align_up(w, 256) + 2 * (size_t)g.L * align_up(cnnk_layernorm_workspace_bytes(&ln), 256);
+    w = align_up(w, 256) + (size_t)g.L * (2 * align_up(cnnk_layernorm_workspace_bytes(&ln), 256) + gelu_sums_bytes(g));
   }
   return align_up(w, 256);
 }
@@ -209,9 +212,10 @@ int update_params(const Geo& g, const cnnk_vit_buffers* buf, int k0, int k1, flo
 
 // The backward pass and the update with the products that only the update waits for in groups: the data-gradient
 // chain runs on `st`; the weight gradients of group_blocks(g) transformer blocks, with the bias gradients (column
-// sums of an operand that those products load anyway), the final sums of the blocks' layer norms and the update of
-// the blocks' parameters follow as three launches, on the second stream if there is one.  GELU's gradient is taken
-// in the epilogue of fc2's data gradient.  Per block 7 launches and half an event pair instead of 24 and 7: at batch
+// sums of an operand that those products load anyway), the final sums of the blocks' layer norms and of fc1's bias
+// gradients and the update of the blocks' parameters follow as four launches, on the second stream if there is one.
+// GELU's gradient is taken in the epilogue of fc2's data gradient, which leaves partial sums of the unrounded products
+// for fc1's bias.  Per block 7.5 launches and half an event pair instead of 24 and 7: at batch
 // 8 the step was bound by enqueueing them, and at batch 64 split products for a fraction of the device each took 270
 // us a block where the grouped ones take 200.
 int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffers* buf, const Arena& A, float lr, float mu, float wd,
@@ -222,16 +226,18 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
   const cnnk_ln_desc ln_cls = {g.B, d, g.dtype, v->ln_eps, (long long)T * d};
   const cnnk_attn_desc ad = {g.B, T, v->heads, d / v->heads, g.dtype};
   const cnnk_embed_desc ed = {g.B, v->image, v->patch, d, g.dtype};
-  const size_t ln_bytes = align_up(cnnk_layernorm_workspace_bytes(&ln), 256), whole = workspace(v, g);
+  const size_t ln_bytes = align_up(cnnk_layernorm_workspace_bytes(&ln), 256), gelu_bytes = gelu_sums_bytes(g), whole = workspace(v, g);
   char* const base = (char*)buf->arena;
   auto at = [&](int id, int l) -> bf16_t* { return (bf16_t*)(base + A.off[id] + A.size[id] * (size_t)(per_layer(id) ? l : 0)); };
   auto P = [&](int k) { return (float*)buf->param[k]; };
   auto Wm = [&](int k) { return (const bf16_t*)buf->param_lp[k]; };
   auto Gr = [&](int k) { return (float*)buf->grad[k]; };
-  // the workspace: what a call needs, then the layer norms' partial sums (they live until their group's final sums)
+  // the workspace: what a call needs, then the partial sums of the layer norms and of fc1's bias gradients (they live
+  // until their group's final sums)
   char* const ws = (char*)buf->ws;
-  const size_t wsb = whole - 2 * (size_t)g.L * ln_bytes;
+  const size_t wsb = whole - (size_t)g.L * (2 * ln_bytes + gelu_bytes);
   char* const ln_parts = ws + wsb;
+  char* const gelu_parts = ln_parts + 2 * (size_t)g.L * ln_bytes;
   const hipStream_t side = two ? (hipStream_t)buf->aux_stream : st;
   void* const side_ws = two ? ws + buf->ws_bytes / 2 / 256 * 256 : ws;
   int rc = cnnk_fill_zero(at(CNNK_VIT_DXOUT, g.L - 1), A.size[CNNK_VIT_DXOUT], st);
@@ -239,16 +245,16 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
     rc = cnnk_layernorm_bwd(&ln_cls, at(CNNK_VIT_DF, 0), at(CNNK_VIT_XOUT, g.L - 1), P(p_tail), (const float*)at(X_STATSF, 0), nullptr,
                             at(CNNK_VIT_DXOUT, g.L - 1), Gr(p_tail), Gr(p_tail + 1), ws, wsb, st);
   GemmWgrad pend[32];
-  LnFinalizeTable sums;
+  ColumnSums sums, gelu_sums;
   int np = 0;
-  sums.count = 0;
+  sums.count = gelu_sums.count = 0;
   auto defer = [&](const bf16_t* dy, const bf16_t* x, int kw, int kb, long long r, int K, int N) {
-    pend[np++] = GemmWgrad{dy, x, Gr(kw), Gr(kb), r, K, N};
+    pend[np++] = GemmWgrad{dy, x, Gr(kw), kb < 0 ? nullptr : Gr(kb), r, K, N};
   };
   auto norm_bwd = [&](int slot, const bf16_t* dy, const bf16_t* x, int kg, const void* stats, const bf16_t* dres, bf16_t* dx) -> int {
     float* part = (float*)(ln_parts + (size_t)slot * ln_bytes);
     const int i = sums.count++;
-    sums.part[i] = part; sums.dgamma[i] = Gr(kg); sums.dbeta[i] = Gr(kg + 1);
+    sums.part[i] = part; sums.out0[i] = Gr(kg); sums.out1[i] = Gr(kg + 1);
     return ln_bwd_rows_partial(&ln, dy, x, P(kg), (const float*)stats, dres, dx, part, st);
   };
   for (int l = g.L - 1; l >= 0 && rc == CNNK_OK; --l) {
@@ -256,7 +262,10 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
     const bf16_t* xin = l ? at(CNNK_VIT_XOUT, l - 1) : at(CNNK_VIT_TOK, 0);
     bf16_t* dxin = l ? at(CNNK_VIT_DXOUT, l - 1) : at(CNNK_VIT_DTOK, 0);
     const bf16_t *dxo = at(CNNK_VIT_DXOUT, l), *du = at(CNNK_VIT_DU, l), *dxm = at(CNNK_VIT_DXMID, l), *dqkv = at(CNNK_VIT_DQKV, l);
-    rc = gemm_bf16_dgrad_gelu(rows, m, d, dxo, Wm(p0 + B_W2), at(CNNK_VIT_U, l), at(CNNK_VIT_DG, l), at(CNNK_VIT_DU, l), st);
+    float* const du_part = (float*)(gelu_parts + (size_t)l * gelu_bytes);
+    rc = gemm_bf16_dgrad_gelu(rows, m, d, dxo, Wm(p0 + B_W2), at(CNNK_VIT_U, l), at(CNNK_VIT_DG, l), at(CNNK_VIT_DU, l), du_part, st);
+    const int ig = gelu_sums.count++;
+    gelu_sums.part[ig] = du_part; gelu_sums.out0[ig] = Gr(p0 + B_C1); gelu_sums.out1[ig] = Gr(p0 + B_C1) + m / 2;
     if (rc == CNNK_OK) rc = gemm_bf16_dgrad(rows, d, m, du, Wm(p0 + B_W1), at(CNNK_VIT_DH2, l), st);
     if (rc == CNNK_OK) rc = norm_bwd(2 * l + 1, at(CNNK_VIT_DH2, l), at(CNNK_VIT_XMID, l), p0 + B_G2, at(X_STATS2, l), dxo, at(CNNK_VIT_DXMID, l));
     if (rc == CNNK_OK) rc = gemm_bf16_dgrad(rows, d, d, dxm, Wm(p0 + B_WO), at(CNNK_VIT_DO, l), st);
@@ -264,7 +273,7 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
     if (rc == CNNK_OK) rc = gemm_bf16_dgrad(rows, d, 3 * d, dqkv, Wm(p0 + B_WQKV), at(CNNK_VIT_DH, l), st);
     if (rc == CNNK_OK) rc = norm_bwd(2 * l, at(CNNK_VIT_DH, l), xin, p0 + B_G1, at(X_STATS1, l), dxm, dxin);
     defer(dxo, at(CNNK_VIT_G, l), p0 + B_W2, p0 + B_C2, rows, m, d);
-    defer(du, at(CNNK_VIT_H2, l), p0 + B_W1, p0 + B_C1, rows, d, m);
+    defer(du, at(CNNK_VIT_H2, l), p0 + B_W1, -1, rows, d, m);
     defer(dxm, at(CNNK_VIT_O, l), p0 + B_WO, p0 + B_BO, rows, d, d);
     defer(dqkv, at(CNNK_VIT_H, l), p0 + B_WQKV, p0 + B_BQKV, rows, d, 3 * d);
     if (l == 0 && rc == CNNK_OK) {
@@ -275,11 +284,12 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
     if (two && (hipEventRecord((hipEvent_t)buf->ev_fork, st) != hipSuccess || hipStreamWaitEvent(side, (hipEvent_t)buf->ev_fork, 0) != hipSuccess))
       return CNNK_ERR_HIP;
     rc = gemm_bf16_wgrad_group(pend, np, side_ws, side);
-    if (rc == CNNK_OK) rc = ln_bwd_finalize_group(&ln, sums, side);
+    if (rc == CNNK_OK) rc = column_sums_group(sums, ln_bwd_parts(&ln), d, side);
+    if (rc == CNNK_OK) rc = column_sums_group(gelu_sums, gemm_bf16_dgrad_gelu_parts(rows, m, d), m / 2, side);
     const int last = l + G < g.L ? l + G : g.L;
     if (rc == CNNK_OK) rc = update_params(g, buf, l ? p0 : 0, P_BLOCK0 + B_COUNT * last, lr, mu, wd, side);
     np = 0;
-    sums.count = 0;
+    sums.count = gelu_sums.count = 0;
   }
   if (rc == CNNK_OK) rc = update_params(g, buf, p_tail, p_tail + 4, lr, mu, wd, st);
   if (two && rc == CNNK_OK && (hipEventRecord((hipEvent_t)buf->ev_join, side) != hipSuccess || hipStreamWaitEvent(st, (hipEvent_t)buf->ev_join, 0) != hipSuccess))

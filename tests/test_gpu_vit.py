@@ -535,3 +535,30 @@ def test_grouped_backward_matches_call_by_call(batch, image, patch, dim, layers,
             # the two differ in the order of fp32 sums and in gelu's derivative (1e-7 each): where that moves a stored
             # bf16 gradient by a unit (2^-8), the layers below see an error of that size in few elements
             assert (a - b).norm() <= 1e-2 * b.norm() + 1e-12, (name, ((a - b).norm() / b.norm()).item())
+
+
+# every tile shape of the data gradient that takes GELU's gradient (tuning key 15), ragged in rows and columns, and the
+# shapes that the sizes choose (0) for one tile and for several
+@pytest.mark.parametrize("batch,image,patch,dim,mlp,shape", [(9, 64, 8, 128, 200, s) for s in (0, 1, 2, 16, 17, 18, 19, 20)] +
+                         [(1, 16, 16, 64, 72, 0), (40, 32, 4, 192, 768, 0)])
+def test_grouped_step_sums_the_unrounded_products_for_the_bias_of_the_activation(batch, image, patch, dim, mlp, shape):
+    """dc1 = column sums of dg * gelu'(u) before the products are stored: fp32 sums of fp32 products, so within some
+    units of 2^-24 of the sums' terms (the stored bf16 products are off by 2^-9 each)."""
+    from paper_2503_23186_amd import cnnk
+    from paper_2503_23186_amd.vit import VitRunner
+    net = WL.ViT("vit", batch, "bf16", image, patch, dim, dim // 64, 2, mlp)
+    inp = WL.make_vit_inputs(net, 13)
+    cnnk.cnnk_tune(15, shape)
+    try:
+        run = VitRunner(net)
+        run.load(inp["x"], inp["labels"], inp["params"], inp["mom"])
+        run.step(0.05, 0.9, 1e-3)
+        torch.cuda.synchronize()
+    finally:
+        cnnk.cnnk_tune(15, 0)
+    for l in range(2):
+        dg, u, du = (run.tensor(n, l).view(-1, mlp).double() for n in ("DG", "U", "DU"))
+        terms = dg * (0.5 * torch.erfc(-u / 2 ** 0.5) + u * torch.exp(-0.5 * u * u) / (2 * torch.pi) ** 0.5)
+        assert bool(((du - terms).abs() <= 2 ** -8 * terms.abs() + 1e-6 * dg.abs()).all())
+        err = (run.grad[run.names.index("c1.%d" % l)].double() - terms.sum(0)).abs()
+        assert bool((err <= 2 ** -20 * terms.abs().sum(0) + 1e-30).all()), (l, (err / terms.abs().sum(0)).max().item())
