@@ -129,7 +129,7 @@ __global__ void __launch_bounds__(C::THREADS, C::WPE) conv_gemm_kernel(ConvGemmA
   ld.init(a, cls, M, m0, n0, kg * nst, wave, lane);
   f32x16_t acc[TM][TN];
   float rs[TM];
-  tile_main_loop<C, false>(ld, nst, kg, wave, lane, smem, acc, false, rs);
+  tile_main_loop<C, false, false>(ld, nst, kg, wave, lane, smem, acc, false, rs);
   tile_join_groups<C>(acc, kg, tid, smem);
 
   if constexpr (EP == STATS) {

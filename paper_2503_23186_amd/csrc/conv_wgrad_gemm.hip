@@ -96,7 +96,7 @@ __global__ void __launch_bounds__(C::THREADS, C::WPE) wgrad_gemm_kernel(WgArgs a
   ld.init(a, k0, q0, m_begin, m_end, wave, lane);
   f32x16_t acc[TM][TN];
   float rs[TM];
-  tile_main_loop<C, false>(ld, (m_end - m_begin + C::BK - 1) / C::BK, 0, wave, lane, smem, acc, false, rs);
+  tile_main_loop<C, false, false>(ld, (m_end - m_begin + C::BK - 1) / C::BK, 0, wave, lane, smem, acc, false, rs);
   float* out = a.part + (size_t)z * a.Cout * a.Q;
 #pragma unroll
   for (int i = 0; i < TM; ++i)

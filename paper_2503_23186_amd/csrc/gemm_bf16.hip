@@ -43,6 +43,7 @@ struct Args {
   int M, N, K;        // output rows, output columns, reduction length
   int lda, ldb, ldc;
   int k_per_split;    // reduction elements per blockIdx.z (a multiple of BK)
+  int fold;           // EPI 2, tiles that have the registers: stages between two folds of the accumulators
   int mtiles, ntiles;
   unsigned a_bytes, b_bytes, c_bytes;
 };
@@ -84,6 +85,11 @@ template <class C> struct DenseLoader {
   }
 };
 
+// Rows between two folds of a weight gradient's accumulators, near 3.4 sqrt(rows), where the errors of the two chains
+// balance (a chain's grows with the root of its steps; 1568 rows 8.7e-8 with 128 and 9.3e-8 with 256, 12608 rows the
+// same with 256 and 512, 27648 rows 2.0e-7 and 1.75e-7).
+__host__ __device__ __forceinline__ int fold_rows(int rows) { return rows <= 2048 ? 128 : rows <= 10240 ? 256 : 512; }
+
 // One workgroup's tile (mt, nt) over the reduction range of split z.
 template <class C, int EPI>
 __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) {
@@ -110,9 +116,10 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
   // the operand is in their registers, and the vector ALU has room beside the MFMAs
   constexpr bool ROWS = EPI == 2 && KG == 1;
   const bool row_sums = ROWS && a.rsum != nullptr && nt == 0 && wn == 0;
+  constexpr bool FOLD = EPI == 2 && TM * TN <= 6;
   f32x16_t acc[TM][TN];
   float rs[TM];
-  tile_main_loop<C, ROWS>(ld, nst, kg, wave, lane, smem, acc, row_sums, rs);
+  tile_main_loop<C, ROWS, FOLD>(ld, nst, kg, wave, lane, smem, acc, row_sums, rs, a.fold);
   if (EPI != 2 || KG > 1) tile_join_groups<C>(acc, kg, tid, smem);
   if (kg > 0) return;
   if (EPI == 2) {
@@ -245,7 +252,9 @@ __global__ void __launch_bounds__(256 * KG, (Cfg<ATR, BTR, TM, TN, BK, RB, NSTAG
 
 // Several weight gradients in one launch.  Alone, one of ViT-B/16's has 18 to 72 tiles of 256 x 128 for 256
 // CUs and had to be split three to ten ways over its rows, each split a partial to write and to add up; the
-// tiles of two blocks together fill the device unsplit.
+// tiles of a block together fill the device unsplit.  Tiles of 192 x 128 at most: a wavefront then has registers for
+// the second set of accumulators that an unsplit sum over all rows needs to be as exact as a split one (ViT-B/16 at
+// batch 64, step 11.32 ms; 128 x 128 tiles 11.62; 256 x 128 without the second set 11.21).
 constexpr int kGroupMax = 32;
 struct GroupProblem {
   const bf16_t* dy;
@@ -276,6 +285,7 @@ __global__ void __launch_bounds__(256, (Cfg<true, true, TM, TN, BK, RB, NSTAGE, 
   a.a_bytes = (unsigned)p.rows * (unsigned)p.N * 2u; a.b_bytes = (unsigned)p.rows * (unsigned)p.K * 2u;
   const int stages = ((p.rows + BK - 1) / BK + ga.splits - 1) / ga.splits;
   a.k_per_split = stages * BK;
+  a.fold = fold_rows(p.rows) / BK;
   if (ga.splits > 1) {
     a.part = ga.part + ga.off[i];
     a.rsum = p.db ? a.part + (size_t)p.N * p.K : nullptr;
@@ -486,6 +496,7 @@ int gemm_bf16_wgrad(long long rows, int K, int N, const bf16_t* x, const bf16_t*
     if (small >= 0 && small != T128) {
       a.part = dw;
       a.k_per_split = (int)rows;
+      a.fold = fold_rows((int)rows) / 64;
       return launch_small<true, true, 2>(a, small, st);
     }
   }
@@ -502,7 +513,7 @@ int gemm_bf16_wgrad(long long rows, int K, int N, const bf16_t* x, const bf16_t*
 // ---- groups of weight gradients --------------------------------------------------------------------------
 namespace {
 struct GroupPlan {
-  bool large;      // 256 x 128 tiles, else 64 x 128
+  bool large;      // 192 x 128 tiles, else 64 x 128
   int tiles, splits;
 };
 int group_tiles(const GemmWgrad* p, int n, int bm) {
@@ -510,12 +521,12 @@ int group_tiles(const GemmWgrad* p, int n, int bm) {
   for (int i = 0; i < n; ++i) t += ceil_div(p[i].N, bm) * ceil_div(p[i].K, 128);
   return t;
 }
-// 256 x 128 tiles where they give every CU one (unsplit), 64 x 128 tiles otherwise, the row range then split
+// 192 x 128 tiles where they give every CU one (unsplit), 64 x 128 tiles otherwise, the row range then split
 // until the device holds two workgroups per CU (but never below eight stages of 64 rows each).
 GroupPlan plan_group(const GemmWgrad* p, int n) {
   GroupPlan g;
-  g.tiles = group_tiles(p, n, 256);
-  g.large = g.tiles >= 192;
+  g.tiles = group_tiles(p, n, 192);
+  g.large = g.tiles >= 256;
   g.splits = 1;
   if (g.large) return g;
   g.tiles = group_tiles(p, n, 64);
@@ -534,7 +545,7 @@ size_t group_elems(const GemmWgrad* p, int n) {
 }  // namespace
 
 int gemm_bf16_wgrad_group_max() { return kGroupMax; }
-int gemm_bf16_wgrad_tiles(int K, int N) { return ceil_div(N, 256) * ceil_div(K, 128); }
+int gemm_bf16_wgrad_tiles(int K, int N) { return ceil_div(N, 192) * ceil_div(K, 128); }
 
 size_t gemm_bf16_wgrad_group_ws(const GemmWgrad* p, int n) {
   const GroupPlan g = plan_group(p, n);
@@ -551,7 +562,7 @@ int gemm_bf16_wgrad_group(const GemmWgrad* p, int n, void* ws, hipStream_t st) {
     const int nt = ceil_div(p[i].K, 128);
     a.p[i] = GroupProblem{p[i].dy, p[i].x, p[i].dw, p[i].db, (int)p[i].rows, p[i].K, p[i].N, nt, a.tiles};
     a.off[i] = off;
-    a.tiles += ceil_div(p[i].N, g.large ? 256 : 64) * nt;
+    a.tiles += ceil_div(p[i].N, g.large ? 192 : 64) * nt;
     off += (size_t)p[i].N * p[i].K + p[i].N;
   }
   const dim3 grid(8 * ((a.tiles + 7) / 8), 1, g.splits);
@@ -565,7 +576,7 @@ int gemm_bf16_wgrad_group(const GemmWgrad* p, int n, void* ws, hipStream_t st) {
     return launch_status();
   };
   static bool raised_l = false, raised_s = false;
-  const int rc = g.large ? go(wgrad_group_kernel<4, 2, 32, 64, 3>, Cfg<true, true, 4, 2, 32, 64, 3, 1>::SMEM, &raised_l)
+  const int rc = g.large ? go(wgrad_group_kernel<3, 2, 32, 64, 3>, Cfg<true, true, 3, 2, 32, 64, 3, 1>::SMEM, &raised_l)
                          : go(wgrad_group_kernel<1, 2, 64, 128, 3>, Cfg<true, true, 1, 2, 64, 128, 3, 1>::SMEM, &raised_s);
   if (rc != CNNK_OK || g.splits == 1) return rc;
   size_t blocks = (a.zstride / 4 + 255) / 256;

@@ -110,13 +110,14 @@ bool grouped(const Geo& g) {
   return g.dtype == CNNK_BF16 && linear_dense(rows, g.d, 3 * g.d, g.dtype) && linear_dense(rows, g.d, g.d, g.dtype) &&
          linear_dense(rows, g.d, g.m, g.dtype) && linear_dense(rows, g.m, g.d, g.dtype) && linear_dense((long long)g.B * g.n, g.K0, g.d, g.dtype);
 }
-// Blocks whose weight gradients share a launch: as many as give it about 400 workgroups (two for each of most
-// CUs; ViT-B/16: two blocks of 216), at most seven (28 products and the embedding's fit the table).
+// Blocks whose weight gradients share a launch: one where that gives every CU a workgroup (ViT-B/16, 288 a block: one
+// block / two, step at batch 8 3.24 / 3.22 ms, 16 4.40 / 4.68, 32 6.95 / 7.12, 64 11.64 / 11.79), otherwise as many as give it
+// about 400 (512 columns, 136 a block, 96 images of 65 tokens: one block 2.87, two 2.77, three 2.78; 384 columns, 72 a
+// block, 192 images of 257: one 3.54, four 3.40, six 3.42), at most seven (28 products and the embedding's fit the table).
 int group_blocks(const Geo& g) {
   const int t = gemm_bf16_wgrad_tiles(g.d, 3 * g.d) + gemm_bf16_wgrad_tiles(g.d, g.d) + gemm_bf16_wgrad_tiles(g.d, g.m) + gemm_bf16_wgrad_tiles(g.m, g.d);
-  int n = (400 + t - 1) / t;
-  if (n > 7) n = 7;
-  return n < 1 ? 1 : n;
+  const int n = t >= 256 ? 1 : (400 + t - 1) / t;
+  return n > 7 ? 7 : n;
 }
 // Shapes of the products of the group that ends with block l (the blocks l .. l + group_blocks - 1, or up to the
 // last one); block 0's group has the patch embedding as well.  Returns their number.
@@ -215,9 +216,8 @@ int update_params(const Geo& g, const cnnk_vit_buffers* buf, int k0, int k1, flo
 // sums of an operand that those products load anyway), the final sums of the blocks' layer norms and of fc1's bias
 // gradients and the update of the blocks' parameters follow as four launches, on the second stream if there is one.
 // GELU's gradient is taken in the epilogue of fc2's data gradient, which leaves partial sums of the unrounded products
-// for fc1's bias.  Per block 7.5 launches and half an event pair instead of 24 and 7: at batch
-// 8 the step was bound by enqueueing them, and at batch 64 split products for a fraction of the device each took 270
-// us a block where the grouped ones take 200.
+// for fc1's bias.  Per block of ViT-B/16 11 launches and one event pair instead of 24 and 7: at batch 8 the step was
+// bound by enqueueing them, and at batch 64 split products for a fraction of the device each took 270 us a block.
 int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffers* buf, const Arena& A, float lr, float mu, float wd,
                      bool two, hipStream_t st) {
   const int d = g.d, m = g.m, T = g.T, G = group_blocks(g), p_tail = P_BLOCK0 + B_COUNT * g.L;

@@ -562,3 +562,48 @@ def test_grouped_step_sums_the_unrounded_products_for_the_bias_of_the_activation
         assert bool(((du - terms).abs() <= 2 ** -8 * terms.abs() + 1e-6 * dg.abs()).all())
         err = (run.grad[run.names.index("c1.%d" % l)].double() - terms.sum(0)).abs()
         assert bool((err <= 2 ** -20 * terms.abs().sum(0) + 1e-30).all()), (l, (err / terms.abs().sum(0)).max().item())
+
+
+# A sum of `rows` products runs in steps of 16; two chains of about the root of the steps each leave a relative error of
+# about 2^-24 times the fourth root of the steps / 2 to 3 (1.8e-7 at 12608 rows), one chain of them all four times that.
+def wgrad_bound(rows):
+    return 0.75 * 2.0 ** -24 * (rows / 16) ** 0.25
+
+
+@pytest.mark.parametrize("rows,K,N,shape", [(6240, 384, 1536, 0), (788, 768, 3072, 0), (1576, 768, 768, 0), (1576, 3072, 768, 0), (4097, 200, 72, 0)] +
+                         [(5003, 136, 200, s) for s in (16, 17, 18, 19)])
+def test_linear_weight_gradient_keeps_its_chains_of_sums_short(rows, K, N, shape):
+    from paper_2503_23186_amd import cnnk, vit
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(17)
+    x, dy = (torch.randn((rows, c), generator=g, device="cuda:0").bfloat16() for c in (K, N))
+    dw = torch.zeros((N, K), device="cuda:0")
+    cnnk.cnnk_tune(15, shape)
+    try:
+        need = max(256, vit.cnnk_linear_workspace_bytes(rows, K, N, cnnk.BF16))
+        ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+        vit.cnnk_linear_wgrad(rows, K, N, cnnk.BF16, x, dy, dw, ws, need, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    finally:
+        cnnk.cnnk_tune(15, 0)
+    want = dy.double().T @ x.double()
+    assert ((dw.double() - want).norm() / want.norm()).item() <= wgrad_bound(rows)
+
+
+@pytest.mark.parametrize("batch,image,patch,dim,mlp", [(64, 224, 16, 768, 3072), (15, 60, 4, 768, 3072), (40, 32, 4, 192, 768)])
+def test_grouped_weight_and_bias_gradients_keep_their_chains_of_sums_short(batch, image, patch, dim, mlp):
+    from paper_2503_23186_amd.vit import VitRunner
+    net = WL.ViT("vit", batch, "bf16", image, patch, dim, dim // 64, 2, mlp)
+    inp = WL.make_vit_inputs(net, 19)
+    run = VitRunner(net)
+    run.load(inp["x"], inp["labels"], inp["params"], inp["mom"])
+    run.step(0.05, 0.9, 1e-3)
+    torch.cuda.synchronize()
+    rows, grad = batch * net.tokens, dict(zip(run.names, run.grad))
+    for dy, x, w, b in (("DXOUT", "G", "W2", "c2"), ("DU", "H2", "W1", None), ("DXMID", "O", "Wo", "bo"), ("DQKV", "H", "Wqkv", "bqkv")):
+        d, x = run.tensor(dy, 0).view(rows, -1).double(), run.tensor(x, 0).view(rows, -1).double()
+        want = d.T @ x
+        assert ((grad[w + ".0"].double() - want).norm() / want.norm()).item() <= wgrad_bound(rows), w
+        if b:           # a compensated sum: the rounding of eight terms at a time and of the result
+            want = d.sum(0)
+            assert ((grad[b + ".0"].double() - want).norm() / want.norm()).item() <= 2.0 ** -23, b
