@@ -265,7 +265,10 @@ typedef struct cnnk_buffers {
    * parameters.  aux_stream must have the default priority; several steps may share one (what they
    * put there then runs in the order of the calls).  Both events are hipEvent_t handles created by
    * the caller for this buffer set alone (timing and the system-scope fence may be disabled).
-   * With an aux stream the workspace must be twice cnnk_train_step_workspace_bytes.  Results are
+   * With an aux stream the workspace must be twice cnnk_train_step_workspace_bytes.  Convolutions that
+   * name the same weight: every data gradient takes the weights that the step began with (copies made
+   * before the backward pass; where the kernels read the weights themselves, the second stream stays
+   * unused); their weight gradients are not summed.  Results are
    * bit-reproducible for a given mode; between the modes they differ by fp32 rounding (the forked
    * weight gradients split their reduction over fewer workgroups). */
   void* aux_stream;

@@ -31,6 +31,7 @@ struct Walk {
   size_t x8_off = 0;                 // its 8-channel copy of the network input lives in the same region
   std::vector<size_t> mask_off;      // per layer: offset of its ReLU mask, or (size_t)-1
   size_t mask_bytes = 0;             // ReLU masks (a bit per element) of the batch norms with a residual input
+  bool shared_read = false;          // a weight of several layers is read by a data gradient, not copied before
   double flops = 0;                  // of the convolutions, forward and backward
   int convs = 0;
   int dtype = -1;
@@ -39,10 +40,13 @@ struct Walk {
 // what one stream of a training step needs
 size_t step_workspace(const Walk& w) { return ((w.ws + 255) / 256 * 256 + kStatBytes + w.wt_bytes + w.mask_bytes + 255) / 256 * 256; }
 
-bool dgrad_pretransposed(const cnnk_layer& l) {
+// Whether a layer's data gradient takes a copy of the weights made before the backward pass.  The kernels of
+// conv_gemm.hip read the weights themselves, which the second stream updates as soon as their own layer's data gradient
+// is done: not where a layer that comes later in the backward pass has the same weights.
+bool dgrad_pretransposed(const cnnk_layer& l, bool shared) {
   if (l.op != CNNK_OP_CONV || l.in0 == 0 || l.d.conv.dtype != CNNK_BF16) return false;
   const ConvGeom g = make_geom(&l.d.conv);
-  return conv_mfma_supported(g, CNNK_PASS_DGRAD) && !conv_gemm_supported(g, CNNK_PASS_DGRAD);   // the latter reads the weights as they are
+  return conv_mfma_supported(g, CNNK_PASS_DGRAD) && (shared || !conv_gemm_supported(g, CNNK_PASS_DGRAD));
 }
 
 bool set_elems(std::vector<size_t>& v, int id, size_t n) {
@@ -84,6 +88,9 @@ int walk_layers(const cnnk_layer* L, int n, int n_slots, int n_params, Walk* w) 
   w->param_elems.assign(max_param + 1, 0);
   w->wt_off.assign(n, (size_t)-1);
   w->mask_off.assign(n, (size_t)-1);
+  std::vector<int> conv_uses(max_param + 1, 0);
+  for (int i = 0; i < n; ++i)
+    if (L[i].op == CNNK_OP_CONV && L[i].p0 >= 0) ++conv_uses[L[i].p0];
   for (int i = 0; i < n; ++i) {
     const cnnk_layer& l = L[i];
     int dt = -1;
@@ -102,9 +109,12 @@ int walk_layers(const cnnk_layer* L, int n, int n_slots, int n_params, Walk* w) 
         ++w->convs;
         w->flops += 2.0 * d.N * Ho * Wo * d.Cout * d.R * d.S * d.Cin * (l.in0 == 0 ? 2 : 3);
         for (int p = 0; p < 3; ++p) w->ws = max_sz(w->ws, cnnk_conv2d_workspace_bytes(&d, p));
-        if (dgrad_pretransposed(l)) {
+        if (!ok) break;
+        if (dgrad_pretransposed(l, conv_uses[l.p0] > 1)) {
           w->wt_off[i] = w->wt_bytes;
           w->wt_bytes += align_up((size_t)d.Cout * d.R * d.S * d.Cin * sizeof(bf16_t), 256);
+        } else if (l.in0 != 0 && conv_uses[l.p0] > 1) {
+          w->shared_read = true;
         }
         if (w->x8_layer < 0 && l.in0 == 0 && d.dtype == CNNK_BF16 && conv_pad_supported(make_geom(&d))) {
           w->x8_layer = i;
@@ -247,7 +257,7 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
   hipStream_t aux = nullptr;
   if (B->aux_stream && B->ev_fork && B->ev_join && !timing) {
     if (B->ws_bytes < 2 * ws_one) return CNNK_ERR_WORKSPACE;
-    if (w.flops >= kAuxMinFlops) aux = (hipStream_t)B->aux_stream;
+    if (w.flops >= kAuxMinFlops && !w.shared_read) aux = (hipStream_t)B->aux_stream;
   }
   void* const aux_ws = static_cast<char*>(B->ws) + ws_one;
   const size_t aux_wsb = aux ? B->ws_bytes - ws_one : 0;

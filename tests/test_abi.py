@@ -189,6 +189,26 @@ def test_train_step_checks_the_workspace_before_any_launch(cnnk):
     assert e.value.status == 4
 
 
+@pytest.mark.parametrize("k,stride", [(1, 1), (1, 2), (3, 2)])
+def test_weights_of_several_layers_are_copied_before_the_backward_pass(cnnk, k, stride):
+    """The data gradients of these layers read the weights as they are, and the second stream updates a layer's weights
+    behind its own data gradient: where a later one reads the same weights, the step keeps room for copies."""
+    import workloads as WL
+    from paper_2503_23186_amd.runner import build_c_layers
+    need = []
+    for shared in (False, True):
+        net = WL.Net("shared", 4, "bf16")
+        a = net.conv(net.slot(4, 16, 16, 3), 256, 3, 1)
+        for _ in range(2):
+            a = net.bn(net.conv(a, 256, k, stride))
+        net.fc_loss(net.pool(a, "gap"))
+        convs = [L for L in net.layers if L["op"] == "conv"]
+        if shared:
+            convs[2]["w"] = convs[1]["w"]
+        need.append(cnnk.cnnk_train_step_workspace_bytes(build_c_layers(net.layers, cnnk.BF16), len(net.layers)))
+    assert need[1] - need[0] >= 2 * 256 * k * k * 256 * 2
+
+
 def test_epoch_loop_entry_points_reject_bad_arguments_on_the_host(cnnk):
     """cnnk_bn_relu_infer, cnnk_count_correct and cnnk_eval_step validate before they launch."""
     import workloads as WL

@@ -328,3 +328,35 @@ def test_grouped_weight_gradients_give_the_same_bits(group):
     assert net.conv_flops()[1] > 2e9          # below, the step leaves its second stream unused
     for k, (a, b) in enumerate(zip(*out)):
         assert torch.equal(a, b), k
+
+
+@pytest.mark.parametrize("group", [1, 2])
+@pytest.mark.parametrize("dtype,k,stride,channels", [("bf16", 1, 1, 256), ("bf16", 3, 2, 128), ("bf16", 3, 1, 128), ("f32", 1, 1, 128)])
+def test_layers_with_the_same_weights_take_those_that_the_step_began_with(dtype, k, stride, channels, group):
+    """The second stream updates a layer's weights during the backward pass; the data gradient of a later layer with the
+    same weights is the one-stream step's, bit for bit (a learning rate that moves every weight by its own size)."""
+    from paper_2503_23186_amd import StepRunner, cnnk
+    net = WL.Net("shared", 48, dtype)
+    t = net.conv(net.slot(48, 32, 32, 3), channels, 3, 1)
+    first = None
+    for _ in range(3):
+        t = net.bn(net.conv(t, channels, k, stride))
+        conv = net.layers[-2]
+        first = first or conv
+        conv["w"] = first["w"]
+    net.fc_loss(net.pool(t, "gap"))
+    inp = WL.make_inputs(net, 31)
+    assert net.conv_flops()[1] > 2e9          # below, the step leaves its second stream unused
+    out = []
+    cnnk.cnnk_tune(17, group)
+    try:
+        for two in (False, True):
+            run = StepRunner(net.layers, net.slots, [p["shape"] for p in net.params], net.dtype, two_streams=two)
+            run.load(inp["x"], inp["labels"], inp["params"], inp["mom"])
+            run.step(1e3, 0.9, 0.0)
+            torch.cuda.synchronize()
+            out.append(run)
+    finally:
+        cnnk.cnnk_tune(17, 0)
+    for s in range(1, len(net.slots)):
+        assert torch.equal(out[0].dact[s], out[1].dact[s]), "activation gradient %d" % s
