@@ -186,23 +186,23 @@ def test_fp32_resnet18_narrow():
     check_step(net, inp, runner, out, TOL["f32"])
 
 
-def test_two_streams_match_one_stream():
+def _two_stream_net():
+    """A network whose step uses its second stream (below 2 GFLOP of convolutions it does not)."""
+    net = WL.mini_resnet(batch=48, dtype="bf16", size=32, widths=(64, 128))
+    assert net.conv_flops()[1] > 2e9
+    return net
+
+
+@pytest.mark.parametrize("group", [1, 2])
+def test_two_streams_match_one_stream(group):
     """The weight gradients forked onto a second stream give the results of the single-stream
     order over several consecutive steps (workspace halves and events reused).  The forked
     weight gradients split their pixel range over fewer workgroups, so the fp32 partial sums are
-    grouped differently: equal up to fp32 rounding, and each mode is bit-reproducible."""
-    from paper_2503_23186_amd import StepRunner
-    net = WL.mini_resnet(batch=16, dtype="bf16", widths=(64, 128))
+    grouped differently: equal up to fp32 rounding, and each mode is bit-reproducible.  Forked one by one and in pairs
+    (tune key 17)."""
+    net = _two_stream_net()
     inp = WL.make_inputs(net, 0)
-    runs = []
-    for two in (False, True, True):
-        r = StepRunner(net.layers, net.slots, [p["shape"] for p in net.params], net.dtype, two_streams=two)
-        r.load(inp["x"], inp["labels"], inp["params"], inp["mom"])
-        for _ in range(3):
-            r.step(0.1, 0.9, 1e-4)
-        torch.cuda.synchronize()
-        runs.append(r)
-    a, b, c = runs
+    a, b, c = (_run_steps(net, inp, {17: group}, two_streams=two, steps=3) for two in (False, True, True))
     assert abs(a.loss.item() - b.loss.item()) <= 1e-5 * abs(a.loss.item())
     for k in range(len(net.params)):
         for name in ("grad", "param", "mom"):
@@ -260,7 +260,7 @@ def test_bn_backward_mask_from_y_equals_mask_recomputed_from_x(name):
 def test_weight_transposes_on_either_stream_give_the_same_bits():
     """With a second stream the weight transpositions of the data-gradient kernels run there beside
     the classifier head; tune key 12 keeps them on the main stream.  Same bits either way."""
-    net = WL.mini_resnet(batch=16, dtype="bf16", widths=(64, 128))
+    net = _two_stream_net()
     inp = WL.make_inputs(net, 0)
     a = _run_steps(net, inp, {}, two_streams=True, steps=3)
     b = _run_steps(net, inp, {12: -1}, two_streams=True, steps=3)
