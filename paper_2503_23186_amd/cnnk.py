@@ -278,7 +278,6 @@ def cnnk_eval_step(layers, n_layers, buffers, labels, loss, pred, n_correct=None
 
 # ---- HIP runtime plumbing for callers that time launches with events (no arithmetic here) ----
 _hip = None
-HIP_STREAM_NON_BLOCKING = 0x1
 HIP_EVENT_DISABLE_TIMING = 0x2
 HIP_EVENT_DISABLE_SYSTEM_FENCE = 0x20000000
 
@@ -293,8 +292,6 @@ def _hiprt():
         _hip.hipEventElapsedTime.argtypes = [C.POINTER(C.c_float), C.c_void_p, C.c_void_p]
         _hip.hipEventDestroy.argtypes = [C.c_void_p]
         _hip.hipEventCreateWithFlags.argtypes = [C.POINTER(C.c_void_p), C.c_uint]
-        _hip.hipStreamCreateWithFlags.argtypes = [C.POINTER(C.c_void_p), C.c_uint]
-        _hip.hipStreamDestroy.argtypes = [C.c_void_p]
     return _hip
 
 
@@ -319,38 +316,34 @@ def hip_order_event_create():
 
 
 class AuxStream:
-    """A stream of default priority beside the caller's, shared by everything on the device that keeps a
-    reference (aux_stream()) and destroyed with the last one."""
+    """The second stream of one stream's steps; whoever uses it keeps this object (aux_stream()).  It is what is
+    referred to weakly: a torch.cuda.Stream that is freed leaves weak references to itself dangling."""
 
-    def __init__(self, device):
-        s = C.c_void_p()
-        with torch.cuda.device(device):
-            rc = _hiprt().hipStreamCreateWithFlags(C.byref(s), HIP_STREAM_NON_BLOCKING)
-        if rc != 0:
-            raise RuntimeError("hipStreamCreateWithFlags failed: %d" % rc)
-        self.cuda_stream = s.value
-
-    def __del__(self):
-        if _hip is not None and getattr(self, "cuda_stream", None):
-            _hip.hipStreamDestroy(self.cuda_stream)     # returns at once; the runtime frees it when its work is done
+    def __init__(self, stream):
+        self.stream = stream
 
 
-_aux_streams = weakref.WeakValueDictionary()
+_aux_streams = weakref.WeakValueDictionary()     # (device index, handle of the caller's stream): AuxStream
 _aux_lock = threading.Lock()
 
 
-def aux_stream(device):
-    """The second stream of the training steps on `device`.  One for all of them: work of a step that the
-    caller has enqueued behind another step's would only park another hardware queue on its event waits, and
-    a parked queue slows the ones that run (ResNet-18 b256, three runners in turn: 2.47 ms with a stream
-    each, 2.17 ms with one)."""
+def aux_stream(device, beside):
+    """The second stream (of default priority, from torch's pool) of the training steps that are enqueued on the stream
+    with handle `beside` of `device`.  One for all of them: a step's work there lies between the step's fork and join,
+    so that steps of one stream never wait for each other there, while a second stream of their own for each would
+    only park more hardware queues on event waits, and a parked queue slows the ones that run (ResNet-18 b256,
+    three runners in turn: 2.47 ms with a stream each, 2.17 ms with one).  Steps on different streams get different
+    ones: they stay independent, also where one of them is captured into a graph."""
     device = torch.device(device)
     index = torch.cuda.current_device() if device.index is None else device.index
     with _aux_lock:
-        s = _aux_streams.get(index)
-        if s is None:
-            s = _aux_streams[index] = AuxStream(index)
-        return s
+        aux = _aux_streams.get((index, beside))
+        if aux is None:
+            stream = torch.cuda.Stream(device=index)
+            if stream.cuda_stream == beside:
+                stream = torch.cuda.Stream(device=index)
+            aux = _aux_streams[(index, beside)] = AuxStream(stream)
+        return aux
 
 
 def hip_event_record(ev, stream=0):

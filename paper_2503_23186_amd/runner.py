@@ -125,12 +125,13 @@ class StepRunner:
         b.events = None
         b.n_events = 0
         # second stream (default priority) + two events for the weight gradients
-        self.aux_stream = cnnk.aux_stream(self.dev) if two_streams else None
-        b.aux_stream = self.aux_stream.cuda_stream if two_streams else None
+        self.aux_stream = None
         b.ev_fork = cnnk.hip_order_event_create() if two_streams else None
         b.ev_join = cnnk.hip_order_event_create() if two_streams else None
         self.buffers = b
         self._events = None
+        if two_streams:
+            self._set_aux_stream(torch.cuda.current_stream(self.dev).cuda_stream)
 
     # -- host <-> device copies (not part of the timed path) -------------------------------
     def load(self, x, labels, params, mom):
@@ -150,8 +151,16 @@ class StepRunner:
             if lp is not None:
                 cnnk.cnnk_round_bf16(lp.numel(), self.param[k], lp, s)
 
+    def _set_aux_stream(self, beside):
+        self._beside = beside
+        self._aux = cnnk.aux_stream(self.dev, beside)
+        self.aux_stream = self._aux.stream
+        self.buffers.aux_stream = self.aux_stream.cuda_stream
+
     def step(self, lr=0.1, momentum=0.9, weight_decay=0.0, stream=None):
         s = torch.cuda.current_stream().cuda_stream if stream is None else stream
+        if self.aux_stream is not None and s != self._beside:
+            self._set_aux_stream(s)
         cnnk.cnnk_train_step(self.c_layers, len(self.layers), self.buffers, self.labels, lr, momentum,
                              weight_decay, self.loss, self.pred, s)
 

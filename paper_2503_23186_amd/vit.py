@@ -228,7 +228,7 @@ class VitRunner:
             raise ValueError("unsupported ViT configuration")
         self.arena = torch.zeros(self.arena_bytes, dtype=torch.uint8, device=self.dev)
         self.ws = torch.zeros(max(self.ws_bytes, 256) * (2 if two_streams else 1), dtype=torch.uint8, device=self.dev)
-        self.aux_stream = cnnk.aux_stream(self.dev) if two_streams else None
+        self.aux_stream = None
         n = len(table)
         arr = lambda ts: (C.c_void_p * n)(*[None if t is None else t.data_ptr() for t in ts])
         self._keep = [arr(self.param), arr(self.param_lp), arr(self.grad), arr(self.mom)]
@@ -237,12 +237,14 @@ class VitRunner:
                                   self.x.data_ptr(), self.labels.data_ptr(), self.loss.data_ptr(), self.pred.data_ptr(),
                                   None if self.probs is None else self.probs.data_ptr(), self.arena.data_ptr(),
                                   self.arena_bytes, self.ws.data_ptr(), self.ws.numel(), None, 0,
-                                  self.aux_stream.cuda_stream if two_streams else None,
+                                  None,
                                   cnnk.hip_order_event_create() if two_streams else None,
                                   cnnk.hip_order_event_create() if two_streams else None)
         self.n_calls = cnnk_vit_step_calls(self.desc)
         self.call_names = [cnnk_vit_step_call_name(self.desc, i) for i in range(self.n_calls)]
         self._events = None
+        if two_streams:
+            self._set_aux_stream(torch.cuda.current_stream(self.dev).cuda_stream)
 
     # -- data in ------------------------------------------------------------------------------------
     def load(self, x, labels, params, mom):
@@ -262,8 +264,17 @@ class VitRunner:
                 cnnk.cnnk_round_bf16(p.numel(), p, lp, s)
 
     # -- the step -------------------------------------------------------------------------------------
+    def _set_aux_stream(self, beside):
+        self._beside = beside
+        self._aux = cnnk.aux_stream(self.dev, beside)
+        self.aux_stream = self._aux.stream
+        self.buffers.aux_stream = self.aux_stream.cuda_stream
+
     def step(self, lr, momentum, weight_decay=0.0):
-        cnnk_vit_train_step(self.desc, self.buffers, lr, momentum, weight_decay, torch.cuda.current_stream().cuda_stream)
+        s = torch.cuda.current_stream().cuda_stream
+        if self.aux_stream is not None and s != self._beside:
+            self._set_aux_stream(s)
+        cnnk_vit_train_step(self.desc, self.buffers, lr, momentum, weight_decay, s)
 
     def enable_timing(self, on=True):
         if on and self._events is None:

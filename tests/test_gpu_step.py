@@ -360,3 +360,78 @@ def test_layers_with_the_same_weights_take_those_that_the_step_began_with(dtype,
         cnnk.cnnk_tune(17, 0)
     for s in range(1, len(net.slots)):
         assert torch.equal(out[0].dact[s], out[1].dact[s]), "activation gradient %d" % s
+
+
+def _steps_of(run, n):
+    for _ in range(n):
+        run.step(0.1, 0.9, 1e-4)
+
+
+def _clones(run):
+    return [t.clone() for t in run.param + run.mom + run.grad + [run.loss]]
+
+
+def test_two_runners_on_two_streams_of_two_threads():
+    """Steps of different streams share no stream: two host threads, each with its runner and its stream, leave the bits
+    that either leaves alone; on one stream both use the same second one."""
+    import threading
+    from paper_2503_23186_amd import StepRunner
+    net = _two_stream_net()
+    inputs = [WL.make_inputs(net, s) for s in (37, 38)]
+    make = lambda i: StepRunner(net.layers, net.slots, [p["shape"] for p in net.params], net.dtype)
+    want = []
+    for i in range(2):
+        run = make(i)
+        run.load(inputs[i]["x"], inputs[i]["labels"], inputs[i]["params"], inputs[i]["mom"])
+        _steps_of(run, 6)
+        torch.cuda.synchronize()
+        want.append(_clones(run))
+    runs, streams = [make(0), make(1)], [torch.cuda.Stream(), torch.cuda.Stream()]
+    assert runs[0].aux_stream is runs[1].aux_stream and isinstance(runs[0].aux_stream, torch.cuda.Stream)
+    for r, i in zip(runs, inputs):
+        r.load(i["x"], i["labels"], i["params"], i["mom"])
+    torch.cuda.synchronize()
+
+    def work(k):
+        with torch.cuda.stream(streams[k]):
+            _steps_of(runs[k], 6)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert len({runs[0].aux_stream.cuda_stream, runs[1].aux_stream.cuda_stream} | {s.cuda_stream for s in streams}) == 4
+    for r, w in zip(runs, want):
+        for k, (a, b) in enumerate(zip(_clones(r), w)):
+            assert torch.equal(a, b), k
+
+
+def test_captured_step_beside_steps_of_another_stream():
+    """A step captured into a graph on a stream of its own, while another runner's steps are enqueued on another stream:
+    they run at once and are no part of the graph.  Every replay, with eager work in between, is the eager step."""
+    from paper_2503_23186_amd import StepRunner
+    net = _two_stream_net()
+    inputs = [WL.make_inputs(net, s) for s in (41, 42)]
+    eager, taken, other, alone = (StepRunner(net.layers, net.slots, [p["shape"] for p in net.params], net.dtype) for _ in range(4))
+    for r, i in ((eager, 0), (taken, 0), (other, 1), (alone, 1)):
+        r.load(inputs[i]["x"], inputs[i]["labels"], inputs[i]["params"], inputs[i]["mom"])
+    _steps_of(alone, 3)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, capture_error_mode="thread_local"):
+        _steps_of(taken, 1)
+        with torch.cuda.stream(side):
+            _steps_of(other, 3)
+    side.synchronize()
+    for k, (a, b) in enumerate(zip(_clones(other), _clones(alone))):
+        assert torch.equal(a, b), k
+    for replay in range(3):
+        graph.replay()
+        _steps_of(eager, 1)
+        torch.cuda.synchronize()
+        for k, (a, b) in enumerate(zip(_clones(taken), _clones(eager))):
+            assert torch.equal(a, b), (replay, k)
+    for k, (a, b) in enumerate(zip(_clones(other), _clones(alone))):
+        assert torch.equal(a, b), k

@@ -42,3 +42,27 @@ def test_checkpoint_file_round_trip(tmp_path):
     # floats are stored with repr: an accuracy like 1/3 comes back exactly
     write_checkpoint(p, t, dict(meta, best_acc=1.0 / 3.0))
     assert float(read_checkpoint(p)[1]["best_acc"]) == 1.0 / 3.0
+
+
+def test_second_streams_are_shared_by_the_steps_of_one_stream_only(monkeypatch):
+    """One second stream for all steps that one stream of the caller's carries, another for every other stream, never the
+    caller's own (torch's pool hands the same streams out again), given back with the last runner that holds it."""
+    from paper_2503_23186_amd import cnnk
+    handles = iter([7, 8, 9, 7, 11])
+
+    class Stream:
+        __slots__ = ("cuda_stream",)                     # takes no weak reference
+
+        def __init__(self, device):
+            self.cuda_stream = next(handles)
+
+    monkeypatch.setattr(torch.cuda, "Stream", Stream)
+    held = len(cnnk._aux_streams)
+    a = cnnk.aux_stream("cuda:3", 0)
+    assert cnnk.aux_stream("cuda:3", 0) is a and a.stream.cuda_stream == 7
+    b = cnnk.aux_stream("cuda:3", 8)                     # 8 is the caller's own
+    c = cnnk.aux_stream("cuda:4", 0)
+    assert (b.stream.cuda_stream, c.stream.cuda_stream) == (9, 7) and len(cnnk._aux_streams) == held + 3
+    del a, c
+    assert len(cnnk._aux_streams) == held + 1
+    assert cnnk.aux_stream("cuda:3", 8) is b
