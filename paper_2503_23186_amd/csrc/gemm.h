@@ -12,8 +12,7 @@ int gemm_bf16_fwd(long long rows, int K, int N, const bf16_t* x, const bf16_t* w
 // dx = dy w
 int gemm_bf16_dgrad(long long rows, int K, int N, const bf16_t* dy, const bf16_t* w, bf16_t* dx, hipStream_t st);
 // dg = dy w, du = dg (as stored) * gelu'(u): the data gradient through the layer and the activation before it.
-// sums: [gemm_bf16_dgrad_gelu_parts][K] partial column sums of du before it is rounded, 16-byte aligned; there are at
-// most 2 * ceil(rows / 64) of them.
+// sums: [gemm_bf16_dgrad_gelu_parts][K] partial column sums of du before it is rounded, 16-byte aligned.
 int gemm_bf16_dgrad_gelu_parts(long long rows, int K, int N);
 int gemm_bf16_dgrad_gelu(long long rows, int K, int N, const bf16_t* dy, const bf16_t* w, const bf16_t* u, bf16_t* dg, bf16_t* du,
                          float* sums, hipStream_t st);

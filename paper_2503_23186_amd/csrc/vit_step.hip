@@ -132,11 +132,19 @@ int fill_group(const Geo& g, int l, GemmWgrad* p) {
   return n;
 }
 
-// partial sums of fc1's bias gradient, of one block
-size_t gelu_sums_bytes(const Geo& g) { return align_up(2 * ((g.rows + 63) / 64) * g.m * sizeof(float), 256); }
+// The workspace of a step on one stream, half of it on two: the scratch of a call, then the partial sums of the layer
+// norms and of fc1's bias gradients of `blocks` blocks, which live until their group's final sums.  With a second
+// stream those may come at any time before the join, so every block has partial sums of its own, in the two halves; on
+// one stream the next group takes the last one's place.
+struct Workspace {
+  size_t scratch, ln, gelu, total;      // ln: of one layer norm; gelu: of one fc1
+  int blocks;
+  size_t block() const { return 2 * ln + gelu; }
+};
 
-size_t workspace(const cnnk_vit_desc* v, const Geo& g) {
-  size_t w = 0;
+Workspace workspace(const cnnk_vit_desc* v, const Geo& g) {
+  Workspace ws{};
+  size_t& w = ws.scratch;
   const long long shapes[5][3] = {{(long long)g.B * g.n, g.K0, g.d}, {(long long)g.rows, g.d, 3 * g.d}, {(long long)g.rows, g.d, g.d},
                                   {(long long)g.rows, g.d, g.m}, {(long long)g.rows, g.m, g.d}};
   for (int i = 0; i < 5; ++i) w = max_sz(w, cnnk_linear_workspace_bytes(shapes[i][0], (int)shapes[i][1], (int)shapes[i][2], g.dtype));
@@ -152,9 +160,14 @@ size_t workspace(const cnnk_vit_desc* v, const Geo& g) {
       const int n = fill_group(g, l, p);
       w = max_sz(w, gemm_bf16_wgrad_group_ws(p, n));
     }
-    w = align_up(w, 256) + (size_t)g.L * (2 * align_up(cnnk_layernorm_workspace_bytes(&ln), 256) + gelu_sums_bytes(g));
+    const int group = group_blocks(g), half = (g.L + 1) / 2;
+    ws.blocks = group > half ? (group < g.L ? group : g.L) : half;
+    ws.ln = align_up(cnnk_layernorm_workspace_bytes(&ln), 256);
+    ws.gelu = align_up((size_t)gemm_bf16_dgrad_gelu_parts((long long)g.rows, g.m, g.d) * g.m * sizeof(float), 256);
   }
-  return align_up(w, 256);
+  w = align_up(w, 256);
+  ws.total = w + (size_t)ws.blocks * ws.block();
+  return ws;
 }
 
 // Walks the step's calls in order.  In enumeration mode nothing runs: the walk counts the calls and
@@ -226,20 +239,21 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
   const cnnk_ln_desc ln_cls = {g.B, d, g.dtype, v->ln_eps, (long long)T * d};
   const cnnk_attn_desc ad = {g.B, T, v->heads, d / v->heads, g.dtype};
   const cnnk_embed_desc ed = {g.B, v->image, v->patch, d, g.dtype};
-  const size_t ln_bytes = align_up(cnnk_layernorm_workspace_bytes(&ln), 256), gelu_bytes = gelu_sums_bytes(g), whole = workspace(v, g);
+  const Workspace W = workspace(v, g);
   char* const base = (char*)buf->arena;
   auto at = [&](int id, int l) -> bf16_t* { return (bf16_t*)(base + A.off[id] + A.size[id] * (size_t)(per_layer(id) ? l : 0)); };
   auto P = [&](int k) { return (float*)buf->param[k]; };
   auto Wm = [&](int k) { return (const bf16_t*)buf->param_lp[k]; };
   auto Gr = [&](int k) { return (float*)buf->grad[k]; };
-  // the workspace: what a call needs, then the partial sums of the layer norms and of fc1's bias gradients (they live
-  // until their group's final sums)
   char* const ws = (char*)buf->ws;
-  const size_t wsb = whole - (size_t)g.L * (2 * ln_bytes + gelu_bytes);
-  char* const ln_parts = ws + wsb;
-  char* const gelu_parts = ln_parts + 2 * (size_t)g.L * ln_bytes;
+  const size_t wsb = W.scratch;
   const hipStream_t side = two ? (hipStream_t)buf->aux_stream : st;
-  void* const side_ws = two ? ws + buf->ws_bytes / 2 / 256 * 256 : ws;
+  char* const side_ws = two ? ws + buf->ws_bytes / 2 / 256 * 256 : ws;
+  // partial sums of block l: of its two layer norms, then of fc1's bias gradient
+  auto parts_of = [&](int l) -> char* {
+    if (!two) return ws + W.scratch + (size_t)(l % G) * W.block();
+    return (l < W.blocks ? ws + (size_t)l * W.block() : side_ws + (size_t)(l - W.blocks) * W.block()) + W.scratch;
+  };
   int rc = cnnk_fill_zero(at(CNNK_VIT_DXOUT, g.L - 1), A.size[CNNK_VIT_DXOUT], st);
   if (rc == CNNK_OK)
     rc = cnnk_layernorm_bwd(&ln_cls, at(CNNK_VIT_DF, 0), at(CNNK_VIT_XOUT, g.L - 1), P(p_tail), (const float*)at(X_STATSF, 0), nullptr,
@@ -251,8 +265,8 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
   auto defer = [&](const bf16_t* dy, const bf16_t* x, int kw, int kb, long long r, int K, int N) {
     pend[np++] = GemmWgrad{dy, x, Gr(kw), kb < 0 ? nullptr : Gr(kb), r, K, N};
   };
-  auto norm_bwd = [&](int slot, const bf16_t* dy, const bf16_t* x, int kg, const void* stats, const bf16_t* dres, bf16_t* dx) -> int {
-    float* part = (float*)(ln_parts + (size_t)slot * ln_bytes);
+  auto norm_bwd = [&](int l, int second, const bf16_t* dy, const bf16_t* x, int kg, const void* stats, const bf16_t* dres, bf16_t* dx) -> int {
+    float* part = (float*)(parts_of(l) + second * W.ln);
     const int i = sums.count++;
     sums.part[i] = part; sums.out0[i] = Gr(kg); sums.out1[i] = Gr(kg + 1);
     return ln_bwd_rows_partial(&ln, dy, x, P(kg), (const float*)stats, dres, dx, part, st);
@@ -262,16 +276,16 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
     const bf16_t* xin = l ? at(CNNK_VIT_XOUT, l - 1) : at(CNNK_VIT_TOK, 0);
     bf16_t* dxin = l ? at(CNNK_VIT_DXOUT, l - 1) : at(CNNK_VIT_DTOK, 0);
     const bf16_t *dxo = at(CNNK_VIT_DXOUT, l), *du = at(CNNK_VIT_DU, l), *dxm = at(CNNK_VIT_DXMID, l), *dqkv = at(CNNK_VIT_DQKV, l);
-    float* const du_part = (float*)(gelu_parts + (size_t)l * gelu_bytes);
+    float* const du_part = (float*)(parts_of(l) + 2 * W.ln);
     rc = gemm_bf16_dgrad_gelu(rows, m, d, dxo, Wm(p0 + B_W2), at(CNNK_VIT_U, l), at(CNNK_VIT_DG, l), at(CNNK_VIT_DU, l), du_part, st);
     const int ig = gelu_sums.count++;
     gelu_sums.part[ig] = du_part; gelu_sums.out0[ig] = Gr(p0 + B_C1); gelu_sums.out1[ig] = Gr(p0 + B_C1) + m / 2;
     if (rc == CNNK_OK) rc = gemm_bf16_dgrad(rows, d, m, du, Wm(p0 + B_W1), at(CNNK_VIT_DH2, l), st);
-    if (rc == CNNK_OK) rc = norm_bwd(2 * l + 1, at(CNNK_VIT_DH2, l), at(CNNK_VIT_XMID, l), p0 + B_G2, at(X_STATS2, l), dxo, at(CNNK_VIT_DXMID, l));
+    if (rc == CNNK_OK) rc = norm_bwd(l, 1, at(CNNK_VIT_DH2, l), at(CNNK_VIT_XMID, l), p0 + B_G2, at(X_STATS2, l), dxo, at(CNNK_VIT_DXMID, l));
     if (rc == CNNK_OK) rc = gemm_bf16_dgrad(rows, d, d, dxm, Wm(p0 + B_WO), at(CNNK_VIT_DO, l), st);
     if (rc == CNNK_OK) rc = cnnk_attention_bwd(&ad, at(CNNK_VIT_QKV, l), at(CNNK_VIT_O, l), at(CNNK_VIT_DO, l), (const float*)at(X_LSE, l), at(CNNK_VIT_DQKV, l), st);
     if (rc == CNNK_OK) rc = gemm_bf16_dgrad(rows, d, 3 * d, dqkv, Wm(p0 + B_WQKV), at(CNNK_VIT_DH, l), st);
-    if (rc == CNNK_OK) rc = norm_bwd(2 * l, at(CNNK_VIT_DH, l), xin, p0 + B_G1, at(X_STATS1, l), dxm, dxin);
+    if (rc == CNNK_OK) rc = norm_bwd(l, 0, at(CNNK_VIT_DH, l), xin, p0 + B_G1, at(X_STATS1, l), dxm, dxin);
     defer(dxo, at(CNNK_VIT_G, l), p0 + B_W2, p0 + B_C2, rows, m, d);
     defer(du, at(CNNK_VIT_H2, l), p0 + B_W1, -1, rows, d, m);
     defer(dxm, at(CNNK_VIT_O, l), p0 + B_WO, p0 + B_BO, rows, d, d);
@@ -438,7 +452,7 @@ extern "C" size_t cnnk_vit_arena_bytes(const cnnk_vit_desc* v) {
 extern "C" size_t cnnk_vit_workspace_bytes(const cnnk_vit_desc* v) {
   Geo g;
   if (validate(v, &g) != CNNK_OK) return 0;
-  return workspace(v, g);
+  return workspace(v, g).total;
 }
 
 extern "C" int cnnk_vit_tensor(const cnnk_vit_desc* v, int id, int layer, size_t* offset, size_t* bytes) {
@@ -498,7 +512,7 @@ extern "C" int cnnk_vit_eval_step(const cnnk_vit_desc* v, const cnnk_vit_buffers
   if (rc != CNNK_OK) return rc;
   rc = check_buffers(v, g, buf, false);
   if (rc != CNNK_OK) return rc;
-  if (!buf->ws || buf->ws_bytes < workspace(v, g)) return CNNK_ERR_WORKSPACE;
+  if (!buf->ws || buf->ws_bytes < workspace(v, g).total) return CNNK_ERR_WORKSPACE;
   cnnk_vit_buffers b = *buf;          // one stream, no per-call events
   b.events = nullptr; b.n_events = 0; b.aux_stream = nullptr;
   Walk w = {true, 0, -1, nullptr, 0, CNNK_OK, nullptr, (hipStream_t)stream};
@@ -515,7 +529,7 @@ extern "C" int cnnk_vit_train_step(const cnnk_vit_desc* v, const cnnk_vit_buffer
   const int rcb = check_buffers(v, g, buf, true);
   if (rcb != CNNK_OK) return rcb;
   const bool two_streams = buf->aux_stream && buf->ev_fork && buf->ev_join && !buf->events;
-  if (!buf->ws || buf->ws_bytes < workspace(v, g) * (two_streams ? 2 : 1)) return CNNK_ERR_WORKSPACE;
+  if (!buf->ws || buf->ws_bytes < workspace(v, g).total * (two_streams ? 2 : 1)) return CNNK_ERR_WORKSPACE;
   if ((((size_t)buf->arena) & 255) != 0 || (((size_t)buf->ws) & 255) != 0) return CNNK_ERR_UNSUPPORTED;
   Walk w = {true, 0, -1, nullptr, 0, CNNK_OK, nullptr, (hipStream_t)stream};
   if (buf->events) {

@@ -227,7 +227,7 @@ class VitRunner:
         if self.arena_bytes == 0:
             raise ValueError("unsupported ViT configuration")
         self.arena = torch.zeros(self.arena_bytes, dtype=torch.uint8, device=self.dev)
-        self.ws = torch.zeros(max(self.ws_bytes, 256) * (2 if two_streams else 1), dtype=torch.uint8, device=self.dev)
+        self.ws = torch.empty(max(self.ws_bytes, 256) * (2 if two_streams else 1), dtype=torch.uint8, device=self.dev)
         self.aux_stream = None
         n = len(table)
         arr = lambda ts: (C.c_void_p * n)(*[None if t is None else t.data_ptr() for t in ts])

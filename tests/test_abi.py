@@ -209,6 +209,15 @@ def test_weights_of_several_layers_are_copied_before_the_backward_pass(cnnk, k, 
     assert need[1] - need[0] >= 2 * 256 * k * k * 256 * 2
 
 
+def test_transformer_workspace_holds_partial_sums_of_half_the_blocks(cnnk):
+    """A step on two streams has twice the workspace, for the partial sums of every block; one on one stream needs a
+    group's.  ViT-B/16 at batch 64: a block's two layer norms leave 9.7 MB, fc1's bias gradient 1.2 MB."""
+    from paper_2503_23186_amd import vit
+    need = [vit.cnnk_vit_workspace_bytes(vit.vit_desc(64, 224, 16, 768, 12, layers, 3072, 100, cnnk.BF16)) for layers in (2, 12)]
+    block = 2 * vit.cnnk_layernorm_workspace_bytes(vit.ln_desc(64 * 197, 768, cnnk.BF16)) + 2 * 99 * 3072 * 4
+    assert 0 < need[1] - need[0] <= 5 * block + 4096
+
+
 def test_epoch_loop_entry_points_reject_bad_arguments_on_the_host(cnnk):
     """cnnk_bn_relu_infer, cnnk_count_correct and cnnk_eval_step validate before they launch."""
     import workloads as WL

@@ -607,3 +607,27 @@ def test_grouped_weight_and_bias_gradients_keep_their_chains_of_sums_short(batch
         if b:           # a compensated sum: the rounding of eight terms at a time and of the result
             want = d.sum(0)
             assert ((grad[b + ".0"].double() - want).norm() / want.norm()).item() <= 2.0 ** -23, b
+
+
+@pytest.mark.parametrize("two_streams", [True, False])
+@pytest.mark.parametrize("batch,image,patch,dim,layers,mlp", [(3, 32, 8, 768, 5, 3072), (9, 64, 8, 128, 9, 200)])
+def test_step_needs_nothing_of_its_workspace_but_the_room(batch, image, patch, dim, layers, mlp, two_streams):
+    """Same bits from a workspace of the size that the library asks for, whatever it holds, and no byte behind it."""
+    from paper_2503_23186_amd.vit import VitRunner
+    net = WL.ViT("vit", batch, "bf16", image, patch, dim, dim // 64, layers, mlp)
+    inp = WL.make_vit_inputs(net, 23)
+    out = []
+    for fill in (0x00, 0xff):
+        run = VitRunner(net, two_streams=two_streams)
+        room = run.ws.numel()
+        assert room == run.ws_bytes * (2 if two_streams else 1)
+        guarded = torch.full((room + 4096,), fill, dtype=torch.uint8, device="cuda:0")
+        run.buffers.ws = guarded.data_ptr()
+        run.load(inp["x"], inp["labels"], inp["params"], inp["mom"])
+        for _ in range(2):
+            run.step(0.05, 0.9, 1e-3)
+        torch.cuda.synchronize()
+        assert bool((guarded[room:] == fill).all())
+        out.append([t.clone() for t in run.param + run.mom + run.grad])
+    for name, a, b in zip(3 * run.names, *out):
+        assert torch.equal(a, b), name
