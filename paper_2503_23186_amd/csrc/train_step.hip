@@ -14,10 +14,15 @@ namespace {
 // grid budget (in compute units) of a weight gradient that runs beside the backward pass: measured
 // optimum on ResNet-18 b256 (96..128 are within 1 %, 64 and 192 are 3 % slower)
 constexpr int kAuxWgradCus = 112;
-// Flops of the convolutions of a step from which its second stream is used.  Below, the step is a chain of
-// launches of a few us and the events between the streams cost more than the overlap gives (tiny CNN of
-// 21 MFLOP: 184 us with, 160 us without; VGG-style network at batch 16, 7 GFLOP: even).
-constexpr double kAuxMinFlops = 2e9;
+// Work for the second stream from which a step uses it: the flops of the convolutions, forward and backward, and 4500 for
+// every element of their weights (their gradient, momentum and update move about 24 bytes each).  Below, the step is a
+// chain of launches of a few us, and the events between the streams (50 to 80 us a step) cost more than the overlap
+// gives.  us per step with one stream / two, by GF and million weights: tiny CNN b512 0.9 GF 640 / 663; 6-layer ResNet
+// 0.3 M b16 13 GF 302 / 347, b48 39 GF 366 / 372, b64 52 GF 380 / 376; VGG-style 1.1 M b16 15 GF 350 / 360, b32 29 GF
+// 370 / 384, b48 44 GF 397 / 404, b64 58 GF 412 / 416, b96 88 GF 482 / 448; twelve 3x3 layers 1.6 M b16 40 GF 663 / 604;
+// 24 1x1 layers 1.5 M 37 GF 958 / 1112; ResNet-18 11 M b1 3 GF 1062 / 1024, b8 27 GF 1114 / 1056; ResNet-50 24 M b1 8 GF
+// 2512 / 2385; WRN-28-10 36 M b1 31 GF 2362 / 2202.
+constexpr double kAuxMinWork = 46e9, kAuxWorkPerWeight = 4500;
 constexpr int kStatSlots = 4;   // convolutions whose per-channel sums may be pending at once
 constexpr size_t kStatBytes = kStatSlots * 2 * 2048 * sizeof(float);
 
@@ -33,6 +38,7 @@ struct Walk {
   size_t mask_bytes = 0;             // ReLU masks (a bit per element) of the batch norms with a residual input
   bool shared_read = false;          // a weight of several layers is read by a data gradient, not copied before
   double flops = 0;                  // of the convolutions, forward and backward
+  double weights = 0;                // their elements
   int convs = 0;
   int dtype = -1;
 };
@@ -107,6 +113,7 @@ int walk_layers(const cnnk_layer* L, int n, int n_slots, int n_params, Walk* w) 
              set_elems(w->slot_elems, l.out, (size_t)d.N * Ho * Wo * d.Cout) &&
              set_elems(w->param_elems, l.p0, (size_t)d.Cout * d.R * d.S * d.Cin);
         ++w->convs;
+        w->weights += (double)d.Cout * d.R * d.S * d.Cin;
         w->flops += 2.0 * d.N * Ho * Wo * d.Cout * d.R * d.S * d.Cin * (l.in0 == 0 ? 2 : 3);
         for (int p = 0; p < 3; ++p) w->ws = max_sz(w->ws, cnnk_conv2d_workspace_bytes(&d, p));
         if (!ok) break;
@@ -257,7 +264,7 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
   hipStream_t aux = nullptr;
   if (B->aux_stream && B->ev_fork && B->ev_join && !timing) {
     if (B->ws_bytes < 2 * ws_one) return CNNK_ERR_WORKSPACE;
-    if (w.flops >= kAuxMinFlops && !w.shared_read) aux = (hipStream_t)B->aux_stream;
+    if (w.flops + kAuxWorkPerWeight * w.weights >= kAuxMinWork && !w.shared_read) aux = (hipStream_t)B->aux_stream;
   }
   void* const aux_ws = static_cast<char*>(B->ws) + ws_one;
   const size_t aux_wsb = aux ? B->ws_bytes - ws_one : 0;

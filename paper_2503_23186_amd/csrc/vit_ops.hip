@@ -435,9 +435,12 @@ inline unsigned grid_for(size_t work_items, unsigned cap = 8192) {
 }
 inline int ln_nq(int C) { return C <= 256 ? 1 : C <= 1024 ? 4 : 16; }
 // Workgroups of the layer-norm backward pass: every wavefront gets the same number of rows, one up to 1600 rows (a
-// second one is another chain of latencies: 1576 x 768 12.6 us with two, 10.6 with one), at least two beyond (the
-// partial sums cost the final launch more than that saves: 3152 x 768 16.3 us with one, 12.5 with two), and no more
-// workgroups than are resident at once (12608 x 1024: 34.1 us with 20 workgroups more than that, 30.0 without).
+// second one is another chain of latencies), at least two beyond (half the partial sums), and no more workgroups than
+// are resident at once (12608 x 1024: 34.1 us with 20 workgroups more than that, 30.0 without).  us with one row a
+// wavefront / two, 768 columns: the call with its final sums, 1300 rows 9.4 / 10.5, 1576 10.4 / 9.4, 2000 13.5 / 12.6, 2364
+// 13.0 / 12.4, 3152 16.1 / 12.2; a step of six blocks, which has the final sums in another launch beside, 1379 rows
+// 1646 / 1660, 1576 1669 / 1692, 1970 1793 / 1809, 2364 1887 / 1903, 2758 2588 / 2582, 3152 2256 / 2243.  The line lies
+// between the two.
 inline int ln_bwd_blocks(int rows, int C) {
   const int most = 4 * (C <= 768 ? 1024 : C <= 1024 ? 768 : 512);
   int per = (rows + most - 1) / most;

@@ -186,10 +186,14 @@ def test_fp32_resnet18_narrow():
     check_step(net, inp, runner, out, TOL["f32"])
 
 
+def uses_second_stream(net):
+    """Steps of little work leave it unused; 46 GFLOP of convolutions are enough whatever their weights."""
+    return net.conv_flops()[1] > 46e9
+
+
 def _two_stream_net():
-    """A network whose step uses its second stream (below 2 GFLOP of convolutions it does not)."""
-    net = WL.mini_resnet(batch=48, dtype="bf16", size=32, widths=(64, 128))
-    assert net.conv_flops()[1] > 2e9
+    net = WL.mini_resnet(batch=64, dtype="bf16", size=32, widths=(64, 128))
+    assert uses_second_stream(net)
     return net
 
 
@@ -311,7 +315,7 @@ def test_grouped_weight_gradients_give_the_same_bits(group):
     """Weight gradients forked onto the second stream one by one and several at a time, their reductions and updates
     in one launch: the same kernels and orders of summation, so the same bits after two steps."""
     from paper_2503_23186_amd import StepRunner, cnnk
-    net = WL.mini_resnet(batch=48, dtype="bf16", size=32, widths=(32, 72))
+    net = WL.mini_resnet(batch=224, dtype="bf16", size=32, widths=(32, 72))
     inp = WL.make_inputs(net, 29)
     out = []
     for g in (1, group):
@@ -325,13 +329,13 @@ def test_grouped_weight_gradients_give_the_same_bits(group):
         finally:
             cnnk.cnnk_tune(17, 0)
         out.append([t.clone() for t in run.param + run.mom + run.grad + [t for t in run.dact if t is not None]])
-    assert net.conv_flops()[1] > 2e9          # below, the step leaves its second stream unused
+    assert uses_second_stream(net)
     for k, (a, b) in enumerate(zip(*out)):
         assert torch.equal(a, b), k
 
 
 @pytest.mark.parametrize("group", [1, 2])
-@pytest.mark.parametrize("dtype,k,stride,channels", [("bf16", 1, 1, 256), ("bf16", 3, 2, 128), ("bf16", 3, 1, 128), ("f32", 1, 1, 128)])
+@pytest.mark.parametrize("dtype,k,stride,channels", [("bf16", 1, 1, 256), ("bf16", 3, 2, 256), ("bf16", 3, 1, 128), ("f32", 1, 1, 256)])
 def test_layers_with_the_same_weights_take_those_that_the_step_began_with(dtype, k, stride, channels, group):
     """The second stream updates a layer's weights during the backward pass; the data gradient of a later layer with the
     same weights is the one-stream step's, bit for bit (a learning rate that moves every weight by its own size)."""
@@ -346,7 +350,7 @@ def test_layers_with_the_same_weights_take_those_that_the_step_began_with(dtype,
         conv["w"] = first["w"]
     net.fc_loss(net.pool(t, "gap"))
     inp = WL.make_inputs(net, 31)
-    assert net.conv_flops()[1] > 2e9          # below, the step leaves its second stream unused
+    assert uses_second_stream(net)
     out = []
     cnnk.cnnk_tune(17, group)
     try:
