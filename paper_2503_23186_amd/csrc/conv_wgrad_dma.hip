@@ -17,6 +17,7 @@
 // hardware fixes the LDS address of every lane).
 #include "common.h"
 #include "conv.h"
+#include "mfma_tile.h"
 
 namespace {
 
@@ -25,28 +26,6 @@ constexpr int PS = 128;           // output pixels per stage
 constexpr int CT = 64;            // channels per operand tile (64 k, 64 c)
 constexpr int ROW_B = 64;         // bytes of a plane row (32 channels)
 constexpr int DY_PLANE = PS * ROW_B;
-
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
-
-// Buffer descriptor as four scalar words (base, no stride, size in bytes, raw 32-bit data format).
-__device__ __forceinline__ i32x4_t make_desc(const void* p, unsigned bytes) {
-  const unsigned long long a = reinterpret_cast<unsigned long long>(p);
-  return i32x4_t{(int)(unsigned)a, (int)((unsigned)(a >> 32) & 0xffffu), (int)bytes, 0x00020000};
-}
-// One direct load: lane i of the wave moves 16 bytes from byte offset voff of the buffer to LDS
-// address lds_addr + 16*i (zeros when voff is out of range).  Written as assembly so that the
-// compiler does not track it: it would otherwise make every LDS read that follows wait for all
-// outstanding direct loads, which defeats the prefetch.  The waits are explicit in the kernel.
-__device__ __forceinline__ void load16_to_lds(i32x4_t desc, unsigned lds_addr, unsigned voff) {
-  // M0 carries the LDS address of such a load; it is put back so the statement is invisible to the
-  // compiler's own uses of that register.
-  unsigned keep;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-               : "=&s"(keep)
-               : "s"(lds_addr), "v"(voff), "s"(desc)
-               : "memory");
-}
 
 struct WgDmaArgs {
   const bf16_t* x;
