@@ -278,6 +278,7 @@ def cnnk_eval_step(layers, n_layers, buffers, labels, loss, pred, n_correct=None
 
 # ---- HIP runtime plumbing for callers that time launches with events (no arithmetic here) ----
 _hip = None
+HIP_STREAM_NON_BLOCKING = 0x1
 HIP_EVENT_DISABLE_TIMING = 0x2
 HIP_EVENT_DISABLE_SYSTEM_FENCE = 0x20000000
 
@@ -292,6 +293,8 @@ def _hiprt():
         _hip.hipEventElapsedTime.argtypes = [C.POINTER(C.c_float), C.c_void_p, C.c_void_p]
         _hip.hipEventDestroy.argtypes = [C.c_void_p]
         _hip.hipEventCreateWithFlags.argtypes = [C.POINTER(C.c_void_p), C.c_uint]
+        _hip.hipStreamCreateWithFlags.argtypes = [C.POINTER(C.c_void_p), C.c_uint]
+        _hip.hipStreamDestroy.argtypes = [C.c_void_p]
     return _hip
 
 
@@ -316,11 +319,36 @@ def hip_order_event_create():
 
 
 class AuxStream:
-    """The second stream of one stream's steps; whoever uses it keeps this object (aux_stream()).  It is what is
-    referred to weakly: a torch.cuda.Stream that is freed leaves weak references to itself dangling."""
+    """The second stream of one stream's steps (aux_stream()), a stream of its own and not one of torch's pool: the
+    runtime lays streams on four hardware queues, and every fourth stream of a pool lies on the caller's, where nothing
+    overlaps (WRN-28-10 b128 8.09 ms there, 6.51 with the others and with this one; ResNet-18 b256 2.68 and 2.05;
+    ResNet-50 b256 9.13 and 7.82).  Destroyed with the last object that keeps it.  While a stream is captured none is created: then
+    the pool's serves, whose queue the graph does not use."""
 
-    def __init__(self, stream):
-        self.stream = stream
+    def __init__(self, index, beside):
+        self._own = None
+        if torch.cuda.is_current_stream_capturing():
+            self.stream = torch.cuda.Stream(device=index)
+            if self.stream.cuda_stream == beside:
+                self.stream = torch.cuda.Stream(device=index)
+            self.cuda_stream = self.stream.cuda_stream
+            return
+        s = C.c_void_p()
+        with torch.cuda.device(index):
+            rc = _hiprt().hipStreamCreateWithFlags(C.byref(s), HIP_STREAM_NON_BLOCKING)
+        if rc != 0:
+            raise RuntimeError("hipStreamCreateWithFlags failed: %d" % rc)
+        self._own = self.cuda_stream = s.value
+
+    def as_torch(self, device):
+        """The stream for torch's calls; it keeps this object."""
+        s = torch.cuda.ExternalStream(self.cuda_stream, device=device)
+        s.kept = self
+        return s
+
+    def __del__(self):
+        if _hip is not None and getattr(self, "_own", None):
+            _hip.hipStreamDestroy(self._own)     # returns at once; the runtime frees it when its work is done
 
 
 _aux_streams = weakref.WeakValueDictionary()     # (device index, handle of the caller's stream): AuxStream
@@ -328,21 +356,18 @@ _aux_lock = threading.Lock()
 
 
 def aux_stream(device, beside):
-    """The second stream (of default priority, from torch's pool) of the training steps that are enqueued on the stream
-    with handle `beside` of `device`.  One for all of them: a step's work there lies between the step's fork and join,
-    so that steps of one stream never wait for each other there, while a second stream of their own for each would
-    only park more hardware queues on event waits, and a parked queue slows the ones that run (ResNet-18 b256,
-    three runners in turn: 2.47 ms with a stream each, 2.17 ms with one).  Steps on different streams get different
-    ones: they stay independent, also where one of them is captured into a graph."""
+    """The second stream (of default priority) of the training steps that are enqueued on the stream with handle `beside`
+    of `device`.  One for all of them: a step's work there lies between the step's fork and join, so that steps of one
+    stream never wait for each other there, while a second stream of their own for each would only park more hardware
+    queues on event waits, and a parked queue slows the ones that run (ResNet-18 b256, three runners in turn: 2.47 ms
+    with a stream each, 2.17 ms with one).  Steps on different streams get different ones: they stay independent, also
+    where one of them is captured into a graph."""
     device = torch.device(device)
     index = torch.cuda.current_device() if device.index is None else device.index
     with _aux_lock:
         aux = _aux_streams.get((index, beside))
         if aux is None:
-            stream = torch.cuda.Stream(device=index)
-            if stream.cuda_stream == beside:
-                stream = torch.cuda.Stream(device=index)
-            aux = _aux_streams[(index, beside)] = AuxStream(stream)
+            aux = _aux_streams[(index, beside)] = AuxStream(index, beside)
         return aux
 
 

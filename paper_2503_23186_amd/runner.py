@@ -153,8 +153,7 @@ class StepRunner:
 
     def _set_aux_stream(self, beside):
         self._beside = beside
-        self._aux = cnnk.aux_stream(self.dev, beside)
-        self.aux_stream = self._aux.stream
+        self.aux_stream = cnnk.aux_stream(self.dev, beside).as_torch(self.dev)
         self.buffers.aux_stream = self.aux_stream.cuda_stream
 
     def step(self, lr=0.1, momentum=0.9, weight_decay=0.0, stream=None):

@@ -391,7 +391,7 @@ def test_two_runners_on_two_streams_of_two_threads():
         torch.cuda.synchronize()
         want.append(_clones(run))
     runs, streams = [make(0), make(1)], [torch.cuda.Stream(), torch.cuda.Stream()]
-    assert runs[0].aux_stream is runs[1].aux_stream and isinstance(runs[0].aux_stream, torch.cuda.Stream)
+    assert runs[0].aux_stream.cuda_stream == runs[1].aux_stream.cuda_stream and isinstance(runs[0].aux_stream, torch.cuda.Stream)
     for r, i in zip(runs, inputs):
         r.load(i["x"], i["labels"], i["params"], i["mom"])
     torch.cuda.synchronize()

@@ -45,24 +45,45 @@ def test_checkpoint_file_round_trip(tmp_path):
 
 
 def test_second_streams_are_shared_by_the_steps_of_one_stream_only(monkeypatch):
-    """One second stream for all steps that one stream of the caller's carries, another for every other stream, never the
-    caller's own (torch's pool hands the same streams out again), given back with the last runner that holds it."""
+    """One second stream for all steps that one stream of the caller's carries, another for every other stream, destroyed
+    with the last object that keeps it; while a stream is captured one of torch's pool, never the caller's own."""
+    import contextlib
     from paper_2503_23186_amd import cnnk
-    handles = iter([7, 8, 9, 7, 11])
+    made, destroyed, capturing = iter(range(101, 200)), [], [False]
+
+    class Hip:
+        @staticmethod
+        def hipStreamCreateWithFlags(handle, flags):
+            assert not capturing[0]
+            handle._obj.value = next(made)
+            return 0
+
+        @staticmethod
+        def hipStreamDestroy(handle):
+            destroyed.append(handle)
 
     class Stream:
         __slots__ = ("cuda_stream",)                     # takes no weak reference
+        pool = iter([7, 8, 9])
 
         def __init__(self, device):
-            self.cuda_stream = next(handles)
+            self.cuda_stream = next(self.pool)
 
+    monkeypatch.setattr(cnnk, "_hip", Hip)
+    monkeypatch.setattr(cnnk, "_hiprt", lambda: Hip)
     monkeypatch.setattr(torch.cuda, "Stream", Stream)
+    monkeypatch.setattr(torch.cuda, "device", lambda index: contextlib.nullcontext())
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing[0])
     held = len(cnnk._aux_streams)
     a = cnnk.aux_stream("cuda:3", 0)
-    assert cnnk.aux_stream("cuda:3", 0) is a and a.stream.cuda_stream == 7
-    b = cnnk.aux_stream("cuda:3", 8)                     # 8 is the caller's own
-    c = cnnk.aux_stream("cuda:4", 0)
-    assert (b.stream.cuda_stream, c.stream.cuda_stream) == (9, 7) and len(cnnk._aux_streams) == held + 3
+    assert cnnk.aux_stream("cuda:3", 0) is a and a.cuda_stream == 101
+    b, c = cnnk.aux_stream("cuda:3", 55), cnnk.aux_stream("cuda:4", 0)
+    assert (b.cuda_stream, c.cuda_stream) == (102, 103) and len(cnnk._aux_streams) == held + 3
     del a, c
-    assert len(cnnk._aux_streams) == held + 1
-    assert cnnk.aux_stream("cuda:3", 8) is b
+    assert destroyed == [101, 103] and len(cnnk._aux_streams) == held + 1
+    assert cnnk.aux_stream("cuda:3", 55) is b
+    capturing[0] = True
+    d, e = cnnk.aux_stream("cuda:3", 77), cnnk.aux_stream("cuda:3", 8)
+    assert (d.cuda_stream, e.cuda_stream) == (7, 9) and cnnk.aux_stream("cuda:3", 55) is b
+    del b, d, e
+    assert destroyed == [101, 103, 102] and len(cnnk._aux_streams) == held
