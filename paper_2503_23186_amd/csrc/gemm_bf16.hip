@@ -43,9 +43,9 @@ struct Args {
   int M, N, K;        // output rows, output columns, reduction length
   int lda, ldb, ldc;
   int k_per_split;    // reduction elements per blockIdx.z (a multiple of BK)
-  int fold;           // EPI 2, tiles that have the registers: stages between two folds of the accumulators
   int mtiles, ntiles;
   unsigned a_bytes, b_bytes, c_bytes;
+  int fold;           // EPI 2, tiles that have the registers: stages between two folds of the accumulators
 };
 
 // the operands of a dense product
@@ -84,6 +84,11 @@ template <class C> struct DenseLoader {
     return kk0[j] + t * C::BK < kend ? voff[j] + (unsigned)t * (j < C::NLOAD_A ? vinc_a : vinc_b) : kOobOffset;
   }
 };
+
+// v of the lane N before this one in its sixteen, around the end (an operand modifier, no pass through LDS)
+template <int N> __device__ __forceinline__ float row_rotated(float v) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x120 + N, 0xf, 0xf, true));
+}
 
 // Rows between two folds of a weight gradient's accumulators, near 3.4 sqrt(rows), where the errors of the two chains
 // balance (a chain's grows with the root of its steps; 1568 rows 8.7e-8 with 128 and 9.3e-8 with 256, 12608 rows the
@@ -215,9 +220,12 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) cs[j][e] += __shfl_xor(cs[j][e], o, 64);
+      for (int e = 0; e < 8; ++e) {
+        cs[j][e] += row_rotated<8>(cs[j][e]);
+        cs[j][e] += row_rotated<4>(cs[j][e]);
+        cs[j][e] += row_rotated<2>(cs[j][e]);
+        cs[j][e] += row_rotated<1>(cs[j][e]);
+      }
       const int col = n0 + wn * (TN * 32) + j * 32 + g * 8;
       if (i16 == 0 && col < a.N) {
         float* q = a.part + (size_t)(mt * C::WM + wm) * a.N + col;

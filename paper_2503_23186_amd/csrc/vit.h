@@ -14,14 +14,12 @@ int ln_bwd_parts(const cnnk_ln_desc* d);       // rows of those partial sums
 
 // The final sums of several tables of partial column sums [parts][2 * C] in one launch: out0 gets the first C columns,
 // out1 the others.
-constexpr int kColumnSumsMax = 64;
+constexpr int kColumnSumsMax = 32;
 struct ColumnSums {
   int count;
-  const float* part[kColumnSumsMax];
-  float* out0[kColumnSumsMax];
-  float* out1[kColumnSumsMax];
+  struct { const float* part; float *out0, *out1; int parts, C; } it[kColumnSumsMax];
 };
-int column_sums_group(const ColumnSums& t, int parts, int C, hipStream_t st);
+int column_sums_group(const ColumnSums& t, hipStream_t st);
 
 // cnnk_vit_embed_bwd on checked arguments; dbe null: the caller gets it elsewhere
 int embed_bwd(const cnnk_embed_desc* d, const void* dtok, void* dz, float* dbe, float* dcls, float* dpos, hipStream_t st);

@@ -213,11 +213,13 @@ __global__ void __launch_bounds__(kT) colsum_finalize_kernel(const float* __rest
 }
 
 // The same for several tables of partials, one per blockIdx.y.
-__global__ void __launch_bounds__(kT) column_sums_group_kernel(ColumnSums t, int nb, int C) {
+__global__ void __launch_bounds__(kT) column_sums_group_kernel(ColumnSums t) {
   __shared__ float sm[4][64];
   const int cl = threadIdx.x & 63, pl = threadIdx.x >> 6;
+  const int nb = t.it[blockIdx.y].parts, C = t.it[blockIdx.y].C;
   const int c = blockIdx.x * 64 + cl, n = 2 * C;
-  const float* __restrict__ part = t.part[blockIdx.y];
+  if ((int)blockIdx.x * 64 >= n) return;      // the launch is as wide as the widest table
+  const float* __restrict__ part = t.it[blockIdx.y].part;
   float s = 0.f;
   if (c < n) {
     int b = pl;
@@ -234,7 +236,7 @@ __global__ void __launch_bounds__(kT) column_sums_group_kernel(ColumnSums t, int
   __syncthreads();
   if (pl == 0 && c < n) {
     const float r = (sm[0][cl] + sm[1][cl]) + (sm[2][cl] + sm[3][cl]);
-    if (c < C) t.out0[blockIdx.y][c] = r; else t.out1[blockIdx.y][c - C] = r;
+    if (c < C) t.it[blockIdx.y].out0[c] = r; else t.it[blockIdx.y].out1[c - C] = r;
   }
 }
 
@@ -512,9 +514,11 @@ int ln_bwd_rows_partial(const cnnk_ln_desc* d, const void* dy, const void* x, co
 
 int ln_bwd_parts(const cnnk_ln_desc* d) { return ln_bwd_blocks(d->rows, d->C); }
 
-int column_sums_group(const ColumnSums& t, int parts, int C, hipStream_t st) {
+int column_sums_group(const ColumnSums& t, hipStream_t st) {
   if (t.count == 0) return CNNK_OK;
-  column_sums_group_kernel<<<dim3((2 * C + 63) / 64, t.count), kT, 0, st>>>(t, parts, C);
+  int C = 0;
+  for (int i = 0; i < t.count; ++i) C = t.it[i].C > C ? t.it[i].C : C;
+  column_sums_group_kernel<<<dim3((2 * C + 63) / 64, t.count), kT, 0, st>>>(t);
   return launch_status();
 }
 

@@ -227,9 +227,9 @@ int update_params(const Geo& g, const cnnk_vit_buffers* buf, int k0, int k1, flo
 // The backward pass and the update with the products that only the update waits for in groups: the data-gradient
 // chain runs on `st`; the weight gradients of group_blocks(g) transformer blocks, with the bias gradients (column
 // sums of an operand that those products load anyway), the final sums of the blocks' layer norms and of fc1's bias
-// gradients and the update of the blocks' parameters follow as four launches, on the second stream if there is one.
+// gradients and the update of the blocks' parameters follow as three launches, on the second stream if there is one.
 // GELU's gradient is taken in the epilogue of fc2's data gradient, which leaves partial sums of the unrounded products
-// for fc1's bias.  Per block of ViT-B/16 11 launches and one event pair instead of 24 and 7: at batch 8 the step was
+// for fc1's bias.  Per block of ViT-B/16 10 launches and one event pair instead of 24 and 7: at batch 8 the step was
 // bound by enqueueing them, and at batch 64 split products for a fraction of the device each took 270 us a block.
 int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffers* buf, const Arena& A, float lr, float mu, float wd,
                      bool two, hipStream_t st) {
@@ -259,16 +259,16 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
     rc = cnnk_layernorm_bwd(&ln_cls, at(CNNK_VIT_DF, 0), at(CNNK_VIT_XOUT, g.L - 1), P(p_tail), (const float*)at(X_STATSF, 0), nullptr,
                             at(CNNK_VIT_DXOUT, g.L - 1), Gr(p_tail), Gr(p_tail + 1), ws, wsb, st);
   GemmWgrad pend[32];
-  ColumnSums sums, gelu_sums;
+  ColumnSums sums;
+  const int ln_parts = ln_bwd_parts(&ln), gelu_parts = gemm_bf16_dgrad_gelu_parts(rows, m, d);
   int np = 0;
-  sums.count = gelu_sums.count = 0;
+  sums.count = 0;
   auto defer = [&](const bf16_t* dy, const bf16_t* x, int kw, int kb, long long r, int K, int N) {
     pend[np++] = GemmWgrad{dy, x, Gr(kw), kb < 0 ? nullptr : Gr(kb), r, K, N};
   };
   auto norm_bwd = [&](int l, int second, const bf16_t* dy, const bf16_t* x, int kg, const void* stats, const bf16_t* dres, bf16_t* dx) -> int {
     float* part = (float*)(parts_of(l) + second * W.ln);
-    const int i = sums.count++;
-    sums.part[i] = part; sums.out0[i] = Gr(kg); sums.out1[i] = Gr(kg + 1);
+    sums.it[sums.count++] = {part, Gr(kg), Gr(kg + 1), ln_parts, d};
     return ln_bwd_rows_partial(&ln, dy, x, P(kg), (const float*)stats, dres, dx, part, st);
   };
   for (int l = g.L - 1; l >= 0 && rc == CNNK_OK; --l) {
@@ -278,8 +278,7 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
     const bf16_t *dxo = at(CNNK_VIT_DXOUT, l), *du = at(CNNK_VIT_DU, l), *dxm = at(CNNK_VIT_DXMID, l), *dqkv = at(CNNK_VIT_DQKV, l);
     float* const du_part = (float*)(parts_of(l) + 2 * W.ln);
     rc = gemm_bf16_dgrad_gelu(rows, m, d, dxo, Wm(p0 + B_W2), at(CNNK_VIT_U, l), at(CNNK_VIT_DG, l), at(CNNK_VIT_DU, l), du_part, st);
-    const int ig = gelu_sums.count++;
-    gelu_sums.part[ig] = du_part; gelu_sums.out0[ig] = Gr(p0 + B_C1); gelu_sums.out1[ig] = Gr(p0 + B_C1) + m / 2;
+    sums.it[sums.count++] = {du_part, Gr(p0 + B_C1), Gr(p0 + B_C1) + m / 2, gelu_parts, m / 2};
     if (rc == CNNK_OK) rc = gemm_bf16_dgrad(rows, d, m, du, Wm(p0 + B_W1), at(CNNK_VIT_DH2, l), st);
     if (rc == CNNK_OK) rc = norm_bwd(l, 1, at(CNNK_VIT_DH2, l), at(CNNK_VIT_XMID, l), p0 + B_G2, at(X_STATS2, l), dxo, at(CNNK_VIT_DXMID, l));
     if (rc == CNNK_OK) rc = gemm_bf16_dgrad(rows, d, d, dxm, Wm(p0 + B_WO), at(CNNK_VIT_DO, l), st);
@@ -298,12 +297,11 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
     if (two && (hipEventRecord((hipEvent_t)buf->ev_fork, st) != hipSuccess || hipStreamWaitEvent(side, (hipEvent_t)buf->ev_fork, 0) != hipSuccess))
       return CNNK_ERR_HIP;
     rc = gemm_bf16_wgrad_group(pend, np, side_ws, side);
-    if (rc == CNNK_OK) rc = column_sums_group(sums, ln_bwd_parts(&ln), d, side);
-    if (rc == CNNK_OK) rc = column_sums_group(gelu_sums, gemm_bf16_dgrad_gelu_parts(rows, m, d), m / 2, side);
+    if (rc == CNNK_OK) rc = column_sums_group(sums, side);
     const int last = l + G < g.L ? l + G : g.L;
     if (rc == CNNK_OK) rc = update_params(g, buf, l ? p0 : 0, P_BLOCK0 + B_COUNT * last, lr, mu, wd, side);
     np = 0;
-    sums.count = gelu_sums.count = 0;
+    sums.count = 0;
   }
   if (rc == CNNK_OK) rc = update_params(g, buf, p_tail, p_tail + 4, lr, mu, wd, st);
   if (two && rc == CNNK_OK && (hipEventRecord((hipEvent_t)buf->ev_join, side) != hipSuccess || hipStreamWaitEvent(st, (hipEvent_t)buf->ev_join, 0) != hipSuccess))
