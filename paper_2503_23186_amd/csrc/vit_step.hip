@@ -110,20 +110,25 @@ bool grouped(const Geo& g) {
   return g.dtype == CNNK_BF16 && linear_dense(rows, g.d, 3 * g.d, g.dtype) && linear_dense(rows, g.d, g.d, g.dtype) &&
          linear_dense(rows, g.d, g.m, g.dtype) && linear_dense(rows, g.m, g.d, g.dtype) && linear_dense((long long)g.B * g.n, g.K0, g.d, g.dtype);
 }
-// Blocks whose weight gradients share a launch: one where that gives every CU a workgroup (ViT-B/16, 288 a block: one
-// block / two, step at batch 8 3.24 / 3.22 ms, 16 4.40 / 4.68, 32 6.95 / 7.12, 64 11.64 / 11.79), otherwise as many as give it
-// about 400 (512 columns, 136 a block, 96 images of 65 tokens: one block 2.87, two 2.77, three 2.78; 384 columns, 72 a
-// block, 192 images of 257: one 3.54, four 3.40, six 3.42), at most seven (28 products and the embedding's fit the table).
-int group_blocks(const Geo& g) {
+// Blocks whose weight gradients share a launch.  On a second stream one where that gives every CU a workgroup (ViT-B/16,
+// 288 a block: one block / two, step at batch 8 3.24 / 3.22 ms, 16 4.40 / 4.68, 32 6.95 / 7.12, 64 11.64 / 11.79), otherwise as
+// many as give it about 400 (512 columns, 136 a block, 96 images of 65 tokens: one block 2.87, two 2.77, three 2.78; 384
+// columns, 72 a block, 192 images of 257: one 3.54, four 3.40, six 3.42).  On one stream nothing runs beside the launch, and
+// the more workgroups it has, the less of it is a last round that is nearly empty (one block / three / seven, ViT-B/16 at
+// batch 8 3.57 / 3.31 / 3.28 ms, 64 12.82 / 11.58 / 11.50; 512 columns 3.08 / 2.92 / 2.83; 384 columns 3.70 / 3.64 / 3.34).
+// At most seven (28 products and the embedding's fit the table).
+constexpr int kMostBlocks = 7;
+int group_blocks(const Geo& g, bool two) {
+  if (!two) return kMostBlocks;
   const int t = gemm_bf16_wgrad_tiles(g.d, 3 * g.d) + gemm_bf16_wgrad_tiles(g.d, g.d) + gemm_bf16_wgrad_tiles(g.d, g.m) + gemm_bf16_wgrad_tiles(g.m, g.d);
   const int n = t >= 256 ? 1 : (400 + t - 1) / t;
-  return n > 7 ? 7 : n;
+  return n > kMostBlocks ? kMostBlocks : n;
 }
-// Shapes of the products of the group that ends with block l (the blocks l .. l + group_blocks - 1, or up to the
-// last one); block 0's group has the patch embedding as well.  Returns their number.
-int fill_group(const Geo& g, int l, GemmWgrad* p) {
+// Shapes of the products of the group of `blocks` blocks that ends with block l (or up to the last one); block 0's
+// group has the patch embedding as well.  Returns their number.
+int fill_group(const Geo& g, int l, int blocks, GemmWgrad* p) {
   int n = 0;
-  const int end = l + group_blocks(g) < g.L ? l + group_blocks(g) : g.L;
+  const int end = l + blocks < g.L ? l + blocks : g.L;
   for (int k = l; k < end; ++k) {
     const int kn[4][2] = {{g.m, g.d}, {g.d, g.m}, {g.d, g.d}, {g.d, 3 * g.d}};
     for (int q = 0; q < 4; ++q) p[n++] = GemmWgrad{nullptr, nullptr, nullptr, nullptr, (long long)g.rows, kn[q][0], kn[q][1]};
@@ -155,13 +160,16 @@ Workspace workspace(const cnnk_vit_desc* v, const Geo& g) {
   cnnk_fc_desc fc = {g.B, g.d, g.classes, g.dtype};
   w = max_sz(w, cnnk_fc_workspace_bytes(&fc));
   if (grouped(g)) {
-    for (int l = 0; l < g.L; l += group_blocks(g)) {
-      GemmWgrad p[32];
-      const int n = fill_group(g, l, p);
-      w = max_sz(w, gemm_bf16_wgrad_group_ws(p, n));
+    for (int two = 0; two < 2; ++two) {
+      const int group = group_blocks(g, two != 0);
+      for (int l = 0; l < g.L; l += group) {
+        GemmWgrad p[32];
+        const int n = fill_group(g, l, group, p);
+        w = max_sz(w, gemm_bf16_wgrad_group_ws(p, n));
+      }
     }
-    const int group = group_blocks(g), half = (g.L + 1) / 2;
-    ws.blocks = group > half ? (group < g.L ? group : g.L) : half;
+    const int one = group_blocks(g, false), half = (g.L + 1) / 2;
+    ws.blocks = one > half ? (one < g.L ? one : g.L) : half;
     ws.ln = align_up(cnnk_layernorm_workspace_bytes(&ln), 256);
     ws.gelu = align_up((size_t)gemm_bf16_dgrad_gelu_parts((long long)g.rows, g.m, g.d) * g.m * sizeof(float), 256);
   }
@@ -225,7 +233,7 @@ int update_params(const Geo& g, const cnnk_vit_buffers* buf, int k0, int k1, flo
 }
 
 // The backward pass and the update with the products that only the update waits for in groups: the data-gradient
-// chain runs on `st`; the weight gradients of group_blocks(g) transformer blocks, with the bias gradients (column
+// chain runs on `st`; the weight gradients of group_blocks() transformer blocks, with the bias gradients (column
 // sums of an operand that those products load anyway), the final sums of the blocks' layer norms and of fc1's bias
 // gradients and the update of the blocks' parameters follow as three launches, on the second stream if there is one.
 // GELU's gradient is taken in the epilogue of fc2's data gradient, which leaves partial sums of the unrounded products
@@ -233,7 +241,7 @@ int update_params(const Geo& g, const cnnk_vit_buffers* buf, int k0, int k1, flo
 // bound by enqueueing them, and at batch 64 split products for a fraction of the device each took 270 us a block.
 int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffers* buf, const Arena& A, float lr, float mu, float wd,
                      bool two, hipStream_t st) {
-  const int d = g.d, m = g.m, T = g.T, G = group_blocks(g), p_tail = P_BLOCK0 + B_COUNT * g.L;
+  const int d = g.d, m = g.m, T = g.T, G = group_blocks(g, two), p_tail = P_BLOCK0 + B_COUNT * g.L;
   const long long rows = (long long)g.rows, prow = (long long)g.B * g.n;
   const cnnk_ln_desc ln = {(int)g.rows, d, g.dtype, v->ln_eps, 0};
   const cnnk_ln_desc ln_cls = {g.B, d, g.dtype, v->ln_eps, (long long)T * d};
