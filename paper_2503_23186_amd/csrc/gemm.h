@@ -29,7 +29,10 @@ struct GemmWgrad {
   long long rows;
   int K, N;
 };
+// splits: parts of the rows that are summed apart and then added; the sums depend on it and on nothing else of the group
+// (gemm_bf16_wgrad_group_splits: what fills the device best for a group).
 int gemm_bf16_wgrad_group_max();
 int gemm_bf16_wgrad_tiles(int K, int N);      // workgroups of a large group that one layer stands for
-size_t gemm_bf16_wgrad_group_ws(const GemmWgrad* p, int n);      // reads rows, K, N only
-int gemm_bf16_wgrad_group(const GemmWgrad* p, int n, void* ws, hipStream_t st);
+int gemm_bf16_wgrad_group_splits(const GemmWgrad* p, int n);               // these two read rows, K, N only
+size_t gemm_bf16_wgrad_group_ws(const GemmWgrad* p, int n, int splits);
+int gemm_bf16_wgrad_group(const GemmWgrad* p, int n, int splits, void* ws, hipStream_t st);

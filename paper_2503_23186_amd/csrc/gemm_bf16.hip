@@ -520,31 +520,14 @@ int gemm_bf16_wgrad(long long rows, int K, int N, const bf16_t* x, const bf16_t*
 
 // ---- groups of weight gradients --------------------------------------------------------------------------
 namespace {
-struct GroupPlan {
-  bool large;      // 192 x 128 tiles, else 64 x 128
-  int tiles, splits;
-};
 int group_tiles(const GemmWgrad* p, int n, int bm) {
   int t = 0;
   for (int i = 0; i < n; ++i) t += ceil_div(p[i].N, bm) * ceil_div(p[i].K, 128);
   return t;
 }
-// 192 x 128 tiles where they give every CU one (unsplit), 64 x 128 tiles otherwise, the row range then split
-// until the device holds two workgroups per CU (but never below eight stages of 64 rows each).
-GroupPlan plan_group(const GemmWgrad* p, int n) {
-  GroupPlan g;
-  g.tiles = group_tiles(p, n, 192);
-  g.large = g.tiles >= 256;
-  g.splits = 1;
-  if (g.large) return g;
-  g.tiles = group_tiles(p, n, 64);
-  long long rows = p[0].rows;
-  for (int i = 1; i < n; ++i) rows = p[i].rows < rows ? p[i].rows : rows;
-  g.splits = 512 / g.tiles;
-  if (g.splits > (int)(rows / 512)) g.splits = (int)(rows / 512);
-  if (g.splits < 1) g.splits = 1;
-  return g;
-}
+// 192 x 128 tiles where they give every CU one, 64 x 128 tiles otherwise.  Either adds up the same products in the same
+// order.
+bool group_large(const GemmWgrad* p, int n) { return group_tiles(p, n, 192) >= 256; }
 size_t group_elems(const GemmWgrad* p, int n) {
   size_t e = 0;
   for (int i = 0; i < n; ++i) e += (size_t)p[i].N * p[i].K + p[i].N;
@@ -555,25 +538,35 @@ size_t group_elems(const GemmWgrad* p, int n) {
 int gemm_bf16_wgrad_group_max() { return kGroupMax; }
 int gemm_bf16_wgrad_tiles(int K, int N) { return ceil_div(N, 192) * ceil_div(K, 128); }
 
-size_t gemm_bf16_wgrad_group_ws(const GemmWgrad* p, int n) {
-  const GroupPlan g = plan_group(p, n);
-  return g.splits > 1 ? (size_t)g.splits * group_elems(p, n) * sizeof(float) : 0;
+// Unsplit with the large tiles; with the small ones the row range is split until the device holds two workgroups per CU
+// (but never below eight stages of 64 rows each).
+int gemm_bf16_wgrad_group_splits(const GemmWgrad* p, int n) {
+  if (group_large(p, n)) return 1;
+  long long rows = p[0].rows;
+  for (int i = 1; i < n; ++i) rows = p[i].rows < rows ? p[i].rows : rows;
+  int splits = 512 / group_tiles(p, n, 64);
+  if (splits > (int)(rows / 512)) splits = (int)(rows / 512);
+  return splits < 1 ? 1 : splits;
 }
 
-int gemm_bf16_wgrad_group(const GemmWgrad* p, int n, void* ws, hipStream_t st) {
-  if (n < 1 || n > kGroupMax) return CNNK_ERR_SHAPE;
-  const GroupPlan g = plan_group(p, n);
+size_t gemm_bf16_wgrad_group_ws(const GemmWgrad* p, int n, int splits) {
+  return splits > 1 ? (size_t)splits * group_elems(p, n) * sizeof(float) : 0;
+}
+
+int gemm_bf16_wgrad_group(const GemmWgrad* p, int n, int splits, void* ws, hipStream_t st) {
+  if (n < 1 || n > kGroupMax || splits < 1) return CNNK_ERR_SHAPE;
+  const bool large = group_large(p, n);
   GroupArgs a{};
-  a.count = n; a.splits = g.splits; a.part = (float*)ws; a.zstride = group_elems(p, n);
+  a.count = n; a.splits = splits; a.part = (float*)ws; a.zstride = group_elems(p, n);
   size_t off = 0;
   for (int i = 0; i < n; ++i) {
     const int nt = ceil_div(p[i].K, 128);
     a.p[i] = GroupProblem{p[i].dy, p[i].x, p[i].dw, p[i].db, (int)p[i].rows, p[i].K, p[i].N, nt, a.tiles};
     a.off[i] = off;
-    a.tiles += ceil_div(p[i].N, g.large ? 192 : 64) * nt;
+    a.tiles += ceil_div(p[i].N, large ? 192 : 64) * nt;
     off += (size_t)p[i].N * p[i].K + p[i].N;
   }
-  const dim3 grid(8 * ((a.tiles + 7) / 8), 1, g.splits);
+  const dim3 grid(8 * ((a.tiles + 7) / 8), 1, splits);
   auto go = [&](auto kern, int smem, bool* raised) -> int {
     if (!*raised) {
       if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess)
@@ -584,9 +577,9 @@ int gemm_bf16_wgrad_group(const GemmWgrad* p, int n, void* ws, hipStream_t st) {
     return launch_status();
   };
   static bool raised_l = false, raised_s = false;
-  const int rc = g.large ? go(wgrad_group_kernel<3, 2, 32, 64, 3>, Cfg<true, true, 3, 2, 32, 64, 3, 1>::SMEM, &raised_l)
-                         : go(wgrad_group_kernel<1, 2, 64, 128, 3>, Cfg<true, true, 1, 2, 64, 128, 3, 1>::SMEM, &raised_s);
-  if (rc != CNNK_OK || g.splits == 1) return rc;
+  const int rc = large ? go(wgrad_group_kernel<3, 2, 32, 64, 3>, Cfg<true, true, 3, 2, 32, 64, 3, 1>::SMEM, &raised_l)
+                       : go(wgrad_group_kernel<1, 2, 64, 128, 3>, Cfg<true, true, 1, 2, 64, 128, 3, 1>::SMEM, &raised_s);
+  if (rc != CNNK_OK || splits == 1) return rc;
   size_t blocks = (a.zstride / 4 + 255) / 256;
   if (blocks > 2048) blocks = 2048;
   sum_group_kernel<<<(unsigned)blocks, 256, 0, st>>>(a);

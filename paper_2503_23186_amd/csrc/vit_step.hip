@@ -137,6 +137,14 @@ int fill_group(const Geo& g, int l, int blocks, GemmWgrad* p) {
   return n;
 }
 
+// Into how many parts the rows of every weight gradient are split: what fills the device best for a group of the step
+// with two streams, and the same for every group of either, so that the sums are the same bits.
+int group_splits(const Geo& g) {
+  GemmWgrad p[32];
+  const int n = fill_group(g, 0, group_blocks(g, true), p);
+  return gemm_bf16_wgrad_group_splits(p, n);
+}
+
 // The workspace of a step on one stream, half of it on two: the scratch of a call, then the partial sums of the layer
 // norms and of fc1's bias gradients of `blocks` blocks, which live until their group's final sums.  With a second
 // stream those may come at any time before the join, so every block has partial sums of its own, in the two halves; on
@@ -165,7 +173,7 @@ Workspace workspace(const cnnk_vit_desc* v, const Geo& g) {
       for (int l = 0; l < g.L; l += group) {
         GemmWgrad p[32];
         const int n = fill_group(g, l, group, p);
-        w = max_sz(w, gemm_bf16_wgrad_group_ws(p, n));
+        w = max_sz(w, gemm_bf16_wgrad_group_ws(p, n, group_splits(g)));
       }
     }
     const int one = group_blocks(g, false), half = (g.L + 1) / 2;
@@ -268,7 +276,7 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
                             at(CNNK_VIT_DXOUT, g.L - 1), Gr(p_tail), Gr(p_tail + 1), ws, wsb, st);
   GemmWgrad pend[32];
   ColumnSums sums;
-  const int ln_parts = ln_bwd_parts(&ln), gelu_parts = gemm_bf16_dgrad_gelu_parts(rows, m, d);
+  const int splits = group_splits(g), ln_parts = ln_bwd_parts(&ln), gelu_parts = gemm_bf16_dgrad_gelu_parts(rows, m, d);
   int np = 0;
   sums.count = 0;
   auto defer = [&](const bf16_t* dy, const bf16_t* x, int kw, int kb, long long r, int K, int N) {
@@ -304,7 +312,7 @@ int backward_grouped(const cnnk_vit_desc* v, const Geo& g, const cnnk_vit_buffer
     if (l % G != 0 || rc != CNNK_OK) continue;
     if (two && (hipEventRecord((hipEvent_t)buf->ev_fork, st) != hipSuccess || hipStreamWaitEvent(side, (hipEvent_t)buf->ev_fork, 0) != hipSuccess))
       return CNNK_ERR_HIP;
-    rc = gemm_bf16_wgrad_group(pend, np, side_ws, side);
+    rc = gemm_bf16_wgrad_group(pend, np, splits, side_ws, side);
     if (rc == CNNK_OK) rc = column_sums_group(sums, side);
     const int last = l + G < g.L ? l + G : g.L;
     if (rc == CNNK_OK) rc = update_params(g, buf, l ? p0 : 0, P_BLOCK0 + B_COUNT * last, lr, mu, wd, side);

@@ -423,6 +423,19 @@ def test_second_stream_changes_no_bit(K, dtype):
         assert torch.equal(a.param[k], b.param[k]) and torch.equal(a.mom[k], b.mom[k]) and torch.equal(a.grad[k], b.grad[k]), a.names[k]
 
 
+# ragged groups: two and one blocks left over on two streams, two on one; rows split over workgroups (64 columns); a group
+# that one stream makes large and two streams small
+@pytest.mark.parametrize("batch,image,patch,dim,layers,mlp", [(24, 32, 4, 384, 8, 1536), (40, 32, 4, 192, 9, 768), (70, 32, 4, 64, 9, 256),
+                                                              (3, 32, 8, 768, 9, 3072)])
+def test_second_stream_changes_no_bit_of_grouped_gradients(batch, image, patch, dim, layers, mlp):
+    net = WL.ViT("vit", batch, "bf16", image, patch, dim, dim // 64, layers, mlp)
+    inp = WL.make_vit_inputs(net, 29)
+    a, b = (run_hip(net, inp, 0.05, 0.9, 1e-3, two_streams=two) for two in (False, True))
+    torch.cuda.synchronize()
+    for k, name in enumerate(a.names):
+        assert torch.equal(a.grad[k], b.grad[k]) and torch.equal(a.param[k], b.param[k]), name
+
+
 # ---- the epoch loop around the step ---------------------------------------------------------------------
 def _loop_case(dtype):
     net = WL.vit_mini(batch=4, dtype=dtype, image=32, patch=8, dim=128, heads=2, layers=2, mlp=256, classes=10)
