@@ -491,3 +491,26 @@ def test_global_average_pool(K, shape, dtype):
     # bf16 storage: eight significant bits, so a rounding of 2^-8 of the largest element plus the fp32 sum's
     # own error; fp32: 1024 additions in short chains
     assert max_rel_err(host(got), ref.pool_fwd(x, "gap")[0]) <= (4e-3 if dtype == "bf16" else 1e-6)
+
+
+# a thread per channel octet, from 1 MiB a position on: the first batch that takes it, one image fewer, and a last
+# workgroup that is not full; one position too few, whole eights, and remainders of one and seven
+@pytest.mark.parametrize("dtype,N,C", [("bf16", 512, 1024), ("bf16", 511, 1024), ("bf16", 1025, 520), ("f32", 256, 1024), ("f32", 255, 1024)])
+@pytest.mark.parametrize("H,W", [(3, 5), (4, 4), (5, 5), (1, 23)])
+def test_global_average_pool_many_octets(K, dtype, N, C, H, W):
+    x = rep(np.random.default_rng(N + H).standard_normal((N, H, W, C), dtype=np.float32), dtype)
+    d = K.pool_desc(N, H, W, C, K.BF16 if dtype == "bf16" else K.F32, K.POOL_GAP)
+    x[0, 0, 0, 0] = x[N - 1, H - 1, W - 1, C - 1] = np.inf
+    x[0, H - 1, 0, 1] = -np.inf
+    x[0, 0, 0, 2] = np.nan
+    got = torch.full((N + 1, 1, 1, C), 7.0, dtype=dev(x[:1], dtype).dtype, device="cuda:0")
+    K.cnnk_pool_fwd(d, dev(x, dtype), got, None)
+    torch.cuda.synchronize()
+    got = host(got)
+    assert (got[N] == 7.0).all()
+    want = x.mean(axis=(1, 2), dtype=np.float64, keepdims=True)
+    odd = ~np.isfinite(want)
+    assert odd.sum() == 4 and np.array_equal(got[:N][odd], want[odd], equal_nan=True)
+    got[:N][odd] = want[odd] = 0
+    # as above: one rounding of the stored mean, and at most seven fp32 additions in a chain
+    assert max_rel_err(got[:N], want) <= (4e-3 if dtype == "bf16" else 1e-6)
