@@ -11,6 +11,7 @@
 // (lane i at base + 16 i), the layout is produced by which global bytes each lane asks for.
 #pragma once
 #include "common.h"
+#include "compensated.h"
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x8_t __attribute__((ext_vector_type(8)));
@@ -213,13 +214,7 @@ __device__ __forceinline__ void tile_main_loop(LD& ld, int nst, int kg, int wave
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks][i], bfr[ks][j], acc[i][j], 0, 0, 0);
       if (ROWS && row_sums) {
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-          for (int i = 0; i < TM; ++i) {
-            const float v = sum8(af[ks][i]) - lost[i], t2 = rs[i] + v;
-            lost[i] = (t2 - rs[i]) - v;
-            rs[i] = t2;
-          }
+        for (int i = 0; i < TM; ++i) compensated_add(sum8(af[0][i]) + sum8(af[1][i]), rs[i], lost[i]);
       }
     }
     cur += STAGE_B;

@@ -1,6 +1,7 @@
 // Pooling, element-wise sums and gradient routing: bandwidth-bound kernels moving vectors of 8
 // channels per thread (NHWC, C a multiple of 8).
 #include "common.h"
+#include "compensated.h"
 
 namespace {
 constexpr int kT = 256;
@@ -100,12 +101,8 @@ __global__ void __launch_bounds__(kT) gap_fwd_many_kernel(const T* __restrict__ 
   for (int e = 0; e < 8; ++e) acc[e] = low[e] = 0.f;
   auto add = [&](const float (&v)[8][8]) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float t = (((v[0][e] + v[1][e]) + (v[2][e] + v[3][e])) + ((v[4][e] + v[5][e]) + (v[6][e] + v[7][e]))) - low[e];
-      const float s = acc[e] + t;
-      low[e] = __builtin_amdgcn_fmed3f((s - acc[e]) - t, -0x1p104f, 0x1p104f);     // at most 2^103; of an infinite s NaN, which stays out
-      acc[e] = s;
-    }
+    for (int e = 0; e < 8; ++e)
+      compensated_add(((v[0][e] + v[1][e]) + (v[2][e] + v[3][e])) + ((v[4][e] + v[5][e]) + (v[6][e] + v[7][e])), acc[e], low[e]);
   };
   const T* at = x + n * HW * C + c8 * 8;
   int p = 0;

@@ -1,5 +1,6 @@
 """Device arithmetic that has a header of its own, compiled for the CPU: the division by a runtime constant that the
-kernels decode pixel indices with (csrc/fastdiv.h), GELU's derivative (csrc/gelu.h)."""
+kernels decode pixel indices with (csrc/fastdiv.h), GELU's derivative (csrc/gelu.h), the compensated sum
+(csrc/compensated.h)."""
 import os
 import subprocess
 
@@ -86,3 +87,42 @@ def test_gelu_derivative_is_as_exact_as_the_textbook_form_in_fp32(tmp_path):
     with erff and expf."""
     run = run_on_cpu(tmp_path, GELU_PROGRAM)
     assert run.returncode == 0, run.stdout
+
+
+SUM_PROGRAM = r"""
+#include <cmath>
+#include <cstdio>
+#include <vector>
+#include "compensated.h"
+float sum_of(const std::vector<float>& v) {
+  float s = 0.f, lost = 0.f;
+  for (float x : v) compensated_add(x, s, lost);
+  return s;
+}
+int main() {
+  const float inf = INFINITY;
+  int bad = 0;
+  auto expect = [&](bool ok, const char* what) { if (!ok) { printf("%s\n", what); ++bad; } };
+  expect(sum_of({1, inf, 2, -3, 4}) == inf, "an infinity among finite terms");
+  expect(sum_of({inf}) == inf && sum_of({inf, inf, 1}) == inf, "infinities of one sign");
+  expect(sum_of({5, -inf, 2, 3}) == -inf, "a negative infinity");
+  expect(std::isnan(sum_of({inf, 1, -inf, 2})), "infinities of both signs");
+  expect(std::isnan(sum_of({1, NAN, 2})), "a NaN");
+  expect(sum_of({3e38f, 3e38f, 1, 2}) == inf && sum_of({-3e38f, -3e38f, 1}) == -inf, "a sum past the largest number");
+  std::vector<float> v;
+  double want = 0;
+  unsigned r = 1;
+  for (int i = 0; i < 100000; ++i) {
+    r = r * 1664525u + 1013904223u;
+    v.push_back((float)(r >> 8) * 0x1p-24f + 0.5f);
+    want += v.back();
+  }
+  expect(std::fabs(sum_of(v) - want) <= want * 0x1p-23, "1e5 terms: two roundings");
+  return bad;
+}
+"""
+
+
+def test_compensated_sum_keeps_what_it_rounds_off_and_passes_infinities_on(tmp_path):
+    run = run_on_cpu(tmp_path, SUM_PROGRAM)
+    assert run.returncode == 0, run.stdout + run.stderr

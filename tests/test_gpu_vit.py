@@ -622,6 +622,28 @@ def test_grouped_weight_and_bias_gradients_keep_their_chains_of_sums_short(batch
             assert ((grad[b + ".0"].double() - want).norm() / want.norm()).item() <= 2.0 ** -23, b
 
 
+def test_infinite_gradient_makes_an_infinite_bias_gradient():
+    """One image, so that one row of the last block's output has a gradient: the gradient of that block's last bias is
+    this row, also where it overflows (a huge scale of the final norm on one channel)."""
+    from paper_2503_23186_amd.vit import VitRunner
+    net = WL.ViT("vit", 1, "bf16", 16, 16, 64, 1, 1, 72)
+    inp = WL.make_vit_inputs(net, 29)
+    p = inp["params"]
+    for name in ("cls", "pos", "Wo.0", "bo.0", "W2.0", "c2.0"):
+        p[name] = p[name] * 2.0 ** -6
+    p["gf"][7] = 2.0 ** 119
+    p["bf"][7] = 0
+    p["Wh"][:, 7] = np.where(np.arange(len(p["Wh"])) == inp["labels"][0], 1.0, -1.0)
+    p["cls"][7], p["pos"][0, 7] = -2.0 ** -10, -2.0 ** -10      # below the mean: the label's logit is the lowest
+    run = VitRunner(net)
+    run.load(inp["x"], inp["labels"], p, inp["mom"])
+    run.step(0.05, 0.9, 1e-3)
+    torch.cuda.synchronize()
+    dx = run.tensor("DXOUT", 0).view(2, 64).float()
+    assert bool(dx[0, 7].isinf()) and bool(dx[0].isfinite().any()) and not bool(dx.isnan().any()) and not bool(dx[1].any())
+    assert torch.equal(run.grad[run.names.index("c2.0")], dx[0])
+
+
 @pytest.mark.parametrize("two_streams", [True, False])
 @pytest.mark.parametrize("batch,image,patch,dim,layers,mlp", [(3, 32, 8, 768, 5, 3072), (9, 64, 8, 128, 9, 200)])
 def test_step_needs_nothing_of_its_workspace_but_the_room(batch, image, patch, dim, layers, mlp, two_streams):
