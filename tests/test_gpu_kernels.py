@@ -152,6 +152,13 @@ def test_direct_load_kernels_every_tile(K, shape, tile):
         K.cnnk_tune(16, 0)
 
 
+# 1x1 stride-2 data gradients, of whose four output parities three have no tap: channels that end inside a tile (also
+# with the second tile of columns empty but for some), single rows and columns of pixels, one pixel
+@pytest.mark.parametrize("shape", [(5, 7, 7, 160, 64, 1, 2), (3, 1, 9, 72, 96, 1, 2), (2, 8, 1, 264, 32, 1, 2), (1, 1, 1, 64, 64, 1, 2)])
+def test_parities_without_a_tap_are_zero(K, shape):
+    test_conv_fwd_dgrad_wgrad(K, shape, "bf16")
+
+
 WG_SHAPES = [(4, 8, 8, 64, 128), (3, 16, 16, 64, 64), (2, 32, 32, 128, 64), (18, 4, 4, 64, 64), (5, 8, 8, 192, 64),
              (1, 32, 32, 64, 64)]
 
