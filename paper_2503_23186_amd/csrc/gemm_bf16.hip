@@ -2,7 +2,7 @@
 // cores (v_mfma_f32_32x32x16_bf16, fp32 accumulation): y = x W^T (+ bias, + GELU), dx = dy W,
 // dW = dy^T x.  One kernel, three operand orientations.
 //
-// Large problems (small ones: see kTiles): workgroup tile 256 x 128 (or 192 x 128), four wavefronts of 128 x 64 (0.75 KB of LDS operand reads per
+// Large problems (all shapes: kTiles): workgroup tile 256 x 128 (or 192 x 128), four wavefronts of 128 x 64 (0.75 KB of LDS operand reads per
 // MFMA), LDS stage buffers filled straight from memory (buffer_load ... lds; out-of-range rows deposit
 // zeros), one barrier per stage, two workgroups per CU.  Two configurations: 32 reduction elements per
 // stage in 64-byte LDS rows with three stage buffers (loads two stages ahead), or - for the long
@@ -352,38 +352,49 @@ int launch_cfg(Args& a, int splits, hipStream_t st) {
   a.ntiles = (a.N + C::BN - 1) / C::BN;
   return launch(gemm_kernel<ATR, BTR, EPI, TM, TN, BK, RB, NST, KG>, &raised, C::THREADS, C::SMEM, a, splits, st);
 }
-// The tile shapes besides the large ones, and what a launch of each costs.  With few tiles the device is
-// bound by the latency of the operand loads and by how many CUs have a tile at all, so small problems want
-// small tiles, 128-byte operand rows and two groups of wavefronts on one tile (KG = 2: twice the loads in
-// flight per CU).  Estimated time (us) of a launch, from a sweep over 197..12608 rows and 384..3072 columns
-// and reductions (mean loss against the fastest shape 1 %):
-//   one workgroup per CU at a time (KG = 2):  rounds * (fixed + stages per group * stage)
-//   several:   rounds of resident workgroups * fixed + tiles per CU * stages * stage
-// Measured before / after, us: 788 x 3072 -> 768 41.8 / 13.8, 788 x 768 -> 2304 17.1 / 10.7, 197 x 768 -> 768
-// 15.0 / 6.1, 1576 x 768 -> 768 15.3 / 8.3, 6240 x 384 -> 384 10.7 / 7.3.
-enum { T64 = 0, T64G2, T64x128, T64x128G2, T128, T_SMALL };
+// The tile shapes and what a launch of each costs.  With few tiles the device is bound by the latency of the operand
+// loads and by how many CUs have a tile at all, so small problems want small tiles, 128-byte operand rows and two
+// groups of wavefronts on one tile (KG = 2: twice the loads in flight per CU); large ones 256 x 128 or 192 x 128 tiles,
+// with 64-byte rows and three stage buffers or with 128-byte rows and two (L192_WIDE: one load request per line).
+// Estimated time (us) of a launch in rounds of resident workgroups; a round with c of them on a CU takes
+//   c * tile + stages * max(alone, c * stage),      stages of 64 reduction elements (per group)
+// and the launch `start` besides.  Constants fitted to a sweep of all shapes over 64 to 25216 rows and eighteen pairs
+// of widths from 128 to 4096, forward, with GELU, with a residual, data gradient (1152 points): what is chosen
+// takes 0.6 % more than the fastest shape in the mean, and 3 % more than the fixed choice of 256 or 192 rows by rounds
+// (128-byte rows from a reduction of 2048 on) at three of them.  That choice / this one, us: 788 x 3072 -> 768 42.4 /
+// 13.6, 788 x 768 -> 2304 17.2 / 9.9, 197 x 768 -> 768 15.2 / 6.2, 1576 x 768 -> 768 15.7 / 8.1, 3152 x 768 -> 3072 with GELU 31.1
+// / 28.4, 6240 x 384 -> 384 10.6 / 6.9, 12608 x 768 -> 768 with a residual 27.9 / 25.2, 12608 x 768 -> 2304 61.0 / 55.0.
+enum { T64 = 0, T64G2, T64x128, T64x128G2, T128, T_SMALL, L256 = T_SMALL, L192, L192_WIDE, T_SHAPES };
 struct TileCost {
   int rows, cols, kgroups, resident;      // workgroup tile, groups of wavefronts, workgroups per CU
-  float fixed, stage;                     // us; a natural operand, 64 reduction elements per stage
-  float fixed_tt, stage_tt;               // both operands through the transposing load (weight gradient)
+  float start, tile, stage, alone;        // us
 };
-constexpr TileCost kTiles[T_SMALL] = {{64, 64, 1, 3, 4.2f, 0.195f, 4.1f, 0.23f},
-                                      {64, 64, 2, 1, 4.3f, 0.35f, 4.2f, 0.41f},
-                                      {64, 128, 1, 2, 4.6f, 0.335f, 4.1f, 0.345f},
-                                      {64, 128, 2, 1, 4.1f, 0.645f, 4.4f, 0.635f},
-                                      {128, 128, 1, 2, 6.1f, 0.54f, 1e9f, 0.f}};
+constexpr TileCost kTiles[T_SHAPES] = {{64, 64, 1, 3, 1.84f, 1.00f, 0.237f, 0.367f},  {64, 64, 2, 1, 0.597f, 2.89f, 0.231f, 0.461f},
+                                       {64, 128, 1, 2, 1.66f, 1.78f, 0.228f, 0.702f}, {64, 128, 2, 1, 0.288f, 4.27f, 0.671f, 0.576f},
+                                       {128, 128, 1, 2, 1.93f, 3.33f, 0.302f, 0.859f}, {256, 128, 1, 2, 2.59f, 4.57f, 0.861f, 1.62f},
+                                       {192, 128, 1, 2, 2.27f, 5.27f, 0.708f, 1.09f}, {192, 128, 1, 2, 2.13f, 4.62f, 0.346f, 0.912f}};
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
-float tile_time(int tiles, int resident, int stages, int kgroups, float fixed, float stage) {
-  if (kgroups > 1) return ceil_div(tiles, 256) * (fixed + ceil_div(stages, kgroups) * stage);
-  return ceil_div(tiles, 256 * resident) * fixed + (float)ceil_div(tiles, 256) * stages * stage;
+float tile_time(const TileCost& t, int out_rows, int out_cols, int k) {
+  const int tiles = ceil_div(out_rows, t.rows) * ceil_div(out_cols, t.cols), slots = 256 * t.resident;
+  const float stages = (float)k / 64 / t.kgroups;
+  auto round = [&](int c) { return c * t.tile + stages * (c * t.stage > t.alone ? c * t.stage : t.alone); };
+  return t.start + tiles / slots * round(t.resident) + (tiles % slots ? round(ceil_div(tiles % slots, 256)) : 0.f);
 }
-// the fastest of the small shapes for out_rows x out_cols outputs, or -1 if `best` (us) is less
-int pick_small(int out_rows, int out_cols, int k, bool tt, float best) {
+// The same for the weight gradient (both operands through the transposing load; T128 has no such kernel), unsplit, up
+// to 5000 rows: fixed and stage in us of a sweep over 197 to 3152 rows.  Beyond, the split launch and its sum are faster
+// (fastest in 67 of 72 at 8192 rows and more; 4 of 36 at 4096 and 4728, where this estimate decides): 12608 x 2048 -> 512
+// 51.7 us, 70.3 unsplit.
+struct WgradCost { float fixed, stage; };
+constexpr WgradCost kWgrad[T128] = {{4.1f, 0.23f}, {4.2f, 0.41f}, {4.1f, 0.345f}, {4.4f, 0.635f}};
+constexpr int kWgradUnsplitRows = 5000;
+// the fastest of the small shapes for a weight gradient, or -1 if `best` (us) is less
+int pick_wgrad(int out_rows, int out_cols, int rows, float best) {
   int pick = -1;
-  for (int c = 0; c < T_SMALL; ++c) {
+  for (int c = 0; c < T128 && rows <= kWgradUnsplitRows; ++c) {
     const TileCost& t = kTiles[c];
-    const int tiles = ceil_div(out_rows, t.rows) * ceil_div(out_cols, t.cols);
-    const float us = tile_time(tiles, t.resident, ceil_div(k, 64), t.kgroups, tt ? t.fixed_tt : t.fixed, tt ? t.stage_tt : t.stage);
+    const int tiles = ceil_div(out_rows, t.rows) * ceil_div(out_cols, t.cols), stages = ceil_div(rows, 64);
+    const float us = t.kgroups > 1 ? ceil_div(tiles, 256) * (kWgrad[c].fixed + ceil_div(stages, t.kgroups) * kWgrad[c].stage)
+                                   : ceil_div(tiles, 256 * t.resident) * kWgrad[c].fixed + (float)ceil_div(tiles, 256) * stages * kWgrad[c].stage;
     if (us < best) { best = us; pick = c; }
   }
   return pick;
@@ -401,25 +412,25 @@ int launch_small(Args& a, int shape, hipStream_t st) {
     default: return CNNK_ERR_UNSUPPORTED;
   }
 }
-// The shape of a launch of an orientation with a natural operand: one of kTiles or a large one, 256 x 128 and
-// 192 x 128 tiles with 64-byte rows, and for reductions from 2048 on 192 x 128 tiles with 128-byte rows (64 reduction
-// elements per stage, loads one stage ahead: -15 % on 12608 x 3072 -> 768).  Their constants are in the
-// same units as kTiles; the tuning table forces a shape (15 = 1 / 2: 64- / 128-byte rows of the large
-// ones, 16 + n: small shape n; -1: no such shape).
-enum { L256 = T_SMALL, L192, L192_WIDE };
+// The shape of a launch of an orientation with a natural operand.  The tuning table forces one (15 = 1 / 2: the large
+// ones with 64- / 128-byte rows, 16 + n: small shape n; -1: no such shape).  With a reduction below 2048 the large ones
+// only where every CU gets a tile: launches that follow one another in a step find cold operands, and a CU without a
+// tile has nothing to hide that behind (1576 x 768 -> 3072 with GELU, 216 tiles of 192 rows, in a step: 24.0 us, 22.3
+// with 128 x 128 tiles; launched alone 21.8 and 20.8).
 int nat_shape(int M, int N, int K) {
   const int force = g_cnnk_tune[15];
   if (force >= 16) return force - 16 < T_SMALL ? force - 16 : -1;
-  const int n128 = ceil_div(N, 128), t192 = ceil_div(M, 192) * n128, t256 = ceil_div(M, 256) * n128;
-  const bool wide = force == 2 || (force != 1 && K >= 2048);
-  const float us192 = tile_time(t192, 2, ceil_div(K, 32), 1, 7.8f, 0.47f);
-  const float us256 = tile_time(t256, 2, ceil_div(K, 32), 1, 11.8f, 0.38f);
-  const float us = wide ? tile_time(t192, 2, ceil_div(K, 64), 1, 1.2f, 0.85f) : us192 < us256 ? us192 : us256;
-  if (force == 0) {
-    const int small = pick_small(M, N, K, false, us);
-    if (small >= 0) return small;
+  int first = T64, last = L192_WIDE;
+  if (force == 1) { first = L256; last = L192; }
+  if (force == 2) first = L192_WIDE;
+  int best = first;
+  float best_us = 1e30f;
+  for (int c = first; c <= last; ++c) {
+    if (force == 0 && c >= T_SMALL && K < 2048 && ceil_div(M, kTiles[c].rows) * ceil_div(N, 128) < 256) continue;
+    const float us = tile_time(kTiles[c], M, N, K);
+    if (us < best_us) { best_us = us; best = c; }
   }
-  return wide ? L192_WIDE : us192 < us256 ? L192 : L256;
+  return best;
 }
 template <bool BTR, int EPI>
 int launch_nat(Args& a, hipStream_t st) {
@@ -466,8 +477,7 @@ int gemm_bf16_dgrad(long long rows, int K, int N, const bf16_t* dy, const bf16_t
 
 int gemm_bf16_dgrad_gelu_parts(long long rows, int K, int N) {
   const int shape = nat_shape((int)rows, K, N);
-  const int bm = shape < 0 ? 64 : shape < T_SMALL ? kTiles[shape].rows : shape == L256 ? 256 : 192;
-  return 2 * ceil_div((int)rows, bm);
+  return 2 * ceil_div((int)rows, shape < 0 ? 64 : kTiles[shape].rows);
 }
 
 int gemm_bf16_dgrad_gelu(long long rows, int K, int N, const bf16_t* dy, const bf16_t* w, const bf16_t* u, bf16_t* dg, bf16_t* du,
@@ -498,9 +508,9 @@ int gemm_bf16_wgrad(long long rows, int K, int N, const bf16_t* x, const bf16_t*
   a.a_bytes = (unsigned)(rows * N * 2); a.b_bytes = (unsigned)(rows * K * 2);
   const int force = g_cnnk_tune[15];
   if (force == 0 || force >= 16) {
-    // the split launch and its sum, in the units of kTiles
+    // the split launch and its sum, in the units of kWgrad
     const float us = 12.f + 0.6f * stages + 0.2f * splits;
-    const int small = force >= 16 ? force - 16 : pick_small(N, K, (int)rows, true, us);
+    const int small = force >= 16 ? force - 16 : pick_wgrad(N, K, (int)rows, us);
     if (small >= 0 && small != T128) {
       a.part = dw;
       a.k_per_split = (int)rows;
