@@ -617,7 +617,7 @@ def test_grouped_weight_and_bias_gradients_keep_their_chains_of_sums_short(batch
         d, x = run.tensor(dy, 0).view(rows, -1).double(), run.tensor(x, 0).view(rows, -1).double()
         want = d.T @ x
         assert ((grad[w + ".0"].double() - want).norm() / want.norm()).item() <= wgrad_bound(rows), w
-        if b:           # a compensated sum: the rounding of eight terms at a time and of the result
+        if b:           # a compensated sum: the roundings of sixteen terms at a time and of the result
             want = d.sum(0)
             assert ((grad[b + ".0"].double() - want).norm() / want.norm()).item() <= 2.0 ** -23, b
 
