@@ -75,7 +75,8 @@ const char* cnnk_version(void);
  * keys 0, 1, 2 and 14 keep layers off them, too); 13 = pixel tiles that one workgroup of
  * the 3x3 stride-1 LDS-patch kernels walks (0: as many as still leave two workgroups per CU; -1: one, and no
  * split of the reduction over two groups of wavefronts on grids of fewer than 512 workgroups); 17 = layers whose
- * weight gradients cnnk_train_step forks onto its second stream together (1: one by one; at most 16).
+ * weight gradients cnnk_train_step forks onto its second stream together (1: one by one; at most 16); 18 = workgroups on
+ * an XCD of the kernels whose workgroups walk several tiles (0: as many as the device holds; -1: one to a tile).
  * Process-wide, not thread-safe. */
 int cnnk_tune(int key, int value);
 

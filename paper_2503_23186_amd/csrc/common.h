@@ -90,6 +90,20 @@ __device__ __forceinline__ void store8(float* p, const float* f) {
   *reinterpret_cast<float4*>(p + 4) = make_float4(f[4], f[5], f[6], f[7]);
 }
 
+// eight bf16 plus eight bf16, rounded again
+__device__ __forceinline__ uint4 add_bf16x8(uint4 a, uint4 b) {
+  float x[8], y[8];
+  unpack8(a, x);
+  unpack8(b, y);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x[e] += y[e];
+  return uint4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
+}
+// v of the lane N before this one in its sixteen, around the end (an operand modifier, no pass through LDS)
+template <int N> __device__ __forceinline__ float row_rotated(float v) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x120 + N, 0xf, 0xf, true));
+}
+
 // Sum over the 64 lanes of a wavefront (result valid in every lane).
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -100,6 +114,13 @@ __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
+}
+
+// n / d of wavefront-uniform 0 <= n < 2^20, d >= 1, without the compiler's integer division (about 150 clocks in front of a
+// kernel's first load).  Exact: (n + 1/2) / d is at least 1 / (2 d) from a whole number, which the two roundings (below
+// 2^-22 of the quotient) do not reach; with d = 1 exact up to 2^23.
+__device__ __forceinline__ int uniform_div(int n, int d) {
+  return __builtin_amdgcn_readfirstlane((int)(((float)n + 0.5f) * __builtin_amdgcn_rcpf((float)d)));
 }
 
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }

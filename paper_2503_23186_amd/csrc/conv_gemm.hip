@@ -59,8 +59,8 @@ template <class C> struct ConvLoader {
     b_rs = make_desc(args.wt, args.wt_bytes);
     const int t0 = args.tt.begin[cls], t1 = args.tt.begin[cls + 1];
     nchunk = args.Cs / C::BK;
-    tap = t0 + stage0 / nchunk;
-    chunk = stage0 % nchunk;
+    tap = t0 + uniform_div(stage0, nchunk);
+    chunk = stage0 - (tap - t0) * nchunk;
     tap_end = t1;
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
@@ -104,77 +104,40 @@ template <class C> struct ConvLoader {
   }
 };
 
+// Writes one tile out: rows m0 .., columns n0 .. of class cls.  S: LDS of the epilogue (the strips, then the sums), free
+// to use; called by every wavefront that holds accumulators (group 0).
 template <class C, int EP>
-__global__ void __launch_bounds__(C::THREADS, C::WPE) conv_gemm_kernel(ConvGemmArgs a) {
-  constexpr int TM = C::TM, TN = C::TN, KG = C::KG;
-  extern __shared__ __align__(16) unsigned char smem[];   // stage buffers, nothing else
-  const int lane = threadIdx.x & 63;
-  const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
-  const int tid = threadIdx.x & 255;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+__device__ __forceinline__ void conv_gemm_epilogue(const ConvGemmArgs& a, int cls, int M, int mt, int nt, f32x16_t (&acc)[C::TM][C::TN], int tid,
+                                                   unsigned char* smem) {
+  constexpr int TM = C::TM, TN = C::TN;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / C::WN, wn = wave % C::WN, g = lane >> 4, i16 = lane & 15;
-  // an XCD (every 8th workgroup) owns a contiguous range of the tile list, channel tiles of a pixel tile side by
-  // side: they read the same pixels, which its L2 then holds
-  const int cls = blockIdx.z;
-  const int M = a.Nimg * a.tt.Hm[cls] * a.tt.Wm[cls];
-  const int tiles = ((M + C::BM - 1) / C::BM) * a.ntiles, chunk = (tiles + 7) >> 3;
-  const int tile = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= chunk || tile >= tiles) return;
-  const int mt = tile / a.ntiles, nt = tile - mt * a.ntiles;
   const int m0 = mt * C::BM, n0 = nt * C::BN;
-  const int total = (a.tt.begin[cls + 1] - a.tt.begin[cls]) * (a.Cs / C::BK);
-  // An output parity that no tap reaches: nothing to add, or zeros.  Three of four of a 1x1 stride-2 layer, bound by the
-  // stores; through the epilogue below / from here, us: 64 images 56 x 56, 64 <- 128 channels 11.2 / 9.6, 32 of 56 x 56,
-  // 256 <- 512 21.8 / 19.6.
-  if (total == 0) {
-    if (a.accumulate) return;
-    const __amdgpu_buffer_rsrc_t z_rs = make_rsrc(a.dst, a.dst_bytes);
-    for (int k = threadIdx.x; k < C::BM * (C::BN / 8); k += C::THREADS) {
-      const int m = m0 + k / (C::BN / 8), col = n0 + k % (C::BN / 8) * 8;
-      int q, jj, n, ii;
-      a.tt.dW[cls].divmod(m < M ? m : 0, &q, &jj);
-      a.tt.dH[cls].divmod(q, &n, &ii);
-      const int at = (n * a.Hd + ii * a.os + a.tt.oh[cls]) * a.Wd + jj * a.os + a.tt.ow[cls];
-      buffer_store16(z_rs, make_uint4(0u, 0u, 0u, 0u), m < M && col < a.Cd ? (unsigned)(at * a.Cd + col) * 2u : kOobOffset);
-    }
-    return;
-  }
-  const int nst = (total + KG - 1) / KG;       // per group; the last one's stages past the end load zeros
-  ConvLoader<C> ld;
-  ld.init(a, cls, M, m0, n0, kg * nst, wave, lane);
-  f32x16_t acc[TM][TN];
-  float rs[TM];
-  tile_main_loop<C, false, false>(ld, nst, kg, wave, lane, smem, acc, false, rs);
-  tile_join_groups<C>(acc, kg, tid, smem);
-
   if constexpr (EP == STATS) {
     // column sums and sums of squares of the fp32 accumulators over the tile's rows (rows past M are zeros):
     // per wavefront, then the wavefronts that share the columns in order, one partial per pixel tile
-    float* red = reinterpret_cast<float*>(smem + C::HAND_B + C::NW * 32 * SP);     // [2][WM][BN]
-    static_assert(C::HAND_B + C::NW * 32 * SP + 2 * C::WM * C::BN * 4 <= C::SMEM, "LDS");
-    if (kg == 0) {
+    float* red = reinterpret_cast<float*>(smem + C::NW * 32 * SP);     // [2][WM][BN]
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        float s1 = 0.f, s2 = 0.f;
+    for (int j = 0; j < TN; ++j) {
+      float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float v = acc[i][j][r];
-            s1 += v;
-            s2 = fmaf(v, v, s2);
-          }
-        s1 += __shfl_xor(s1, 32, 64);
-        s2 += __shfl_xor(s2, 32, 64);
-        if (lane < 32) {
-          const int c = wn * TN * 32 + j * 32 + lane;
-          red[wm * C::BN + c] = s1;
-          red[(C::WM + wm) * C::BN + c] = s2;
+        for (int r = 0; r < 16; ++r) {
+          const float v = acc[i][j][r];
+          s1 += v;
+          s2 = fmaf(v, v, s2);
         }
+      s1 += __shfl_xor(s1, 32, 64);
+      s2 += __shfl_xor(s2, 32, 64);
+      if (lane < 32) {
+        const int c = wn * TN * 32 + j * 32 + lane;
+        red[wm * C::BN + c] = s1;
+        red[(C::WM + wm) * C::BN + c] = s2;
       }
     }
-    __syncthreads();
-    if (kg == 0 && tid < 2 * C::BN) {
+    workgroup_barrier();
+    if (tid < 2 * C::BN) {
       const int v = tid / C::BN, c = tid % C::BN;
       float t = red[v * C::WM * C::BN + c];
 #pragma unroll
@@ -182,9 +145,7 @@ __global__ void __launch_bounds__(C::THREADS, C::WPE) conv_gemm_kernel(ConvGemmA
       if (n0 + c < a.Cd) a.stats[((size_t)v * a.Cd + n0 + c) * a.mtiles + mt] = t;
     }
   }
-  if (kg > 0) return;
-
-  unsigned char* S = smem + C::HAND_B + wave * (32 * SP);
+  unsigned char* S = smem + wave * (32 * SP);
   const __amdgpu_buffer_rsrc_t d_rs = make_rsrc(a.dst, a.dst_bytes);
   const bool add = EP == TAIL ? a.tail.res != nullptr : a.accumulate != 0;
   const __amdgpu_buffer_rsrc_t r_rs = make_rsrc(EP == TAIL ? a.tail.res : a.dst, a.dst_bytes);
@@ -247,6 +208,66 @@ __global__ void __launch_bounds__(C::THREADS, C::WPE) conv_gemm_kernel(ConvGemmA
   }
 }
 
+template <class C, int EP>
+__global__ void __launch_bounds__(C::THREADS, C::WPE) conv_gemm_kernel(ConvGemmArgs a) {
+  constexpr int TM = C::TM, TN = C::TN, KG = C::KG;
+  extern __shared__ __align__(16) unsigned char smem[];   // stage buffers, nothing else
+  const int lane = threadIdx.x & 63;
+  const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+  const int tid = threadIdx.x & 255;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // an XCD (every 8th workgroup) owns a contiguous range of the tile list, channel tiles of a pixel tile side by
+  // side: they read the same pixels, which its L2 then holds.  Its workgroups take every step-th tile of the range.
+  const int cls = blockIdx.z;
+  const int M = a.Nimg * a.tt.Hm[cls] * a.tt.Wm[cls];
+  const int tiles = ((M + C::BM - 1) / C::BM) * a.ntiles, chunk = (tiles + 7) >> 3, step = (int)gridDim.x >> 3;
+  const int first = (blockIdx.x & 7) * chunk, l = blockIdx.x >> 3, mine = min(chunk, tiles - first);
+  if (l >= mine) return;
+  const int total = (a.tt.begin[cls + 1] - a.tt.begin[cls]) * (a.Cs / C::BK);
+  // An output parity that no tap reaches: nothing to add, or zeros.  Three of four of a 1x1 stride-2 layer, bound by the
+  // stores; through the epilogue below / from here, us: 64 images 56 x 56, 64 <- 128 channels 11.2 / 9.6, 32 of 56 x 56,
+  // 256 <- 512 21.8 / 19.6.
+  if (total == 0) {
+    if (a.accumulate) return;
+    const __amdgpu_buffer_rsrc_t z_rs = make_rsrc(a.dst, a.dst_bytes);
+    for (int tile = first + l; tile < first + mine; tile += step) {
+      const int mt = tile / a.ntiles, m0 = mt * C::BM, n0 = (tile - mt * a.ntiles) * C::BN;
+      for (int k = threadIdx.x; k < C::BM * (C::BN / 8); k += C::THREADS) {
+        const int m = m0 + k / (C::BN / 8), col = n0 + k % (C::BN / 8) * 8;
+        int q, jj, n, ii;
+        a.tt.dW[cls].divmod(m < M ? m : 0, &q, &jj);
+        a.tt.dH[cls].divmod(q, &n, &ii);
+        const int at = (n * a.Hd + ii * a.os + a.tt.oh[cls]) * a.Wd + jj * a.os + a.tt.ow[cls];
+        buffer_store16(z_rs, make_uint4(0u, 0u, 0u, 0u), m < M && col < a.Cd ? (unsigned)(at * a.Cd + col) * 2u : kOobOffset);
+      }
+    }
+    return;
+  }
+  ConvLoader<C> ld;
+  if constexpr (KG > 1) {
+    // one tile to a workgroup (the grid has one for each), its stages split over the groups; the last group's stages
+    // past the end load zeros
+    const int tile = first + l, mt = uniform_div(tile, a.ntiles), nt = tile - mt * a.ntiles, nst = (total + KG - 1) / KG;
+    ld.init(a, cls, M, mt * C::BM, nt * C::BN, kg * nst, wave, lane);
+    tile_stream<C, 0, false, false>(ld, 1, nst, kg, wave, lane, smem, false, 0, [](int) {}, [](int) {},
+                                    [&](int, f32x16_t (&acc)[TM][TN], float (&)[TM], unsigned char*) __attribute__((always_inline)) {
+      tile_join_groups<C>(acc, kg, tid, smem);
+      if (kg == 0) conv_gemm_epilogue<C, EP>(a, cls, M, mt, nt, acc, tid, smem + C::HAND_B);
+      else if (EP == STATS) workgroup_barrier();        // the epilogue's barrier is the workgroup's
+    });
+  } else {
+    auto next = [&](int k) __attribute__((always_inline)) {
+      const int tile = first + l + k * step, mt = uniform_div(tile, a.ntiles), nt = tile - mt * a.ntiles;
+      ld.init(a, cls, M, mt * C::BM, nt * C::BN, 0, wave, lane);
+    };
+    tile_stream<C, TM * TN * 2, false, false>(ld, (mine - l + step - 1) / step, total, 0, wave, lane, smem, false, 0, next, [](int) {},
+                                [&](int k, f32x16_t (&acc)[TM][TN], float (&)[TM], unsigned char* strip) __attribute__((always_inline)) {
+                                  const int tile = first + l + k * step, mt = uniform_div(tile, a.ntiles);
+                                  conv_gemm_epilogue<C, EP>(a, cls, M, mt, tile - mt * a.ntiles, acc, tid, strip);
+                                });
+  }
+}
+
 // ---- host side -------------------------------------------------------------------------------------------
 template <class C, int EP>
 int launch(ConvGemmArgs& a, long maxM, hipStream_t st) {
@@ -259,14 +280,16 @@ int launch(ConvGemmArgs& a, long maxM, hipStream_t st) {
   }
   a.mtiles = (int)((maxM + C::BM - 1) / C::BM);
   a.ntiles = (a.Cd + C::BN - 1) / C::BN;
-  const int tiles = a.mtiles * a.ntiles;
-  hipLaunchKernelGGL(kern, dim3(8 * ((tiles + 7) / 8), 1, a.tt.nclass), dim3(C::THREADS), C::SMEM, st, a);
+  // as many workgroups as the device holds at a time, each walking several tiles where there are more (tuning key 18)
+  const int per_xcd = (a.mtiles * a.ntiles + 7) / 8, most = C::KG > 1 || g_cnnk_tune[18] < 0 ? per_xcd : g_cnnk_tune[18] > 0 ? g_cnnk_tune[18] : 32 * C::RESIDENT;
+  hipLaunchKernelGGL(kern, dim3(8 * (per_xcd < most ? per_xcd : most), 1, a.tt.nclass), dim3(C::THREADS), C::SMEM, st, a);
   return launch_status();
 }
 
-// Tile shapes and the time (us) of a launch, fitted to a sweep over 1x1 and strided 3x3 layers of 16 to 2048
-// channels on 4 x 4 to 32 x 32 images at batch 24 to 256, forward and data gradient (mean loss against the fastest
-// shape 2 %, largest 25 %):
+// Tile shapes and the time (us) of a launch, fitted to a sweep over 1x1 and strided 3x3 layers of 64 to 2048
+// channels on 4 x 4 to 32 x 32 images at batch 16 to 256, forward and data gradient, on operands that the L2s do not
+// hold (mean loss against the fastest shape 0.7 %, largest 22 %; with the constants fitted before the tiles were
+// streamed 2.9 %: 256 -> 256 3x3 strided at 16 x 16, batch 200, 37 -> 30 us, 1024 -> 2048 strided data gradient 30 -> 25):
 //   one workgroup per CU at a time (two groups of wavefronts):  fixed + rounds * (tile + stages per group * stage)
 //   several:  fixed + tile * tiles / 256 + max(tiles per CU * stages * stage, rounds of resident ones * stages * alone)
 // `stage` is the time of a stage while other workgroups keep the CU busy, `alone` its latency; a stage is 64 channels
@@ -274,10 +297,10 @@ int launch(ConvGemmArgs& a, long maxM, hipStream_t st) {
 // pixels, 256 rows where memory bounds (fewest weight reads per pixel).
 struct Shape { int bm, bn, kgroups, resident; float fixed, tile, stage, alone; };
 constexpr int kShapes = 8;
-constexpr Shape kShape[kShapes] = {{64, 64, 1, 3, 3.8f, 0.73f, 0.09f, 0.47f},  {64, 64, 2, 1, 2.7f, 2.45f, 0.53f, 0.f},
-                                   {64, 128, 1, 2, 4.1f, 1.12f, 0.32f, 0.51f}, {64, 128, 2, 1, 2.5f, 3.15f, 0.71f, 0.f},
-                                   {128, 128, 1, 2, 5.3f, 1.30f, 0.60f, 0.48f}, {128, 64, 1, 2, 4.2f, 1.30f, 0.35f, 0.56f},
-                                   {256, 64, 1, 2, 5.5f, 2.00f, 0.60f, 0.79f}, {256, 128, 1, 2, 6.5f, 1.90f, 1.24f, 1.20f}};
+constexpr Shape kShape[kShapes] = {{64, 64, 1, 3, 2.99f, 0.664f, 0.09f, 0.517f}, {64, 64, 2, 1, 2.21f, 2.45f, 0.53f, 0.f},
+                                   {64, 128, 1, 2, 3.79f, 1.12f, 0.32f, 0.439f}, {64, 128, 2, 1, 2.46f, 2.73f, 0.691f, 0.f},
+                                   {128, 128, 1, 2, 5.3f, 1.30f, 0.60f, 0.71f}, {128, 64, 1, 2, 4.2f, 0.962f, 0.35f, 0.56f},
+                                   {256, 64, 1, 2, 5.5f, 2.00f, 0.60f, 1.13f}, {256, 128, 1, 2, 6.5f, 1.90f, 1.18f, 1.30f}};
 inline long ceil_div(long a, long b) { return (a + b - 1) / b; }
 
 template <bool BTR, int EP>

@@ -90,25 +90,25 @@ __global__ void __launch_bounds__(C::THREADS, C::WPE) wgrad_gemm_kernel(WgArgs a
   // same pixels, which its L2 then holds
   const int per = (a.items + 7) >> 3, l = blockIdx.x >> 3, item = (blockIdx.x & 7) * per + l;
   if (l >= per || item >= a.items) return;
-  const int z = item / a.tiles, tile = item - z * a.tiles, mt = tile / a.ntiles, nt = tile - mt * a.ntiles;
+  const int z = uniform_div(item, a.tiles), tile = item - z * a.tiles, mt = uniform_div(tile, a.ntiles), nt = tile - mt * a.ntiles;
   const int k0 = mt * C::BM, q0 = nt * C::BN, m_begin = z * a.chunk, m_end = min(m_begin + a.chunk, a.M);
   WgLoader<C, LIN> ld;
   ld.init(a, k0, q0, m_begin, m_end, wave, lane);
-  f32x16_t acc[TM][TN];
-  float rs[TM];
-  tile_main_loop<C, false, false>(ld, (m_end - m_begin + C::BK - 1) / C::BK, 0, wave, lane, smem, acc, false, rs);
-  float* out = a.part + (size_t)z * a.Cout * a.Q;
+  tile_stream<C, 0, false, false>(ld, 1, (m_end - m_begin + C::BK - 1) / C::BK, 0, wave, lane, smem, false, 0, [](int) {}, [](int) {},
+                                  [&](int, f32x16_t (&acc)[TM][TN], float (&)[TM], unsigned char*) __attribute__((always_inline)) {
+    float* out = a.part + (size_t)z * a.Cout * a.Q;
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int col = q0 + wn * (TN * 32) + j * 32 + (lane & 31);
+      for (int j = 0; j < TN; ++j) {
+        const int col = q0 + wn * (TN * 32) + j * 32 + (lane & 31);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = k0 + wm * (TM * 32) + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
-        if (row < a.Cout && col < a.Q) out[(size_t)row * a.Q + col] = acc[i][j][r];
+        for (int r = 0; r < 16; ++r) {
+          const int row = k0 + wm * (TM * 32) + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+          if (row < a.Cout && col < a.Q) out[(size_t)row * a.Q + col] = acc[i][j][r];
+        }
       }
-    }
+  });
 }
 
 struct Plan { int bm, bn, chunk, splits; };

@@ -85,17 +85,115 @@ template <class C> struct DenseLoader {
   }
 };
 
-// v of the lane N before this one in its sixteen, around the end (an operand modifier, no pass through LDS)
-template <int N> __device__ __forceinline__ float row_rotated(float v) {
-  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x120 + N, 0xf, 0xf, true));
-}
-
 // Rows between two folds of a weight gradient's accumulators, near 3.4 sqrt(rows), where the errors of the two chains
 // balance (a chain's grows with the root of its steps; 1568 rows 8.7e-8 with 128 and 9.3e-8 with 256, 12608 rows the
 // same with 256 and 512, 27648 rows 2.0e-7 and 1.75e-7).
 __host__ __device__ __forceinline__ int fold_rows(int rows) { return rows <= 2048 ? 128 : rows <= 10240 ? 256 : 512; }
 
-// One workgroup's tile (mt, nt) over the reduction range of split z.
+// Writes a tile out.  prefetch() fetches what its first rows need besides the accumulators.
+template <class C, int EPI> struct GemmEpilogue {
+  static constexpr int TM = C::TM, TN = C::TN;
+  static constexpr int STORES = TM * TN * 2 * (EPI == 1 || EPI == 4 ? 2 : 1);
+  uint4 rv[2][TN][2];
+  float bv[TN];
+  // Loads and stores are buffer operations: a position outside the output reads zeros and
+  // stores nothing, without a branch, so the number in flight is known and a wait is for what it needs.
+  static __device__ __forceinline__ unsigned place(const Args& a, int m0, int n0, int i, int j, int rb, int lane, int wave) {
+    const int wm = wave / C::WN, wn = wave % C::WN, g = lane >> 4, i16 = lane & 15;
+    const int row = m0 + wm * (TM * 32) + i * 32 + rb * 16 + i16, col = n0 + wn * (TN * 32) + j * 32 + g * 8;
+    return row < a.M && col < a.N ? (unsigned)(row * a.ldc + col) * 2u : kOobOffset;
+  }
+  // the residual (or gelu's argument) of a 32-row block is fetched while the block before it is worked on
+  __device__ __forceinline__ void fetch(const Args& a, int m0, int n0, int i, int lane, int wave) {
+    const __amdgpu_buffer_rsrc_t r_rs = make_rsrc(a.res, a.c_bytes);
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) rv[i & 1][j][rb] = buffer_load16(r_rs, place(a, m0, n0, i, j, rb, lane, wave), 0);
+  }
+  __device__ __forceinline__ void prefetch(const Args& a, int mt, int nt, int lane, int wave) {
+    const int m0 = mt * C::BM, n0 = nt * C::BN, wn = wave % C::WN;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int colv = n0 + wn * (TN * 32) + j * 32 + (lane & 31);
+      bv[j] = (a.bias && colv < a.N) ? a.bias[colv] : 0.f;
+    }
+    if (EPI == 3 || EPI == 4) fetch(a, m0, n0, 0, lane, wave);
+  }
+  // S0: LDS for a strip per wavefront
+  __device__ __forceinline__ void write(const Args& a, int mt, int nt, f32x16_t (&acc)[TM][TN], int lane, int wave, unsigned char* S0) {
+    const int wm = wave / C::WN, wn = wave % C::WN, g = lane >> 4, i16 = lane & 15;
+    const int m0 = mt * C::BM, n0 = nt * C::BN;
+    unsigned char* S = S0 + wave * (32 * SP);
+    const __amdgpu_buffer_rsrc_t c_rs = make_rsrc(a.C, a.c_bytes);
+    const __amdgpu_buffer_rsrc_t c2_rs = EPI == 1 || EPI == 4 ? make_rsrc(a.C2, a.c_bytes) : c_rs;
+    float cs[TN][8];      // EPI 4: this lane's rows' share of the column sums
+    if (EPI == 4) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) cs[j][e] = 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if ((EPI == 3 || EPI == 4) && i + 1 < TM) fetch(a, m0, n0, i + 1, lane, wave);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        float v[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = acc[i][j][r] + bv[j];
+        uint4 o[2];
+        strip_transpose(S, lane, v, o);
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) {
+          if (EPI == 3) o[rb] = add_bf16x8(o[rb], rv[i & 1][j][rb]);     // + residual: the sum of two stored values, rounded again
+          buffer_store16(c_rs, o[rb], place(a, m0, n0, i, j, rb, lane, wave));
+          if (EPI == 4) {     // the gradient of the activation's argument, from the gradient as stored
+            float x[8], r[8];
+            unpack8(o[rb], x);
+            unpack8(rv[i & 1][j][rb], r);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              x[e] *= gelu_grad_f(r[e]);
+              cs[j][e] += x[e];            // a row past the end adds zero
+            }
+            buffer_store16(c2_rs, uint4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])}, place(a, m0, n0, i, j, rb, lane, wave));
+          }
+        }
+        if (EPI == 1) {
+          // the activation of the value as stored
+#pragma unroll
+          for (int r = 0; r < 16; ++r) v[r] = gelu_f(bf16_to_f32(f32_to_bf16_hw(v[r])));
+          strip_transpose(S, lane, v, o);
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb) buffer_store16(c2_rs, o[rb], place(a, m0, n0, i, j, rb, lane, wave));
+        }
+      }
+    }
+    if (EPI == 4) {
+      // the bias gradient of the layer below sums the products before they are rounded: one partial row per row of
+      // wavefronts, its sixteen lanes of a column added first
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          cs[j][e] += row_rotated<8>(cs[j][e]);
+          cs[j][e] += row_rotated<4>(cs[j][e]);
+          cs[j][e] += row_rotated<2>(cs[j][e]);
+          cs[j][e] += row_rotated<1>(cs[j][e]);
+        }
+        const int col = n0 + wn * (TN * 32) + j * 32 + g * 8;
+        if (i16 == 0 && col < a.N) {
+          float* q = a.part + (size_t)(mt * C::WM + wm) * a.N + col;
+          *reinterpret_cast<float4*>(q) = make_float4(cs[j][0], cs[j][1], cs[j][2], cs[j][3]);
+          *reinterpret_cast<float4*>(q + 4) = make_float4(cs[j][4], cs[j][5], cs[j][6], cs[j][7]);
+        }
+      }
+    }
+  }
+};
+
+// One workgroup's tile (mt, nt) over the reduction range of split z: a weight gradient, or two groups of wavefronts.
 template <class C, int EPI>
 __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) {
   constexpr int TM = C::TM, TN = C::TN, BK = C::BK, KG = C::KG;
@@ -104,7 +202,7 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
   const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);   // reduction group
   const int tid = threadIdx.x & 255;                                                     // within the group
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / C::WN, wn = wave % C::WN, h = lane >> 5, g = lane >> 4, i16 = lane & 15;
+  const int wm = wave / C::WN, wn = wave % C::WN, h = lane >> 5;
   const int m0 = mt * C::BM, n0 = nt * C::BN;
   int kbeg = z * a.k_per_split;
   int kend = kbeg + a.k_per_split;
@@ -122,140 +220,103 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
   constexpr bool ROWS = EPI == 2 && KG == 1;
   const bool row_sums = ROWS && a.rsum != nullptr && nt == 0 && wn == 0;
   constexpr bool FOLD = EPI == 2 && TM * TN <= 6;
-  f32x16_t acc[TM][TN];
-  float rs[TM];
-  tile_main_loop<C, ROWS, FOLD>(ld, nst, kg, wave, lane, smem, acc, row_sums, rs, a.fold);
-  if (EPI != 2 || KG > 1) tile_join_groups<C>(acc, kg, tid, smem);
-  if (kg > 0) return;
-  if (EPI == 2) {
-    float* out = a.part + (size_t)z * a.zstride;
-    if (row_sums) {
+  tile_stream<C, 0, ROWS, FOLD>(ld, 1, nst, kg, wave, lane, smem, row_sums, a.fold, [](int) {}, [](int) {},
+                                [&](int, f32x16_t (&acc)[TM][TN], float (&rs)[TM], unsigned char*) __attribute__((always_inline)) {
+    if (KG > 1) tile_join_groups<C>(acc, kg, tid, smem);
+    if (kg > 0) return;
+    if constexpr (EPI == 2) {
+      float* out = a.part + (size_t)z * a.zstride;
+      if (row_sums) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const float t = rs[i] + __shfl_xor(rs[i], 32, 64);     // the two halves of every reduction step
-        const int row = m0 + wm * (TM * 32) + i * 32 + lane;
-        if (lane < 32 && row < a.M) a.rsum[(size_t)z * a.zstride + row] = t;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = n0 + wn * (TN * 32) + j * 32 + (lane & 31);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = m0 + wm * (TM * 32) + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
-          if (row < a.M && col < a.N) out[(size_t)row * a.ldc + col] = acc[i][j][r];
+        for (int i = 0; i < TM; ++i) {
+          const float t = rs[i] + __shfl_xor(rs[i], 32, 64);     // the two halves of every reduction step
+          const int row = m0 + wm * (TM * 32) + i * 32 + lane;
+          if (lane < 32 && row < a.M) a.rsum[(size_t)z * a.zstride + row] = t;
         }
       }
-    return;
-  }
-  unsigned char* S = smem + C::HAND_B + wave * (32 * SP);   // behind the accumulators just taken over
-  // Loads and stores of the epilogue are buffer operations: a position outside the output reads zeros and
-  // stores nothing, without a branch, so the number in flight is known and a wait is for what it needs.
-  const __amdgpu_buffer_rsrc_t c_rs = make_rsrc(a.C, a.c_bytes);
-  const __amdgpu_buffer_rsrc_t c2_rs = EPI == 1 || EPI == 4 ? make_rsrc(a.C2, a.c_bytes) : c_rs;
-  const __amdgpu_buffer_rsrc_t r_rs = EPI == 3 || EPI == 4 ? make_rsrc(a.res, a.c_bytes) : c_rs;
-  auto place = [&](int i, int j, int rb) __attribute__((always_inline)) -> unsigned {
-    const int row = m0 + wm * (TM * 32) + i * 32 + rb * 16 + i16, col = n0 + wn * (TN * 32) + j * 32 + g * 8;
-    return row < a.M && col < a.N ? (unsigned)(row * a.ldc + col) * 2u : kOobOffset;
-  };
-  // the residual (or gelu's argument) of a 32-row block is fetched while the block before it is worked on
-  uint4 rv[2][TN][2];
-  auto fetch = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb) rv[i & 1][j][rb] = buffer_load16(r_rs, place(i, j, rb), 0);
-  };
-  if (EPI == 3 || EPI == 4) fetch(0);
-  float cs[TN][8];      // EPI 4: this lane's rows' share of the column sums
-  if (EPI == 4) {
+        for (int j = 0; j < TN; ++j) {
+          const int col = n0 + wn * (TN * 32) + j * 32 + (lane & 31);
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) cs[j][e] = 0.f;
-  }
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    if ((EPI == 3 || EPI == 4) && i + 1 < TM) fetch(i + 1);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int colv = n0 + wn * (TN * 32) + j * 32 + (lane & 31);
-      const float bv = (a.bias && colv < a.N) ? a.bias[colv] : 0.f;
-      float v[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) v[r] = acc[i][j][r] + bv;
-      uint4 o[2];
-      strip_transpose(S, lane, v, o);
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb) {
-        if (EPI == 3) o[rb] = add_bf16x8(o[rb], rv[i & 1][j][rb]);     // + residual: the sum of two stored values, rounded again
-        buffer_store16(c_rs, o[rb], place(i, j, rb));
-        if (EPI == 4) {     // the gradient of the activation's argument, from the gradient as stored
-          float x[8], r[8];
-          unpack8(o[rb], x);
-          unpack8(rv[i & 1][j][rb], r);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            x[e] *= gelu_grad_f(r[e]);
-            cs[j][e] += x[e];            // a row past the end adds zero
+          for (int r = 0; r < 16; ++r) {
+            const int row = m0 + wm * (TM * 32) + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+            if (row < a.M && col < a.N) out[(size_t)row * a.ldc + col] = acc[i][j][r];
           }
-          buffer_store16(c2_rs, uint4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])}, place(i, j, rb));
         }
-      }
-      if (EPI == 1) {
-        // the activation of the value as stored
-#pragma unroll
-        for (int r = 0; r < 16; ++r) v[r] = gelu_f(bf16_to_f32(f32_to_bf16_hw(v[r])));
-        strip_transpose(S, lane, v, o);
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb) buffer_store16(c2_rs, o[rb], place(i, j, rb));
-      }
+    } else {
+      GemmEpilogue<C, EPI> ep;
+      ep.prefetch(a, mt, nt, lane, wave);
+      ep.write(a, mt, nt, acc, lane, wave, smem + C::HAND_B);      // behind the accumulators just taken over
+    }
+  });
+}
+
+// Tile number l of the XCD that this workgroup runs on (workgroups that share its L2 are every 8th), false past the last.
+// An XCD owns a contiguous range of the row-major tile list, i.e. a band of tile rows, and walks it column by
+// column: the workgroups in flight on it then share the band's rows of A, which stay in its L2,
+// while B streams through once per XCD.
+__device__ __forceinline__ bool band_tile(const Args& a, int l, int* mt_out, int* nt_out) {
+  const int ntot = a.mtiles * a.ntiles, chunk = (ntot + 7) >> 3;
+  const int c0 = (blockIdx.x & 7) * chunk, c1 = min(c0 + chunk, ntot);
+  if (c0 + l >= c1) return false;
+  const int r0 = uniform_div(c0, a.ntiles), s0 = c0 - r0 * a.ntiles, r1 = uniform_div(c1 - 1, a.ntiles), e1 = (c1 - 1) - r1 * a.ntiles + 1;
+  if (r0 == r1) {
+    *mt_out = r0;
+    *nt_out = s0 + l;
+    return true;
+  }
+  // Column nt has the whole rows between, the band's first row from column s0 on, its last row up to column e1: three
+  // ranges of columns of equal height.  (Counted column by column, 48 columns took 1 us.)
+  const int whole = r1 - r0 - 1, lo = min(s0, e1), hi = max(s0, e1);
+  int h = whole + 1, first = 0, col = 0;                  // columns below lo: no first row, but the last
+  if (l >= lo * h) {
+    l -= lo * h;
+    col = lo;
+    h = whole + (s0 < e1 ? 2 : 0);
+    first = s0 < e1 ? 1 : 0;
+    if (l >= (hi - lo) * h) {
+      l -= (hi - lo) * h;
+      col = hi;
+      h = whole + 1;
+      first = 1;
     }
   }
-  if (EPI == 4) {
-    // the bias gradient of the layer below sums the products before they are rounded: one partial row per row of
-    // wavefronts, its sixteen lanes of a column added first
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        cs[j][e] += row_rotated<8>(cs[j][e]);
-        cs[j][e] += row_rotated<4>(cs[j][e]);
-        cs[j][e] += row_rotated<2>(cs[j][e]);
-        cs[j][e] += row_rotated<1>(cs[j][e]);
-      }
-      const int col = n0 + wn * (TN * 32) + j * 32 + g * 8;
-      if (i16 == 0 && col < a.N) {
-        float* q = a.part + (size_t)(mt * C::WM + wm) * a.N + col;
-        *reinterpret_cast<float4*>(q) = make_float4(cs[j][0], cs[j][1], cs[j][2], cs[j][3]);
-        *reinterpret_cast<float4*>(q + 4) = make_float4(cs[j][4], cs[j][5], cs[j][6], cs[j][7]);
-      }
-    }
-  }
+  const int q = uniform_div(l, h);
+  *nt_out = col + q;
+  *mt_out = r0 + (l - q * h) + (1 - first);
+  return true;
 }
 
 template <bool ATR, bool BTR, int EPI, int TM, int TN, int BK, int RB, int NSTAGE, int KG>
 __global__ void __launch_bounds__(256 * KG, (Cfg<ATR, BTR, TM, TN, BK, RB, NSTAGE, KG>::WPE)) gemm_kernel(Args a) {
-  // workgroups that share an XCD's L2 (every 8th) walk consecutive tiles: same rows of A, all of B
-  // (the grid is 8 * ceil(tiles / 8) workgroups; the few past the end leave at once).  An XCD owns a
-  // contiguous range of the row-major tile list, i.e. a band of tile rows, and walks it column by
-  // column: the workgroups in flight on it then share the band's rows of A, which stay in its L2,
-  // while B streams through once per XCD.
-  const int ntot = a.mtiles * a.ntiles, chunk = (ntot + 7) >> 3;
-  const int c0 = (blockIdx.x & 7) * chunk, c1 = min(c0 + chunk, ntot);
-  int l = blockIdx.x >> 3;
-  if (c0 + l >= c1) return;
-  const int r0 = c0 / a.ntiles, s0 = c0 - r0 * a.ntiles, r1 = (c1 - 1) / a.ntiles, e1 = (c1 - 1) - r1 * a.ntiles + 1;
-  int mt = r0, nt = 0;
-  for (; nt < a.ntiles; ++nt) {
-    const int first = nt >= s0 ? 1 : 0;                 // the band's first row has this column
-    const int cnt = r0 == r1 ? ((nt >= s0 && nt < e1) ? 1 : 0) : (r1 - r0 - 1) + first + (nt < e1 ? 1 : 0);
-    if (l < cnt) { mt = r0 + l + (1 - first); break; }
-    l -= cnt;
+  using C = Cfg<ATR, BTR, TM, TN, BK, RB, NSTAGE, KG>;
+  int mt, nt;
+  const int l = blockIdx.x >> 3, step = gridDim.x >> 3;
+  if (!band_tile(a, l, &mt, &nt)) return;
+  if constexpr (EPI == 2 || KG > 1) {
+    gemm_tile<C, EPI>(a, mt, nt, blockIdx.z);
+  } else {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int ntot = a.mtiles * a.ntiles, chunk = (ntot + 7) >> 3, mine = min(chunk, ntot - (int)(blockIdx.x & 7) * chunk);
+    DenseLoader<C> ld;
+    GemmEpilogue<C, EPI> ep;
+    // the tile whose products are formed; the loads may already be at the next one
+    int cmt = 0, cnt = 0;
+    tile_stream<C, GemmEpilogue<C, EPI>::STORES, false, false>(
+        ld, (mine - l + step - 1) / step, (a.K + BK - 1) / BK, 0, wave, lane, smem, false, 0,
+        [&](int k) __attribute__((always_inline)) {
+          if (k > 0) band_tile(a, l + k * step, &mt, &nt);
+          ld.init(a, mt * C::BM, nt * C::BN, 0, a.K, wave, lane);
+        },
+        [&](int k) __attribute__((always_inline)) {
+          band_tile(a, l + k * step, &cmt, &cnt);
+          ep.prefetch(a, cmt, cnt, lane, wave);
+        },
+        [&](int, f32x16_t (&acc)[TM][TN], float (&)[TM], unsigned char* strip) __attribute__((always_inline)) { ep.write(a, cmt, cnt, acc, lane, wave, strip); });
   }
-  gemm_tile<Cfg<ATR, BTR, TM, TN, BK, RB, NSTAGE, KG>, EPI>(a, mt, nt, blockIdx.z);
 }
 
 // Several weight gradients in one launch.  Alone, one of ViT-B/16's has 18 to 72 tiles of 256 x 128 for 256
@@ -335,13 +396,13 @@ __global__ void __launch_bounds__(256) sum_partials_kernel(const float* __restri
 }
 
 template <typename Kern>
-int launch(Kern kern, bool* raised, int threads, int smem_bytes, const Args& a, int splits, hipStream_t st) {
+int launch(Kern kern, bool* raised, int threads, int smem_bytes, int per_xcd, const Args& a, int splits, hipStream_t st) {
   if (!*raised) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem_bytes) != hipSuccess)
       return CNNK_ERR_HIP;
     *raised = true;
   }
-  hipLaunchKernelGGL(kern, dim3(8 * ((a.mtiles * a.ntiles + 7) / 8), 1, splits), dim3(threads), smem_bytes, st, a);
+  hipLaunchKernelGGL(kern, dim3(8 * per_xcd, 1, splits), dim3(threads), smem_bytes, st, a);
   return launch_status();
 }
 template <bool ATR, bool BTR, int EPI, int TM, int TN, int BK, int RB, int NST, int KG>
@@ -350,7 +411,10 @@ int launch_cfg(Args& a, int splits, hipStream_t st) {
   using C = Cfg<ATR, BTR, TM, TN, BK, RB, NST, KG>;
   a.mtiles = (a.M + C::BM - 1) / C::BM;
   a.ntiles = (a.N + C::BN - 1) / C::BN;
-  return launch(gemm_kernel<ATR, BTR, EPI, TM, TN, BK, RB, NST, KG>, &raised, C::THREADS, C::SMEM, a, splits, st);
+  // As many workgroups as the device holds at a time, each walking several tiles where there are more (tuning key 18).  12608 x
+  // 768 -> 3072 83 -> 77 us, -> 2304 63 -> 58, against one to a tile; up to one round of tiles nothing changes.
+  const int tiles = (a.mtiles * a.ntiles + 7) / 8, most = EPI == 2 || KG > 1 || g_cnnk_tune[18] < 0 ? tiles : g_cnnk_tune[18] > 0 ? g_cnnk_tune[18] : 32 * C::RESIDENT;
+  return launch(gemm_kernel<ATR, BTR, EPI, TM, TN, BK, RB, NST, KG>, &raised, C::THREADS, C::SMEM, tiles < most ? tiles : most, a, splits, st);
 }
 // The tile shapes and what a launch of each costs.  With few tiles the device is bound by the latency of the operand
 // loads and by how many CUs have a tile at all, so small problems want small tiles, 128-byte operand rows and two
@@ -371,7 +435,8 @@ struct TileCost {
 };
 constexpr TileCost kTiles[T_SHAPES] = {{64, 64, 1, 3, 1.84f, 1.00f, 0.237f, 0.367f},  {64, 64, 2, 1, 0.597f, 2.89f, 0.231f, 0.461f},
                                        {64, 128, 1, 2, 1.66f, 1.78f, 0.228f, 0.702f}, {64, 128, 2, 1, 0.288f, 4.27f, 0.671f, 0.576f},
-                                       {128, 128, 1, 2, 1.93f, 3.33f, 0.302f, 0.859f}, {256, 128, 1, 2, 2.59f, 4.57f, 0.861f, 1.62f},
+                                       {128, 128, 1, 2, 1.93f, 3.33f, 0.302f, 0.859f},
+                                       {256, 128, 1, 2, 2.59f, 4.57f, 0.861f, 1.62f},
                                        {192, 128, 1, 2, 2.27f, 5.27f, 0.708f, 1.09f}, {192, 128, 1, 2, 2.13f, 4.62f, 0.346f, 0.912f}};
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 float tile_time(const TileCost& t, int out_rows, int out_cols, int k) {

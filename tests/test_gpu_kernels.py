@@ -152,6 +152,18 @@ def test_direct_load_kernels_every_tile(K, shape, tile):
         K.cnnk_tune(16, 0)
 
 
+# the same with one workgroup on each XCD, which then walks several tiles (tuning key 18): one to nine stages a tile, ragged
+# tiles, strided data gradients with parities of different sizes
+@pytest.mark.parametrize("tile", [0, 2, 4, 5, 6, 7])
+@pytest.mark.parametrize("shape", [(5, 16, 16, 64, 136, 1, 1), (9, 15, 13, 64, 160, 3, 2), (6, 16, 16, 320, 264, 1, 1), (17, 8, 8, 96, 96, 1, 1)])
+def test_direct_load_kernels_that_walk_several_tiles(K, shape, tile):
+    K.cnnk_tune(18, 1)
+    try:
+        test_direct_load_kernels_every_tile(K, shape, tile)
+    finally:
+        K.cnnk_tune(18, 0)
+
+
 # 1x1 stride-2 data gradients, of whose four output parities three have no tap: channels that end inside a tile (also
 # with the second tile of columns empty but for some), single rows and columns of pixels, one pixel
 @pytest.mark.parametrize("shape", [(5, 7, 7, 160, 64, 1, 2), (3, 1, 9, 72, 96, 1, 2), (2, 8, 1, 264, 32, 1, 2), (1, 1, 1, 64, 64, 1, 2)])

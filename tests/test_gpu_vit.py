@@ -160,6 +160,22 @@ def test_linear_small_tiles(K, rows, Kd, N, shape):
         cnnk.cnnk_tune(15, 0)
 
 
+# One workgroup on each of the eight XCDs (tuning key 18), so that each walks several tiles: reductions shorter than the
+# pipeline (one stage), of its length and longer, ragged tiles in the middle and at the end of a walk, fewer tiles than
+# XCDs.  Shapes: 16, 18 and 20 are the small ones with one group of wavefronts, 1 and 2 the large ones.
+@pytest.mark.parametrize("shape", [16, 18, 20, 1, 2])
+@pytest.mark.parametrize("rows,Kd,N", [(1600, 64, 264), (1090, 128, 200), (2500, 200, 136), (777, 392, 648), (300, 72, 136)])
+def test_linear_workgroups_that_walk_several_tiles(K, rows, Kd, N, shape):
+    from paper_2503_23186_amd import cnnk
+    cnnk.cnnk_tune(15, shape)
+    cnnk.cnnk_tune(18, 1)
+    try:
+        _linear_case(K, rows, Kd, N, "bf16")
+    finally:
+        cnnk.cnnk_tune(15, 0)
+        cnnk.cnnk_tune(18, 0)
+
+
 def _linear_case(K, rows, Kd, N, dtype):
     rng = np.random.default_rng(rows + Kd + N)
     x = rep(rng.standard_normal((rows, Kd)), dtype)
