@@ -35,25 +35,23 @@ inline int reduce_blocks(size_t m, int C) {
 }
 
 // Sum the NV per-thread vectors of 8 channels over the threads that share a channel octet and
-// write them to part[v][c][blockIdx.x] (workgroup index fastest, so the finaliser reads rows).
-template <int NV>
-__device__ __forceinline__ void block_reduce_store(float (*acc)[8], int lanes, int rows, int C,
-                                                   float* __restrict__ part) {
+// write them to part[v][c][block] (row block fastest, so the finaliser reads rows).
+template <int NV, class W>
+__device__ __forceinline__ void block_reduce_store(float (*acc)[8], const W& w, int C, float* __restrict__ part) {
   __shared__ float red[kT * 8];
-  const int tid = threadIdx.x;
-  const int o = tid % lanes, rl = tid / lanes;
+  const int tid = threadIdx.x, width = w.lanes * 8;
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     __syncthreads();
-    if (rl < rows) {
+    if (w.rl < w.rows) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) red[(rl * lanes + o) * 8 + e] = acc[v][e];
+      for (int e = 0; e < 8; ++e) red[tid * 8 + e] = acc[v][e];
     }
     __syncthreads();
-    for (int i = tid; i < C; i += kT) {
+    for (int i = tid; i < width; i += kT) {
       float s = 0.f;
-      for (int r = 0; r < rows; ++r) s += red[(r * lanes) * 8 + i];
-      part[((size_t)v * C + i) * gridDim.x + blockIdx.x] = s;
+      for (int r = 0; r < w.rows; ++r) s += red[r * width + i];
+      part[((size_t)v * C + w.slab0 + i) * w.blocks + w.block] = s;
     }
   }
 }
@@ -103,40 +101,99 @@ __device__ __forceinline__ void finalize_sums(const float* __restrict__ part, in
 }
 
 // Row walk of the reductions and of the element-wise kernels: a thread owns one octet of
-// channels (o = tid % (C/8)) for the whole launch, keeps that octet's coefficients in registers, and
-// walks rows blockIdx.x*rows + tid/(C/8), +gridDim.x*rows, ... four rows in flight.  No per-vector
-// index arithmetic beyond one multiply-add, no per-vector coefficient loads.
-template <typename T, typename F>
-__device__ __forceinline__ void for_rows4(size_t m, int C, int lanes, int rows, F body) {
-  const int tid = threadIdx.x, o = tid % lanes, rl = tid / lanes;
-  if (rl >= rows) return;
-  const size_t step = (size_t)gridDim.x * rows;
-  size_t r = (size_t)blockIdx.x * rows + rl;
-  for (; r + 3 * step < m; r += 4 * step) {
-    const size_t i0 = r * C + o * 8, d = step * C;
-    body(i0, i0 + d, i0 + 2 * d, i0 + 3 * d, std::integral_constant<int, 4>{});
+// channels for the whole launch, keeps that octet's coefficients in registers, and walks rows
+// first, first + step, ..., four rows in flight.  No per-vector index arithmetic beyond one multiply-add, no
+// per-vector coefficient loads.
+//
+// Without SLAB a workgroup takes whole rows; with it, 64 of the channels (a 128-byte line of bf16 per row) of 32 rows at a time, the
+// slabs of a row block being consecutive workgroups.  A slab's workgroup needs the sums of its own channels only, and a tensor of C channels has C / 64
+// times fewer partial sums per channel, so few that every consumer can add them up for itself (slab_sums).
+constexpr int kSlab = 64;
+template <bool SLAB> struct RowWalk {
+  int lanes, rows, rl;     // octets and rows of a workgroup's pass, this thread's row in it (none from `rows` on)
+  int c, slab0;            // its first channel; the workgroup's
+  int block, blocks;       // row block of the workgroup, of how many
+  __device__ __forceinline__ RowWalk(int C) {
+    const int slabs = SLAB ? C / kSlab : 1;
+    block = SLAB ? uniform_div(blockIdx.x, slabs) : blockIdx.x;
+    blocks = SLAB ? uniform_div(gridDim.x, slabs) : gridDim.x;
+    slab0 = SLAB ? ((int)blockIdx.x - block * slabs) * kSlab : 0;
+    lanes = SLAB ? kSlab / 8 : C / 8;
+    rows = kT / lanes;
+    rl = threadIdx.x / lanes;
+    c = slab0 + (threadIdx.x - rl * lanes) * 8;
   }
-  for (; r < m; r += step) {
-    const size_t i0 = r * C + o * 8;
-    body(i0, i0, i0, i0, std::integral_constant<int, 1>{});
+  template <typename F> __device__ __forceinline__ void rows4(size_t m, int C, F body) const {
+    if (rl >= rows) return;
+    const size_t step = (size_t)blocks * rows;
+    size_t r = (size_t)block * rows + rl;
+    for (; r + 3 * step < m; r += 4 * step) {
+      const size_t i0 = r * C + c, d = step * C;
+      body(i0, i0 + d, i0 + 2 * d, i0 + 3 * d, std::integral_constant<int, 4>{});
+    }
+    for (; r < m; r += step) {
+      const size_t i0 = r * C + c;
+      body(i0, i0, i0, i0, std::integral_constant<int, 1>{});
+    }
   }
+};
+
+// The sums of a workgroup's slab out of the partials part[v][c][0..nb): four threads to a channel, up to 32 loads in flight each,
+// added in double in a fixed order.  sum[v][channel of the slab], behind a barrier.
+__device__ __forceinline__ void slab_sums(const float* __restrict__ part, int nb, int C, int slab0, float (*sum)[kSlab]) {
+  const int q = threadIdx.x & 3, ch = threadIdx.x >> 2;
+  const float* p[2] = {part + (size_t)(slab0 + ch) * nb, part + (size_t)(C + slab0 + ch) * nb};
+  double s[2] = {0.0, 0.0};
+  if ((nb & 3) == 0) {
+    for (int k0 = q * 4; k0 < nb; k0 += 64) {
+      float4 v[2][4];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[t][k] = *reinterpret_cast<const float4*>(p[t] + (k0 + 16 * k < nb ? k0 + 16 * k : 0));
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (k0 + 16 * k < nb) s[t] += ((double)v[t][k].x + (double)v[t][k].y) + ((double)v[t][k].z + (double)v[t][k].w);
+    }
+  } else {
+    for (int k0 = q; k0 < nb; k0 += 32) {
+      float v[2][8];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[t][k] = p[t][k0 + 4 * k < nb ? k0 + 4 * k : 0];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (k0 + 4 * k < nb) s[t] += (double)v[t][k];
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    s[t] += __shfl_xor(s[t], 1, 64);
+    s[t] += __shfl_xor(s[t], 2, 64);
+    if (q == 0) sum[t][ch] = (float)s[t];
+  }
+  __syncthreads();
 }
 
 // Partial sums of (x - shift) and (x - shift)^2 with shift = x[0][c] (keeps fp32 sums benign).
 template <typename T>
 __global__ void __launch_bounds__(kT) stats_partial_kernel(const T* __restrict__ x, size_t m, int C,
                                                            float* __restrict__ part) {
-  const int lanes = C / 8, rows = kT / lanes;
-  const int tid = threadIdx.x, o = tid % lanes, rl = tid / lanes;
+  const RowWalk<false> w(C);
   float acc[2][8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[0][e] = acc[1][e] = 0.f;
-  if (rl < rows) {
+  if (w.rl < w.rows) {
     float sh[8];
-    load8(x + o * 8, sh);
+    load8(x + w.c, sh);
     // four rows per round, all loads issued before the first use (a plain row loop is compiled to
     // one load in flight per thread)
-    for_rows4<T>(m, C, lanes, rows, [&](size_t i0, size_t i1, size_t i2, size_t i3, auto NN) {
+    w.rows4(m, C, [&](size_t i0, size_t i1, size_t i2, size_t i3, auto NN) {
       constexpr int n = decltype(NN)::value;
       const size_t idx[4] = {i0, i1, i2, i3};
       float v[4][8];
@@ -155,7 +212,7 @@ __global__ void __launch_bounds__(kT) stats_partial_kernel(const T* __restrict__
       }
     });
   }
-  block_reduce_store<2>(acc, lanes, rows, C, part);
+  block_reduce_store<2>(acc, w, C, part);
 }
 
 // mode 0: write save_mean / save_invstd (+ running stats); mode 1: write plain sum, sum of squares.
@@ -258,12 +315,11 @@ __device__ __forceinline__ void bn_scale_bias(float g, float b, float mu, float 
   *bi = fmaf(-mu, *sc, b);
 }
 
-template <typename T>
-__device__ __forceinline__ void bn_apply_rows(const T* __restrict__ x, const T* __restrict__ res, T* __restrict__ y,
+template <typename T, class W>
+__device__ __forceinline__ void bn_apply_rows(const W& w, const T* __restrict__ x, const T* __restrict__ res, T* __restrict__ y,
                                               size_t m, int C, int relu, const float* sc, const float* bi,
                                               unsigned char* __restrict__ mask = nullptr) {
-  const int lanes = C / 8, rows = kT / lanes;
-  for_rows4<T>(m, C, lanes, rows, [&](size_t i0, size_t i1, size_t i2, size_t i3, auto NN) {
+  w.rows4(m, C, [&](size_t i0, size_t i1, size_t i2, size_t i3, auto NN) {
     constexpr int n = decltype(NN)::value;
     const size_t idx[4] = {i0, i1, i2, i3};
     float v[4][8], r[4][8];
@@ -308,15 +364,15 @@ __global__ void __launch_bounds__(kT) bn_apply_kernel(const T* __restrict__ x, c
                                                       const float* __restrict__ mean,
                                                       const float* __restrict__ invstd, T* __restrict__ y,
                                                       size_t m, int C, int relu, unsigned char* __restrict__ mask) {
-  const int o = threadIdx.x % (C / 8);
+  const RowWalk<false> w(C);
   float g[8], b[8], mu[8], is[8], sc[8], bi[8];
-  load8(gamma + o * 8, g);
-  load8(beta + o * 8, b);
-  load8(mean + o * 8, mu);
-  load8(invstd + o * 8, is);
+  load8(gamma + w.c, g);
+  load8(beta + w.c, b);
+  load8(mean + w.c, mu);
+  load8(invstd + w.c, is);
 #pragma unroll
   for (int e = 0; e < 8; ++e) bn_scale_bias(g[e], b[e], mu[e], is[e], &sc[e], &bi[e]);
-  bn_apply_rows<T>(x, res, y, m, C, relu, sc, bi, mask);
+  bn_apply_rows<T>(w, x, res, y, m, C, relu, sc, bi, mask);
 }
 
 // Inference mode: the running statistics stand in for the batch's; nothing is reduced or updated.
@@ -327,37 +383,44 @@ __global__ void __launch_bounds__(kT) bn_infer_kernel(const T* __restrict__ x, c
                                                       const float* __restrict__ rmean,
                                                       const float* __restrict__ rvar, float eps,
                                                       T* __restrict__ y, size_t m, int C, int relu) {
-  const int o = threadIdx.x % (C / 8);
+  const RowWalk<false> w(C);
   float g[8], b[8], mu[8], var[8], sc[8], bi[8];
-  load8(gamma + o * 8, g);
-  load8(beta + o * 8, b);
-  load8(rmean + o * 8, mu);
-  load8(rvar + o * 8, var);
+  load8(gamma + w.c, g);
+  load8(beta + w.c, b);
+  load8(rmean + w.c, mu);
+  load8(rvar + w.c, var);
 #pragma unroll
   for (int e = 0; e < 8; ++e) bn_scale_bias(g[e], b[e], mu[e], 1.f / sqrtf(var[e] + eps), &sc[e], &bi[e]);
-  bn_apply_rows<T>(x, res, y, m, C, relu, sc, bi);
+  bn_apply_rows<T>(w, x, res, y, m, C, relu, sc, bi);
 }
 
 // Normalise (+ residual) (+ ReLU) with the statistics taken directly from per-channel sums
 // (sum x, sum x^2 over m positions, e.g. from the convolution that produced x): every thread
 // derives mean / invstd of its 8 channels itself, so no separate statistics kernel runs.
-// Workgroup 0 also writes save_mean / save_invstd and updates the running statistics.
-template <typename T>
+// The first row block also writes save_mean / save_invstd and updates the running statistics.
+// SLAB: the sums come as nb partials per channel (ch_sum: part[2][C][nb]) and are added up here.
+template <typename T, bool SLAB>
 __global__ void __launch_bounds__(kT) bn_apply_sums_kernel(const T* __restrict__ x, const T* __restrict__ res,
                                                            const float* __restrict__ gamma,
                                                            const float* __restrict__ beta,
                                                            const float* __restrict__ ch_sum,
-                                                           const float* __restrict__ ch_sumsq, float inv_m,
+                                                           const float* __restrict__ ch_sumsq, int nb, float inv_m,
                                                            float unbias, float eps, float momentum,
                                                            float* __restrict__ save_mean,
                                                            float* __restrict__ save_invstd,
                                                            float* __restrict__ rmean, float* __restrict__ rvar,
                                                            T* __restrict__ y, size_t m, int C, int relu,
                                                            unsigned char* __restrict__ mask) {
-  if (blockIdx.x == 0) {
-    for (int c = threadIdx.x; c < C; c += kT) {
-      const float mu = ch_sum[c] * inv_m;
-      const float var = fmaxf(fmaf(ch_sumsq[c], inv_m, -mu * mu), 0.f);
+  __shared__ __align__(16) float sums[2][kSlab];
+  const RowWalk<SLAB> w(C);
+  if (SLAB) slab_sums(ch_sum, nb, C, w.slab0, sums);
+  const float* p1 = SLAB ? sums[0] : ch_sum;
+  const float* p2 = SLAB ? sums[1] : ch_sumsq;
+  if (w.block == 0) {
+    for (int k = threadIdx.x; k < (SLAB ? kSlab : C); k += kT) {
+      const int c = w.slab0 + k;
+      const float mu = p1[k] * inv_m;
+      const float var = fmaxf(fmaf(p2[k], inv_m, -mu * mu), 0.f);
       save_mean[c] = mu;
       save_invstd[c] = rsqrtf(var + eps);
       if (rmean) {
@@ -366,12 +429,11 @@ __global__ void __launch_bounds__(kT) bn_apply_sums_kernel(const T* __restrict__
       }
     }
   }
-  const int o = threadIdx.x % (C / 8);
   float s1[8], s2[8], g[8], b[8], sc[8], bi[8];
-  load8(ch_sum + o * 8, s1);
-  load8(ch_sumsq + o * 8, s2);
-  load8(gamma + o * 8, g);
-  load8(beta + o * 8, b);
+  load8(p1 + (w.c - w.slab0), s1);
+  load8(p2 + (w.c - w.slab0), s2);
+  load8(gamma + w.c, g);
+  load8(beta + w.c, b);
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const float mu = s1[e] * inv_m;
@@ -379,14 +441,14 @@ __global__ void __launch_bounds__(kT) bn_apply_sums_kernel(const T* __restrict__
     const float is = rsqrtf(var + eps);
     bn_scale_bias(g[e], b[e], mu, is, &sc[e], &bi[e]);
   }
-  bn_apply_rows<T>(x, res, y, m, C, relu, sc, bi, mask);
+  bn_apply_rows<T>(w, x, res, y, m, C, relu, sc, bi, mask);
 }
 
 // Partial sums of dz and dz*xhat.  MODE 0: no ReLU; 1: mask [y > 0]; 2: mask [x*sc + bi > 0]
 // recomputed with the forward's arithmetic (y is not read); 4: `y` is the mask that the forward pass kept, one bit
 // per element.  The element-wise kernel also knows MODE 3: dz was written by this kernel into dres (the residual
 // gradient is dz itself), read it there.
-template <typename T, int MODE>
+template <typename T, int MODE, bool SLAB>
 __global__ void __launch_bounds__(kT) bwd_partial_kernel(const T* __restrict__ dy, const T* __restrict__ x,
                                                          const void* __restrict__ y_or_mask,
                                                          const float* __restrict__ gamma,
@@ -396,25 +458,24 @@ __global__ void __launch_bounds__(kT) bwd_partial_kernel(const T* __restrict__ d
                                                          float* __restrict__ part, T* __restrict__ dz_out) {
   const T* __restrict__ y = (const T*)y_or_mask;
   const unsigned char* __restrict__ mask = (const unsigned char*)y_or_mask;
-  const int lanes = C / 8, rows = kT / lanes;
-  const int tid = threadIdx.x, o = tid % lanes, rl = tid / lanes;
+  const RowWalk<SLAB> w(C);
   float acc[2][8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[0][e] = acc[1][e] = 0.f;
-  if (rl < rows) {
+  if (w.rl < w.rows) {
     float mu[8], is[8], sc[8], bi[8];
-    load8(mean + o * 8, mu);
-    load8(invstd + o * 8, is);
+    load8(mean + w.c, mu);
+    load8(invstd + w.c, is);
     if (MODE == 2) {
       float ga[8], be[8];
-      load8(gamma + o * 8, ga);
-      load8(beta + o * 8, be);
+      load8(gamma + w.c, ga);
+      load8(beta + w.c, be);
 #pragma unroll
       for (int e = 0; e < 8; ++e) bn_scale_bias(ga[e], be[e], mu[e], is[e], &sc[e], &bi[e]);
     }
     // four rows per round, all loads issued before the first use (a plain row loop is compiled to
     // one load in flight per thread)
-    for_rows4<T>(m, C, lanes, rows, [&](size_t i0, size_t i1, size_t i2, size_t i3, auto NN) {
+    w.rows4(m, C, [&](size_t i0, size_t i1, size_t i2, size_t i3, auto NN) {
       constexpr int n = decltype(NN)::value;
       const size_t idx[4] = {i0, i1, i2, i3};
       float g[4][8], xv[4][8], yv[4][8];
@@ -455,7 +516,7 @@ __global__ void __launch_bounds__(kT) bwd_partial_kernel(const T* __restrict__ d
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[1][e] *= is[e];
   }
-  block_reduce_store<2>(acc, lanes, rows, C, part);
+  block_reduce_store<2>(acc, w, C, part);
 }
 
 __global__ void __launch_bounds__(kT) bwd_finalize_kernel(const float* __restrict__ part, int nb, int C,
@@ -478,29 +539,39 @@ __global__ void __launch_bounds__(kT) bwd_finalize_wide_kernel(const float* __re
   dgamma[blockIdx.x] = (float)s2;
 }
 
-template <typename T, int MODE>
+// SLAB: the sums come as nb partials per channel (part[2][C][nb]) and are added up here; the first row block writes
+// dgamma and dbeta.  Otherwise it reads them.
+template <typename T, int MODE, bool SLAB>
 __global__ void __launch_bounds__(kT) bwd_apply_kernel(const T* __restrict__ dy, const T* __restrict__ x,
                                                        const void* __restrict__ y_or_mask, const float* __restrict__ gamma,
                                                        const float* __restrict__ beta,
                                                        const float* __restrict__ mean,
                                                        const float* __restrict__ invstd,
-                                                       const float* __restrict__ dgamma,
-                                                       const float* __restrict__ dbeta, T* __restrict__ dx,
+                                                       const float* __restrict__ part, int nb,
+                                                       float* __restrict__ dgamma,
+                                                       float* __restrict__ dbeta, T* __restrict__ dx,
                                                        T* __restrict__ dres, size_t m, int C, float inv_m,
                                                        int flags) {
+  __shared__ __align__(16) float sums[2][kSlab];
   const T* __restrict__ y = (const T*)y_or_mask;
   const unsigned char* __restrict__ mask = (const unsigned char*)y_or_mask;
-  const int lanes = C / 8, rows = kT / lanes;
-  const int o = threadIdx.x % lanes;
+  const RowWalk<SLAB> w(C);
+  if (SLAB) {
+    slab_sums(part, nb, C, w.slab0, sums);
+    if (w.block == 0 && threadIdx.x < kSlab) {
+      dbeta[w.slab0 + threadIdx.x] = sums[0][threadIdx.x];
+      dgamma[w.slab0 + threadIdx.x] = sums[1][threadIdx.x];
+    }
+  }
   // dx = a * (dz - (dbeta + xhat * dgamma) / m), xhat = (x - mu) * is, a = gamma * is
   float a[8], mu[8], is[8], dgm[8], dbm[8], sc[8], bi[8];
   {
     float ga[8], dg[8], db[8];
-    load8(gamma + o * 8, ga);
-    load8(mean + o * 8, mu);
-    load8(invstd + o * 8, is);
-    load8(dgamma + o * 8, dg);
-    load8(dbeta + o * 8, db);
+    load8(gamma + w.c, ga);
+    load8(mean + w.c, mu);
+    load8(invstd + w.c, is);
+    load8(SLAB ? &sums[1][w.c - w.slab0] : dgamma + w.c, dg);
+    load8(SLAB ? &sums[0][w.c - w.slab0] : dbeta + w.c, db);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       a[e] = ga[e] * is[e];
@@ -509,12 +580,12 @@ __global__ void __launch_bounds__(kT) bwd_apply_kernel(const T* __restrict__ dy,
     }
     if (MODE == 2) {
       float be[8];
-      load8(beta + o * 8, be);
+      load8(beta + w.c, be);
 #pragma unroll
       for (int e = 0; e < 8; ++e) bn_scale_bias(ga[e], be[e], mu[e], is[e], &sc[e], &bi[e]);
     }
   }
-  for_rows4<T>(m, C, lanes, rows, [&](size_t i0, size_t i1, size_t i2, size_t i3, auto NN) {
+  w.rows4(m, C, [&](size_t i0, size_t i1, size_t i2, size_t i3, auto NN) {
     constexpr int n = decltype(NN)::value;
     const size_t idx[4] = {i0, i1, i2, i3};
     float g[4][8], xv[4][8], yv[4][8];
@@ -576,6 +647,22 @@ inline unsigned row_blocks(size_t m, int C) {
   return (unsigned)(b < 1 ? 1 : b);
 }
 
+// Whether a batch norm's last pass adds up nb partials per channel itself instead of reading what a finalising launch left (4 to 5 us, two
+// of them to a batch norm's forward and backward, and as much enqueueing).  Every workgroup reads the 512 nb bytes of its slab's
+// partials first, so there is a limit.  us per step with none, up to 16, 64, 128, 256 partials (tuning key 19): ResNet-18 b32
+// 1095, 1040, 1013, 1005, 1003; b77 1389, 1369, 1339, 1343, 1325; b256 2055, 2056, 2022, 2018, 2008; ResNet-50 b16 2603, 2323, 2270, 2261, 2262;
+// b256 7751, 7698, 7571, 7566, 7652; VGG-style b128 467, 465, 459, 457, 457; WRN-28-10 b128 6504, 6548, 6478, 6465, 6481.  Fewer partials by more
+// rows to a thread in the first backward pass: slower wherever that leaves fewer than 256 workgroups (ResNet-50 b256 7566, at most 128 row blocks 7623).
+inline bool slab_pays(int C, int nb) { return C % kSlab == 0 && nb <= (g_cnnk_tune[19] ? g_cnnk_tune[19] : 128); }
+// rows per thread and workgroups of a pass in slabs, as reduce_blocks and row_blocks have them without
+inline int slab_blocks(size_t m, int C) {
+  const size_t slabs = C / kSlab, rows = kT / (kSlab / 8);
+  size_t nb = (m + rows * 8 - 1) / (rows * 8);
+  if (nb * slabs < 256) nb = (m + rows * 4 - 1) / (rows * 4);
+  const size_t cap = kMaxBlocks / slabs;
+  return (int)(nb > cap ? cap : nb);
+}
+
 int validate_bn(const cnnk_bn_desc* d) {
   if (!d) return CNNK_ERR_NULL;
   if (d->N <= 0 || d->H <= 0 || d->W <= 0 || d->C <= 0) return CNNK_ERR_SHAPE;
@@ -586,7 +673,14 @@ int validate_bn(const cnnk_bn_desc* d) {
 
 }  // namespace
 
+thread_local PartSums* t_cnnk_part_sums = nullptr;
+
 int channel_sums_finalize(const float* part, int nb, int C, float* ch_sum, float* ch_sumsq, hipStream_t st) {
+  if (t_cnnk_part_sums && slab_pays(C, nb)) {
+    t_cnnk_part_sums->part = part;
+    t_cnnk_part_sums->nb = nb;
+    return CNNK_OK;
+  }
   if (nb >= kWideFinalize) sums_finalize_wide_kernel<<<C, kT, 0, st>>>(part, nb, C, ch_sum, ch_sumsq);
   else sums_finalize_kernel<<<fin_blocks(C), kT, 0, st>>>(part, nb, C, ch_sum, ch_sumsq);
   return launch_status();
@@ -617,7 +711,7 @@ extern "C" size_t cnnk_bn_workspace_bytes(const cnnk_bn_desc* d) {
 
 int bn_relu_fwd(const cnnk_bn_desc* d, const void* x, const void* residual, const float* gamma, const float* beta, void* y,
                 unsigned char* mask, float* save_mean, float* save_invstd, float* running_mean, float* running_var,
-                const float* ch_sum, const float* ch_sumsq, void* ws, size_t ws_bytes, void* stream) {
+                const float* ch_sum, const float* ch_sumsq, const PartSums* partials, void* ws, size_t ws_bytes, void* stream) {
   int rc = validate_bn(d);
   if (rc != CNNK_OK) return rc;
   if (!x || !gamma || !beta || !y || !save_mean || !save_invstd) return CNNK_ERR_NULL;
@@ -642,19 +736,21 @@ int bn_relu_fwd(const cnnk_bn_desc* d, const void* x, const void* residual, cons
                                                                      running_mean, running_var);
     }
   } else {
-    // statistics handed in as sums: one fused kernel (statistics + normalise)
+    // statistics handed in as sums, or as few partial sums: one fused kernel (statistics + normalise)
     const float inv_m = (float)(1.0 / (double)m);
     const float unbias = m > 1 ? (float)((double)m / ((double)m - 1.0)) : 1.f;
-    if (d->dtype == CNNK_BF16)
-      bn_apply_sums_kernel<bf16_t><<<row_blocks(m, C), kT, 0, st>>>((const bf16_t*)x, (const bf16_t*)residual, gamma, beta,
-                                                                 ch_sum, ch_sumsq, inv_m, unbias, d->eps, d->momentum,
-                                                                 save_mean, save_invstd, running_mean, running_var,
-                                                                 (bf16_t*)y, m, C, d->relu, mask);
-    else
-      bn_apply_sums_kernel<float><<<row_blocks(m, C), kT, 0, st>>>((const float*)x, (const float*)residual, gamma, beta,
-                                                                ch_sum, ch_sumsq, inv_m, unbias, d->eps, d->momentum,
-                                                                save_mean, save_invstd, running_mean, running_var,
-                                                                (float*)y, m, C, d->relu, mask);
+    const int nb = partials ? partials->nb : 0;
+    const float* sum = nb ? partials->part : ch_sum;
+#define CNNK_BN_SUMS(T, SLAB)                                                                                                     \
+  bn_apply_sums_kernel<T, SLAB><<<SLAB ? slab_blocks(m, C) * (C / kSlab) : row_blocks(m, C), kT, 0, st>>>(                        \
+      (const T*)x, (const T*)residual, gamma, beta, sum, ch_sumsq, nb, inv_m, unbias, d->eps, d->momentum, save_mean,            \
+      save_invstd, running_mean, running_var, (T*)y, m, C, d->relu, mask)
+    if (d->dtype == CNNK_BF16) {
+      if (nb) CNNK_BN_SUMS(bf16_t, true); else CNNK_BN_SUMS(bf16_t, false);
+    } else {
+      if (nb) CNNK_BN_SUMS(float, true); else CNNK_BN_SUMS(float, false);
+    }
+#undef CNNK_BN_SUMS
     return launch_status();
   }
   if (launch_status() != CNNK_OK) return CNNK_ERR_HIP;
@@ -672,7 +768,7 @@ extern "C" int cnnk_bn_relu_fwd(const cnnk_bn_desc* d, const void* x, const void
                                 float* running_mean, float* running_var, const float* ch_sum,
                                 const float* ch_sumsq, void* ws, size_t ws_bytes, void* stream) {
   return bn_relu_fwd(d, x, residual, gamma, beta, y, nullptr, save_mean, save_invstd, running_mean, running_var, ch_sum,
-                     ch_sumsq, ws, ws_bytes, stream);
+                     ch_sumsq, nullptr, ws, ws_bytes, stream);
 }
 
 extern "C" int cnnk_bn_relu_infer(const cnnk_bn_desc* d, const void* x, const void* residual, const float* gamma,
@@ -701,22 +797,33 @@ static int bn_bwd_launch(const cnnk_bn_desc* d, const void* dy, const void* x, c
                          void* dresidual, int flags, float* dgamma, float* dbeta, float* part, hipStream_t st) {
   const size_t m = (size_t)d->N * d->H * d->W;
   const int C = d->C;
-  const int nb = reduce_blocks(m, C);
   const float inv_m = (float)(1.0 / (double)m);
   // a residual gradient that is written, not accumulated, is written by the first pass already
   const bool dz_first = (MODE == 1 || MODE == 4) && dresidual && !(flags & 2);
-  bwd_partial_kernel<T, MODE><<<nb, kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta, save_mean,
-                                                 save_invstd, m, C, part, dz_first ? (T*)dresidual : nullptr);
+  constexpr int APPLY = MODE == 1 || MODE == 4 ? 3 : MODE;      // the last pass behind dz_first
+  T* const dz = dz_first ? (T*)dresidual : nullptr;
+  const int nbs = C % kSlab == 0 ? slab_blocks(m, C) : 0;
+  if (nbs > 0 && slab_pays(C, nbs) && (size_t)nbs * 2 * C * sizeof(float) <= channel_stats_ws(m, C)) {
+    const unsigned grid = (unsigned)nbs * (C / kSlab);
+    bwd_partial_kernel<T, MODE, true><<<grid, kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta, save_mean, save_invstd, m, C, part, dz);
+    if (dz_first)
+      bwd_apply_kernel<T, APPLY, true><<<grid, kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta, save_mean, save_invstd, part, nbs,
+                                                            dgamma, dbeta, (T*)dx, (T*)dresidual, m, C, inv_m, flags);
+    else
+      bwd_apply_kernel<T, MODE, true><<<grid, kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta, save_mean, save_invstd, part, nbs,
+                                                           dgamma, dbeta, (T*)dx, (T*)dresidual, m, C, inv_m, flags);
+    return launch_status();
+  }
+  const int nb = reduce_blocks(m, C);
+  bwd_partial_kernel<T, MODE, false><<<nb, kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta, save_mean, save_invstd, m, C, part, dz);
   if (nb >= kWideFinalize) bwd_finalize_wide_kernel<<<C, kT, 0, st>>>(part, nb, C, dgamma, dbeta);
   else bwd_finalize_kernel<<<fin_blocks(C), kT, 0, st>>>(part, nb, C, dgamma, dbeta);
   if (dz_first)
-    bwd_apply_kernel<T, 3><<<row_blocks(m, C), kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta,
-                                                            save_mean, save_invstd, dgamma, dbeta, (T*)dx,
-                                                            (T*)dresidual, m, C, inv_m, flags);
+    bwd_apply_kernel<T, APPLY, false><<<row_blocks(m, C), kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta, save_mean, save_invstd,
+                                                                       nullptr, 0, dgamma, dbeta, (T*)dx, (T*)dresidual, m, C, inv_m, flags);
   else
-    bwd_apply_kernel<T, MODE><<<row_blocks(m, C), kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta,
-                                                               save_mean, save_invstd, dgamma, dbeta, (T*)dx,
-                                                               (T*)dresidual, m, C, inv_m, flags);
+    bwd_apply_kernel<T, MODE, false><<<row_blocks(m, C), kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta, save_mean, save_invstd,
+                                                                      nullptr, 0, dgamma, dbeta, (T*)dx, (T*)dresidual, m, C, inv_m, flags);
   return launch_status();
 }
 

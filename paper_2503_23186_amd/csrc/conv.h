@@ -129,7 +129,7 @@ size_t conv_pad_ws(const ConvGeom& g, int pass, bool want_stats);
 int conv_pad_fwd(const ConvGeom& g, const bf16_t* x, const bf16_t* w, bf16_t* y, float* ch_sum, float* ch_sumsq,
                  void* ws, hipStream_t st, const ConvTail* tail = nullptr);
 int conv_pad_wgrad(const ConvGeom& g, const bf16_t* x, const bf16_t* dy, float* dw, void* ws, hipStream_t st);
-// Hook 1 of 3 (see "Hooks between cnnk_train_step and the convolution entry points" below).
+// Hook 1 of 4 (see "Hooks between cnnk_train_step and the convolution entry points" below).
 // The forward and the weight-gradient call of such a layer both need the 8-channel copy of x.  When
 // set (per host thread), the forward call writes it to buf and sets valid, and a weight-gradient
 // call that finds valid set reads it there instead of padding x again (the caller vouches that x
@@ -155,9 +155,9 @@ int conv_first_wgrad(const ConvGeom& g, const bf16_t* x, const bf16_t* dy, float
 int channel_sums_finalize(const float* part, int nb, int C, float* ch_sum, float* ch_sumsq, hipStream_t st);
 
 // ---- Hooks between cnnk_train_step and the convolution entry points -----------------------------
-// cnnk_train_step calls the public entry points (cnnk_conv2d_fwd / _wgrad) and passes three extra
+// cnnk_train_step calls the public entry points (cnnk_conv2d_fwd / _wgrad) and passes four extra
 // pieces of context through the per-thread pointers below (t_cnnk_x8_cache above, t_cnnk_sgd_fuse,
-// t_cnnk_wgrad_cus).  Contract, the same for all three: the step sets the pointer immediately
+// t_cnnk_wgrad_cus, t_cnnk_part_sums).  Contract, the same for all four: the step sets the pointer immediately
 // before ONE entry-point call on the same host thread and resets it to its neutral value (nullptr /
 // 256) right after that call returns, whatever the call's status; an entry point reads it once, at
 // entry.  Outside cnnk_train_step the values are always neutral, so a direct caller of the C ABI
@@ -167,7 +167,7 @@ int channel_sums_finalize(const float* part, int nb, int C, float* ch_sum, float
 // first launch; harmless to set twice, so unsynchronised first launches from two threads are
 // benign) and the cnnk_tune table (explicitly documented as not thread-safe).
 //
-// Hook 2 of 3.  When set (per host thread), the next split-K reduction of a weight gradient also applies the
+// Hook 2 of 4.  When set (per host thread), the next split-K reduction of a weight gradient also applies the
 // SGD-momentum update of that parameter in the same launch (out = sum of partials is still
 // written as the gradient): g' = g + wd*w; v <- mu*v + g'; w <- w - lr*v; optional bf16 copy.
 // wait (nullable): an event the stream waits for between the weight-gradient kernel and the
@@ -203,11 +203,19 @@ extern thread_local SgdFuse* t_cnnk_sgd_fuse;
 
 constexpr int kTuneKeys = 24;
 extern int g_cnnk_tune[kTuneKeys];
-// Hook 3 of 3.  Compute units the weight-gradient kernels size their grids for (256 = the whole device).  The
+// Hook 3 of 4.  Compute units the weight-gradient kernels size their grids for (256 = the whole device).  The
 // training step lowers it for the weight gradients it runs on its second stream, beside the rest
 // of the backward pass: fewer, longer-lived workgroups leave the other stream room to run.
 // Workspace sizes are always computed for the whole device (the upper bound).
 extern thread_local int t_cnnk_wgrad_cus;
+
+// Hook 4 of 4.  When set, a forward convolution whose batch norm is the very next call on the same stream and workspace may leave
+// its per-channel sums as partials part[2][C][nb] in the workspace (nb > 0) instead of adding them up in a launch of its own.
+struct PartSums {
+  const float* part;
+  int nb;
+};
+extern thread_local PartSums* t_cnnk_part_sums;
 
 // Forward convolution with a tail (no per-channel sums), for the shapes a matrix-core kernel takes
 // (conv_tail_supported); CNNK_ERR_UNSUPPORTED, and nothing launched, for the others.
@@ -216,10 +224,11 @@ int conv_fwd_tail(const cnnk_conv_desc* d, const void* x, const void* w, void* y
                   size_t ws_bytes, hipStream_t st);
 
 // cnnk_bn_relu_fwd / _bwd with the ReLU mask kept from one to the other: a bit per element (NHWC order, the lowest bit
-// of a byte first), m * C / 8 bytes.  Backward: with a mask, y is not read and may be null.
+// of a byte first), m * C / 8 bytes.  Backward: with a mask, y is not read and may be null.  partials (nullable): where its nb is not
+// 0 they stand in for ch_sum and ch_sumsq, whose contents are then not read.
 int bn_relu_fwd(const cnnk_bn_desc* d, const void* x, const void* residual, const float* gamma, const float* beta, void* y,
                 unsigned char* mask, float* save_mean, float* save_invstd, float* running_mean, float* running_var,
-                const float* ch_sum, const float* ch_sumsq, void* ws, size_t ws_bytes, void* stream);
+                const float* ch_sum, const float* ch_sumsq, const PartSums* partials, void* ws, size_t ws_bytes, void* stream);
 int bn_relu_bwd(const cnnk_bn_desc* d, const void* dy, const void* x, const void* y, const unsigned char* mask, const float* gamma,
                 const float* beta, const float* save_mean, const float* save_invstd, void* dx, void* dresidual, int flags,
                 float* dgamma, float* dbeta, void* ws, size_t ws_bytes, void* stream);

@@ -330,6 +330,11 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
     if (t.count > 0) r = conv_transpose_weights_multi(t, s_);
     return r;
   };
+  // Whether convolution i may leave its channel sums as partials in the workspace: its batch norm is the next call there.
+  auto takes_partials = [&](int i) {
+    return i + 1 < n && L[i + 1].op == CNNK_OP_BN && L[i + 1].in0 == L[i].out && L[i + 1].d.bn.C == L[i].d.conv.Cout;
+  };
+  PartSums handed{nullptr, 0};     // the last convolution's
   bool wt_forked = false;
   bool x8_valid = false;   // the forward pass left the first layer's 8-channel input copy in place
   // ---- forward pass and loss ---------------------------------------------------------------
@@ -343,14 +348,16 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
           hipStreamWaitEvent(aux, (hipEvent_t)B->ev_fork, 0) != hipSuccess)
         return CNNK_ERR_HIP;
       const bool sums = c.d.conv.Cout % 8 == 0 && c.d.conv.Cout <= 2048;
+      PartSums ps{nullptr, 0};
+      if (sums && takes_partials(s0)) t_cnnk_part_sums = &ps;
       rc = cnnk_conv2d_fwd(&c.d.conv, B->act[c.in0], B->param_lp[c.p0], B->act[c.out], sums ? aux_stat : nullptr,
                            sums ? aux_stat + 2048 : nullptr, aux_scratch, aux_scratch_b, aux);
+      t_cnnk_part_sums = nullptr;
       if (rc != CNNK_OK) return rc;
       float* run = B->bn_running ? B->bn_running[s0 + 1] : nullptr;
-      rc = cnnk_bn_relu_fwd(&b.d.bn, B->act[b.in0], nullptr, B->param[b.p0], B->param[b.p1], B->act[b.out],
-                            B->bn_save[s0 + 1], B->bn_save[s0 + 1] + b.d.bn.C, run, run ? run + b.d.bn.C : nullptr,
-                            sums ? aux_stat : nullptr, sums ? aux_stat + 2048 : nullptr, aux_scratch, aux_scratch_b,
-                            aux);
+      rc = bn_relu_fwd(&b.d.bn, B->act[b.in0], nullptr, B->param[b.p0], B->param[b.p1], B->act[b.out], nullptr,
+                       B->bn_save[s0 + 1], B->bn_save[s0 + 1] + b.d.bn.C, run, run ? run + b.d.bn.C : nullptr,
+                       sums ? aux_stat : nullptr, sums ? aux_stat + 2048 : nullptr, &ps, aux_scratch, aux_scratch_b, aux);
       if (rc != CNNK_OK) return rc;
       if (hipEventRecord((hipEvent_t)B->ev_join, aux) != hipSuccess) return CNNK_ERR_HIP;
     }
@@ -374,8 +381,11 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
         // the 8-channel copy of the network input is kept for this layer's weight gradient
         X8Cache x8c{reinterpret_cast<bf16_t*>(wt_region + w.x8_off), false};
         if (i == w.x8_layer) t_cnnk_x8_cache = &x8c;
+        handed.nb = 0;
+        if (ssum && takes_partials(i)) t_cnnk_part_sums = &handed;
         rc = cnnk_conv2d_fwd(&l.d.conv, B->act[l.in0], wt, B->act[l.out], ssum, ssum ? ssum + 2048 : nullptr, ws, wsb,
                              stream);
+        t_cnnk_part_sums = nullptr;
         t_cnnk_x8_cache = nullptr;
         if (i == w.x8_layer) x8_valid = x8c.valid;
         if (sb >= 0) stat_slot[sb] = l.out;
@@ -390,7 +400,8 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
         const float* ssum = sb >= 0 ? stat_base + (size_t)sb * 4096 : nullptr;
         rc = bn_relu_fwd(&l.d.bn, B->act[l.in0], l.in1 >= 0 ? B->act[l.in1] : nullptr, B->param[l.p0], B->param[l.p1],
                          B->act[l.out], mask_of(i), B->bn_save[i], B->bn_save[i] + C, run, run ? run + C : nullptr, ssum,
-                         ssum ? ssum + 2048 : nullptr, ws, wsb, stream);
+                         ssum ? ssum + 2048 : nullptr, ssum ? &handed : nullptr, ws, wsb, stream);
+        handed.nb = 0;
         if (sb >= 0) stat_slot[sb] = -1;
         break;
       }

@@ -304,7 +304,11 @@ def test_conv_patch_kernels_without_the_pixel_permutation(K, shape):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("shape,relu,with_res", [((3, 9, 7, 64), True, False), ((2, 16, 16, 160), True, True),
                                                   ((5, 4, 4, 512), False, False), ((8, 32, 32, 16), True, False),
-                                                  ((2, 3, 3, 2048), False, True), ((64, 8, 8, 24), True, True)])
+                                                  ((2, 3, 3, 2048), False, True), ((64, 8, 8, 24), True, True),
+                                                  # the passes in slabs of 64 channels: a row past the 32 of one pass, 128 partials,
+                                                  # one more (general); few rows would leave a variance near 0 in some channel
+                                                  ((33, 1, 1, 128), True, False), ((16, 32, 32, 64), True, True),
+                                                  ((16385, 1, 1, 64), True, True), ((33, 2, 2, 320), True, False)])
 def test_bn_relu_fwd_bwd(K, shape, relu, with_res, dtype):
     N, H, W, Cc = shape
     rng = np.random.default_rng(21)

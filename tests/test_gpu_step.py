@@ -310,6 +310,25 @@ def test_kept_relu_masks_give_the_gradients_that_y_gives(dtype, C, size, batch):
     assert checked == 3
 
 
+@pytest.mark.parametrize("two_streams", [True, False])
+@pytest.mark.parametrize("widths,size,batch", [((64, 128), 8, 1), ((64, 128), 8, 21), ((64, 192), 16, 16), ((128, 512), 8, 37), ((72, 136), 8, 5)])
+def test_batch_norms_that_add_up_the_partial_sums_agree_with_the_finalising_launch(widths, size, batch, two_streams):
+    """A convolution's few partial sums per channel go straight to the batch norm behind it (widths of 64 channels; key 19 = -1
+    keeps the launch that adds them up).  Both add in double and round once: statistics to a few ulp where the inputs are the
+    same bits, the whole step to what a flipped bf16 rounding does."""
+    net = WL.mini_resnet(batch=batch, dtype="bf16", size=size, widths=widths)
+    inp = WL.make_inputs(net, 31)
+    a = _run_steps(net, inp, {}, two_streams, steps=1)
+    b = _run_steps(net, inp, {19: -1}, two_streams, steps=1)
+    first = next(i for i, L in enumerate(net.layers) if L["op"] == "bn")
+    assert torch.allclose(a.bn_save[first], b.bn_save[first], rtol=1e-6, atol=1e-7)
+    for i, L in enumerate(net.layers):
+        if L["op"] == "bn":
+            assert (a.bn_save[i] - b.bn_save[i]).norm() <= 1e-2 * b.bn_save[i].norm(), i
+            assert torch.isfinite(a.bn_save[i]).all()
+    assert abs(a.loss.item() - b.loss.item()) <= 1e-2 * abs(b.loss.item())
+
+
 @pytest.mark.parametrize("group", [2, 5, 16])
 def test_grouped_weight_gradients_give_the_same_bits(group):
     """Weight gradients forked onto the second stream one by one and several at a time, their reductions and updates
