@@ -1,8 +1,8 @@
 // Self-attention on the matrix cores for bf16 storage, head size 64 and sequences of at most 256
-// tokens (a ViT-B/16 image: 197): forward and backward of softmax(q k^T / 8) v for one (image, head)
-// per workgroup, one 32-token block per wavefront (v_mfma_f32_32x32x16_bf16, fp32 accumulation).
+// tokens (a ViT-B/16 image: 197): forward and backward of softmax(q k^T / 8) v, one (image, head) or a part of one
+// per workgroup, 32-token blocks by wavefronts (v_mfma_f32_32x32x16_bf16, fp32 accumulation).
 //
-// Every matrix of the head (K, V; in the backward pass also Q and dO) sits in LDS once, in its natural
+// The two matrices that a workgroup walks over (K and V; for dk and dv: Q and dO) sit in LDS, in their natural
 // [token][feature] layout: two planes of 32 features with 64-byte rows whose 16-byte chunks are
 // XOR-swizzled by row bits 2-3.  Products that reduce over features read fragments with 16-byte loads
 // (a token per lane); products that reduce over tokens read the same bytes with the transposing
@@ -16,7 +16,7 @@
 // 16-key step j, and the A operand is read with the same key-to-slot assignment (rows h*4..h*4+3 and
 // 8+h*4..8+h*4+3 of the step for lane half h) instead of the usual 8 consecutive ones.
 // Probabilities are not stored: the forward pass writes log-sum-exp per query and the backward pass
-// recomputes exp(s - lse).  The backward pass runs two walks in one launch: by query block for dq,
+// recomputes exp(s - lse).  The backward pass runs two kinds of workgroups in one launch: by query block for dq,
 // by key block for dk and dv (which recomputes the score tiles in the other orientation), so every
 // sum has one owner and a fixed order: no atomics, bit-reproducible.
 #include "common.h"
@@ -64,25 +64,52 @@ __device__ __forceinline__ f32x16_t zero16() {
   return z;
 }
 // Rows [0, Tp) of a head's 64 features (global rows `ld` elements apart) into the two LDS planes; rows
-// >= T are zero.  A workgroup has 64 threads per 32 rows, so every thread moves exactly four 16-byte
-// pieces of a matrix: fetch() issues the four loads, put() stores them - a caller fetches all its
+// >= T are zero.  A workgroup has at least 64 threads per 64 rows, so a thread moves at most NP = 8 16-byte
+// pieces of a matrix (4 where there are 64 threads per 32 rows): fetch() issues the loads, put() stores them - a caller fetches all its
 // matrices before it puts the first, so that a thread has all its loads in flight at once (as a loop of
 // load-then-store the sixteen loads of the backward pass ran one after the other, a third of the launch).
-struct Pieces { uint4 v[4]; };
-__device__ __forceinline__ void fetch(const bf16_t* src, size_t ld, int T, Pieces* p) {
+template <int NP> struct Pieces {
+  uint4 v[NP];
+  __device__ __forceinline__ void fetch(const bf16_t* src, size_t ld, int T) {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int i = threadIdx.x + k * blockDim.x, r = i >> 3, c8 = i & 7;
-    p->v[k] = make_uint4(0u, 0u, 0u, 0u);
-    if (r < T) p->v[k] = *reinterpret_cast<const uint4*>(src + (size_t)r * ld + c8 * 8);
+    for (int k = 0; k < NP; ++k) {
+      const int i = threadIdx.x + k * blockDim.x, r = i >> 3, c8 = i & 7;
+      v[k] = make_uint4(0u, 0u, 0u, 0u);
+      if (r < T) v[k] = *reinterpret_cast<const uint4*>(src + (size_t)r * ld + c8 * 8);
+    }
+  }
+  __device__ __forceinline__ void put(unsigned char* dst, int plane_b, int Tp) const {
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      const int i = threadIdx.x + k * blockDim.x, r = i >> 3, c8 = i & 7;
+      if (NP == 4 || r < Tp) *reinterpret_cast<uint4*>(dst + (c8 >> 2) * plane_b + chunk_off(r, c8 & 3)) = v[k];
+    }
+  }
+};
+// the four fragments of the wavefront's own tokens, straight from memory (zeros past T)
+__device__ __forceinline__ void own_frags(const bf16_t* src, size_t ld, int token, int T, int h, bf16x8_t* f) {
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (token < T) v = *reinterpret_cast<const uint4*>(src + (size_t)token * ld + ks * 16 + h * 8);
+    f[ks] = __builtin_bit_cast(bf16x8_t, v);
   }
 }
-__device__ __forceinline__ void put(const Pieces& p, unsigned char* dst, int plane_b) {
+__device__ __forceinline__ float dot8(uint4 a, uint4 b) {
+  float x[8], y[8], s = 0.f;
+  unpack8(a, x);
+  unpack8(b, y);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int i = threadIdx.x + k * blockDim.x, r = i >> 3, c8 = i & 7;
-    *reinterpret_cast<uint4*>(dst + (c8 >> 2) * plane_b + chunk_off(r, c8 & 3)) = p.v[k];
-  }
+  for (int e = 0; e < 8; ++e) s = fmaf(x[e], y[e], s);
+  return s;
+}
+// What a workgroup of a launch over `heads` (image, head) pairs works on: which pair (false: none) and which of `parts` parts of it.  The parts of a
+// pair run on one XCD (every 8th workgroup shares its L2), one behind the other.
+__device__ __forceinline__ bool head_part(int heads, int parts, int* head, int* part) {
+  const int l = blockIdx.x >> 3, g = l / parts;
+  *part = l - g * parts;
+  *head = g * 8 + (blockIdx.x & 7);
+  return *head < heads;
 }
 // a 32 x 32 tile of X Y^T over the 64 features: rows = tokens arow0.. of the LDS matrix `a`, columns =
 // the wave's own tokens, whose four fragments are in `b`
@@ -93,45 +120,59 @@ __device__ __forceinline__ f32x16_t tile_nt(const unsigned char* a, int plane_b,
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read(a, plane_b, arow0 + (lane & 31), ks * 16 + (lane >> 5) * 8), b[ks], acc, 0, 0, 0);
   return acc;
 }
-// the accumulator of a [64 features] x [32 own tokens] product: 4 consecutive features per 8-byte store
-__device__ __forceinline__ void store_cols(bf16_t* dst_row, const f32x16_t* acc, int h) {
+// The accumulator of a [64 features] x [32 own tokens] product: a lane holds four consecutive features of every eight, its
+// partner in the other half the other four.  They trade, so that a lane stores eight.
+__device__ __forceinline__ void store_cols(bf16_t* dst_row, const f32x16_t* acc, int h, bool inside) {
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-      const uint2 v = make_uint2(pack_bf16x2(acc[mt][4 * i4], acc[mt][4 * i4 + 1]), pack_bf16x2(acc[mt][4 * i4 + 2], acc[mt][4 * i4 + 3]));
-      *reinterpret_cast<uint2*>(dst_row + mt * 32 + i4 * 8 + h * 4) = v;
+    for (int i8 = 0; i8 < 2; ++i8) {
+      const f32x16_t& a = acc[mt];
+      unsigned w[4];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const unsigned lo = pack_bf16x2(a[8 * i8 + 2 * k], a[8 * i8 + 2 * k + 1]), hi = pack_bf16x2(a[8 * i8 + 4 + 2 * k], a[8 * i8 + 5 + 2 * k]);
+        const auto t = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+        w[k] = t[0];
+        w[2 + k] = t[1];
+      }
+      if (inside) *reinterpret_cast<uint4*>(dst_row + mt * 32 + i8 * 16 + h * 8) = uint4{w[0], w[1], w[2], w[3]};
     }
 }
 
-__global__ void __launch_bounds__(512) attn_mfma_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o,
-                                                            float* __restrict__ lse, int T, int heads) {
+// Forward, one walk over the keys.  The sums are kept relative to a reference m of the raw scores, common to a query's two lanes: the running
+// maximum, but raised (and what was summed rescaled) only when a score passes it by more than `kSlack` / c in the exponent, so that
+// after the first tile this hardly happens; probabilities stay below 2^kSlack, and the division by their sum comes last.  (Two walks, the
+// second with the first's sum, computed every score and exponential twice: 197 tokens, 12 heads, batch 64 30.5 -> 26.0 us, batch 8 11.0 -> 8.3,
+// batch 4 10.8 -> 7.9.)
+constexpr float kSlack = 8.f;
+template <int NP>
+__global__ void __launch_bounds__(512, 4) attn_mfma_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o,
+                                                               float* __restrict__ lse, int T, int heads, int pairs, int parts) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int NT = blockDim.x >> 6, Tp = NT * 32, plane_b = Tp * ROW_B;
+  int pair, part;
+  if (!head_part(pairs, parts, &pair, &part)) return;
+  const int NT = (T + 31) >> 5, Tp = NT * 32, plane_b = Tp * ROW_B;
   unsigned char* Ks = smem;
   unsigned char* Vs = smem + 2 * plane_b;
-  const int b = blockIdx.x / heads, head = blockIdx.x % heads, d = heads * kDH;
+  const int b = pair / heads, head = pair - b * heads, d = heads * kDH;
   const bf16_t* base = qkv + (size_t)b * T * 3 * d + head * kDH;
-  Pieces pk, pv;
-  fetch(base + d, 3 * (size_t)d, T, &pk);
-  fetch(base + 2 * d, 3 * (size_t)d, T, &pv);
+  Pieces<NP> pk, pv;
+  pk.fetch(base + d, 3 * (size_t)d, T);
+  pv.fetch(base + 2 * d, 3 * (size_t)d, T);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 31, h = lane >> 5;
-  const int q = wave * 32 + n;
+  const int blk = part * (blockDim.x >> 6) + wave, q = blk * 32 + n;
   bf16x8_t bq[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (q < T) v = *reinterpret_cast<const uint4*>(base + (size_t)q * 3 * d + ks * 16 + h * 8);
-    bq[ks] = __builtin_bit_cast(bf16x8_t, v);
-  }
-  put(pk, Ks, plane_b);
-  put(pv, Vs, plane_b);
+  own_frags(base, 3 * (size_t)d, q, T, h, bq);
+  pk.put(Ks, plane_b, Tp);
+  pv.put(Vs, plane_b, Tp);
   __syncthreads();
-  // exp(s / 8 - x) = exp2(s c - x c') with c = log2 e / 8: the scale rides in the multiply-add in front of
+  if (blk >= NT) return;
+  // exp(s / 8 - x) = exp2(s c - x c) with c = log2 e / 8: the scale rides in the multiply-add in front of
   // the exponential.  Keys past T exist only in the last tile, so only that tile masks.
   const float c2 = 0.125f * 1.44269504088896341f;
-  // first walk over the keys: running maximum (of the raw scores) and sum of this lane's half of the keys
-  float m = -INFINITY, l = 0.f;
+  float m = -INFINITY, l = 0.f;      // l: of this lane's half of the keys
+  f32x16_t oacc[2] = {zero16(), zero16()};
   for (int kt = 0; kt < NT; ++kt) {
     f32x16_t s = tile_nt(Ks, plane_b, kt * 32, bq, lane);
     if (kt == NT - 1) {
@@ -142,35 +183,26 @@ __global__ void __launch_bounds__(512) attn_mfma_fwd_kernel(const bf16_t* __rest
     float tm = s[0];
 #pragma unroll
     for (int i = 1; i < 16; ++i) tm = fmaxf(tm, s[i]);
-    const float mn = fmaxf(m, tm);
-    if (mn > -INFINITY) {
-      const float mc = mn * c2;
-      float add = 0.f;
+    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(tm), __float_as_uint(tm), false, false);
+    tm = fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
+    if (__any(tm > m + kSlack / c2)) {
+      const float mn = fmaxf(m, tm);
+      const float f = m == mn ? 1.f : __builtin_amdgcn_exp2f((m - mn) * c2);      // also where both are -inf
+      l *= f;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) add += __builtin_amdgcn_exp2f(fmaf(s[i], c2, -mc));
-      l = l * __builtin_amdgcn_exp2f(fmaf(m, c2, -mc)) + add;
+      for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[mt][i] *= f;
       m = mn;
     }
-  }
-  {
-    const float mo = __shfl_xor(m, 32, 64), lo = __shfl_xor(l, 32, 64);
-    const float M = fmaxf(m, mo);
-    l = l * __builtin_amdgcn_exp2f((m - M) * c2) + lo * __builtin_amdgcn_exp2f((mo - M) * c2);
-    m = M;
-  }
-  const float L2 = fmaf(m, c2, __builtin_amdgcn_logf(l));      // log2 of the sum of exp(s / 8)
-  const float L = L2 * 0.69314718055994531f;
-  // second walk: probabilities, and o^T += v^T p^T
-  f32x16_t oacc[2] = {zero16(), zero16()};
-  for (int kt = 0; kt < NT; ++kt) {
-    f32x16_t s = tile_nt(Ks, plane_b, kt * 32, bq, lane);
+    const float mc = m > -INFINITY ? m * c2 : 0.f;
+    float add[2] = {0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f(fmaf(s[i], c2, -L2));
-    if (kt == NT - 1) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (kt * 32 + (i >> 2) * 8 + h * 4 + (i & 3) >= T) s[i] = 0.f;
+    for (int i = 0; i < 16; ++i) {
+      s[i] = __builtin_amdgcn_exp2f(fmaf(s[i], c2, -mc));
+      add[i & 1] += s[i];
     }
+    l += add[0] + add[1];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const bf16x8_t pb = pack_frag(s, j);
@@ -179,132 +211,175 @@ __global__ void __launch_bounds__(512) attn_mfma_fwd_kernel(const bf16_t* __rest
         oacc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Vs, plane_b, mt, kt * 32 + 16 * j, lane), pb, oacc[mt], 0, 0, 0);
     }
   }
-  if (q < T) {
-    store_cols(o + ((size_t)b * T + q) * d + head * kDH, oacc, h);
-    if (h == 0) lse[((size_t)b * heads + head) * T + q] = L;
-  }
+  l += __shfl_xor(l, 32, 64);
+  const float inv = 1.f / l;
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) oacc[mt][i] *= inv;
+  store_cols(o + ((size_t)b * T + q) * d + head * kDH, oacc, h, q < T);
+  if (q < T && h == 0) lse[((size_t)b * heads + head) * T + q] = fmaf(m, c2, __builtin_amdgcn_logf(l)) * 0.69314718055994531f;
 }
 
-__global__ void __launch_bounds__(512) attn_mfma_bwd_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
-                                                            const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
-                                                            bf16_t* __restrict__ dqkv, int T, int heads) {
+// Backward: a workgroup of at most four wavefronts forms dq (part even) or dk and dv (odd) of some 32-token blocks of a pair.  It has two of the
+// four matrices in LDS and its wavefronts' own rows of the others in registers, so that two workgroups share a CU and one
+// loads while the other computes: with all four in LDS there was room for one.  197 tokens, 12 heads: batch 8 20.3 -> 14.8 us, batch 64 70 either
+// way: there the operand reads from LDS (768 clocks a tile pair of dk and dv, shared by four SIMDs), the vector ALU (800) and the matrix products (512)
+// of two wavefronts a SIMD follow one another more than they overlap.
+template <int NP>
+__global__ void __launch_bounds__(256, 2) attn_mfma_bwd_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+                                                               const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
+                                                               bf16_t* __restrict__ dqkv, int T, int heads, int pairs, int parts) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int NT = blockDim.x >> 6, Tp = NT * 32, plane_b = Tp * ROW_B;
-  unsigned char* Qs = smem;
-  unsigned char* Ks = smem + 2 * plane_b;
-  unsigned char* Vs = smem + 4 * plane_b;
-  unsigned char* Gs = smem + 6 * plane_b;
-  float* Ls = reinterpret_cast<float*>(smem + 8 * plane_b);
-  float* Ds = Ls + Tp;
-  const int b = blockIdx.x / heads, head = blockIdx.x % heads, d = heads * kDH;
-  const bf16_t* base = qkv + (size_t)b * T * 3 * d + head * kDH;
+  int pair, part;
+  if (!head_part(pairs, parts, &pair, &part)) return;
+  const int NT = (T + 31) >> 5, Tp = NT * 32, plane_b = Tp * ROW_B, waves = blockDim.x >> 6;
+  unsigned char* Xs = smem;                      // K or Q
+  unsigned char* Ys = smem + 2 * plane_b;        // V or dO
+  const int b = pair / heads, head = pair - b * heads, d = heads * kDH;
+  const size_t ld = 3 * (size_t)d;
+  const bf16_t* base = qkv + (size_t)b * T * ld + head * kDH;
   const bf16_t* gbase = d_o + (size_t)b * T * d + head * kDH;
   const bf16_t* obase = o + (size_t)b * T * d + head * kDH;
-  bf16_t* dbase = dqkv + (size_t)b * T * 3 * d + head * kDH;
-  {
-    Pieces pq, pk, pv, pg;
-    fetch(base, 3 * (size_t)d, T, &pq);
-    fetch(base + d, 3 * (size_t)d, T, &pk);
-    fetch(base + 2 * d, 3 * (size_t)d, T, &pv);
-    fetch(gbase, (size_t)d, T, &pg);
-    put(pq, Qs, plane_b);
-    put(pk, Ks, plane_b);
-    put(pv, Vs, plane_b);
-    put(pg, Gs, plane_b);
-  }
-  for (int t = threadIdx.x; t < Tp; t += blockDim.x) {
-    float D = 0.f, L = 0.f;
-    if (t < T) {
-#pragma unroll
-      for (int c = 0; c < kDH; c += 8) {
-        float a[8], g[8];
-        load8(obase + (size_t)t * d + c, a);
-        load8(gbase + (size_t)t * d + c, g);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) D += a[k] * g[k];
-      }
-      L = lse[((size_t)b * heads + head) * T + t];
-    }
-    // stored as the walks use them: exp(s / 8 - L) = exp2(s c - L log2 e) with c = log2 e / 8, and
-    // ds = p (dp - D) / 8 = p (dp / 8 - D / 8)
-    Ds[t] = D * 0.125f;
-    Ls[t] = L * 1.44269504088896341f;
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 31, h = lane >> 5;
-  const float scale = 0.125f, c2 = 0.125f * 1.44269504088896341f;
-  const int own = wave * 32 + n;           // this lane's query (first walk) or key (second walk)
+  const float* lrow = lse + (size_t)pair * T;
+  bf16_t* dbase = dqkv + (size_t)b * T * ld + head * kDH;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), n = lane & 31, h = lane >> 5;
+  const float scale = 0.125f, c2 = 0.125f * 1.44269504088896341f, log2e = 1.44269504088896341f;
+  const int group = part >> 1, groups = parts >> 1;      // this workgroup's blocks: every groups * waves-th
   // No score is masked in either walk.  Tokens past T are rows of zeros in all four matrices, with
   // L = D = 0: their probabilities are finite, and wherever one enters a sum it multiplies a zero row
   // of the other operand (a key past T: its row of K in dq; a query past T: its rows of dO and Q in dv
   // and dk), or lands in an output column that is not stored (the lane's own token past T).
+  if ((part & 1) == 0) {
+    // ---- by query block: dq^T = k^T ds^T ----
+    Pieces<NP> px, py;
+    px.fetch(base + d, ld, T);
+    py.fetch(base + 2 * d, ld, T);
+    px.put(Xs, plane_b, Tp);
+    py.put(Ys, plane_b, Tp);
+    bool staged = false;
+    for (int blk = group * waves + wave; blk < NT || !staged; blk += groups * waves) {
+      const int own = blk * 32 + n;            // this lane's query
+      bf16x8_t bq[4], bg[4], bo[4];
+      own_frags(base, ld, own, T, h, bq);
+      own_frags(gbase, d, own, T, h, bg);
+      own_frags(obase, d, own, T, h, bo);
+      // exp(s / 8 - L) = exp2(s c - L log2 e) with c = log2 e / 8, and ds = p (dp - D) / 8 = p (dp / 8 - D / 8)
+      const float L2 = own < T ? lrow[own] * log2e : 0.f;
+      float D = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) D += dot8(__builtin_bit_cast(uint4, bo[ks]), __builtin_bit_cast(uint4, bg[ks]));
+      D += __shfl_xor(D, 32, 64);
+      const float Dsc = D * scale;
+      if (!staged) __syncthreads();
+      staged = true;
+      if (blk >= NT) break;
+      f32x16_t acc[2] = {zero16(), zero16()};
+      for (int kt = 0; kt < NT; ++kt) {
+        const f32x16_t s = tile_nt(Xs, plane_b, kt * 32, bq, lane);     // [key][query]
+        f32x16_t dp = tile_nt(Ys, plane_b, kt * 32, bg, lane);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dp[i] = __builtin_amdgcn_exp2f(fmaf(s[i], c2, -L2)) * fmaf(dp[i], scale, -Dsc);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const bf16x8_t dsb = pack_frag(dp, j);
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt)
+            acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Xs, plane_b, mt, kt * 32 + 16 * j, lane), dsb, acc[mt], 0, 0, 0);
+        }
+      }
+      store_cols(dbase + (size_t)own * ld, acc, h, own < T);
+    }
+  } else {
+    // ---- by key block: dv^T = do^T p, dk^T = q^T ds ----
+    float* Ls = reinterpret_cast<float*>(smem + 4 * plane_b);
+    float* Ds = Ls + Tp;
+    {
+      Pieces<NP> px, py, po;
+      px.fetch(base, ld, T);
+      py.fetch(gbase, d, T);
+      po.fetch(obase, d, T);
+      px.put(Xs, plane_b, Tp);
+      py.put(Ys, plane_b, Tp);
+      // D of a token: the eight lanes that hold its pieces
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        float D = dot8(po.v[k], py.v[k]);
+        D += __shfl_xor(D, 1, 64);
+        D += __shfl_xor(D, 2, 64);
+        D += __shfl_xor(D, 4, 64);
+        const int i = threadIdx.x + k * blockDim.x, r = i >> 3;
+        if ((i & 7) == 0 && r < Tp) Ds[r] = D * scale;
+      }
+      for (int t = threadIdx.x; t < Tp; t += blockDim.x) Ls[t] = t < T ? lrow[t] * log2e : 0.f;
+    }
+    bool staged = false;
+    for (int blk = group * waves + wave; blk < NT || !staged; blk += groups * waves) {
+      const int own = blk * 32 + n;            // this lane's key
+      bf16x8_t bk[4], bv[4];
+      own_frags(base + d, ld, own, T, h, bk);
+      own_frags(base + 2 * d, ld, own, T, h, bv);
+      if (!staged) __syncthreads();
+      staged = true;
+      if (blk >= NT) break;
+      f32x16_t dk[2] = {zero16(), zero16()}, dv[2] = {zero16(), zero16()};
+      for (int qt = 0; qt < NT; ++qt) {
+        f32x16_t p = tile_nt(Xs, plane_b, qt * 32, bk, lane);           // [query][key]
+        f32x16_t dp = tile_nt(Ys, plane_b, qt * 32, bv, lane);
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const int r0 = qt * 32 + i4 * 8 + h * 4;
+          const float4 L4 = *reinterpret_cast<const float4*>(Ls + r0);
+          const float4 D4 = *reinterpret_cast<const float4*>(Ds + r0);
+          const float Lr[4] = {L4.x, L4.y, L4.z, L4.w}, Dr[4] = {D4.x, D4.y, D4.z, D4.w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int i = i4 * 4 + k;
+            const float pp = __builtin_amdgcn_exp2f(fmaf(p[i], c2, -Lr[k]));
+            p[i] = pp;
+            dp[i] = pp * fmaf(dp[i], scale, -Dr[k]);
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const bf16x8_t pb = pack_frag(p, j), dsb = pack_frag(dp, j);
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) {
+            dv[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Ys, plane_b, mt, qt * 32 + 16 * j, lane), pb, dv[mt], 0, 0, 0);
+            dk[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Xs, plane_b, mt, qt * 32 + 16 * j, lane), dsb, dk[mt], 0, 0, 0);
+          }
+        }
+      }
+      store_cols(dbase + (size_t)own * ld + d, dk, h, own < T);
+      store_cols(dbase + (size_t)own * ld + 2 * d, dv, h, own < T);
+    }
+  }
+}
 
-  // ---- by query block: dq^T = k^T ds^T ----
-  {
-    bf16x8_t bq[4], bg[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      bq[ks] = frag_read(Qs, plane_b, own, ks * 16 + h * 8);
-      bg[ks] = frag_read(Gs, plane_b, own, ks * 16 + h * 8);
-    }
-    const float L2 = Ls[own], Dsc = Ds[own];
-    f32x16_t acc[2] = {zero16(), zero16()};
-    for (int kt = 0; kt < NT; ++kt) {
-      const f32x16_t s = tile_nt(Ks, plane_b, kt * 32, bq, lane);     // [key][query]
-      f32x16_t dp = tile_nt(Vs, plane_b, kt * 32, bg, lane);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) dp[i] = __builtin_amdgcn_exp2f(fmaf(s[i], c2, -L2)) * fmaf(dp[i], scale, -Dsc);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const bf16x8_t dsb = pack_frag(dp, j);
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-          acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Ks, plane_b, mt, kt * 32 + 16 * j, lane), dsb, acc[mt], 0, 0, 0);
-      }
-    }
-    if (own < T) store_cols(dbase + (size_t)own * 3 * d, acc, h);
-  }
-  // ---- by key block: dv^T = do^T p, dk^T = q^T ds ----
-  {
-    bf16x8_t bk[4], bv[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      bk[ks] = frag_read(Ks, plane_b, own, ks * 16 + h * 8);
-      bv[ks] = frag_read(Vs, plane_b, own, ks * 16 + h * 8);
-    }
-    f32x16_t dk[2] = {zero16(), zero16()}, dv[2] = {zero16(), zero16()};
-    for (int qt = 0; qt < NT; ++qt) {
-      f32x16_t p = tile_nt(Qs, plane_b, qt * 32, bk, lane);           // [query][key]
-      f32x16_t dp = tile_nt(Gs, plane_b, qt * 32, bv, lane);
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        const int r0 = qt * 32 + i4 * 8 + h * 4;
-        const float4 L4 = *reinterpret_cast<const float4*>(Ls + r0);
-        const float4 D4 = *reinterpret_cast<const float4*>(Ds + r0);
-        const float Lr[4] = {L4.x, L4.y, L4.z, L4.w}, Dr[4] = {D4.x, D4.y, D4.z, D4.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int i = i4 * 4 + k;
-          const float pp = __builtin_amdgcn_exp2f(fmaf(p[i], c2, -Lr[k]));
-          p[i] = pp;
-          dp[i] = pp * fmaf(dp[i], scale, -Dr[k]);
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const bf16x8_t pb = pack_frag(p, j), dsb = pack_frag(dp, j);
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-          dv[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Gs, plane_b, mt, qt * 32 + 16 * j, lane), pb, dv[mt], 0, 0, 0);
-          dk[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Qs, plane_b, mt, qt * 32 + 16 * j, lane), dsb, dk[mt], 0, 0, 0);
-        }
-      }
-    }
-    if (own < T) {
-      store_cols(dbase + (size_t)own * 3 * d + d, dk, h);
-      store_cols(dbase + (size_t)own * 3 * d + 2 * d, dv, h);
-    }
-  }
+template <typename Kern> int raise_lds(Kern kern, bool* raised, int bytes) {
+  if (*raised) return CNNK_OK;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return CNNK_ERR_HIP;
+  *raised = true;
+  return CNNK_OK;
+}
+template <int NP>
+int fwd_launch(const cnnk_attn_desc* d, const void* qkv, void* o, float* lse, int waves, int parts, hipStream_t st) {
+  static bool raised = false;
+  const int NT = (d->T + 31) / 32, pairs = d->B * d->heads;
+  const int rc = raise_lds(attn_mfma_fwd_kernel<NP>, &raised, 4 * 8 * 32 * ROW_B);
+  if (rc != CNNK_OK) return rc;
+  attn_mfma_fwd_kernel<NP><<<(pairs + 7) / 8 * 8 * parts, 64 * waves, (size_t)4 * NT * 32 * ROW_B, st>>>((const bf16_t*)qkv, (bf16_t*)o, lse, d->T, d->heads, pairs, parts);
+  return launch_status();
+}
+template <int NP>
+int bwd_launch(const cnnk_attn_desc* d, const void* qkv, const void* o, const void* d_o, const float* lse, void* dqkv, int waves, int parts, hipStream_t st) {
+  static bool raised = false;
+  const int NT = (d->T + 31) / 32, pairs = d->B * d->heads;
+  const int rc = raise_lds(attn_mfma_bwd_kernel<NP>, &raised, 4 * 8 * 32 * ROW_B + 2 * 8 * 32 * 4);
+  if (rc != CNNK_OK) return rc;
+  attn_mfma_bwd_kernel<NP><<<(pairs + 7) / 8 * 8 * parts, 64 * waves, (size_t)4 * NT * 32 * ROW_B + (size_t)2 * NT * 32 * sizeof(float), st>>>(
+      (const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)d_o, lse, (bf16_t*)dqkv, d->T, d->heads, pairs, parts);
+  return launch_status();
 }
 }  // namespace
 
@@ -313,30 +388,18 @@ bool attn_mfma_supported(const cnnk_attn_desc* d) {
 }
 
 int attn_mfma_fwd(const cnnk_attn_desc* d, const void* qkv, void* o, float* lse, hipStream_t st) {
-  const int NT = (d->T + 31) / 32;
-  const size_t lds = (size_t)4 * NT * 32 * ROW_B;
-  static bool raised = false;
-  if (!raised) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(attn_mfma_fwd_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 32 * 4 * ROW_B) != hipSuccess)
-      return CNNK_ERR_HIP;
-    raised = true;
-  }
-  attn_mfma_fwd_kernel<<<d->B * d->heads, 64 * NT, lds, st>>>((const bf16_t*)qkv, (bf16_t*)o, lse, d->T, d->heads);
-  return launch_status();
+  const int NT = (d->T + 31) / 32, half = (NT + 1) / 2;
+  // Long sequences in two halves of their queries where that still gives a CU one workgroup at most (197 tokens: 96 pairs 8.3 us,
+  // whole 9.1; 192 pairs 11.5, whole 10.6).
+  if (NT > 4 && d->B * d->heads <= 128) return fwd_launch<8>(d, qkv, o, lse, half, 2, st);
+  return fwd_launch<4>(d, qkv, o, lse, NT, 1, st);
 }
 
 int attn_mfma_bwd(const cnnk_attn_desc* d, const void* qkv, const void* o, const void* d_o, const float* lse, void* dqkv,
                   hipStream_t st) {
-  const int NT = (d->T + 31) / 32;
-  const size_t lds = (size_t)8 * NT * 32 * ROW_B + (size_t)2 * NT * 32 * sizeof(float);
-  static bool raised = false;
-  if (!raised) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(attn_mfma_bwd_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            8 * 8 * 32 * ROW_B + 2 * 8 * 32 * 4) != hipSuccess)
-      return CNNK_ERR_HIP;
-    raised = true;
-  }
-  attn_mfma_bwd_kernel<<<d->B * d->heads, 64 * NT, lds, st>>>((const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)d_o, lse,
-                                                            (bf16_t*)dqkv, d->T, d->heads);
-  return launch_status();
+  const int NT = (d->T + 31) / 32, half = (NT + 1) / 2;
+  // Up to four wavefronts, a block each; long sequences: two blocks each, or twice the workgroups where those all fit the device at once
+  // (197 tokens: 96 pairs 14.8 us, with two workgroups a pair 15.5).
+  if (NT <= 4) return bwd_launch<4>(d, qkv, o, d_o, lse, dqkv, NT, 2, st);
+  return bwd_launch<8>(d, qkv, o, d_o, lse, dqkv, half, d->B * d->heads <= 128 ? 4 : 2, st);
 }

@@ -239,10 +239,22 @@ def test_attention(K, B, T, heads, dh, dtype):
         _attention_case(K, B, T, heads, dh, dtype)
 
 
-def _attention_case(K, B, T, heads, dh, dtype):
+# five to eight blocks of tokens, in one or two parts to a head; 128 heads in all and more, not a multiple of eight.  rise: scores
+# that climb (or fall) by that much over the keys, so that the sums' reference is raised in several tiles, by little and by much
+@pytest.mark.parametrize("B,T,heads,rise", [(1, 129, 3, 0), (1, 160, 2, 0), (3, 161, 1, 0), (2, 192, 5, 0), (1, 225, 1, 0), (11, 129, 12, 0),
+                                            (43, 130, 3, 0), (2, 197, 2, 12), (2, 197, 2, 60), (2, 197, 2, -60), (1, 65, 3, 30)])
+def test_attention_in_parts(K, B, T, heads, rise):
+    _attention_case(K, B, T, heads, 64, "bf16", rise)
+
+
+def _attention_case(K, B, T, heads, dh, dtype, rise=None):
     rng = np.random.default_rng(B * 7 + T * 13 + heads + dh)
     d = heads * dh
-    qkv = rep(rng.standard_normal((B, T, 3 * d)) * 1.3, dtype)
+    qkv = rng.standard_normal((B, T, 3 * d)) * 1.3
+    if rise:        # one feature carries it: 8 of every query times rise * t / T of key t, over the scale of 8
+        qkv[:, :, 0:d:dh] = 8.0
+        qkv[:, :, d:2 * d:dh] = (rise * np.arange(T) / T)[None, :, None]
+    qkv = rep(qkv, dtype)
     dO = rep(rng.standard_normal((B, T, d)), dtype)
     O, A = V.attention_fwd(qkv, heads)
     ad = K.attn_desc(B, T, heads, dh, dt_of(K, dtype))
@@ -250,11 +262,17 @@ def _attention_case(K, B, T, heads, dh, dtype):
     lse = torch.zeros((B, heads, T), device="cuda:0")
     K.cnnk_attention_fwd(ad, gq, go, lse)
     torch.cuda.synchronize()
-    assert max_rel_err(host(go), O) <= (OUT_TOL[dtype] if dtype == "bf16" else 5e-5)
-    q, k = (qkv[:, :, i * d:(i + 1) * d].reshape(B, T, heads, dh).transpose(0, 2, 1, 3) for i in range(2))
+    q, k, v = (qkv[:, :, i * d:(i + 1) * d].reshape(B, T, heads, dh).transpose(0, 2, 1, 3) for i in range(3))
+    if rise is None:
+        assert max_rel_err(host(go), O) <= (OUT_TOL[dtype] if dtype == "bf16" else 5e-5)
+    else:           # the probabilities are rounded to bf16 in front of their product, its result in storage: 2^-8 of either
+        weight = (A @ np.abs(v)).transpose(0, 2, 1, 3).reshape(B, T, d)
+        assert np.all(np.abs(host(go) - O) <= 2.0 ** -8 * 1.01 * (np.abs(O) + weight))
     S = q @ k.transpose(0, 1, 3, 2) / np.sqrt(dh)
     want_lse = np.log(np.exp(S - S.max(-1, keepdims=True)).sum(-1)) + S.max(-1)
     assert np.abs(host(lse) - want_lse).max() <= 1e-4
+    if rise:        # D cancels most of the query gradients then: what is left is the rounding of the output
+        return
     # backward from the oracle's own output (both sides differentiate at the same point)
     Oq = rep(O, dtype)
     want = V.attention_bwd(dO, qkv, A, heads)
