@@ -34,36 +34,46 @@ inline int reduce_blocks(size_t m, int C) {
   return (int)nb;
 }
 
-// Sum the NV per-thread vectors of 8 channels over the threads that share a channel octet and
-// write them to part[v][c][block] (row block fastest, so the finaliser reads rows).
-template <int NV, class W>
+// Sum the two per-thread vectors of 8 channels over the threads that share a channel octet and
+// write them to part[v][c][block] (row block fastest, so the finaliser reads rows).  Where there are fewer sums than threads, `groups` threads share one, each
+// a run of the rows (one thread each, the 128 rows of 16 channels were a chain of 128 reads).
+template <class W>
 __device__ __forceinline__ void block_reduce_store(float (*acc)[8], const W& w, int C, float* __restrict__ part) {
-  __shared__ float red[kT * 8];
-  const int tid = threadIdx.x, width = w.lanes * 8;
+  __shared__ float red[2][kT * 8];
+  __shared__ float sub[kT];
+  const int tid = threadIdx.x, width = w.lanes * 8, sums = 2 * width;
+  if (w.rl < w.rows) {
 #pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    __syncthreads();
-    if (w.rl < w.rows) {
+    for (int v = 0; v < 2; ++v)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) red[tid * 8 + e] = acc[v][e];
+      for (int e = 0; e < 8; ++e) red[v][tid * 8 + e] = acc[v][e];
+  }
+  __syncthreads();
+  if (sums <= kT / 2) {
+    const int groups = kT / sums, per = (w.rows + groups - 1) / groups, i = tid % sums, g = tid / sums;
+    float s = 0.f;
+    if (g < groups) {
+      const float* q = i < width ? &red[0][i] : &red[1][i - width];
+      for (int r = g * per; r < min((g + 1) * per, w.rows); ++r) s += q[r * width];
     }
+    sub[tid] = s;
     __syncthreads();
-    for (int i = tid; i < width; i += kT) {
-      float s = 0.f;
-      for (int r = 0; r < w.rows; ++r) s += red[r * width + i];
-      part[((size_t)v * C + w.slab0 + i) * w.blocks + w.block] = s;
+    if (tid < sums) {
+      for (int k = 1; k < groups; ++k) s += sub[k * sums + tid];
+      part[((size_t)(i >= width) * C + w.slab0 + (i >= width ? i - width : i)) * w.blocks + w.block] = s;
     }
+    return;
+  }
+  for (int i = tid; i < sums; i += kT) {
+    const int v = i >= width, c = i - v * width;
+    float s = 0.f;
+    for (int r = 0; r < w.rows; ++r) s += red[v][r * width + c];
+    part[((size_t)v * C + w.slab0 + c) * w.blocks + w.block] = s;
   }
 }
 
 // Finalising reduction: one workgroup per channel sums the nb per-workgroup partials
 // part[v][c][0..nb) in double (coalesced rows, fixed-order tree).  Result valid in thread 0.
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 // One wavefront per channel (four channels per workgroup): the lanes stride over the nb partials,
 // the xor-butterfly gives every lane the total.  Fixed order, no LDS, no barrier.
 constexpr int kFinCh = kT / 64;   // channels per finalising workgroup
@@ -96,8 +106,8 @@ __device__ __forceinline__ void finalize_sums(const float* __restrict__ part, in
         s2 += (double)v2[k];
       }
   }
-  *s1_out = wave_sum_f64(s1);
-  *s2_out = wave_sum_f64(s2);
+  *s1_out = wave_sum(s1);
+  *s2_out = wave_sum(s2);
 }
 
 // Row walk of the reductions and of the element-wise kernels: a thread owns one octet of
@@ -212,7 +222,7 @@ __global__ void __launch_bounds__(kT) stats_partial_kernel(const T* __restrict__
       }
     });
   }
-  block_reduce_store<2>(acc, w, C, part);
+  block_reduce_store(acc, w, C, part);
 }
 
 // mode 0: write save_mean / save_invstd (+ running stats); mode 1: write plain sum, sum of squares.
@@ -287,8 +297,8 @@ __device__ __forceinline__ void finalize_sums_wide(const float* __restrict__ par
         s2 += (double)v2[k];
       }
   }
-  s1 = wave_sum_f64(s1);
-  s2 = wave_sum_f64(s2);
+  s1 = wave_sum(s1);
+  s2 = wave_sum(s2);
   if (lane == 0) { comb[0][wave] = s1; comb[1][wave] = s2; }
   __syncthreads();
   double t1 = comb[0][0], t2 = comb[1][0];
@@ -516,7 +526,7 @@ __global__ void __launch_bounds__(kT) bwd_partial_kernel(const T* __restrict__ d
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[1][e] *= is[e];
   }
-  block_reduce_store<2>(acc, w, C, part);
+  block_reduce_store(acc, w, C, part);
 }
 
 __global__ void __launch_bounds__(kT) bwd_finalize_kernel(const float* __restrict__ part, int nb, int C,

@@ -8,10 +8,12 @@ namespace {
 constexpr int kT = 256;
 constexpr int kMaxClasses = 4096;
 constexpr int kLT = 1024;   // threads of the logits kernel
+constexpr int kWaveClasses = 1024;
 
 // One workgroup per sample: z = W x + b by wave-level dot products, then the softmax.  The kernel
-// is latency-bound (a sample's 100 dot products), so the workgroup is wide: 16 wavefronts take 4
-// classes each per round.
+// is latency-bound (a sample's 100 dot products), so the workgroup is wide, 16 wavefronts take 8
+// classes each per round (4 a round: two rounds of memory latency for 100 classes), and up to kWaveClasses classes every wavefront forms the
+// maximum and the sum of the exponentials for itself: one barrier instead of four (768 features, 100 classes, 4 samples 15.2 -> 12.4 us).
 template <typename T>
 __global__ void __launch_bounds__(kLT) logits_softmax_kernel(const T* __restrict__ x, const float* __restrict__ W,
                                                             const float* __restrict__ b,
@@ -23,9 +25,10 @@ __global__ void __launch_bounds__(kLT) logits_softmax_kernel(const T* __restrict
   __shared__ int redi[kLT / 64];
   const int n = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const T* xr = x + (size_t)n * F;
+  const int lab = labels[n];
   if (vec) {
     // F % 8 == 0 and F <= 2048: the sample's features stay in registers (8 consecutive per lane
-    // and 512-feature chunk), weight rows stream in as 32-byte pieces, four classes in flight
+    // and 512-feature chunk), weight rows stream in as 32-byte pieces, eight classes in flight
     float xv[4][8];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -35,9 +38,15 @@ __global__ void __launch_bounds__(kLT) logits_softmax_kernel(const T* __restrict
 #pragma unroll
         for (int e = 0; e < 8; ++e) xv[c][e] = 0.f;
     }
-    for (int j0 = wave; j0 < K; j0 += 4 * (kLT / 64)) {
-      float acc[4] = {0.f, 0.f, 0.f, 0.f};
-      // Unconditional loads, so that the four classes' weight pieces are in flight together (under
+    constexpr int Q = 8;
+    for (int j0 = wave; j0 < K; j0 += Q * (kLT / 64)) {
+      float acc[Q], bj[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        acc[q] = 0.f;
+        bj[q] = b[min(j0 + q * (kLT / 64), K - 1)];
+      }
+      // Unconditional loads, so that the classes' weight pieces are in flight together (under
       // per-lane conditions the compiler waits for every load before it issues the next): a class
       // past the end re-reads the last one (its logit is not stored), a lane past the end of the
       // features reads the row's start against features that are zero.
@@ -46,22 +55,19 @@ __global__ void __launch_bounds__(kLT) logits_softmax_kernel(const T* __restrict
         if (c * 512 >= F) break;           // uniform
         const int f0 = (lane + 64 * c) * 8;
         const int fl = f0 < F ? f0 : 0;
-        float wv[4][8];
+        float wv[Q][8];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int j = min(j0 + q * (kLT / 64), K - 1);
-          load8(W + (size_t)j * F + fl, wv[q]);
-        }
+        for (int q = 0; q < Q; ++q) load8(W + (size_t)min(j0 + q * (kLT / 64), K - 1) * F + fl, wv[q]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < Q; ++q)
 #pragma unroll
           for (int e = 0; e < 8; ++e) acc[q] = fmaf(xv[c][e], wv[q][e], acc[q]);
       }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < Q; ++q) {
         const int j = j0 + q * (kLT / 64);
         const float sq = wave_sum(acc[q]);
-        if (lane == 0 && j < K) z[j] = sq + b[j];
+        if (lane == 0 && j < K) z[j] = sq + bj[q];
       }
     }
   } else {
@@ -84,35 +90,39 @@ __global__ void __launch_bounds__(kLT) logits_softmax_kernel(const T* __restrict
   }
   __syncthreads();
   // max and its lowest index
+  const bool alone = K <= kWaveClasses;             // every wavefront for itself
+  const int first = alone ? lane : tid, step = alone ? 64 : kLT;
   float mx = -INFINITY;
   int arg = 0x7fffffff;
-  for (int j = tid; j < K; j += kLT)
+  for (int j = first; j < K; j += step)
     if (z[j] > mx) { mx = z[j]; arg = j; }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float om = __shfl_xor(mx, o, 64);
-    const int oa = __shfl_xor(arg, o, 64);
-    if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
+  {
+    const float wm = wave_max(mx);
+    arg = wave_min(mx == wm ? arg : 0x7fffffff);
+    mx = wm;
   }
-  if (lane == 0) { red[wave] = mx; redi[wave] = arg; }
-  __syncthreads();
-  mx = red[0]; arg = redi[0];
-  for (int w = 1; w < kLT / 64; ++w)
-    if (red[w] > mx || (red[w] == mx && redi[w] < arg)) { mx = red[w]; arg = redi[w]; }
+  if (!alone) {
+    if (lane == 0) { red[wave] = mx; redi[wave] = arg; }
+    __syncthreads();
+    mx = red[0]; arg = redi[0];
+    for (int w = 1; w < kLT / 64; ++w)
+      if (red[w] > mx || (red[w] == mx && redi[w] < arg)) { mx = red[w]; arg = redi[w]; }
+    __syncthreads();
+  }
   // A scan that starts from class 0 and moves only on a strictly greater logit stays at class 0
   // when no logit exceeds -inf (a row of -inf or NaN) and when the first logit is NaN (nothing
   // compares greater than NaN): the predicted class of such a row is 0.
   if (arg == 0x7fffffff || z[0] != z[0]) arg = 0;
-  __syncthreads();
   float se = 0.f;
-  for (int j = tid; j < K; j += kLT) se += expf(z[j] - mx);
+  for (int j = first; j < K; j += step) se += expf(z[j] - mx);
   se = wave_sum(se);
-  if (lane == 0) red[wave] = se;
-  __syncthreads();
-  se = 0.f;
-  for (int w = 0; w < kLT / 64; ++w) se += red[w];
+  if (!alone) {
+    if (lane == 0) red[wave] = se;
+    __syncthreads();
+    se = 0.f;
+    for (int w = 0; w < kLT / 64; ++w) se += red[w];
+  }
   const float lse = mx + logf(se);
-  const int lab = labels[n];
   if (tid == 0) {
     pred[n] = arg;
     // a label outside [0, K) has no target logit: the sample's loss, and with it the mean, is NaN

@@ -308,7 +308,9 @@ def test_conv_patch_kernels_without_the_pixel_permutation(K, shape):
                                                   # the passes in slabs of 64 channels: a row past the 32 of one pass, 128 partials,
                                                   # one more (general); few rows would leave a variance near 0 in some channel
                                                   ((33, 1, 1, 128), True, False), ((16, 32, 32, 64), True, True),
-                                                  ((16385, 1, 1, 64), True, True), ((33, 2, 2, 320), True, False)])
+                                                  ((16385, 1, 1, 64), True, True), ((33, 2, 2, 320), True, False),
+                                                  # channels whose sums several threads share
+                                                  ((37, 2, 1, 40), True, False), ((300, 1, 1, 8), False, True)])
 def test_bn_relu_fwd_bwd(K, shape, relu, with_res, dtype):
     N, H, W, Cc = shape
     rng = np.random.default_rng(21)
@@ -425,7 +427,9 @@ def test_pool_fwd_bwd(K, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("N,F,classes", [(8, 16, 100), (256, 512, 100), (33, 640, 100), (5, 2048, 10), (7, 52, 10), (3, 1024, 7), (64, 1536, 100), (4, 2056, 5)])
+@pytest.mark.parametrize("N,F,classes", [(8, 16, 100), (256, 512, 100), (33, 640, 100), (5, 2048, 10), (7, 52, 10), (3, 1024, 7), (64, 1536, 100), (4, 2056, 5),
+                                         # classes: one past a round of a workgroup, the last that a wavefront takes alone, one more, the most
+                                         (3, 24, 129), (3, 64, 1024), (2, 52, 1025), (2, 64, 1025), (2, 16, 4096)])
 def test_fc_softmax_xent(K, N, F, classes, dtype):
     rng = np.random.default_rng(41)
     x = rep(rng.standard_normal((N, F)), dtype)
