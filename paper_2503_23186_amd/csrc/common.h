@@ -90,6 +90,14 @@ __device__ __forceinline__ void store8(float* p, const float* f) {
   *reinterpret_cast<float4*>(p + 4) = make_float4(f[4], f[5], f[6], f[7]);
 }
 
+// store8 that leaves in f what was stored
+__device__ __forceinline__ void store8_back(bf16_t* p, float* f) {
+  const uint4 v = {pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7])};
+  *reinterpret_cast<uint4*>(p) = v;
+  unpack8(v, f);
+}
+__device__ __forceinline__ void store8_back(float* p, float* f) { store8(p, f); }
+
 // eight bf16 plus eight bf16, rounded again
 __device__ __forceinline__ uint4 add_bf16x8(uint4 a, uint4 b) {
   float x[8], y[8];

@@ -214,6 +214,7 @@ extern thread_local int t_cnnk_wgrad_cus;
 struct PartSums {
   const float* part;
   int nb;
+  bool shifted;        // of add_stats: relative to the first row, any nb
 };
 extern thread_local PartSums* t_cnnk_part_sums;
 
@@ -236,5 +237,9 @@ int bn_relu_bwd(const cnnk_bn_desc* d, const void* dy, const void* x, const void
 // per-channel sum / sum of squares of a tensor with C channels (used when the conv kernel
 // itself does not produce them)
 size_t channel_stats_ws(size_t m, int C);
+// y = a + b with the partial sums that the batch norm of y, the very next call, begins with (channel_stats_ws bytes of ws)
+int add_stats(int dtype, const void* a, const void* b, void* y, size_t m, int C, PartSums* out, void* ws, hipStream_t st);
+// d0 = src and d1 = src, or += where acc0, acc1 say so: cnnk_grad_route to two different tensors with one read
+int grad_route2(size_t n, int dtype, const void* src, void* d0, int acc0, void* d1, int acc1, hipStream_t st);
 int channel_stats(int dtype, const void* x, size_t m, int C, float* ch_sum, float* ch_sumsq, void* ws,
                   hipStream_t st);

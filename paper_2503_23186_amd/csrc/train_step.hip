@@ -334,7 +334,7 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
   auto takes_partials = [&](int i) {
     return i + 1 < n && L[i + 1].op == CNNK_OP_BN && L[i + 1].in0 == L[i].out && L[i + 1].d.bn.C == L[i].d.conv.Cout;
   };
-  PartSums handed{nullptr, 0};     // the last convolution's
+  PartSums handed{nullptr, 0, false};     // the last layer's
   bool wt_forked = false;
   bool x8_valid = false;   // the forward pass left the first layer's 8-channel input copy in place
   // ---- forward pass and loss ---------------------------------------------------------------
@@ -348,7 +348,7 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
           hipStreamWaitEvent(aux, (hipEvent_t)B->ev_fork, 0) != hipSuccess)
         return CNNK_ERR_HIP;
       const bool sums = c.d.conv.Cout % 8 == 0 && c.d.conv.Cout <= 2048;
-      PartSums ps{nullptr, 0};
+      PartSums ps{nullptr, 0, false};
       if (sums && takes_partials(s0)) t_cnnk_part_sums = &ps;
       rc = cnnk_conv2d_fwd(&c.d.conv, B->act[c.in0], B->param_lp[c.p0], B->act[c.out], sums ? aux_stat : nullptr,
                            sums ? aux_stat + 2048 : nullptr, aux_scratch, aux_scratch_b, aux);
@@ -381,7 +381,7 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
         // the 8-channel copy of the network input is kept for this layer's weight gradient
         X8Cache x8c{reinterpret_cast<bf16_t*>(wt_region + w.x8_off), false};
         if (i == w.x8_layer) t_cnnk_x8_cache = &x8c;
-        handed.nb = 0;
+        handed = {nullptr, 0, false};
         if (ssum && takes_partials(i)) t_cnnk_part_sums = &handed;
         rc = cnnk_conv2d_fwd(&l.d.conv, B->act[l.in0], wt, B->act[l.out], ssum, ssum ? ssum + 2048 : nullptr, ws, wsb,
                              stream);
@@ -400,8 +400,8 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
         const float* ssum = sb >= 0 ? stat_base + (size_t)sb * 4096 : nullptr;
         rc = bn_relu_fwd(&l.d.bn, B->act[l.in0], l.in1 >= 0 ? B->act[l.in1] : nullptr, B->param[l.p0], B->param[l.p1],
                          B->act[l.out], mask_of(i), B->bn_save[i], B->bn_save[i] + C, run, run ? run + C : nullptr, ssum,
-                         ssum ? ssum + 2048 : nullptr, ssum ? &handed : nullptr, ws, wsb, stream);
-        handed.nb = 0;
+                         ssum ? ssum + 2048 : nullptr, &handed, ws, wsb, stream);
+        handed = {nullptr, 0, false};
         if (sb >= 0) stat_slot[sb] = -1;
         break;
       }
@@ -409,7 +409,13 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
         rc = cnnk_pool_fwd(&l.d.pool, B->act[l.in0], B->act[l.out], B->pool_idx[i], stream);
         break;
       case CNNK_OP_ADD:
-        rc = cnnk_add(w.slot_elems[l.out], w.dtype, B->act[l.in0], B->act[l.in1], B->act[l.out], stream);
+        // a batch norm of the sum that comes next starts from partial sums made here
+        if (i + 1 < n && L[i + 1].op == CNNK_OP_BN && L[i + 1].in0 == l.out && g_cnnk_tune[20] >= 0) {
+          const size_t rows = w.slot_elems[l.out] / L[i + 1].d.bn.C;
+          rc = add_stats(w.dtype, B->act[l.in0], B->act[l.in1], B->act[l.out], rows, L[i + 1].d.bn.C, &handed, ws, (hipStream_t)stream);
+        } else {
+          rc = cnnk_add(w.slot_elems[l.out], w.dtype, B->act[l.in0], B->act[l.in1], B->act[l.out], stream);
+        }
         break;
       case CNNK_OP_FC_LOSS:
         if (aux && g_cnnk_tune[12] >= 0) {
@@ -601,6 +607,11 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
         break;
       case CNNK_OP_ADD: {
         const int ins[2] = {l.in0, l.in1};
+        if (l.in0 != 0 && l.in1 != 0 && B->dact[l.in0] != B->dact[l.in1] && g_cnnk_tune[20] >= 0) {
+          rc = grad_route2(w.slot_elems[l.out], w.dtype, B->dact[l.out], B->dact[l.in0], written[l.in0], B->dact[l.in1], written[l.in1], (hipStream_t)stream);
+          written[l.in0] = written[l.in1] = 1;
+          break;
+        }
         for (int k = 0; k < 2 && rc == CNNK_OK; ++k) {
           if (ins[k] == 0) continue;
           rc = cnnk_grad_route(w.slot_elems[l.out], w.dtype, B->dact[l.out], B->dact[ins[k]], written[ins[k]], stream);

@@ -329,6 +329,20 @@ def test_batch_norms_that_add_up_the_partial_sums_agree_with_the_finalising_laun
     assert abs(a.loss.item() - b.loss.item()) <= 1e-2 * abs(b.loss.item())
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("widths,size,batch", [((8, 16), 8, 1), ((24, 40), 12, 5), ((64, 160), 16, 9)])
+def test_sums_that_make_their_batch_norms_partial_sums_give_the_same_bits(widths, size, batch, dtype):
+    """A sum in front of a batch norm leaves that one's partial sums, and its gradient goes to both summands in one launch; key 20 = -1
+    keeps the launches apart.  The same rows, values and orders of summation: the same bits after two steps."""
+    net = WL.mini_preact(batch=batch, dtype=dtype, size=size, widths=widths)
+    inp = WL.make_inputs(net, 37, perturb_bn=True)
+    a, b = _run_steps(net, inp, {}, True), _run_steps(net, inp, {20: -1}, True)
+    _assert_same_bits(net, a, b)
+    for i, L in enumerate(net.layers):
+        if L["op"] == "bn":
+            assert torch.equal(a.bn_save[i], b.bn_save[i]) and torch.equal(a.bn_running[i], b.bn_running[i])
+
+
 @pytest.mark.parametrize("group", [2, 5, 16])
 def test_grouped_weight_gradients_give_the_same_bits(group):
     """Weight gradients forked onto the second stream one by one and several at a time, their reductions and updates
