@@ -35,8 +35,8 @@ inline int reduce_blocks(size_t m, int C) {
 }
 
 // Sum the two per-thread vectors of 8 channels over the threads that share a channel octet and
-// write them to part[v][c][block] (row block fastest, so the finaliser reads rows).  Where there are fewer sums than threads, `groups` threads share one, each
-// a run of the rows (one thread each, the 128 rows of 16 channels were a chain of 128 reads).
+// write them to part[v][c][block] (row block fastest, so the finaliser reads rows).  Up to 32 channels wide `groups` threads share a sum, each
+// a run of the rows (one thread each, the 128 rows of 16 channels were a chain of 128 reads: 8 x 32 x 32 7.5 -> 5.2 us).
 template <class W>
 __device__ __forceinline__ void block_reduce_store(float (*acc)[8], const W& w, int C, float* __restrict__ part) {
   __shared__ float red[2][kT * 8];
@@ -49,7 +49,7 @@ __device__ __forceinline__ void block_reduce_store(float (*acc)[8], const W& w, 
       for (int e = 0; e < 8; ++e) red[v][tid * 8 + e] = acc[v][e];
   }
   __syncthreads();
-  if (sums <= kT / 2) {
+  if (sums <= kT / 4) {
     const int groups = kT / sums, per = (w.rows + groups - 1) / groups, i = tid % sums, g = tid / sums;
     float s = 0.f;
     if (g < groups) {

@@ -398,6 +398,18 @@ int attn_mfma_fwd(const cnnk_attn_desc* d, const void* qkv, void* o, float* lse,
 int attn_mfma_bwd(const cnnk_attn_desc* d, const void* qkv, const void* o, const void* d_o, const float* lse, void* dqkv,
                   hipStream_t st) {
   const int NT = (d->T + 31) / 32, half = (NT + 1) / 2;
+  // a launch has fewer than 2^32 threads, here at most 128 to 512 a head
+  constexpr long kMaxPairs = 1L << 22;
+  if ((long)d->B * d->heads > kMaxPairs && d->B > 1) {
+    cnnk_attn_desc part = *d;
+    part.B = d->B / 2;
+    const size_t rows = (size_t)part.B * d->T, width = (size_t)d->heads * kDH;
+    int rc = attn_mfma_bwd(&part, qkv, o, d_o, lse, dqkv, st);
+    if (rc != CNNK_OK) return rc;
+    part.B = d->B - part.B;
+    return attn_mfma_bwd(&part, (const bf16_t*)qkv + rows * 3 * width, (const bf16_t*)o + rows * width, (const bf16_t*)d_o + rows * width,
+                         lse + rows * d->heads, (bf16_t*)dqkv + rows * 3 * width, st);
+  }
   // Up to four wavefronts, a block each; long sequences: two blocks each, or twice the workgroups where those all fit the device at once
   // (197 tokens: 96 pairs 14.8 us, with two workgroups a pair 15.5).
   if (NT <= 4) return bwd_launch<4>(d, qkv, o, d_o, lse, dqkv, NT, 2, st);
