@@ -104,8 +104,8 @@ template <class C> struct ConvLoader {
   }
 };
 
-// Writes one tile out: rows m0 .., columns n0 .. of class cls.  S: LDS of the epilogue (the strips, then the sums), free
-// to use; called by every wavefront that holds accumulators (group 0).
+// Writes tile (mt, nt) of class cls out.  smem: EPI_B bytes of LDS that are free to use (the strips, then the sums); called by every
+// wavefront that holds accumulators (group 0).
 template <class C, int EP>
 __device__ __forceinline__ void conv_gemm_epilogue(const ConvGemmArgs& a, int cls, int M, int mt, int nt, f32x16_t (&acc)[C::TM][C::TN], int tid,
                                                    unsigned char* smem) {
@@ -208,10 +208,10 @@ __device__ __forceinline__ void conv_gemm_epilogue(const ConvGemmArgs& a, int cl
   }
 }
 
-template <class C, int EP>
+template <class C, int EP, bool WALK>
 __global__ void __launch_bounds__(C::THREADS, C::WPE) conv_gemm_kernel(ConvGemmArgs a) {
   constexpr int TM = C::TM, TN = C::TN, KG = C::KG;
-  extern __shared__ __align__(16) unsigned char smem[];   // stage buffers, nothing else
+  extern __shared__ __align__(16) unsigned char smem[];   // stage buffers, and the epilogue's room where it has its own
   const int lane = threadIdx.x & 63;
   const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
   const int tid = threadIdx.x & 255;
@@ -244,15 +244,15 @@ __global__ void __launch_bounds__(C::THREADS, C::WPE) conv_gemm_kernel(ConvGemmA
     return;
   }
   ConvLoader<C> ld;
-  if constexpr (KG > 1) {
-    // one tile to a workgroup (the grid has one for each), its stages split over the groups; the last group's stages
-    // past the end load zeros
+  if constexpr (!WALK) {
+    // one tile to a workgroup (the grid has one for each), its stages split over the groups, if there are several; the
+    // last group's stages past the end load zeros
     const int tile = first + l, mt = uniform_div(tile, a.ntiles), nt = tile - mt * a.ntiles, nst = (total + KG - 1) / KG;
     ld.init(a, cls, M, mt * C::BM, nt * C::BN, kg * nst, wave, lane);
     tile_stream<C, 0, false, false>(ld, 1, nst, kg, wave, lane, smem, false, 0, [](int) {}, [](int) {},
-                                    [&](int, f32x16_t (&acc)[TM][TN], float (&)[TM], unsigned char*) __attribute__((always_inline)) {
-      tile_join_groups<C>(acc, kg, tid, smem);
-      if (kg == 0) conv_gemm_epilogue<C, EP>(a, cls, M, mt, nt, acc, tid, smem + C::HAND_B);
+                                    [&](int, f32x16_t (&acc)[TM][TN], float (&)[TM], unsigned char* strip) __attribute__((always_inline)) {
+      if (KG > 1) tile_join_groups<C>(acc, kg, tid, smem);
+      if (kg == 0) conv_gemm_epilogue<C, EP>(a, cls, M, mt, nt, acc, tid, KG > 1 ? smem + C::HAND_B : strip);
       else if (EP == STATS) workgroup_barrier();        // the epilogue's barrier is the workgroup's
     });
   } else {
@@ -269,27 +269,34 @@ __global__ void __launch_bounds__(C::THREADS, C::WPE) conv_gemm_kernel(ConvGemmA
 }
 
 // ---- host side -------------------------------------------------------------------------------------------
-template <class C, int EP>
-int launch(ConvGemmArgs& a, long maxM, hipStream_t st) {
+template <class C, int EP, bool WALK>
+int launch_grid(const ConvGemmArgs& a, int per_xcd, hipStream_t st) {
   static bool raised = false;
-  auto kern = conv_gemm_kernel<C, EP>;
+  auto kern = conv_gemm_kernel<C, EP, WALK>;
   if (!raised) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM) != hipSuccess)
       return CNNK_ERR_HIP;
     raised = true;
   }
+  hipLaunchKernelGGL(kern, dim3(8 * per_xcd, 1, a.tt.nclass), dim3(C::THREADS), C::SMEM, st, a);
+  return launch_status();
+}
+template <class C, int EP>
+int launch(ConvGemmArgs& a, long maxM, hipStream_t st) {
   a.mtiles = (int)((maxM + C::BM - 1) / C::BM);
   a.ntiles = (a.Cd + C::BN - 1) / C::BN;
-  // as many workgroups as the device holds at a time, each walking several tiles where there are more (tuning key 18)
-  const int per_xcd = (a.mtiles * a.ntiles + 7) / 8, most = C::KG > 1 || g_cnnk_tune[18] < 0 ? per_xcd : g_cnnk_tune[18] > 0 ? g_cnnk_tune[18] : 32 * C::RESIDENT;
-  hipLaunchKernelGGL(kern, dim3(8 * (per_xcd < most ? per_xcd : most), 1, a.tt.nclass), dim3(C::THREADS), C::SMEM, st, a);
-  return launch_status();
+  // as many workgroups as the device holds at a time, each walking several tiles where there are more (tuning key 18);
+  // otherwise the kernel that has one tile only, whose start is 0.2 to 0.5 us shorter
+  const int per_xcd = (a.mtiles * a.ntiles + 7) / 8, most = !C::WALKS || g_cnnk_tune[18] < 0 ? per_xcd : g_cnnk_tune[18] > 0 ? g_cnnk_tune[18] : 32 * C::RESIDENT;
+  if constexpr (C::WALKS)
+    if (per_xcd > most) return launch_grid<C, EP, true>(a, most, st);
+  return launch_grid<C, EP, false>(a, per_xcd, st);
 }
 
 // Tile shapes and the time (us) of a launch, fitted to a sweep over 1x1 and strided 3x3 layers of 64 to 2048
 // channels on 4 x 4 to 32 x 32 images at batch 16 to 256, forward and data gradient, on operands that the L2s do not
-// hold (mean loss against the fastest shape 0.7 %, largest 22 %; with the constants fitted before the tiles were
-// streamed 2.9 %: 256 -> 256 3x3 strided at 16 x 16, batch 200, 37 -> 30 us, 1024 -> 2048 strided data gradient 30 -> 25):
+// hold (866 points, with the 64 x 64 tile as it is now, one to a workgroup: mean loss against the fastest shape 2.1 %, largest 30 %;
+// 256 -> 256 3x3 strided at 16 x 16, batch 200, 30 us, 1024 -> 2048 strided data gradient 25):
 //   one workgroup per CU at a time (two groups of wavefronts):  fixed + rounds * (tile + stages per group * stage)
 //   several:  fixed + tile * tiles / 256 + max(tiles per CU * stages * stage, rounds of resident ones * stages * alone)
 // `stage` is the time of a stage while other workgroups keep the CU busy, `alone` its latency; a stage is 64 channels

@@ -83,7 +83,7 @@ template <class C, bool LIN> struct WgLoader {
 template <class C, bool LIN>
 __global__ void __launch_bounds__(C::THREADS, C::WPE) wgrad_gemm_kernel(WgArgs a) {
   constexpr int TM = C::TM, TN = C::TN;
-  extern __shared__ __align__(16) unsigned char smem[];   // stage buffers, nothing else
+  extern __shared__ __align__(16) unsigned char smem[];   // stage buffers (no epilogue needs LDS here)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int wm = wave / C::WN, wn = wave % C::WN, h = lane >> 5;
   // an XCD (every 8th workgroup) owns a contiguous range of the list (split, tile): the tiles of one split read the

@@ -193,11 +193,11 @@ template <class C, int EPI> struct GemmEpilogue {
   }
 };
 
-// One workgroup's tile (mt, nt) over the reduction range of split z: a weight gradient, or two groups of wavefronts.
+// One workgroup's tile (mt, nt) over the reduction range of split z: a weight gradient, two groups of wavefronts, or one tile to a workgroup.
 template <class C, int EPI>
 __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) {
   constexpr int TM = C::TM, TN = C::TN, BK = C::BK, KG = C::KG;
-  extern __shared__ __align__(16) unsigned char smem[];   // stage buffers, nothing else
+  extern __shared__ __align__(16) unsigned char smem[];   // stage buffers, and the epilogue's room where it has its own
   const int lane = threadIdx.x & 63;
   const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);   // reduction group
   const int tid = threadIdx.x & 255;                                                     // within the group
@@ -221,7 +221,7 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
   const bool row_sums = ROWS && a.rsum != nullptr && nt == 0 && wn == 0;
   constexpr bool FOLD = EPI == 2 && TM * TN <= 6;
   tile_stream<C, 0, ROWS, FOLD>(ld, 1, nst, kg, wave, lane, smem, row_sums, a.fold, [](int) {}, [](int) {},
-                                [&](int, f32x16_t (&acc)[TM][TN], float (&rs)[TM], unsigned char*) __attribute__((always_inline)) {
+                                [&](int, f32x16_t (&acc)[TM][TN], float (&rs)[TM], unsigned char* strip) __attribute__((always_inline)) {
     if (KG > 1) tile_join_groups<C>(acc, kg, tid, smem);
     if (kg > 0) return;
     if constexpr (EPI == 2) {
@@ -248,7 +248,7 @@ __device__ __forceinline__ void gemm_tile(const Args& a, int mt, int nt, int z) 
     } else {
       GemmEpilogue<C, EPI> ep;
       ep.prefetch(a, mt, nt, lane, wave);
-      ep.write(a, mt, nt, acc, lane, wave, smem + C::HAND_B);      // behind the accumulators just taken over
+      ep.write(a, mt, nt, acc, lane, wave, KG > 1 ? smem + C::HAND_B : strip);      // HAND_B: behind the accumulators just taken over
     }
   });
 }
@@ -289,13 +289,13 @@ __device__ __forceinline__ bool band_tile(const Args& a, int l, int* mt_out, int
   return true;
 }
 
-template <bool ATR, bool BTR, int EPI, int TM, int TN, int BK, int RB, int NSTAGE, int KG>
+template <bool ATR, bool BTR, int EPI, int TM, int TN, int BK, int RB, int NSTAGE, int KG, bool WALK>
 __global__ void __launch_bounds__(256 * KG, (Cfg<ATR, BTR, TM, TN, BK, RB, NSTAGE, KG>::WPE)) gemm_kernel(Args a) {
   using C = Cfg<ATR, BTR, TM, TN, BK, RB, NSTAGE, KG>;
   int mt, nt;
   const int l = blockIdx.x >> 3, step = gridDim.x >> 3;
   if (!band_tile(a, l, &mt, &nt)) return;
-  if constexpr (EPI == 2 || KG > 1) {
+  if constexpr (!WALK) {
     gemm_tile<C, EPI>(a, mt, nt, blockIdx.z);
   } else {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -407,14 +407,18 @@ int launch(Kern kern, bool* raised, int threads, int smem_bytes, int per_xcd, co
 }
 template <bool ATR, bool BTR, int EPI, int TM, int TN, int BK, int RB, int NST, int KG>
 int launch_cfg(Args& a, int splits, hipStream_t st) {
-  static bool raised = false;
+  static bool raised[2] = {false, false};
   using C = Cfg<ATR, BTR, TM, TN, BK, RB, NST, KG>;
+  constexpr bool WALKS = EPI != 2 && C::WALKS;
   a.mtiles = (a.M + C::BM - 1) / C::BM;
   a.ntiles = (a.N + C::BN - 1) / C::BN;
   // As many workgroups as the device holds at a time, each walking several tiles where there are more (tuning key 18).  12608 x
-  // 768 -> 3072 83 -> 77 us, -> 2304 63 -> 58, against one to a tile; up to one round of tiles nothing changes.
-  const int tiles = (a.mtiles * a.ntiles + 7) / 8, most = EPI == 2 || KG > 1 || g_cnnk_tune[18] < 0 ? tiles : g_cnnk_tune[18] > 0 ? g_cnnk_tune[18] : 32 * C::RESIDENT;
-  return launch(gemm_kernel<ATR, BTR, EPI, TM, TN, BK, RB, NST, KG>, &raised, C::THREADS, C::SMEM, tiles < most ? tiles : most, a, splits, st);
+  // 768 -> 3072 83 -> 77 us, -> 2304 63 -> 58, against one to a tile.  Otherwise the kernel that has one tile only (2 KB of
+  // instructions and about twenty registers less): 788 x 384 -> 384 in 64 x 128 tiles 5.7 -> 5.15 us, 6240 x 3072 -> 768 in 128 x 128 tiles 49.0 -> 46.7.
+  const int tiles = (a.mtiles * a.ntiles + 7) / 8, most = !WALKS || g_cnnk_tune[18] < 0 ? tiles : g_cnnk_tune[18] > 0 ? g_cnnk_tune[18] : 32 * C::RESIDENT;
+  if constexpr (WALKS)
+    if (tiles > most) return launch(gemm_kernel<ATR, BTR, EPI, TM, TN, BK, RB, NST, KG, true>, &raised[1], C::THREADS, C::SMEM, most, a, splits, st);
+  return launch(gemm_kernel<ATR, BTR, EPI, TM, TN, BK, RB, NST, KG, false>, &raised[0], C::THREADS, C::SMEM, tiles, a, splits, st);
 }
 // The tile shapes and what a launch of each costs.  With few tiles the device is bound by the latency of the operand
 // loads and by how many CUs have a tile at all, so small problems want small tiles, 128-byte operand rows and two
@@ -423,11 +427,12 @@ int launch_cfg(Args& a, int splits, hipStream_t st) {
 // Estimated time (us) of a launch in rounds of resident workgroups; a round with c of them on a CU takes
 //   c * tile + stages * max(alone, c * stage),      stages of 64 reduction elements (per group)
 // and the launch `start` besides.  Constants fitted to a sweep of all shapes over 64 to 25216 rows and eighteen pairs
-// of widths from 128 to 4096, forward, with GELU, with a residual, data gradient (1152 points): what is chosen
-// takes 0.6 % more than the fastest shape in the mean, and 3 % more than the fixed choice of 256 or 192 rows by rounds
-// (128-byte rows from a reduction of 2048 on) at three of them.  That choice / this one, us: 788 x 3072 -> 768 42.4 /
-// 13.6, 788 x 768 -> 2304 17.2 / 9.9, 197 x 768 -> 768 15.2 / 6.2, 1576 x 768 -> 768 15.7 / 8.1, 3152 x 768 -> 3072 with GELU 31.1
-// / 28.4, 6240 x 384 -> 384 10.6 / 6.9, 12608 x 768 -> 768 with a residual 27.9 / 25.2, 12608 x 768 -> 2304 61.0 / 55.0.
+// of widths from 128 to 4096, forward, with GELU, with a residual, data gradient (1152 points), of kernels that had one tile
+// to a workgroup and read operands and issued loads in another order.  With the present kernels, on operands that the L2s do not hold,
+// 197 to 12608 rows and ten pairs of widths, forward and data gradient (120 points): what is chosen takes 2.3 % more than the fastest
+// shape in the mean and 18 % at worst (3152 x 2304 -> 768 27.6 us in 64 x 64 tiles, 23.5 in 64 x 128).  The choice of 256 or 192 rows
+// that was there before them / this one, us, both with the kernels of that time: 788 x 3072 -> 768 42.4 / 13.6, 788 x 768 -> 2304 17.2 / 9.9, 197 x
+// 768 -> 768 15.2 / 6.2, 1576 x 768 -> 768 15.7 / 8.1, 6240 x 384 -> 384 10.6 / 6.9, 12608 x 768 -> 2304 61.0 / 55.0.
 enum { T64 = 0, T64G2, T64x128, T64x128G2, T128, T_SMALL, L256 = T_SMALL, L192, L192_WIDE, T_SHAPES };
 struct TileCost {
   int rows, cols, kgroups, resident;      // workgroup tile, groups of wavefronts, workgroups per CU

@@ -40,19 +40,23 @@ template <bool ATR_, bool BTR_, int TM_, int TN_, int WN_, int BK_, int RB_, int
   static constexpr int LPR = RB / 16, RPL = 1024 / RB;   // lanes per LDS row, rows per direct load
   static constexpr int PC = RB / 2, PLANE_B = BK * RB;   // a transposed operand: planes of BK reduction rows x PC columns
   static constexpr int KS = BK / 16;                     // MFMA reduction steps per stage
-  // LDS of the epilogue: a strip per wavefront, and two sums per column and row of wavefronts.  It takes a stage buffer
-  // that is done with, or, where that is smaller, room of its own.
+  // Whether workgroups walk several tiles.  Not with a single block to a wavefront, where a walk's registers and instructions cost
+  // more than the start of a tile: 12608 x 768 -> 768 in 64 x 64 tiles 33.0 us, one to a workgroup 32.1; 200 images of 16 x 16, 128 ->
+  // 256 3x3 strided 31.4 and 26.5.
+  static constexpr bool WALKS = KG == 1 && TM * TN > 1;
+  // LDS of the epilogue: a strip per wavefront, and two sums per column and row of wavefronts.  In a walk it takes room of its
+  // own where that costs no workgroup, otherwise the stage buffer that is done with; behind a single tile the first ones.
   static constexpr int EPI_B = NW * 32 * SP + 2 * WM * BN * 4;
-  static constexpr bool EPI_OWN = KG == 1 && (STAGE_B < EPI_B || 160 * 1024 / (NST * STAGE_B + EPI_B) == 160 * 1024 / (NST * STAGE_B));
+  static constexpr bool EPI_OWN = WALKS && 160 * 1024 / (NST * STAGE_B + EPI_B) == 160 * 1024 / (NST * STAGE_B);
   static constexpr int SMEM = KG * NST * STAGE_B + (EPI_OWN ? EPI_B : 0);
   static constexpr int HAND_B = (KG - 1) * TM * TN * 16 * 256 * 4;   // accumulators of the groups past the first
   // wavefronts per SIMD the register allocation leaves room for: two workgroups per CU where their LDS fits (and where
   // it does not, no more registers either: past 256 the accumulators would move between the two register files)
   static constexpr int WPE = KG == 1 ? (NW == 8 && 2 * SMEM <= 160 * 1024 ? 4 : 2) : KG * (2 * SMEM <= 160 * 1024 ? 2 : 1);
-  // workgroups that a CU holds by their LDS (at most three: what the registers of the smallest tiles leave)
-  static constexpr int RESIDENT = 3 * SMEM <= 160 * 1024 ? 3 : 2 * SMEM <= 160 * 1024 ? 2 : 1;
+  // workgroups that a CU holds by their LDS (at most four: what the registers of the tiles that walk leave)
+  static constexpr int RESIDENT = 160 * 1024 / SMEM < 4 ? 160 * 1024 / SMEM : 4;
   static_assert(A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "every load of a wavefront belongs to one operand");
-  static_assert(SMEM <= 160 * 1024 && HAND_B + EPI_B <= SMEM, "LDS");
+  static_assert(SMEM <= 160 * 1024 && HAND_B + EPI_B <= SMEM && (!WALKS || EPI_OWN || STAGE_B >= EPI_B), "LDS");
   static_assert((ATR || BK * 2 == RB) && (BTR || BK * 2 == RB), "a natural operand's LDS row is its BK reduction elements");
   static_assert((BM % PC == 0 || !ATR) && (BN % PC == 0 || !BTR), "whole planes");
   static_assert(NLOAD * (NST - 2) < 64, "the waits encode the number of loads in flight in six bits");
@@ -176,10 +180,12 @@ template <int N> __device__ __forceinline__ void wait_vm() {
 // (a CU takes 64 bytes a clock: 512 clocks for 128 x 128 x 64), then reading the operands (latency), then the
 // products took 0.69 us a stage of 128 x 128 x 64 whose products take 0.22, with the loads three stages ahead and nothing else
 // on the CU.
-// So the direct loads are issued one by one between products; the operands of a reduction step are read under the
-// products of the step before it, and with more than two buffers those of a stage's first step under the last products
+// So the operands of a reduction step are read under the products of the step before it, and with more than two buffers the
+// direct loads are issued one by one between products and the operands of a stage's first step are read under the last products
 // of the stage before (CROSS).  Not with two buffers, and not with a single block to a wavefront, where that takes two thirds of a
 // stage off the time the loads have: 788 x 768 -> 3072 with GELU in a step, weights out of memory, 17.0 us, CROSS 21.1.
+// With two buffers the loads have one stage's time, and all are issued in front of it: 128 x 128 tiles, one to a workgroup, 6240 x
+// 3072 -> 768 49.0 us, between the products of half the stage 52.1; walking, 12608 x 768 -> 3072 82.5 and 86.4.
 //
 // LD: a_rs, b_rs (buffer descriptors); begin(t) in front of the loads of stage t of its tile (stages in order; past the last one
 // every offset is out of range), offset(j) of this lane's 16 bytes in load j; next(k) points it at the workgroup's k-th tile (k ascending, each once).
@@ -192,14 +198,14 @@ template <int N> __device__ __forceinline__ void wait_vm() {
 // the accumulators are set aside and begun anew every `fold` stages, and what was set aside is added in a chain of its
 // own: two chains of about the square root of the steps instead of one of all of them, for reductions of thousands of steps
 // (relative error of a product of 12608 rows 1.7e-7 instead of 7.1e-7).  The workgroup's LDS holds the stage buffers (of
-// group kg: kg * NST ..) and, behind them, the epilogue's room where it has its own (LDS address 0).  Every
+// group kg: kg * NST ..) and, behind them, the epilogue's room where it has its own (LDS address 0); ntiles is 1 where C::WALKS is not set.  Every
 // wavefront of the workgroup runs the same number of stages.  On return all direct loads have landed.
 template <class C, int E, bool ROWS, bool FOLD, class LD, class NEXT, class PRE, class EPI>
 __device__ __forceinline__ void tile_stream(LD& ld, int ntiles, int nst, int kg, int wave, int lane, unsigned char* smem, bool row_sums, int fold,
                                             NEXT next, PRE prefetch, EPI epilogue) {
   constexpr int TM = C::TM, TN = C::TN, STAGE_B = C::STAGE_B, NST = C::NST, KS = C::KS, NLOAD = C::NLOAD, MM = TM * TN;
   constexpr bool CROSS = NST > 2 && MM > 1;              // the operands of a stage's first step are read under the stage before
-  constexpr int LK = CROSS ? KS - 1 : MM > 1 ? (KS + 1) / 2 : 1;               // reduction steps that the loads of a stage are spread over
+  constexpr int LK = CROSS ? KS - 1 : 1;                 // reduction steps that the loads of a stage are spread over
   constexpr int PER = (NLOAD + LK - 1) / LK;             // direct loads in each of them
   static_assert(KS % 2 == 0 && LK >= 1, "two operand sets take turns");
   const int total = ntiles * nst;
@@ -245,10 +251,16 @@ __device__ __forceinline__ void tile_stream(LD& ld, int ntiles, int nst, int kg,
     if (!CROSS) {
       wait_stage(more);
       __builtin_amdgcn_s_barrier();
-      read(0, cur, 0);
     }
     if (last) prefetch(k);
     if (more) ld.begin(p_st);
+    if (!CROSS) {
+      if (more && MM > 1) {                // two buffers: the loads have one stage's time, all of it
+#pragma unroll
+        for (int c = 0; c < NLOAD; ++c) load(fill, c);
+      }
+      read(0, cur, 0);
+    }
     float pair[ROWS ? TM : 1];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -271,7 +283,7 @@ __device__ __forceinline__ void tile_stream(LD& ld, int ntiles, int nst, int kg,
 #pragma unroll
       for (int m = 0; m < MM; ++m) {
         acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[set][m / TN], bfr[set][m % TN], acc[m / TN][m % TN], 0, 0, 0);
-        if (more && ks < LK && MM > 1) {
+        if (more && ks < LK && CROSS) {
 #pragma unroll
           for (int c = PER * m / MM; c < PER * (m + 1) / MM; ++c, ++j)
             if (j < NLOAD) {
@@ -347,9 +359,10 @@ __device__ __forceinline__ void tile_stream(LD& ld, int ntiles, int nst, int kg,
         for (int r = 0; r < 16; ++r) acc[m / TN][m % TN][r] += aside[m / TN][m % TN][r];
     }
     // The epilogue's room, where it is the buffer of the tile's last stage: every wave is done reading that (CROSS: behind
-    // that stage's barrier), and it is filled again only behind a barrier that all waves reach after their epilogue
+    // that stage's barrier), and it is filled again only behind a barrier that all waves reach after their epilogue.  Where there is
+    // one tile only, every buffer is free by then.
     if (!CROSS && !C::EPI_OWN) workgroup_barrier();
-    epilogue(k, acc, rs, smem + (C::EPI_OWN ? C::KG * NST * STAGE_B : cur == 0 ? (NST - 1) * STAGE_B : cur - STAGE_B));
+    epilogue(k, acc, rs, smem + (C::EPI_OWN ? C::KG * NST * STAGE_B : !C::WALKS ? 0 : cur == 0 ? (NST - 1) * STAGE_B : cur - STAGE_B));
     if (CROSS && !C::EPI_OWN) workgroup_barrier();
     since = 0;
   }
