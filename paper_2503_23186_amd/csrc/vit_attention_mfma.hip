@@ -246,10 +246,10 @@ __global__ void __launch_bounds__(256, 2) attn_mfma_bwd_kernel(const bf16_t* __r
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), n = lane & 31, h = lane >> 5;
   const float scale = 0.125f, c2 = 0.125f * 1.44269504088896341f, log2e = 1.44269504088896341f;
   const int group = part >> 1, groups = parts >> 1;      // this workgroup's blocks: every groups * waves-th
-  // No score is masked in either walk.  Tokens past T are rows of zeros in all four matrices, with
-  // L = D = 0: their probabilities are finite, and wherever one enters a sum it multiplies a zero row
-  // of the other operand (a key past T: its row of K in dq; a query past T: its rows of dO and Q in dv
-  // and dk), or lands in an output column that is not stored (the lane's own token past T).
+  // Tokens past T are rows of zeros in all four matrices.  A query past T has L = D = 0: its probabilities are exp(0 - 0) = 1
+  // and multiply its zero rows of dO and Q in dv and dk, so the walk over the queries masks nothing.  A key past T meets real
+  // queries: its score is 0, and where a query's log-sum-exp lies below -88 its exponential is infinite, times its zero row
+  // of K not a number.  The walk over the keys masks the last tile.  (The lane's own token past T ends in a column that is not stored.)
   if ((part & 1) == 0) {
     // ---- by query block: dq^T = k^T ds^T ----
     Pieces<NP> px, py;
@@ -280,6 +280,11 @@ __global__ void __launch_bounds__(256, 2) attn_mfma_bwd_kernel(const bf16_t* __r
         f32x16_t dp = tile_nt(Ys, plane_b, kt * 32, bg, lane);
 #pragma unroll
         for (int i = 0; i < 16; ++i) dp[i] = __builtin_amdgcn_exp2f(fmaf(s[i], c2, -L2)) * fmaf(dp[i], scale, -Dsc);
+        if (kt == NT - 1) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (kt * 32 + (i >> 2) * 8 + h * 4 + (i & 3) >= T) dp[i] = 0.f;
+        }
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           const bf16x8_t dsb = pack_frag(dp, j);

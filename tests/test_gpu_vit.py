@@ -247,13 +247,21 @@ def test_attention_in_parts(K, B, T, heads, rise):
     _attention_case(K, B, T, heads, 64, "bf16", rise)
 
 
-def _attention_case(K, B, T, heads, dh, dtype, rise=None):
+# scores that all lie far from zero, at lengths that are no multiple of 32: a key past the end has score 0, and its exponential
+# relative to the others' log-sum-exp is beyond every float
+@pytest.mark.parametrize("B,T,heads,shift", [(2, 33, 3, -110), (1, 65, 6, -128), (3, 101, 2, -200), (40, 65, 6, -128), (1, 130, 2, -128), (2, 197, 2, -150),
+                                             (16, 197, 12, -128), (22, 129, 12, -128), (1, 65, 2, 128), (1, 197, 2, 200)])
+def test_attention_scores_far_from_zero(K, B, T, heads, shift):
+    _attention_case(K, B, T, heads, 64, "bf16", 0, shift)
+
+
+def _attention_case(K, B, T, heads, dh, dtype, rise=None, shift=0):
     rng = np.random.default_rng(B * 7 + T * 13 + heads + dh)
     d = heads * dh
     qkv = rng.standard_normal((B, T, 3 * d)) * 1.3
-    if rise:        # one feature carries it: 8 of every query times rise * t / T of key t, over the scale of 8
+    if rise or shift:        # one feature carries it: 8 of every query times shift + rise * t / T of key t, over the scale of 8
         qkv[:, :, 0:d:dh] = 8.0
-        qkv[:, :, d:2 * d:dh] = (rise * np.arange(T) / T)[None, :, None]
+        qkv[:, :, d:2 * d:dh] = (shift + (rise or 0) * np.arange(T) / T)[None, :, None]
     qkv = rep(qkv, dtype)
     dO = rep(rng.standard_normal((B, T, d)), dtype)
     O, A = V.attention_fwd(qkv, heads)
@@ -262,17 +270,16 @@ def _attention_case(K, B, T, heads, dh, dtype, rise=None):
     lse = torch.zeros((B, heads, T), device="cuda:0")
     K.cnnk_attention_fwd(ad, gq, go, lse)
     torch.cuda.synchronize()
-    q, k, v = (qkv[:, :, i * d:(i + 1) * d].reshape(B, T, heads, dh).transpose(0, 2, 1, 3) for i in range(3))
+    split = lambda t, n: [t[:, :, i * d:(i + 1) * d].reshape(B, T, heads, dh).transpose(0, 2, 1, 3) for i in range(n)]
+    join = lambda t: t.transpose(0, 2, 1, 3).reshape(B, T, d)
+    q, k, v = split(qkv, 3)
     if rise is None:
         assert max_rel_err(host(go), O) <= (OUT_TOL[dtype] if dtype == "bf16" else 5e-5)
     else:           # the probabilities are rounded to bf16 in front of their product, its result in storage: 2^-8 of either
-        weight = (A @ np.abs(v)).transpose(0, 2, 1, 3).reshape(B, T, d)
-        assert np.all(np.abs(host(go) - O) <= 2.0 ** -8 * 1.01 * (np.abs(O) + weight))
+        assert np.all(np.abs(host(go) - O) <= 2.0 ** -8 * 1.01 * (np.abs(O) + join(A @ np.abs(v))))
     S = q @ k.transpose(0, 1, 3, 2) / np.sqrt(dh)
     want_lse = np.log(np.exp(S - S.max(-1, keepdims=True)).sum(-1)) + S.max(-1)
     assert np.abs(host(lse) - want_lse).max() <= 1e-4
-    if rise:        # D cancels most of the query gradients then: what is left is the rounding of the output
-        return
     # backward from the oracle's own output (both sides differentiate at the same point)
     Oq = rep(O, dtype)
     want = V.attention_bwd(dO, qkv, A, heads)
@@ -280,7 +287,23 @@ def _attention_case(K, B, T, heads, dh, dtype, rise=None):
     K.cnnk_attention_bwd(ad, gq, dev(Oq, dtype), dev(dO, dtype), lse, gd)
     torch.cuda.synchronize()
     got = host(gd)
-    assert np.all(np.isfinite(got))
+    assert np.isfinite(got).all()
+    if rise or shift:
+        # The large feature's products cancel in the sums, so the bound is made of the terms: half an ulp of bf16 (2^-8) for the
+        # probabilities, for ds = p (dp - D) / 8 and for the result; D is taken of the rounded output; 2e-4 for the exponent (scores of
+        # up to 200 in fp32, five roundings of 2^-24 of 300) and 1e-5 of its operands for the difference.
+        g, o = split(dO, 1)[0], split(O, 1)[0]
+        dA = g @ v.transpose(0, 1, 3, 2)
+        D = (dA * A).sum(-1, keepdims=True)
+        h = 2.0 ** -8 * 1.01
+        e_ds = (A * np.abs(dA - D) * (h + 2e-4) + A * (h * (np.abs(g) * np.abs(o)).sum(-1, keepdims=True) + 1e-5 * (np.abs(dA) + np.abs(D)))) / np.sqrt(dh)
+        e_p = A * (h + 2e-4)
+        T_ = lambda t: t.transpose(0, 1, 3, 2)
+        for i, (name, bound) in enumerate((("q", e_ds @ np.abs(k)), ("k", T_(e_ds) @ np.abs(q)), ("v", T_(e_p) @ np.abs(g)))):
+            part, ref = got[:, :, i * d:(i + 1) * d], want[:, :, i * d:(i + 1) * d]
+            worst = (np.abs(part - ref) / (join(bound) + h * (np.abs(ref) + join(bound)) + 1e-30)).max()
+            assert worst <= 1, (name, worst)
+        return
     for i, name in enumerate("qkv"):
         # D = do . o is taken of the stored (rounded) output: one more rounding than the oracle's exact D.
         # With a single key the query and key gradients are exactly zero: the error is then measured
