@@ -255,6 +255,27 @@ def test_attention_scores_far_from_zero(K, B, T, heads, shift):
     _attention_case(K, B, T, heads, 64, "bf16", 0, shift)
 
 
+# values near the largest float: the result is an average of them and finite, undivided sums of it are not
+@pytest.mark.parametrize("B,T,heads,rise", [(1, 65, 2, 0), (2, 197, 3, 0), (1, 256, 2, 0), (1, 197, 2, 60), (3, 40, 2, -30)])
+def test_attention_of_values_near_the_largest_float(K, B, T, heads, rise):
+    rng = np.random.default_rng(T)
+    d = heads * 64
+    qkv = rng.standard_normal((B, T, 3 * d))
+    qkv[:, :, 0:d:64] = 8.0
+    qkv[:, :, d:2 * d:64] = (rise * np.arange(T) / T)[None, :, None]
+    qkv[:, :, 2 * d + 5::64] = 3e38                                  # one feature of every head, the others as they are
+    qkv[:, :, 2 * d + 9::64] = -1e36 * rng.random((B, T, heads))
+    qkv = rep(qkv, "bf16")
+    O, A = V.attention_fwd(qkv, heads)
+    go, lse = dev(np.zeros((B, T, d)), "bf16"), torch.zeros((B, heads, T), device="cuda:0")
+    K.cnnk_attention_fwd(K.attn_desc(B, T, heads, 64, dt_of(K, "bf16")), dev(qkv, "bf16"), go, lse)
+    torch.cuda.synchronize()
+    got = host(go)
+    weight = (A @ np.abs(qkv[:, :, 2 * d:].reshape(B, T, heads, 64).transpose(0, 2, 1, 3))).transpose(0, 2, 1, 3).reshape(B, T, d)
+    worst = (np.abs(got - O) / (2.0 ** -8 * 1.01 * (np.abs(O) + weight))).max()
+    assert np.isfinite(got).all() and worst <= 1, worst
+
+
 def _attention_case(K, B, T, heads, dh, dtype, rise=None, shift=0):
     rng = np.random.default_rng(B * 7 + T * 13 + heads + dh)
     d = heads * dh
