@@ -16,9 +16,9 @@
 // 16-key step j, and the A operand is read with the same key-to-slot assignment (rows h*4..h*4+3 and
 // 8+h*4..8+h*4+3 of the step for lane half h) instead of the usual 8 consecutive ones.
 // Probabilities are not stored: the forward pass writes log-sum-exp per query and the backward pass
-// recomputes exp(s - lse).  The backward pass runs two kinds of workgroups in one launch: by query block for dq,
-// by key block for dk and dv (which recomputes the score tiles in the other orientation), so every
-// sum has one owner and a fixed order: no atomics, bit-reproducible.
+// recomputes exp(s - lse).  The backward pass walks twice, by query block for dq and
+// by key block for dk and dv (which recomputes the score tiles in the other orientation), in workgroups of their own or one after the
+// other, so every sum has one owner and a fixed order: no atomics, bit-reproducible.
 #include "common.h"
 #include "../../include/cnnk_vit.h"
 
@@ -250,10 +250,147 @@ __global__ void __launch_bounds__(512, 4) attn_mfma_fwd_kernel(const bf16_t* __r
   if (q < T && h == 0) lse[((size_t)b * heads + head) * T + q] = L2 * 0.69314718055994531f;
 }
 
-// Backward: a workgroup of at most four wavefronts forms dq (part even) or dk and dv (odd) of some 32-token blocks of a pair.  It has two of the
+// The backward pass's walks.  X, Y: K and V of all keys for dq, Q and dO of all queries for dk and dv, in LDS; x, y: the lane's own row
+// of the others.
+// Tokens past T are rows of zeros in all four matrices.  A query past T has L = D = 0: its probabilities are exp(0 - 0) = 1
+// and multiply its zero rows of dO and Q in dv and dk, so the walk over the queries masks nothing.  A key past T meets real
+// queries: its score is 0, and where a query's log-sum-exp lies below -88 its exponential is infinite, times its zero row
+// of K not a number.  The walk over the keys masks the last tile.  (The lane's own token past T ends in a column that is not stored.)
+constexpr float kScale = 0.125f, kLog2e = 1.44269504088896341f, kC2 = 0.125f * 1.44269504088896341f;
+// dq^T = k^T ds^T, of the lane's query: exp(s / 8 - L) = exp2(s c - L2) with c = log2 e / 8, and ds = p (dp - D) / 8 = p (dp / 8 - Dsc)
+__device__ __forceinline__ void walk_keys(const unsigned char* Xs, const unsigned char* Ys, int plane_b, int NT, int T, const bf16x8_t* x, const bf16x8_t* y,
+                                          float L2, float Dsc, int lane, f32x16_t (&dq)[2]) {
+  const int h = lane >> 5;
+  dq[0] = dq[1] = zero16();
+  for (int kt = 0; kt < NT; ++kt) {
+    const f32x16_t s = tile_nt(Xs, plane_b, kt * 32, x, lane);     // [key][query]
+    f32x16_t dp = tile_nt(Ys, plane_b, kt * 32, y, lane);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) dp[i] = __builtin_amdgcn_exp2f(fmaf(s[i], kC2, -L2)) * fmaf(dp[i], kScale, -Dsc);
+    if (kt == NT - 1) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (kt * 32 + (i >> 2) * 8 + h * 4 + (i & 3) >= T) dp[i] = 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const bf16x8_t dsb = pack_frag(dp, j);
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+        dq[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Xs, plane_b, mt, kt * 32 + 16 * j, lane), dsb, dq[mt], 0, 0, 0);
+    }
+  }
+}
+// dv^T = do^T p, dk^T = q^T ds, of the lane's key; Ls, Ds: L2 and Dsc of every query
+__device__ __forceinline__ void walk_queries(const unsigned char* Xs, const unsigned char* Ys, const float* Ls, const float* Ds, int plane_b, int NT,
+                                             const bf16x8_t* x, const bf16x8_t* y, int lane, f32x16_t (&dk)[2], f32x16_t (&dv)[2]) {
+  const int h = lane >> 5;
+  dk[0] = dk[1] = zero16();
+  dv[0] = dv[1] = zero16();
+  for (int qt = 0; qt < NT; ++qt) {
+    f32x16_t p = tile_nt(Xs, plane_b, qt * 32, x, lane);           // [query][key]
+    f32x16_t dp = tile_nt(Ys, plane_b, qt * 32, y, lane);
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const int r0 = qt * 32 + i4 * 8 + h * 4;
+      const float4 L4 = *reinterpret_cast<const float4*>(Ls + r0);
+      const float4 D4 = *reinterpret_cast<const float4*>(Ds + r0);
+      const float Lr[4] = {L4.x, L4.y, L4.z, L4.w}, Dr[4] = {D4.x, D4.y, D4.z, D4.w};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int i = i4 * 4 + k;
+        const float pp = __builtin_amdgcn_exp2f(fmaf(p[i], kC2, -Lr[k]));
+        p[i] = pp;
+        dp[i] = pp * fmaf(dp[i], kScale, -Dr[k]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const bf16x8_t pb = pack_frag(p, j), dsb = pack_frag(dp, j);
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        dv[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Ys, plane_b, mt, qt * 32 + 16 * j, lane), pb, dv[mt], 0, 0, 0);
+        dk[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Xs, plane_b, mt, qt * 32 + 16 * j, lane), dsb, dk[mt], 0, 0, 0);
+      }
+    }
+  }
+}
+template <int CTRL> __device__ __forceinline__ float lane_moved(float v) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+// Dsc of the tokens whose pieces of dO and O a thread holds, from the eight lanes of a token; Ls of all tokens
+template <int NP>
+__device__ __forceinline__ void put_sums(const Pieces<NP>& g, const Pieces<NP>& o, const float* lrow, int T, int Tp, float* Ls, float* Ds) {
+#pragma unroll
+  for (int k = 0; k < NP; ++k) {
+    float D = dot8(o.v[k], g.v[k]);
+    D += lane_moved<0xb1>(D);       // from the neighbour, from the other pair of four, from the other four of eight
+    D += lane_moved<0x4e>(D);
+    D += lane_moved<0x141>(D);
+    const int i = threadIdx.x + k * blockDim.x, r = i >> 3;
+    if ((i & 7) == 0 && r < Tp) Ds[r] = D * kScale;
+  }
+  for (int t = threadIdx.x; t < Tp; t += blockDim.x) Ls[t] = t < T ? lrow[t] * kLog2e : 0.f;
+}
+
+// Backward, a workgroup to a pair: all four matrices in LDS, a wavefront to a 32-token block, dq first.  Where the pairs that
+// a CU holds keep it busy this loads everything once; where they do not the kernel below is faster (attn_mfma_bwd has the line).
+__global__ void __launch_bounds__(512) attn_mfma_bwd_whole_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+                                                                  const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
+                                                                  bf16_t* __restrict__ dqkv, int T, int heads) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int NT = blockDim.x >> 6, Tp = NT * 32, plane_b = Tp * ROW_B;
+  unsigned char* Qs = smem;
+  unsigned char* Ks = smem + 2 * plane_b;
+  unsigned char* Vs = smem + 4 * plane_b;
+  unsigned char* Gs = smem + 6 * plane_b;
+  float* Ls = reinterpret_cast<float*>(smem + 8 * plane_b);
+  float* Ds = Ls + Tp;
+  const int pair = blockIdx.x, b = pair / heads, head = pair - b * heads, d = heads * kDH;
+  const size_t ld = 3 * (size_t)d;
+  const bf16_t* base = qkv + (size_t)b * T * ld + head * kDH;
+  bf16_t* dbase = dqkv + (size_t)b * T * ld + head * kDH;
+  {
+    Pieces<4> pq, pk, pv, pg, po;
+    pq.fetch(base, ld, T);
+    pk.fetch(base + d, ld, T);
+    pv.fetch(base + 2 * d, ld, T);
+    pg.fetch(d_o + (size_t)b * T * d + head * kDH, d, T);
+    po.fetch(o + (size_t)b * T * d + head * kDH, d, T);
+    pq.put(Qs, plane_b, Tp);
+    pk.put(Ks, plane_b, Tp);
+    pv.put(Vs, plane_b, Tp);
+    pg.put(Gs, plane_b, Tp);
+    put_sums(pg, po, lse + (size_t)pair * T, T, Tp, Ls, Ds);
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, own = (threadIdx.x >> 6) * 32 + (lane & 31), h = lane >> 5;      // this lane's query, then its key
+  bf16x8_t x[4], y[4];
+  {
+    f32x16_t dq[2];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      x[ks] = frag_read(Qs, plane_b, own, ks * 16 + h * 8);
+      y[ks] = frag_read(Gs, plane_b, own, ks * 16 + h * 8);
+    }
+    walk_keys(Ks, Vs, plane_b, NT, T, x, y, Ls[own], Ds[own], lane, dq);
+    store_cols(dbase + (size_t)own * ld, dq, h, own < T);
+  }
+  f32x16_t dk[2], dv[2];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    x[ks] = frag_read(Ks, plane_b, own, ks * 16 + h * 8);
+    y[ks] = frag_read(Vs, plane_b, own, ks * 16 + h * 8);
+  }
+  walk_queries(Qs, Gs, Ls, Ds, plane_b, NT, x, y, lane, dk, dv);
+  store_cols(dbase + (size_t)own * ld + d, dk, h, own < T);
+  store_cols(dbase + (size_t)own * ld + 2 * d, dv, h, own < T);
+}
+
+// Backward, a pair in parts: a workgroup of at most four wavefronts forms dq (part even) or dk and dv (odd) of some 32-token blocks of a pair.  It has two of the
 // four matrices in LDS and its wavefronts' own rows of the others in registers, so that two workgroups share a CU and one
-// loads while the other computes: with all four in LDS there was room for one.  197 tokens, 12 heads: batch 8 20.3 -> 14.8 us, batch 64 70 either
-// way: there the operand reads from LDS (768 clocks a tile pair of dk and dv, shared by four SIMDs), the vector ALU (800) and the matrix products (512)
+// loads while the other computes: with all four in LDS there is room for one.  197 tokens, 12 heads: batch 8 21.0 -> 16.3 us, batch 64 72 and
+// 68: there the operand reads from LDS (768 clocks a tile pair of dk and dv, shared by four SIMDs), the vector ALU (800) and the matrix products (512)
 // of two wavefronts a SIMD follow one another more than they overlap.
 template <int NP>
 __global__ void __launch_bounds__(256, 2) attn_mfma_bwd_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
@@ -273,14 +410,9 @@ __global__ void __launch_bounds__(256, 2) attn_mfma_bwd_kernel(const bf16_t* __r
   const float* lrow = lse + (size_t)pair * T;
   bf16_t* dbase = dqkv + (size_t)b * T * ld + head * kDH;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), n = lane & 31, h = lane >> 5;
-  const float scale = 0.125f, c2 = 0.125f * 1.44269504088896341f, log2e = 1.44269504088896341f;
   const int group = part >> 1, groups = parts >> 1;      // this workgroup's blocks: every groups * waves-th
-  // Tokens past T are rows of zeros in all four matrices.  A query past T has L = D = 0: its probabilities are exp(0 - 0) = 1
-  // and multiply its zero rows of dO and Q in dv and dk, so the walk over the queries masks nothing.  A key past T meets real
-  // queries: its score is 0, and where a query's log-sum-exp lies below -88 its exponential is infinite, times its zero row
-  // of K not a number.  The walk over the keys masks the last tile.  (The lane's own token past T ends in a column that is not stored.)
   if ((part & 1) == 0) {
-    // ---- by query block: dq^T = k^T ds^T ----
+    // ---- by query block ----
     Pieces<NP> px, py;
     px.fetch(base + d, ld, T);
     py.fetch(base + 2 * d, ld, T);
@@ -293,39 +425,20 @@ __global__ void __launch_bounds__(256, 2) attn_mfma_bwd_kernel(const bf16_t* __r
       own_frags(base, ld, own, T, h, bq);
       own_frags(gbase, d, own, T, h, bg);
       own_frags(obase, d, own, T, h, bo);
-      // exp(s / 8 - L) = exp2(s c - L log2 e) with c = log2 e / 8, and ds = p (dp - D) / 8 = p (dp / 8 - D / 8)
-      const float L2 = own < T ? lrow[own] * log2e : 0.f;
+      const float L2 = own < T ? lrow[own] * kLog2e : 0.f;
       float D = 0.f;
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) D += dot8(__builtin_bit_cast(uint4, bo[ks]), __builtin_bit_cast(uint4, bg[ks]));
       D += __shfl_xor(D, 32, 64);
-      const float Dsc = D * scale;
       if (!staged) __syncthreads();
       staged = true;
       if (blk >= NT) break;
-      f32x16_t acc[2] = {zero16(), zero16()};
-      for (int kt = 0; kt < NT; ++kt) {
-        const f32x16_t s = tile_nt(Xs, plane_b, kt * 32, bq, lane);     // [key][query]
-        f32x16_t dp = tile_nt(Ys, plane_b, kt * 32, bg, lane);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) dp[i] = __builtin_amdgcn_exp2f(fmaf(s[i], c2, -L2)) * fmaf(dp[i], scale, -Dsc);
-        if (kt == NT - 1) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if (kt * 32 + (i >> 2) * 8 + h * 4 + (i & 3) >= T) dp[i] = 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const bf16x8_t dsb = pack_frag(dp, j);
-#pragma unroll
-          for (int mt = 0; mt < 2; ++mt)
-            acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Xs, plane_b, mt, kt * 32 + 16 * j, lane), dsb, acc[mt], 0, 0, 0);
-        }
-      }
-      store_cols(dbase + (size_t)own * ld, acc, h, own < T);
+      f32x16_t dq[2];
+      walk_keys(Xs, Ys, plane_b, NT, T, bq, bg, L2, D * kScale, lane, dq);
+      store_cols(dbase + (size_t)own * ld, dq, h, own < T);
     }
   } else {
-    // ---- by key block: dv^T = do^T p, dk^T = q^T ds ----
+    // ---- by key block ----
     float* Ls = reinterpret_cast<float*>(smem + 4 * plane_b);
     float* Ds = Ls + Tp;
     {
@@ -335,17 +448,7 @@ __global__ void __launch_bounds__(256, 2) attn_mfma_bwd_kernel(const bf16_t* __r
       po.fetch(obase, d, T);
       px.put(Xs, plane_b, Tp);
       py.put(Ys, plane_b, Tp);
-      // D of a token: the eight lanes that hold its pieces
-#pragma unroll
-      for (int k = 0; k < NP; ++k) {
-        float D = dot8(po.v[k], py.v[k]);
-        D += __shfl_xor(D, 1, 64);
-        D += __shfl_xor(D, 2, 64);
-        D += __shfl_xor(D, 4, 64);
-        const int i = threadIdx.x + k * blockDim.x, r = i >> 3;
-        if ((i & 7) == 0 && r < Tp) Ds[r] = D * scale;
-      }
-      for (int t = threadIdx.x; t < Tp; t += blockDim.x) Ls[t] = t < T ? lrow[t] * log2e : 0.f;
+      put_sums(py, po, lrow, T, Tp, Ls, Ds);
     }
     bool staged = false;
     for (int blk = group * waves + wave; blk < NT || !staged; blk += groups * waves) {
@@ -356,34 +459,8 @@ __global__ void __launch_bounds__(256, 2) attn_mfma_bwd_kernel(const bf16_t* __r
       if (!staged) __syncthreads();
       staged = true;
       if (blk >= NT) break;
-      f32x16_t dk[2] = {zero16(), zero16()}, dv[2] = {zero16(), zero16()};
-      for (int qt = 0; qt < NT; ++qt) {
-        f32x16_t p = tile_nt(Xs, plane_b, qt * 32, bk, lane);           // [query][key]
-        f32x16_t dp = tile_nt(Ys, plane_b, qt * 32, bv, lane);
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const int r0 = qt * 32 + i4 * 8 + h * 4;
-          const float4 L4 = *reinterpret_cast<const float4*>(Ls + r0);
-          const float4 D4 = *reinterpret_cast<const float4*>(Ds + r0);
-          const float Lr[4] = {L4.x, L4.y, L4.z, L4.w}, Dr[4] = {D4.x, D4.y, D4.z, D4.w};
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const int i = i4 * 4 + k;
-            const float pp = __builtin_amdgcn_exp2f(fmaf(p[i], c2, -Lr[k]));
-            p[i] = pp;
-            dp[i] = pp * fmaf(dp[i], scale, -Dr[k]);
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const bf16x8_t pb = pack_frag(p, j), dsb = pack_frag(dp, j);
-#pragma unroll
-          for (int mt = 0; mt < 2; ++mt) {
-            dv[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Ys, plane_b, mt, qt * 32 + 16 * j, lane), pb, dv[mt], 0, 0, 0);
-            dk[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_read_tr(Xs, plane_b, mt, qt * 32 + 16 * j, lane), dsb, dk[mt], 0, 0, 0);
-          }
-        }
-      }
+      f32x16_t dk[2], dv[2];
+      walk_queries(Xs, Ys, Ls, Ds, plane_b, NT, bk, bv, lane, dk, dv);
       store_cols(dbase + (size_t)own * ld + d, dk, h, own < T);
       store_cols(dbase + (size_t)own * ld + 2 * d, dv, h, own < T);
     }
@@ -415,6 +492,15 @@ int bwd_launch(const cnnk_attn_desc* d, const void* qkv, const void* o, const vo
       (const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)d_o, lse, (bf16_t*)dqkv, d->T, d->heads, pairs, parts);
   return launch_status();
 }
+int bwd_whole_launch(const cnnk_attn_desc* d, const void* qkv, const void* o, const void* d_o, const float* lse, void* dqkv, hipStream_t st) {
+  static bool raised = false;
+  const int NT = (d->T + 31) / 32;
+  const int rc = raise_lds(attn_mfma_bwd_whole_kernel, &raised, 8 * 8 * 32 * ROW_B + 2 * 8 * 32 * 4);
+  if (rc != CNNK_OK) return rc;
+  attn_mfma_bwd_whole_kernel<<<d->B * d->heads, 64 * NT, (size_t)8 * NT * 32 * ROW_B + (size_t)2 * NT * 32 * sizeof(float), st>>>(
+      (const bf16_t*)qkv, (const bf16_t*)o, (const bf16_t*)d_o, lse, (bf16_t*)dqkv, d->T, d->heads);
+  return launch_status();
+}
 }  // namespace
 
 bool attn_mfma_supported(const cnnk_attn_desc* d) {
@@ -429,23 +515,27 @@ int attn_mfma_fwd(const cnnk_attn_desc* d, const void* qkv, void* o, float* lse,
   return fwd_launch<4>(d, qkv, o, lse, NT, 1, st);
 }
 
+// Which backward kernel.  In parts a pair's work overlaps better within a CU, as a whole it is loaded once and a CU holds nearly as many pairs in
+// less LDS than twice the parts take.  Up to 128 tokens: as a whole where the parts need so many more rounds that they are slower, a round of whole
+// pairs taking about 1.6 rounds of parts.  A CU holds 9, 4, 3, 2 whole pairs of one to four blocks (LDS) and the parts of 4, 2, 1, 1
+// (registers: eight wavefronts).  us, whole / parts / all four matrices in LDS in every case, as before the parts: 32 tokens 768 pairs 11.3 / 11.6 / 11.8, 1536 16.6 /
+// 20.7 / 18.5; 64 tokens 512 pairs 14.9 / 14.0 / 15.2, 576 15.9 / 17.7 / 17.0; 65 tokens 256 pairs 11.7 / 10.3 / 11.8, 576 19.6 / 21.9 / 19.4, 1536 37.5 /
+// 46.2 / 42.4; 128 tokens 512 pairs 25.2 / 27.3 / 26.9, 576 33.9 / 31.5 / 36.4.
+// Longer sequences: four parts where they all fit the device at once, then as a whole while that is one round, or a second one that is
+// nearly full, otherwise two parts of two blocks to a wavefront.  us, whole / two / four parts: 197 tokens 96 pairs 20.8 / 17.6 / 16.3, 160 22.6 / 24.4 / 24.4, 256
+// 26.7 / 28.0 / 31.3, 288 42.8 / 37.1 / 36.3, 512 49.1 / 49.8 / 56.4, 768 71.7 / 68.4 / 76.6.
 int attn_mfma_bwd(const cnnk_attn_desc* d, const void* qkv, const void* o, const void* d_o, const float* lse, void* dqkv,
                   hipStream_t st) {
-  const int NT = (d->T + 31) / 32, half = (NT + 1) / 2;
-  // a launch has fewer than 2^32 threads, here at most 128 to 512 a head
-  constexpr long kMaxPairs = 1L << 22;
-  if ((long)d->B * d->heads > kMaxPairs && d->B > 1) {
-    cnnk_attn_desc part = *d;
-    part.B = d->B / 2;
-    const size_t rows = (size_t)part.B * d->T, width = (size_t)d->heads * kDH;
-    int rc = attn_mfma_bwd(&part, qkv, o, d_o, lse, dqkv, st);
-    if (rc != CNNK_OK) return rc;
-    part.B = d->B - part.B;
-    return attn_mfma_bwd(&part, (const bf16_t*)qkv + rows * 3 * width, (const bf16_t*)o + rows * width, (const bf16_t*)d_o + rows * width,
-                         lse + rows * d->heads, (bf16_t*)dqkv + rows * 3 * width, st);
+  const int NT = (d->T + 31) / 32, half = (NT + 1) / 2, pairs = d->B * d->heads;
+  bool whole;
+  if (NT <= 4) {
+    constexpr int kHeld[4] = {9, 4, 3, 2}, kHeldInParts[4] = {4, 2, 1, 1};
+    const long rounds = (pairs + 256L * kHeld[NT - 1] - 1) / (256 * kHeld[NT - 1]), parts = (pairs + 256L * kHeldInParts[NT - 1] - 1) / (256 * kHeldInParts[NT - 1]);
+    whole = 8 * rounds < 5 * parts;
+  } else {
+    whole = (pairs > 128 && pairs <= 256) || (pairs > 448 && pairs <= 512);
   }
-  // Up to four wavefronts, a block each; long sequences: two blocks each, or twice the workgroups where those all fit the device at once
-  // (197 tokens: 96 pairs 14.8 us, with two workgroups a pair 15.5).
+  if (whole) return bwd_whole_launch(d, qkv, o, d_o, lse, dqkv, st);
   if (NT <= 4) return bwd_launch<4>(d, qkv, o, d_o, lse, dqkv, NT, 2, st);
-  return bwd_launch<8>(d, qkv, o, d_o, lse, dqkv, half, d->B * d->heads <= 128 ? 4 : 2, st);
+  return bwd_launch<8>(d, qkv, o, d_o, lse, dqkv, half, pairs <= 128 ? 4 : 2, st);
 }

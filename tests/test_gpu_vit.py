@@ -247,10 +247,18 @@ def test_attention_in_parts(K, B, T, heads, rise):
     _attention_case(K, B, T, heads, 64, "bf16", rise)
 
 
+# so many heads that the backward pass takes each as a whole: one to eight blocks of tokens, the first count of heads past the line
+# and one more round
+@pytest.mark.parametrize("B,T,heads,rise", [(205, 20, 5, 0), (57, 33, 9, 0), (103, 64, 5, 0), (257, 65, 1, 0), (52, 96, 5, 60), (257, 97, 1, 0), (64, 128, 8, 0),
+                                            (19, 65, 41, 0), (43, 129, 3, -60), (32, 160, 8, 0), (13, 161, 10, 0), (9, 197, 50, 0), (15, 256, 9, 0)])
+def test_attention_as_a_whole(K, B, T, heads, rise):
+    _attention_case(K, B, T, heads, 64, "bf16", rise)
+
+
 # scores that all lie far from zero, at lengths that are no multiple of 32: a key past the end has score 0, and its exponential
 # relative to the others' log-sum-exp is beyond every float
 @pytest.mark.parametrize("B,T,heads,shift", [(2, 33, 3, -110), (1, 65, 6, -128), (3, 101, 2, -200), (40, 65, 6, -128), (1, 130, 2, -128), (2, 197, 2, -150),
-                                             (16, 197, 12, -128), (22, 129, 12, -128), (1, 65, 2, 128), (1, 197, 2, 200)])
+                                             (16, 197, 12, -128), (22, 129, 12, -128), (44, 65, 6, -128), (1, 65, 2, 128), (1, 197, 2, 200)])
 def test_attention_scores_far_from_zero(K, B, T, heads, shift):
     _attention_case(K, B, T, heads, 64, "bf16", 0, shift)
 
