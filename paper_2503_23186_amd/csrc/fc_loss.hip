@@ -11,14 +11,18 @@ constexpr int kLT = 1024;   // threads of the logits kernel
 constexpr int kWaveClasses = 1024;
 
 // One workgroup per sample: z = W x + b by wave-level dot products, then the softmax.  The kernel
-// is latency-bound (a sample's 100 dot products), so the workgroup is wide, 16 wavefronts take 8
-// classes each per round (4 a round: two rounds of memory latency for 100 classes), and up to kWaveClasses classes every wavefront forms the
-// maximum and the sum of the exponentials for itself: one barrier instead of four (768 features, 100 classes, 4 samples 15.2 -> 12.4 us).
-template <typename T>
+// is latency-bound (a sample's 100 dot products) and, with many samples, bound by the L2s' rate: the workgroup is wide, 16 wavefronts take 2
+// classes each per round, and up to kWaveClasses classes every wavefront forms the maximum and the sum of the exponentials for itself:
+// one barrier instead of four.  Two classes and the features that there are (CH pieces of 512) leave the registers to two workgroups a CU;
+// us of the head's two launches, weights not in the L2s, with eight classes a round and room for 2048 features, which spilled / four / two: 8 x 16 -> 10 8.2 /
+// 6.7 / 6.2, 8 x 768 -> 100 15.8 / 15.0 / 12.7, 200 x 2048 -> 100 49.6 / 44.1 / 42.4, 512 x 768 -> 1000 219 / 201 / 193.
+// CH: pieces of 512 features that a wavefront keeps (0: any number of features, any alignment).  Up to two, a class's bias is loaded
+// with its weights; with four, behind its sum (200 x 2048 -> 4096 822 us, 886 with the weights; 8 x 768 -> 100 as given above, 13.9 behind the sum).
+template <typename T, int CH>
 __global__ void __launch_bounds__(kLT) logits_softmax_kernel(const T* __restrict__ x, const float* __restrict__ W,
                                                             const float* __restrict__ b,
                                                             const int* __restrict__ labels, int N, int F, int K,
-                                                            int vec, float* __restrict__ dz, float* __restrict__ loss_n,
+                                                            float* __restrict__ dz, float* __restrict__ loss_n,
                                                             int* __restrict__ pred, float* __restrict__ probs) {
   __shared__ float z[kMaxClasses];
   __shared__ float red[kLT / 64];
@@ -26,32 +30,32 @@ __global__ void __launch_bounds__(kLT) logits_softmax_kernel(const T* __restrict
   const int n = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const T* xr = x + (size_t)n * F;
   const int lab = labels[n];
-  if (vec) {
-    // F % 8 == 0 and F <= 2048: the sample's features stay in registers (8 consecutive per lane
-    // and 512-feature chunk), weight rows stream in as 32-byte pieces, eight classes in flight
-    float xv[4][8];
+  if constexpr (CH > 0) {
+    // F % 8 == 0 and F <= 512 CH: the sample's features stay in registers (8 consecutive per lane
+    // and 512-feature chunk), weight rows stream in as 32-byte pieces, two classes in flight
+    constexpr int Q = 2;
+    float xv[CH][8];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < CH; ++c) {
       const int f0 = (lane + 64 * c) * 8;
       if (c * 512 < F) load8(xr + (f0 < F ? f0 : 0), xv[c]);   // uniform condition: the chunks load together
       if (f0 >= F)
 #pragma unroll
         for (int e = 0; e < 8; ++e) xv[c][e] = 0.f;
     }
-    constexpr int Q = 8;
     for (int j0 = wave; j0 < K; j0 += Q * (kLT / 64)) {
       float acc[Q], bj[Q];
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
         acc[q] = 0.f;
-        bj[q] = b[min(j0 + q * (kLT / 64), K - 1)];
+        if (CH <= 2) bj[q] = b[min(j0 + q * (kLT / 64), K - 1)];
       }
       // Unconditional loads, so that the classes' weight pieces are in flight together (under
       // per-lane conditions the compiler waits for every load before it issues the next): a class
       // past the end re-reads the last one (its logit is not stored), a lane past the end of the
       // features reads the row's start against features that are zero.
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
+      for (int c = 0; c < CH; ++c) {
         if (c * 512 >= F) break;           // uniform
         const int f0 = (lane + 64 * c) * 8;
         const int fl = f0 < F ? f0 : 0;
@@ -67,7 +71,7 @@ __global__ void __launch_bounds__(kLT) logits_softmax_kernel(const T* __restrict
       for (int q = 0; q < Q; ++q) {
         const int j = j0 + q * (kLT / 64);
         const float sq = wave_sum(acc[q]);
-        if (lane == 0 && j < K) z[j] = sq + bj[q];
+        if (lane == 0 && j < K) z[j] = sq + (CH <= 2 ? bj[q] : b[j]);
       }
     }
   } else {
@@ -289,6 +293,15 @@ extern "C" size_t cnnk_fc_workspace_bytes(const cnnk_fc_desc* d) {
 }
 
 namespace {
+template <typename T>
+void launch_logits(const void* x, const float* W, const float* b, const int* labels, int N, int F, int K, bool vec, float* dz, float* loss_n, int* pred,
+                   float* probs, hipStream_t st) {
+  auto run = [&](auto kernel) { kernel<<<N, kLT, 0, st>>>((const T*)x, W, b, labels, N, F, K, dz, loss_n, pred, probs); };
+  if (!vec) run(logits_softmax_kernel<T, 0>);
+  else if (F <= 1024) run(logits_softmax_kernel<T, 2>);
+  else run(logits_softmax_kernel<T, 4>);
+}
+
 // Both entry points of the classifier head: `scratch` holds dz (N * classes floats) and the
 // per-sample losses (N floats); every element is written by the first launch before the second
 // reads it, so its previous contents do not matter.
@@ -304,16 +317,16 @@ int fc_enqueue(const cnnk_fc_desc* d, const void* x, const float* W, const float
   // tensors themselves start on a 16-byte boundary
   const bool aligned = (((uintptr_t)x | (uintptr_t)W) & 15u) == 0;
   const bool vec8 = F % 8 == 0 && aligned;
-  const int vec = (vec8 && F <= 2048) ? 1 : 0;
+  const bool vec = vec8 && F <= 2048;
   if (d->dtype == CNNK_BF16) {
-    logits_softmax_kernel<bf16_t><<<N, kLT, 0, st>>>((const bf16_t*)x, W, b, labels, N, F, K, vec, dz, loss_n, pred, probs);
+    launch_logits<bf16_t>(x, W, b, labels, N, F, K, vec, dz, loss_n, pred, probs, st);
     if (!backward) loss_kernel<<<1, kT, 0, st>>>(loss_n, N, loss);
     else if (vec8)
       fc_bwd_kernel<bf16_t, 1><<<nblk, kT, 0, st>>>(dz, loss_n, (const bf16_t*)x, W, N, F, K, fblocks, loss, dW, db, (bf16_t*)dx);
     else
       fc_bwd_kernel<bf16_t, 0><<<nblk, kT, 0, st>>>(dz, loss_n, (const bf16_t*)x, W, N, F, K, fblocks, loss, dW, db, (bf16_t*)dx);
   } else {
-    logits_softmax_kernel<float><<<N, kLT, 0, st>>>((const float*)x, W, b, labels, N, F, K, vec, dz, loss_n, pred, probs);
+    launch_logits<float>(x, W, b, labels, N, F, K, vec, dz, loss_n, pred, probs, st);
     if (!backward) loss_kernel<<<1, kT, 0, st>>>(loss_n, N, loss);
     else if (vec8)
       fc_bwd_kernel<float, 1><<<nblk, kT, 0, st>>>(dz, loss_n, (const float*)x, W, N, F, K, fblocks, loss, dW, db, (float*)dx);

@@ -429,7 +429,9 @@ def test_pool_fwd_bwd(K, dtype):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("N,F,classes", [(8, 16, 100), (256, 512, 100), (33, 640, 100), (5, 2048, 10), (7, 52, 10), (3, 1024, 7), (64, 1536, 100), (4, 2056, 5),
                                          # classes: one past a round of a workgroup, the last that a wavefront takes alone, one more, the most
-                                         (3, 24, 129), (3, 64, 1024), (2, 52, 1025), (2, 64, 1025), (2, 16, 4096)])
+                                         (3, 24, 129), (3, 64, 1024), (2, 52, 1025), (2, 64, 1025), (2, 16, 4096),
+                                         # features: one to four pieces of 512, whole, one octet more
+                                         (3, 512, 33), (3, 520, 33), (2, 1024, 17), (2, 1032, 33), (2, 1544, 65), (2, 2048, 33)])
 def test_fc_softmax_xent(K, N, F, classes, dtype):
     rng = np.random.default_rng(41)
     x = rep(rng.standard_normal((N, F)), dtype)

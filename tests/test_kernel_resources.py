@@ -39,3 +39,12 @@ def test_small_tiles_leave_the_registers_to_as_many_workgroups_as_lds_holds(kern
     assert len(small) == 13
     for name, (registers, spilled, scratch) in small.items():
         assert registers <= 64 and spilled == 0 and scratch == 0, name
+
+
+def test_classifier_head_keeps_its_registers(kernels):
+    """1024 threads to a workgroup: 128 registers are the most, 64 let a CU hold two workgroups.  Nothing spills, also with the
+    features of a 2048-wide row in registers."""
+    head = {n: v for n, v in kernels.items() if n.startswith("logits_softmax_kernel<")}
+    assert len(head) == 6
+    for name, (registers, spilled, scratch) in head.items():
+        assert spilled == 0 and scratch == 0 and registers <= (128 if ", 4>" in name else 64), (name, registers)
