@@ -88,25 +88,31 @@ __global__ void __launch_bounds__(256) direct_dgrad_kernel(ConvGeom g, const T* 
   Elem<T>::st(dx + idx, acc);
 }
 
-// Partial weight gradient over the output positions [p*chunk, (p+1)*chunk) into part[p][i].
-template <typename T>
+// Partial weight gradient over the output positions [p*chunk, (p+1)*chunk) into part[p][i].  H threads share a sum, a run of the
+// positions each, Q positions a round (see below).
+template <typename T, int H, int Q>
 __global__ void __launch_bounds__(256) direct_wgrad_kernel(ConvGeom g, const T* __restrict__ x,
                                                            const T* __restrict__ dy,
                                                            float* __restrict__ part, int chunk) {
+  __shared__ float other[H > 1 ? 256 / H : 1];
   const int nw = g.Cout * g.R * g.S * g.Cin;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= nw) return;
+  const int col = threadIdx.x % (256 / H), run = H == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / (256 / H));     // whole wavefronts
+  const int mine = blockIdx.x * (256 / H) + col;
+  if (H == 1 && mine >= nw) return;
+  const int i = H == 1 ? mine : min(mine, nw - 1);
   const int c = i % g.Cin;
   int t = i / g.Cin;
   const int s = t % g.S; t /= g.S;
   const int r = t % g.R;
   const int kk = t / g.R;
   const long M = (long)g.N * g.Ho * g.Wo;
-  const long m0 = (long)blockIdx.y * chunk;
-  const long m1 = (m0 + chunk < M) ? m0 + chunk : M;
-  // Sixteen positions per round, all loads issued before the first product (one position at a time is a
-  // chain of memory latencies behind 64-bit divisions: 29 us for a 3->16 gradient of 8192 positions, 64 to a thread;
-  // eight at a time 13.6, sixteen and 32 to a thread 9.7); a position outside the image or the range reads element 0 and multiplies zero.  The
+  const long end = ((long)blockIdx.y + 1) * chunk < M ? ((long)blockIdx.y + 1) * chunk : M;
+  const int per = (chunk + H - 1) / H;
+  const long m0 = (long)blockIdx.y * chunk + run * per;
+  const long m1 = m0 + per < end ? m0 + per : end;
+  // Q positions per round, all loads issued before the first product (one position at a time is a
+  // chain of memory latencies behind 64-bit divisions: 29 us for a 3->16 gradient of 8192 positions, 64 to a sum;
+  // with its reduction eight at a time 14.6, sixteen and two threads to a sum 11.5); a position outside the image or the range reads element 0 and multiplies zero.  The
   // position's coordinates advance by one, as the positions do.
   int wo, ho, n;
   {
@@ -123,7 +129,6 @@ __global__ void __launch_bounds__(256) direct_wgrad_kernel(ConvGeom g, const T* 
     }
   }
   float acc = 0.f;
-  constexpr int Q = 16;
   for (long m = m0; m < m1; m += Q) {
     float dv[Q], xv[Q];
 #pragma unroll
@@ -139,7 +144,13 @@ __global__ void __launch_bounds__(256) direct_wgrad_kernel(ConvGeom g, const T* 
 #pragma unroll
     for (int k = 0; k < Q; ++k) acc = fmaf(dv[k], xv[k], acc);
   }
-  part[(size_t)blockIdx.y * nw + i] = acc;
+  if (H > 1) {
+    if (run == 1) other[col] = acc;
+    __syncthreads();
+    if (run > 0) return;
+    acc += other[col];
+  }
+  if (mine < nw) part[(size_t)blockIdx.y * nw + i] = acc;
 }
 
 // out[i] = sum_p part[p][i], deterministic.  GROUPS thread groups share the P partials of a float4 column (group g takes p = g, g+GROUPS, ...);
@@ -259,7 +270,7 @@ void wgrad_split(const ConvGeom& g, int* chunk, int* P) {
   const long nw = (long)g.Cout * g.R * g.S * g.Cin;
   const long out_blocks = (nw + 255) / 256;
   long want = (2048 + out_blocks - 1) / out_blocks;
-  const long maxP = (M + 31) / 32;
+  const long maxP = (M + 63) / 64;
   if (want > maxP) want = maxP;
   if (want > 4096) want = 4096;
   if (want < 1) want = 1;
@@ -302,12 +313,17 @@ int conv_direct_wgrad(const ConvGeom& g, int dtype, const void* x, const void* d
   int chunk, P;
   wgrad_split(g, &chunk, &P);
   const int nw = g.Cout * g.R * g.S * g.Cin;
-  dim3 grid((nw + 255) / 256, P);
   float* part = (float*)ws;
-  if (dtype == CNNK_BF16)
-    direct_wgrad_kernel<bf16_t><<<grid, 256, 0, st>>>(g, (const bf16_t*)x, (const bf16_t*)dy, part, chunk);
-  else
-    direct_wgrad_kernel<float><<<grid, 256, 0, st>>>(g, (const float*)x, (const float*)dy, part, chunk);
+  // From 17 to 64 positions a sum is three to eight rounds of eight: two threads share it.  (Twice the partial sums instead took twice the
+  // scratch, and their reduction what the shorter sums gave: 512 images of 9 x 9, 5 -> 7 strided, one thread 39 us, twice the sums 60, two threads 34.
+  // Longer sums, one / two threads: 64 x 16 x 16 positions, 16 -> 32 channels 76 / 84.)
+  const bool pairs = chunk > 16 && chunk <= 64;
+  auto run = [&](auto kernel, int cols, auto t) {
+    using T = decltype(t);
+    kernel<<<dim3((nw + cols - 1) / cols, P), 256, 0, st>>>(g, (const T*)x, (const T*)dy, part, chunk);
+  };
+  if (dtype == CNNK_BF16) pairs ? run(direct_wgrad_kernel<bf16_t, 2, 16>, 128, bf16_t{}) : run(direct_wgrad_kernel<bf16_t, 1, 8>, 256, bf16_t{});
+  else pairs ? run(direct_wgrad_kernel<float, 2, 16>, 128, float{}) : run(direct_wgrad_kernel<float, 1, 8>, 256, float{});
   if (launch_status() != CNNK_OK) return CNNK_ERR_HIP;
   return reduce_partials(part, dw, nw, P, st);
 }

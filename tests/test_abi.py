@@ -140,6 +140,16 @@ def test_argument_errors_are_reported_before_any_launch(cnnk):
     assert e.value.status == 1
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("N,H,W,Cin,Cout,k,stride", [(1, 1, 1, 3, 7, 1, 1), (3, 7, 7, 512, 100, 3, 2), (1, 8, 8, 20, 20, 3, 1), (1, 13, 5, 12, 9, 3, 1), (8, 32, 32, 16, 15, 3, 1)])
+def test_scratch_of_a_direct_weight_gradient(cnnk, N, H, W, Cin, Cout, k, stride, dtype):
+    """A partial gradient for every 64 output positions, and none for fewer: the scratch that callers have always been asked for."""
+    d = cnnk.conv_desc(N, H, W, Cin, Cout, k, k, stride, k // 2, dtype)
+    positions = N * ((H + 2 * (k // 2) - k) // stride + 1) * ((W + 2 * (k // 2) - k) // stride + 1)
+    weights = Cout * k * k * Cin
+    assert cnnk.cnnk_conv2d_workspace_bytes(d, cnnk.PASS_WGRAD) <= ((positions + 63) // 64 * weights * 4 + 255) // 256 * 256
+
+
 def test_train_step_validates_the_layer_list(cnnk):
     import workloads as WL
     net = WL.mini_resnet()
