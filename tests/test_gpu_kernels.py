@@ -133,6 +133,18 @@ def test_conv_fwd_dgrad_wgrad(K, shape, dtype):
     assert max_rel_err(host(gdw), dw_ref) <= acc_tol
 
 
+# direct kernels: filter rows of a group of taps, one more, one less and several; sums of 15 to 17, 33, 63 to 65 and 130 positions
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shape", [(1, 3, 5, 5, 7, 3, 1), (1, 4, 4, 3, 5, 3, 1), (1, 17, 1, 9, 4, 1, 1), (1, 3, 11, 7, 9, 1, 1), (3, 7, 6, 10, 6, 3, 2),
+                                   (1, 7, 9, 17, 3, 1, 1), (1, 8, 8, 1, 300, 3, 1), (1, 5, 13, 11, 6, 3, 1), (5, 13, 2, 6, 11, 3, 1), (70, 9, 9, 5, 7, 3, 2)])
+def test_direct_kernels_at_the_edges_of_their_groups(K, shape, dtype):
+    K.cnnk_tune(8, -1)
+    try:
+        test_conv_fwd_dgrad_wgrad(K, shape, dtype)
+    finally:
+        K.cnnk_tune(8, 0)
+
+
 # (N, H, W, Cin, Cout, R, stride): odd images (strided data gradients with parities of different sizes), channel tiles
 # that end inside a tile, 64 and 32 channels per stage in either direction, reductions shorter than the pipeline,
 # more stages than one group of an even split has, and one pixel
