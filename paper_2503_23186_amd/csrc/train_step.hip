@@ -76,6 +76,12 @@ int wgrad_group(const Walk& w) {
 
 size_t max_sz(size_t a, size_t b) { return a > b ? a : b; }
 
+// whether two tensors of `bytes` bytes share memory
+bool share(const void* a, const void* b, size_t bytes) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + bytes && y < x + bytes;
+}
+
 // Checks every layer and gathers tensor sizes and the workspace need.  n_slots/n_params < 0:
 // sizes are unknown (workspace query), ids are only checked for being non-negative.
 int walk_layers(const cnnk_layer* L, int n, int n_slots, int n_params, Walk* w) {
@@ -229,6 +235,7 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
   if (rc != CNNK_OK) return rc;
   if (!B->ws || B->ws_bytes < step_workspace(w)) return CNNK_ERR_WORKSPACE;
   const bool bf16 = w.dtype == CNNK_BF16;
+  const size_t elem = bf16 ? sizeof(bf16_t) : sizeof(float);
   for (size_t s = 0; s < w.slot_elems.size(); ++s) {
     if (w.slot_elems[s] == 0) continue;
     if (!B->act[s] || (s != 0 && !B->dact[s])) return CNNK_ERR_NULL;
@@ -409,8 +416,10 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
         rc = cnnk_pool_fwd(&l.d.pool, B->act[l.in0], B->act[l.out], B->pool_idx[i], stream);
         break;
       case CNNK_OP_ADD:
-        // a batch norm of the sum that comes next starts from partial sums made here
-        if (i + 1 < n && L[i + 1].op == CNNK_OP_BN && L[i + 1].in0 == l.out && g_cnnk_tune[20] >= 0) {
+        // A batch norm of the sum that comes next starts from partial sums made here; not of a sum in place, whose first row (what
+        // the partial sums are relative to) every workgroup reads from both summands while others store
+        if (i + 1 < n && L[i + 1].op == CNNK_OP_BN && L[i + 1].in0 == l.out && g_cnnk_tune[20] >= 0 &&
+            !share(B->act[l.out], B->act[l.in0], w.slot_elems[l.out] * elem) && !share(B->act[l.out], B->act[l.in1], w.slot_elems[l.out] * elem)) {
           const size_t rows = w.slot_elems[l.out] / L[i + 1].d.bn.C;
           rc = add_stats(w.dtype, B->act[l.in0], B->act[l.in1], B->act[l.out], rows, L[i + 1].d.bn.C, &handed, ws, (hipStream_t)stream);
         } else {
@@ -607,7 +616,9 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
         break;
       case CNNK_OP_ADD: {
         const int ins[2] = {l.in0, l.in1};
-        if (l.in0 != 0 && l.in1 != 0 && B->dact[l.in0] != B->dact[l.in1] && g_cnnk_tune[20] >= 0) {
+        const size_t bytes = w.slot_elems[l.out] * elem;
+        if (l.in0 != 0 && l.in1 != 0 && g_cnnk_tune[20] >= 0 && !share(B->dact[l.in0], B->dact[l.in1], bytes) &&
+            !share(B->dact[l.in0], B->dact[l.out], bytes) && !share(B->dact[l.in1], B->dact[l.out], bytes)) {
           rc = grad_route2(w.slot_elems[l.out], w.dtype, B->dact[l.out], B->dact[l.in0], written[l.in0], B->dact[l.in1], written[l.in1], (hipStream_t)stream);
           written[l.in0] = written[l.in1] = 1;
           break;

@@ -343,6 +343,37 @@ def test_sums_that_make_their_batch_norms_partial_sums_give_the_same_bits(widths
             assert torch.equal(a.bn_save[i], b.bn_save[i]) and torch.equal(a.bn_running[i], b.bn_running[i])
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("summand", ["a", "b"])
+def test_sums_in_place(dtype, summand):
+    """The sum of two convolutions' outputs, which nothing else reads, in the memory of one of them, its gradient likewise: the launches
+    that take a sum apart from its batch norm and each gradient from the other, and the same bits as with memory of its own."""
+    from paper_2503_23186_amd import StepRunner
+    net = WL.mini_preact(batch=9, dtype=dtype, size=16, widths=(64, 160))
+    inp = WL.make_inputs(net, 41, perturb_bn=True)
+    runs = []
+    for in_place in (False, True):
+        r = StepRunner(net.layers, net.slots, [p["shape"] for p in net.params], net.dtype)
+        sums = [L for L in net.layers if L["op"] == "add"]
+        assert len(sums) == 2
+        if in_place:
+            for L in sums:
+                r.buffers.act[L["y"]] = r.act[L[summand]].data_ptr()
+                r.buffers.dact[L["y"]] = r.dact[L[summand]].data_ptr()
+        r.load(inp["x"], inp["labels"], inp["params"], inp["mom"])
+        for _ in range(2):
+            r.step(0.1, 0.9, 1e-4)
+        torch.cuda.synchronize()
+        runs.append(r)
+    a, b = runs
+    assert torch.equal(a.loss, b.loss)
+    for k in range(len(net.params)):
+        assert torch.equal(a.grad[k], b.grad[k]) and torch.equal(a.param[k], b.param[k])
+    for i, L in enumerate(net.layers):
+        if L["op"] == "bn":
+            assert torch.equal(a.bn_save[i], b.bn_save[i]) and torch.equal(a.bn_running[i], b.bn_running[i])
+
+
 @pytest.mark.parametrize("group", [2, 5, 16])
 def test_grouped_weight_gradients_give_the_same_bits(group):
     """Weight gradients forked onto the second stream one by one and several at a time, their reductions and updates
