@@ -392,6 +392,40 @@ def test_convolution_tail_of_the_validation_pass(k, stride, c0, c1, size, batch)
         assert max_rel_err(host(run.act[L["y"]]), want) <= (8e-3 if L["op"] == "add" or L["res"] >= 0 else 4e-3), (i, L)
 
 
+# The same tails where a workgroup walks several tiles (tuning key 18 = 1: one workgroup on each XCD, three ragged tiles and more to it),
+# with each tile shape that walks: the bits of one tile to a workgroup.
+@pytest.mark.parametrize("tile", [2, 4, 5, 6, 7])
+def test_convolution_tails_of_workgroups_that_walk(tile):
+    from paper_2503_23186_amd import StepRunner
+    net = WL.Net("tails", 23, "bf16")
+    a = net.bn(net.conv(net.slot(23, 17, 17, 3), 64, 3, 1))
+    r = net.bn(net.conv(a, 136, 1, 2), relu=False)
+    t = net.bn(net.conv(a, 136, 3, 2), relu=True, res=r)
+    u = net.bn(net.conv(a, 288, 1, 1))
+    t = net.add(net.conv(t, 264, 1, 1), net.conv(net.bn(net.conv(u, 96, 1, 1)), 264, 3, 2))
+    net.fc_loss(net.pool(t, "gap"))
+    inp = WL.make_inputs(net, 7, perturb_bn=True)
+    running = perturbed_running(net, 9)
+    acts = []
+    for walk in (-1, 1):
+        cnnk().cnnk_tune(16, tile + 1)
+        cnnk().cnnk_tune(18, walk)
+        try:
+            run = StepRunner(net.layers, net.slots, [p["shape"] for p in net.params], net.dtype)
+            run.load(inp["x"], inp["labels"], inp["params"], inp["mom"])
+            for i, (rm, rv) in running.items():
+                run.bn_running[i].copy_(torch.from_numpy(np.stack([rm, rv]).astype(np.float32)))
+            cnnk().cnnk_eval_step(run.c_layers, len(net.layers), run.buffers, run.labels, run.loss, run.pred, None,
+                                  torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+        finally:
+            cnnk().cnnk_tune(16, 0)
+            cnnk().cnnk_tune(18, 0)
+        acts.append([run.act[L["y"]].clone() for L in net.layers if L["op"] in ("bn", "add")] + [run.loss.clone()])
+    for one, several in zip(*acts):
+        assert torch.isfinite(one.float()).all() and torch.equal(one, several)
+
+
 def test_validation_pass_with_activations_sharing_memory():
     """Activations that are not needed at the same time may share a buffer: a batch norm's output then lies where
     the input of the convolution before it lay, so that layer cannot be the tail of that convolution's launch."""

@@ -176,6 +176,33 @@ def test_linear_workgroups_that_walk_several_tiles(K, rows, Kd, N, shape):
         cnnk.cnnk_tune(18, 0)
 
 
+# The step's own products among them (GELU's derivative and column sums in the data gradient of the second linear layer, residuals,
+# GELU) with one workgroup on each XCD: the bits of one tile to a workgroup.
+@pytest.mark.parametrize("shape", [18, 20, 1, 2])
+@pytest.mark.parametrize("batch,dim,mlp", [(9, 128, 512), (21, 192, 328)])
+def test_steps_whose_workgroups_walk_several_tiles(K, shape, batch, dim, mlp):
+    from paper_2503_23186_amd import cnnk
+    net = WL.vit_mini(batch=batch, dtype="bf16", image=32, patch=4, dim=dim, heads=dim // 64, layers=2, mlp=mlp)
+    inp = WL.make_vit_inputs(net, 6)
+    runs = []
+    for walk in (-1, 1):
+        cnnk.cnnk_tune(15, shape)
+        cnnk.cnnk_tune(18, walk)
+        try:
+            r = K.VitRunner(net)
+            r.load(inp["x"], inp["labels"], inp["params"], inp["mom"])
+            r.step(0.1, 0.9, 0.0)
+            torch.cuda.synchronize()
+        finally:
+            cnnk.cnnk_tune(15, 0)
+            cnnk.cnnk_tune(18, 0)
+        runs.append(r)
+    a, b = runs
+    assert torch.isfinite(a.loss).all() and torch.equal(a.loss, b.loss)
+    for k, name in enumerate(a.names):
+        assert torch.isfinite(a.grad[k]).all() and torch.equal(a.grad[k], b.grad[k]) and torch.equal(a.param[k], b.param[k]), name
+
+
 def _linear_case(K, rows, Kd, N, dtype):
     rng = np.random.default_rng(rows + Kd + N)
     x = rep(rng.standard_normal((rows, Kd)), dtype)
