@@ -76,7 +76,10 @@ const char* cnnk_version(void);
  * the 3x3 stride-1 LDS-patch kernels walks (0: as many as still leave two workgroups per CU; -1: one, and no
  * split of the reduction over two groups of wavefronts on grids of fewer than 512 workgroups); 17 = layers whose
  * weight gradients cnnk_train_step forks onto its second stream together (1: one by one; at most 16); 18 = workgroups on
- * an XCD of the kernels whose workgroups walk several tiles (0: as many as the device holds; -1: one to a tile).
+ * an XCD of the kernels whose workgroups walk several tiles (0: as many as the device holds; -1: one to a tile); 19 =
+ * partial sums a channel up to which a batch norm's last pass adds them up itself (0: 128; -1: none, a launch of its own
+ * adds them up); 20 = -1 makes cnnk_train_step run a sum in front of a batch norm and the batch norm's first pass, and a
+ * sum's gradients to its two summands, in launches of their own.
  * Process-wide, not thread-safe. */
 int cnnk_tune(int key, int value);
 

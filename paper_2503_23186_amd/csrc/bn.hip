@@ -72,10 +72,9 @@ __device__ __forceinline__ void block_reduce_store(float (*acc)[8], const W& w, 
   }
 }
 
-// Finalising reduction: one workgroup per channel sums the nb per-workgroup partials
-// part[v][c][0..nb) in double (coalesced rows, fixed-order tree).  Result valid in thread 0.
-// One wavefront per channel (four channels per workgroup): the lanes stride over the nb partials,
-// the xor-butterfly gives every lane the total.  Fixed order, no LDS, no barrier.
+// Finalising reduction of the nb per-workgroup partials part[v][c][0..nb) in double: one wavefront per channel (four channels
+// per workgroup), the lanes stride over the partials and add up across the wavefront (wave_sum, the total in every
+// lane).  Fixed order, no LDS, no barrier.
 constexpr int kFinCh = kT / 64;   // channels per finalising workgroup
 inline unsigned fin_blocks(int C) { return (unsigned)((C + kFinCh - 1) / kFinCh); }
 

@@ -159,8 +159,9 @@ int channel_sums_finalize(const float* part, int nb, int C, float* ch_sum, float
 // pieces of context through the per-thread pointers below (t_cnnk_x8_cache above, t_cnnk_sgd_fuse,
 // t_cnnk_wgrad_cus, t_cnnk_part_sums).  Contract, the same for all four: the step sets the pointer immediately
 // before ONE entry-point call on the same host thread and resets it to its neutral value (nullptr /
-// 256) right after that call returns, whatever the call's status; an entry point reads it once, at
-// entry.  Outside cnnk_train_step the values are always neutral, so a direct caller of the C ABI
+// 256) right after that call returns, whatever the call's status.  Hooks 1 to 3 are read once, at the entry point's
+// entry; hook 4 is read where a forward path adds up its channel sums, by its last launch helper (channel_sums_finalize,
+// called at most once and with the workspace left alone from there on).  Outside cnnk_train_step the values are always neutral, so a direct caller of the C ABI
 // never sees them, and calls from other host threads are unaffected (thread_local).  The library
 // keeps no other state between calls except two process-wide tables that are written once or by
 // an explicit call: the "dynamic LDS size already raised" flag of each kernel launcher (set on the
@@ -211,6 +212,7 @@ extern thread_local int t_cnnk_wgrad_cus;
 
 // Hook 4 of 4.  When set, a forward convolution whose batch norm is the very next call on the same stream and workspace may leave
 // its per-channel sums as partials part[2][C][nb] in the workspace (nb > 0) instead of adding them up in a launch of its own.
+// They have to stay there until the batch norm's launch: nothing else may be enqueued on that workspace in between.
 struct PartSums {
   const float* part;
   int nb;
