@@ -730,6 +730,13 @@ int validate_bn(const cnnk_bn_desc* d) {
 
 thread_local PartSums* t_cnnk_part_sums = nullptr;
 
+// Rows from which slabs are slower whatever the partials: with 1024 channels and more, passes over whole rows move large tensors
+// faster than passes over 128 bytes of every row.  Backward in bf16, us in slabs / over whole rows and with the launch, without and with a residual: 1024
+// channels 16384 rows 37.6 / 41.8, 50.6 / 52.7; 32768 67.6 / 66.8, 101 / 94; 65536 152 / 136, 212 / 184; 1536 channels 16384 rows 54.5 / 59.6, 77 / 80; 32768
+// 116 / 105, 171 / 140; 2048 channels 16384 rows 64 / 70, 98 / 101; 24576 106 / 105, 158 / 143; 32768 147 / 136, 211 / 188.  960 channels, 32768 rows 62.9 /
+// 64.1, 89 / 103 (more rows have more than 128 partials).
+bool bn_slabs_pay_for(size_t m, int C) { return C < 1024 || m <= 16384; }
+
 int channel_sums_finalize(const float* part, int nb, int C, float* ch_sum, float* ch_sumsq, hipStream_t st) {
   if (t_cnnk_part_sums && slab_pays(C, nb)) {
     t_cnnk_part_sums->part = part;
@@ -868,7 +875,7 @@ static int bn_bwd_launch(const cnnk_bn_desc* d, const void* dy, const void* x, c
   constexpr int APPLY = MODE == 1 || MODE == 4 ? 3 : MODE;      // the last pass behind dz_first
   T* const dz = dz_first ? (T*)dresidual : nullptr;
   const int nbs = C % kSlab == 0 ? slab_blocks(m, C) : 0;
-  if (nbs > 0 && slab_pays(C, nbs) && (size_t)nbs * 2 * C * sizeof(float) <= channel_stats_ws(m, C)) {
+  if (nbs > 0 && bn_slabs_pay_for(m, C) && slab_pays(C, nbs) && (size_t)nbs * 2 * C * sizeof(float) <= channel_stats_ws(m, C)) {
     const unsigned grid = (unsigned)nbs * (C / kSlab);
     bwd_partial_kernel<T, MODE, true><<<grid, kT, 0, st>>>((const T*)dy, (const T*)x, y, gamma, beta, save_mean, save_invstd, m, C, part, dz);
     if (dz_first)

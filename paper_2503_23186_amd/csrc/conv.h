@@ -219,6 +219,8 @@ struct PartSums {
   bool shifted;        // of add_stats: relative to the first row, any nb
 };
 extern thread_local PartSums* t_cnnk_part_sums;
+// whether passes over 64 channels of every row, which is how partials are consumed, pay for m rows of C channels
+bool bn_slabs_pay_for(size_t m, int C);
 
 // Forward convolution with a tail (no per-channel sums), for the shapes a matrix-core kernel takes
 // (conv_tail_supported); CNNK_ERR_UNSUPPORTED, and nothing launched, for the others.

@@ -339,7 +339,8 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
   };
   // Whether convolution i may leave its channel sums as partials in the workspace: its batch norm is the next call there.
   auto takes_partials = [&](int i) {
-    return i + 1 < n && L[i + 1].op == CNNK_OP_BN && L[i + 1].in0 == L[i].out && L[i + 1].d.bn.C == L[i].d.conv.Cout;
+    return i + 1 < n && L[i + 1].op == CNNK_OP_BN && L[i + 1].in0 == L[i].out && L[i + 1].d.bn.C == L[i].d.conv.Cout &&
+           bn_slabs_pay_for((size_t)L[i + 1].d.bn.N * L[i + 1].d.bn.H * L[i + 1].d.bn.W, L[i + 1].d.bn.C);
   };
   PartSums handed{nullptr, 0, false};     // the last layer's
   bool wt_forked = false;

@@ -313,6 +313,28 @@ def test_conv_patch_kernels_without_the_pixel_permutation(K, shape):
     patch_case(K, shape, {7: -1})
 
 
+# Large tensors of 1024 channels and more go over whole rows, which is faster there: the bits of the launches that key 19 = -1 asks for.
+@pytest.mark.parametrize("m,C", [(16385, 1024), (16400, 1088), (16385, 2048)])
+def test_large_wide_batch_norms_take_whole_rows(K, m, C):
+    gen = torch.Generator(device="cuda:0").manual_seed(m + C)
+    x, dy, y = (torch.randn((m, C), generator=gen, device="cuda:0").bfloat16() for _ in range(3))
+    gamma, beta, mean, invstd = (torch.rand(C, generator=gen, device="cuda:0") + 0.5 for _ in range(4))
+    d = K.bn_desc(m, 1, 1, C, K.BF16, True)
+    ws, nb = ws_for(K.cnnk_bn_workspace_bytes(d))
+    got = []
+    for key in (0, -1):
+        out = [torch.zeros_like(x), torch.zeros_like(x), torch.zeros_like(gamma), torch.zeros_like(gamma)]
+        K.cnnk_tune(19, key)
+        try:
+            K.cnnk_bn_relu_bwd(d, dy, x, y, gamma, beta, mean, invstd, out[0], out[1], 0, out[2], out[3], ws, nb)
+            torch.cuda.synchronize()
+        finally:
+            K.cnnk_tune(19, 0)
+        got.append(out)
+    for a, b in zip(*got):
+        assert torch.isfinite(a.float()).all() and torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("shape,relu,with_res", [((3, 9, 7, 64), True, False), ((2, 16, 16, 160), True, True),
                                                   ((5, 4, 4, 512), False, False), ((8, 32, 32, 16), True, False),
@@ -322,7 +344,9 @@ def test_conv_patch_kernels_without_the_pixel_permutation(K, shape):
                                                   ((33, 1, 1, 128), True, False), ((16, 32, 32, 64), True, True),
                                                   ((16385, 1, 1, 64), True, True), ((33, 2, 2, 320), True, False),
                                                   # channels whose sums several threads share
-                                                  ((37, 2, 1, 40), True, False), ((300, 1, 1, 8), False, True)])
+                                                  ((37, 2, 1, 40), True, False), ((300, 1, 1, 8), False, True),
+                                                  # the last rows of 1024 channels that go in slabs
+                                                  ((16384, 1, 1, 1024), True, True)])
 def test_bn_relu_fwd_bwd(K, shape, relu, with_res, dtype):
     N, H, W, Cc = shape
     rng = np.random.default_rng(21)
