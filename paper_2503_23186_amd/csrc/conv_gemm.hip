@@ -346,9 +346,12 @@ void init_divs(Taps* t) {
 
 // 1x1 filters, and 3x3 filters with stride 2.  (3x3 with stride 1 reads every pixel nine times, which the patch
 // kernel's resident input saves: 128 channels at 16 x 16, batch 256: 23 us against 27 us here.)  A reduction of one
-// stage into few channels is left to the gathered kernel, which walks several tiles per workgroup and so has the next
-// tile's loads in flight while it writes: 1x1 of 64 -> 64 channels at 32 x 32, batch 256: 16 us against 19 us; 64 ->
-// 256: 38 us against 36 us here.  Its own tuning keys ask for that kernel, too.
+// stage into few channels is left to the gathered kernel.  The line was drawn when only that one walked several tiles and had the next
+// tile's loads in flight while it wrote; with both walking, us gathered / here on operands that the L2s do not hold, batch 256: plain forward 64 -> 64 at 16
+// x 16 8.1 / 8.7, at 32 x 32 19.2 / 19.6, at 56 x 56 53.5 / 43.7, 64 -> 128 at 32 x 32 30.2 / 32.5, at 16 x 16 12.2 / 10.9; with channel sums (and the
+// launch that adds them up) 12.2 / 12.2, 29.7 / 23.2, 87.1 / 52.5, 37.0 / 37.4, 16.0 / 14.5; batch 8 at 32 x 32, 64 -> 64 5.0 / 4.3.  Over 32, 64 ->
+// 32 to 128 channels, 1 to 256 images of 8 x 8 to 56 x 56 the kernel here takes 0.86 of the gathered one's time, 0.73 to 1.08 plain and 0.59 to 1.01
+// with sums.  Its own tuning keys ask for the gathered kernel, too.
 bool conv_gemm_supported(const ConvGeom& g, int pass) {
   if (g_cnnk_tune[16] < 0 || !conv_mfma_supported(g, pass)) return false;
   const int Cs = pass == CNNK_PASS_FWD ? g.Cin : g.Cout, Cd = pass == CNNK_PASS_FWD ? g.Cout : g.Cin;
