@@ -225,7 +225,7 @@ __global__ void __launch_bounds__(kT) stats_partial_kernel(const T* __restrict__
 }
 
 // y = a + b, and the partial sums of stats_partial_kernel over y as stored: the sum's own pass over it is saved (WRN-28-10 b128, twelve sums
-// of 84 to 21 MB: 10 + 10.5 us a sum in two launches).
+// of 84 to 21 MB: 10 + 10.5 us a sum in two launches).  Where it is the slower one: add_stats_pays.
 template <typename T>
 __global__ void __launch_bounds__(kT) add_stats_kernel(const T* __restrict__ a, const T* __restrict__ b, T* __restrict__ y, size_t m, int C,
                                                        float* __restrict__ part) {
@@ -765,6 +765,12 @@ int channel_stats(int dtype, const void* x, size_t m, int C, float* ch_sum, floa
   }
   return launch_status();
 }
+
+// Few workgroups walk a tensor of many channels (reduce_blocks), too few to add large bf16 ones at the memory rate.  us, in one launch / the sum and the batch
+// norm's first pass: bf16, 384 channels 131072 rows 61.2 / 68.2; 512 channels 32768 rows 25.2 / 29.6, 65536 50.7 / 47.3; 640 channels 65536 rows 67.1 /
+// 57.8; 768 channels 16384 rows 21.4 / 23.7, 32768 49.3 / 40.8; 1024 channels 16384 rows 30.6 / 29.6, 32768 71.0 / 49.4; 2048 channels 8192 rows 29.3 / 32.3,
+// 16384 75.4 / 53.4.  fp32: 512 channels 65536 rows 83.0 / 90.7, 1024 channels 32768 rows 82.9 / 89.9.
+bool add_stats_pays(int dtype, size_t m, int C) { return dtype != CNNK_BF16 || C < 512 || m * C <= (size_t)1 << 24; }
 
 int add_stats(int dtype, const void* a, const void* b, void* y, size_t m, int C, PartSums* out, void* ws, hipStream_t st) {
   const int nb = reduce_blocks(m, C);

@@ -241,7 +241,9 @@ int bn_relu_bwd(const cnnk_bn_desc* d, const void* dy, const void* x, const void
 // per-channel sum / sum of squares of a tensor with C channels (used when the conv kernel
 // itself does not produce them)
 size_t channel_stats_ws(size_t m, int C);
-// y = a + b with the partial sums that the batch norm of y, the very next call, begins with (channel_stats_ws bytes of ws)
+// y = a + b with the partial sums that the batch norm of y, the very next call, begins with (channel_stats_ws bytes of ws), and whether
+// that is faster than the two passes
+bool add_stats_pays(int dtype, size_t m, int C);
 int add_stats(int dtype, const void* a, const void* b, void* y, size_t m, int C, PartSums* out, void* ws, hipStream_t st);
 // d0 = src and d1 = src, or += where acc0, acc1 say so: cnnk_grad_route to two different tensors with one read
 int grad_route2(size_t n, int dtype, const void* src, void* d0, int acc0, void* d1, int acc1, hipStream_t st);

@@ -420,6 +420,7 @@ extern "C" int cnnk_train_step(const cnnk_layer* L, int n, const cnnk_buffers* B
         // A batch norm of the sum that comes next starts from partial sums made here; not of a sum in place, whose first row (what
         // the partial sums are relative to) every workgroup reads from both summands while others store
         if (i + 1 < n && L[i + 1].op == CNNK_OP_BN && L[i + 1].in0 == l.out && g_cnnk_tune[20] >= 0 &&
+            add_stats_pays(w.dtype, w.slot_elems[l.out] / L[i + 1].d.bn.C, L[i + 1].d.bn.C) &&
             !share(B->act[l.out], B->act[l.in0], w.slot_elems[l.out] * elem) && !share(B->act[l.out], B->act[l.in1], w.slot_elems[l.out] * elem)) {
           const size_t rows = w.slot_elems[l.out] / L[i + 1].d.bn.C;
           rc = add_stats(w.dtype, B->act[l.in0], B->act[l.in1], B->act[l.out], rows, L[i + 1].d.bn.C, &handed, ws, (hipStream_t)stream);

@@ -343,6 +343,15 @@ def test_sums_that_make_their_batch_norms_partial_sums_give_the_same_bits(widths
             assert torch.equal(a.bn_save[i], b.bn_save[i]) and torch.equal(a.bn_running[i], b.bn_running[i])
 
 
+def test_sums_of_many_channels_in_front_of_batch_norms():
+    """The first of these sums is past the line beyond which it and the batch norm's partial sums are launches of their own, the second
+    is not: the bits of both apart."""
+    net = WL.mini_preact(batch=33, dtype="bf16", size=32, widths=(512, 1024))
+    inp = WL.make_inputs(net, 37, perturb_bn=True)
+    a, b = _run_steps(net, inp, {}, True), _run_steps(net, inp, {20: -1}, True)
+    _assert_same_bits(net, a, b)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("summand", ["a", "b"])
 def test_sums_in_place(dtype, summand):
